@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
         for (int j = 0; j < KM; ++j) r[j] = RowBuffer(recv + (size_t)s[j] * cpr, cpr, use[j]).load(c);
 #pragma unroll
         for (int j = 0; j < KM; ++j) {
-            dot[j] = chunk_dot<DT>(g, r[j], dot[j]);   // r = 0 for a dropped pair
+            dot[j] = chunk_dot<DT>(g, r[j], dot[j]);
             float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             Chunk<DT>::fma(acc, w[j], g);
             RowBuffer(d_recv + (size_t)s[j] * cpr, cpr, use[j]).template store<STREAM>(c, Chunk<DT>::pack(acc));
@@ -71,14 +71,14 @@ __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
     }
 #pragma unroll
     for (int j = 0; j < KM; ++j) {
-        float v = dot[j];   // 0 for a dropped pair
+        float v = dot[j];
         v += __shfl_xor(v, 32);
         v += __shfl_xor(v, 16);
         v += __shfl_xor(v, 8);
         v += __shfl_xor(v, 4);
         v += __shfl_xor(v, 2);
         v += __shfl_xor(v, 1);
-        if (lane == 0) part[wave][j] = v;
+        if (lane == 0) part[wave][j] = use[j] ? v : 0.f;   // g may hold infinities: zeros for r are not enough
     }
     __syncthreads();
     if (live && seg0 == 0 && lane < k) {
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kThreads) void combine_bwd_short_kernel(
         }
 #pragma unroll
         for (int j = 0; j < KG; ++j) {
-            dot[j] = chunk_dot<DT>(g, r[j], 0.f);   // r = 0 for a dropped pair
+            dot[j] = chunk_dot<DT>(g, r[j], 0.f);
             float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             Chunk<DT>::fma(acc, w[j], g);
             const vec16 o = Chunk<DT>::pack(acc);
@@ -138,7 +138,8 @@ __global__ __launch_bounds__(kThreads) void combine_bwd_short_kernel(
         for (int j = 0; j < KG; ++j) {
             float v = dot[j];
             for (int m = (1 << g_shift) >> 1; m > 0; m >>= 1) v += __shfl_xor(v, m);
-            if (live && c == 0 && (KK > 0 || j0 + j < k)) d_w[(int64_t)t * k + j0 + j] = v;
+            // lane c == 0 has its chunk, so s[j] is -1 for a dropped pair alone (g may hold infinities)
+            if (live && c == 0 && (KK > 0 || j0 + j < k)) d_w[(int64_t)t * k + j0 + j] = s[j] >= 0 ? v : 0.f;
         }
     }
 }

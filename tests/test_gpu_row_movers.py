@@ -74,6 +74,52 @@ def test_combine_and_backward_layouts(T, oracle, dtype, S, chunks, k):
         assert (np.abs(got - want) <= ulp * np.abs(want) + tiny + 1e-40).all()
 
 
+@pytest.mark.parametrize("dtype", [W.BF16, W.F16, W.F32])
+@pytest.mark.parametrize("k", range(1, 9))
+def test_infinities_stay_with_their_pairs(T, dtype, k):
+    """d_topk_w of a dropped pair is 0 whatever dy holds, and infinities, NaN and weights of one token reach no
+    other and no dropped pair, on short rows (3 and 40 chunks), whole wavefronts (64) and several (130)."""
+    tt = {W.BF16: torch.bfloat16, W.F16: torch.float16, W.F32: torch.float32}[dtype]
+    for chunks in (3, 40, 64, 130):
+        S, d = 24, chunks * (4 if dtype == W.F32 else 8)
+        g = torch.Generator(device="cuda").manual_seed(chunks + k)
+        dy = torch.randn(S, d, generator=g, device="cuda").to(tt)
+        K_rows = S * k
+        recv = torch.randn(K_rows, d, generator=g, device="cuda").to(tt)
+        w = torch.rand(S, k, generator=g, device="cuda")
+        slot = torch.randperm(K_rows, generator=g, device="cuda").int().reshape(S, k)
+        slot[:6] = -1                                     # nothing kept
+        slot[6:12, ::2] = -1                              # half of the choices
+        slot[12:14, k - 1] = K_rows                       # beyond the buffer
+        kept = (slot >= 0) & (slot < K_rows)
+        for t, v in ((0, np.inf), (1, -np.inf), (2, np.nan), (6, np.inf), (7, np.nan), (12, -np.inf), (13, np.nan)):
+            dy[t, [0, d // 2, d - 1][t % 3]] = v
+        w[~kept] = float("nan")                           # a dropped pair's weight is not used either
+        d_recv, d_w = torch.full_like(recv, 7.0), torch.full((S, k), 7.0, device="cuda")
+        T.tamoe_combine_bwd(dy, recv, K_rows, slot, w, d_recv, d_w)
+        rows = recv[slot.clamp(0, K_rows - 1).long()].double()
+        terms = dy.double()[:, None, :] * rows
+        want = torch.where(kept, terms.sum(2), 0.0).cpu()
+        got = d_w.cpu().double()
+        finite = torch.isfinite(want)
+        assert torch.equal(torch.isfinite(got), finite) and torch.equal(torch.isnan(got), torch.isnan(want)), chunks
+        assert torch.equal(got[~finite & ~torch.isnan(want)], want[~finite & ~torch.isnan(want)])
+        bound = d * 2.0 ** -24 * torch.where(kept, terms.abs().sum(2), 0.0).cpu()
+        assert ((got - want).abs()[finite] <= bound[finite]).all()
+        assert (got[~kept.cpu()] == 0).all()
+        t, j = torch.nonzero(kept, as_tuple=True)
+        out = torch.full(recv.shape, 7.0, dtype=torch.float64, device="cuda")
+        out[slot[t, j].long()] = w[t, j, None].double() * dy[t].double()
+        there = torch.isfinite(out)
+        assert torch.equal(torch.nan_to_num(d_recv.double()[~there], 5.0), torch.nan_to_num(out[~there], 5.0))
+        # half an ulp is 2^-p of the value for p significant bits; one more rounding in fp32; half the subnormal
+        # spacing of half precision
+        half = {W.F32: 2.0 ** -24, W.BF16: 2.0 ** -8, W.F16: 2.0 ** -11}[dtype]
+        assert ((d_recv.double() - out).abs()[there] <= ((half + 2.0 ** -23) * out.abs() + 2.0 ** -25)[there]).all()
+        y = T.combine(recv, K_rows, slot, w)
+        assert torch.isfinite(y).all() and (y[:6] == 0).all()
+
+
 @pytest.mark.parametrize("P,E,chunks,mean", [(1, 1, 1, 3), (3, 2, 63, 4), (64, 2, 64, 3), (2, 64, 65, 2), (5, 7, 128, 0.3), (128, 1, 8, 5),
                                              (16, 4, 129, 20)])
 @pytest.mark.parametrize("clip", [0, 7])
