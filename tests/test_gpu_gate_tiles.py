@@ -56,3 +56,39 @@ def test_fp32_scores_over_the_exponent_range(T, S, N):
     # and, in the 2-norm of a row, no more than a few roundings of the result
     rel = (lg - ref).norm(dim=1) / ref.norm(dim=1)
     assert rel.max() < 1e-6, rel.max()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("S,N,d", [(40, 8, 40), (40, 8, 64), (40, 8, 192), (9000, 20, 72), (40, 64, 64), (9000, 48, 136), (20000, 64, 72),
+                                   (40, 128, 192), (9000, 100, 200), (20000, 128, 40), (33000, 128, 72), (33000, 65, 128)])
+def test_infinities_in_the_scores(T, dtype, S, N, d):
+    """An expert masked with an infinite weight, infinities and NaN in x (the last elements of a row among them):
+    the scores, and what follows from them, are those of the arithmetic itself."""
+    k = 2
+    g = torch.Generator(device="cuda").manual_seed(S + d)
+    x = torch.randn((S, d), generator=g, device="cuda").to(dtype)
+    w = (torch.randn((N, d), generator=g, device="cuda") / math.sqrt(d)).to(dtype)
+    x[:, d - 1] = 1.0
+    w[3, d - 1] = -math.inf                                      # expert 3 is masked
+    odd = [5, 7, S - 3, S - 2]
+    x[5, d - 2], x[S - 3, 0], x[7, 1], x[S - 2, d - 2] = math.inf, -math.inf, math.nan, math.inf
+    r = T.gate(x, w, 1, k)
+    lg = r["logits"].cpu().double()
+    ref = x.cpu().double() @ w.cpu().double().t()
+    assert torch.equal(torch.isnan(lg), torch.isnan(ref))
+    inf = torch.isinf(ref)
+    assert torch.equal(torch.isinf(lg), inf) and torch.equal(lg[inf], ref[inf])
+    fin = torch.isfinite(ref)
+    mag = torch.nan_to_num(x.cpu().double(), 0, 0, 0).abs() @ torch.nan_to_num(w.cpu().double(), 0, 0, 0).abs().t()
+    assert ((lg - ref).abs()[fin] <= (d + 2) * 2.0 ** -24 * mag[fin]).all()
+    plain = torch.ones(S, dtype=torch.bool)
+    plain[odd] = False
+    prob = torch.softmax(lg[plain], 1)
+    idx, wgt = r["topk_idx"].cpu()[plain].long(), r["topk_w"].cpu()[plain].double()
+    assert ((idx >= 0) & (idx < N) & (idx != 3)).all()
+    assert (wgt - prob.gather(1, idx)).abs().max() < 1e-5
+    assert (wgt - prob.topk(k, 1).values).abs().max() < 1e-5
+    assert (r["c_expert"].sum().item(), r["c_expert"][3].item()) == (int((r["topk_idx"] >= 0).sum()), int((r["topk_idx"] == 3).sum()))
+    # the same without the odd tokens: the masked expert has no share
+    m = T.gate(x[torch.tensor([t for t in range(S) if t not in odd], device="cuda")].contiguous(), w, 1, k)["m"].cpu().double()
+    assert m[3] == 0 and (m - prob.mean(0)).abs().max() < 1e-5
