@@ -177,6 +177,9 @@ size_t tamoe_workspace_bytes(int64_t S, int d, int N, int P, int k, int dtype);
  *   c_expert[e]   = number of (t, j) with topk_idx[t][j] == e        (before any capacity)
  *   c_device[j]   = sum of c_expert over the experts of device j
  *   m[e]          = (1/S) * sum_t G[t][e]                             (0 if S == 0)
+ * TAMOE_F32: a product of two values is formed from bfloat16 parts; what is left out of it is below 2^-22
+ * of the product (of either sign), and values below 2^-108 in magnitude enter with fewer than 24 bits, those
+ * below 2^-126 as zero.
  * x [S,d], w [N,d]: device, `dtype`.   logits [S,N] float, device, may be NULL.
  * topk_idx [S,k] int32, topk_w [S,k] float, m [N] float, c_expert [N] int32,
  * c_device [P] int32: device outputs.  The selection is taken on exactly the fp32 logits that

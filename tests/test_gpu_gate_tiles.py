@@ -58,6 +58,27 @@ def test_fp32_scores_over_the_exponent_range(T, S, N):
     assert rel.max() < 1e-6, rel.max()
 
 
+@pytest.mark.parametrize("S,N,d", [(512, 8, 64), (2048, 8, 1024), (40000, 32, 512), (4096, 64, 1024), (16384, 64, 1024), (20000, 64, 264),
+                                   (4096, 128, 256), (16384, 128, 512), (20000, 128, 1024), (33000, 128, 1024), (33000, 100, 200)])
+def test_fp32_products_keep_their_bits(T, S, N, d):
+    """Rows with one value: the score is one product, off by the rounding of the result (2^-24) and the terms left
+    out (2^-22).  Rows of positive values: the errors of a 32-bit sum have either sign, so their mean over a batch
+    is far below one rounding (2^-28: a sixteenth), where parts cut from every product would add up."""
+    g = torch.Generator(device="cuda").manual_seed(S + d)
+    w = torch.randn((N, d), generator=g, device="cuda")
+    at = torch.randint(0, d, (S, 1), generator=g, device="cuda")
+    one = torch.zeros((S, d), device="cuda").scatter_(1, at, torch.randn((S, 1), generator=g, device="cuda"))
+    ref = one.double() @ w.double().t()
+    err = (T.gate(one, w, 1, 1)["logits"].double() - ref).abs() / ref.abs()
+    assert err.max() <= 2.0 ** -22 + 2.0 ** -24
+    x, w = torch.rand((S, d), generator=g, device="cuda"), w.abs()
+    ref = x.double() @ w.double().t()
+    err = (T.gate(x, w, 1, 1)["logits"].double() - ref) / ref
+    assert err.mean().abs() <= 2.0 ** -28
+    # the roundings of a running sum of d / 8 partial products, 2^-24 at most each and a third of that in the mean
+    assert err.norm() / math.sqrt(err.numel()) <= math.sqrt(d / 8) * 2.0 ** -24 / 3 + 2.0 ** -24
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("S,N,d", [(40, 8, 40), (40, 8, 64), (40, 8, 192), (9000, 20, 72), (40, 64, 64), (9000, 48, 136), (20000, 64, 72),
                                    (40, 128, 192), (9000, 100, 200), (20000, 128, 40), (33000, 128, 72), (33000, 65, 128)])
