@@ -79,9 +79,10 @@ def test_fp32_products_keep_their_bits(T, S, N, d):
     assert err.norm() / math.sqrt(err.numel()) <= math.sqrt(d / 8) * 2.0 ** -24 / 3 + 2.0 ** -24
 
 
-@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
 @pytest.mark.parametrize("S,N,d", [(40, 8, 40), (40, 8, 64), (40, 8, 192), (9000, 20, 72), (40, 64, 64), (9000, 48, 136), (20000, 64, 72),
-                                   (40, 128, 192), (9000, 100, 200), (20000, 128, 40), (33000, 128, 72), (33000, 65, 128)])
+                                   (40, 128, 192), (9000, 100, 200), (20000, 128, 40), (33000, 128, 72), (33000, 65, 128),
+                                   (9000, 8, 1000), (40000, 32, 512), (9000, 64, 1024), (12160, 48, 832), (20000, 64, 1024), (70000, 128, 1024)])
 def test_infinities_in_the_scores(T, dtype, S, N, d):
     """An expert masked with an infinite weight, infinities and NaN in x (the last elements of a row among them):
     the scores, and what follows from them, are those of the arithmetic itself."""
@@ -113,3 +114,24 @@ def test_infinities_in_the_scores(T, dtype, S, N, d):
     # the same without the odd tokens: the masked expert has no share
     m = T.gate(x[torch.tensor([t for t in range(S) if t not in odd], device="cuda")].contiguous(), w, 1, k)["m"].cpu().double()
     assert m[3] == 0 and (m - prob.mean(0)).abs().max() < 1e-5
+
+
+@pytest.mark.parametrize("S,N,d", [(100, 8, 64), (9000, 32, 264), (500, 64, 64), (9000, 64, 136), (20000, 64, 512), (500, 128, 64), (9000, 128, 72),
+                                   (20000, 100, 128), (33000, 128, 136)])
+def test_fp32_scores_of_the_largest_values(T, S, N, d):
+    """Values whose rounding to 8 bits overflows (above (1 - 2^-8) * 2^128), and products and partial sums that do, in
+    a few tokens: finite scores stay finite and right, sums beyond the range are infinite."""
+    g = torch.Generator(device="cuda").manual_seed(S + d)
+    x = torch.randn((S, d), generator=g, device="cuda")
+    w = torch.randn((N, d), generator=g, device="cuda") / math.sqrt(d)
+    big = torch.finfo(torch.float32).max
+    w[:, 0], w[:, 1] = 2.0 ** -20 * w[:, 2], 2.0
+    x[:, :2] = 0.0
+    x[3, 0], x[S // 2, 0], x[S - 1, 0] = big, -big, big * 0.999
+    x[5, 1], x[6, 1] = big, -big
+    lg = T.gate(x, w, 1, 2)["logits"].cpu().double()
+    ref = x.cpu().double() @ w.cpu().double().t()
+    mag = x.cpu().double().abs() @ w.cpu().double().abs().t()
+    over = ref.abs() > big
+    assert over.sum() == 2 * N and torch.equal(torch.isfinite(lg), ~over) and torch.equal(lg[over].sign(), ref[over].sign())
+    assert ((lg - ref).abs()[~over] <= ((d + 4) * 2.0 ** -24 * mag)[~over]).all()
