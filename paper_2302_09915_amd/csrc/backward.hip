@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int rows = (int)(blockDim.x >> 6) / row_waves;                     // rows of this workgroup
     const int in_wg = wave / row_waves, seg0 = wave - in_wg * row_waves;
-    const int64_t t64 = (int64_t)blockIdx.x * rows + in_wg;
+    const int64_t t64 = (int64_t)linear_block() * rows + in_wg;
     const bool live = t64 < S;                                               // the same for the whole wavefront
     const int t = (int)(live ? t64 : S - 1);
     int32_t s[KM];
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void combine_bwd_short_kernel(
     float* __restrict__ d_w) {
     constexpr int KG = KK > 0 ? KK : 4;
     const int k = KK > 0 ? KK : k_arg;
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t i = (int64_t)linear_block() * kThreads + threadIdx.x;
     const int c = (int)i & ((1 << g_shift) - 1);
     const bool live = (i >> g_shift) < S;
     const int t = (int)(live ? i >> g_shift : S - 1);
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restr
     for (int e = tid; e < TAMOE_MAX_EXPERTS + 4; e += kThreads)
         coef[e] = e < N ? scale * (penalty != nullptr ? penalty[e] : 1.0f) * (float)c[e] : 0.f;
     __syncthreads();
-    const int64_t token = ((int64_t)blockIdx.x * kThreads + tid) / LPT;
+    const int64_t token = ((int64_t)linear_block() * kThreads + tid) / LPT;
     const int e0 = (tid % LPT) * 4;
     const bool token_ok = token < S;
     const int64_t tk = token_ok ? token : 0;
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restr
 template <int LPT>
 static void launch_gate_bwd(const float* logits, const int32_t* idx, const float* d_w, const float* penalty,
                             const int32_t* c, float scale, int64_t S, int N, int k, float* d_logits, hipStream_t st) {
-    const dim3 grid((unsigned)ceil_div(S * LPT, kThreads)), block(kThreads);
+    const dim3 grid = grid_of(ceil_div(S * LPT, kThreads), kThreads), block(kThreads);
     const bool vec = N % 4 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0 &&
                      reinterpret_cast<uintptr_t>(d_logits) % 16 == 0;
     if (vec)
@@ -262,7 +262,7 @@ static void launch_combine_bwd_k(const vec16* dy, const vec16* recv, int64_t K_r
     if (rows_by_wave(cpr)) {
         const int rw = row_waves(cpr) < kRowWaves ? row_waves(cpr) : kRowWaves;
         const int rows = rw < 4 ? 4 / rw : 1;
-        const dim3 grid((unsigned)ceil_div(S, rows)), block(rows * rw * 64);
+        const dim3 grid = grid_of(ceil_div(S, rows), rows * rw * 64), block(rows * rw * 64);
         if (stream)
             combine_bwd_kernel<DT, KK, true><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, rw, d_recv, d_w);
         else
@@ -270,7 +270,7 @@ static void launch_combine_bwd_k(const vec16* dy, const vec16* recv, int64_t K_r
     } else {
         int g_shift = 0;
         while ((1 << g_shift) < cpr) ++g_shift;
-        const dim3 grid((unsigned)ceil_div(S << g_shift, kThreads)), block(kThreads);
+        const dim3 grid = grid_of(ceil_div(S << g_shift, kThreads), kThreads), block(kThreads);
         if (stream)
             combine_bwd_short_kernel<DT, KK, true><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, g_shift, d_recv, d_w);
         else

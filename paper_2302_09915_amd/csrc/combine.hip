@@ -23,7 +23,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restri
                                                            int cpr, int wpr, int shift, vec16* __restrict__ y) {
     constexpr int KM = KK > 0 ? KK : TAMOE_MAX_K;
     const int k = KK > 0 ? KK : k_arg;
-    const uint32_t wave = blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wave = linear_block() * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     int tok[U], col[U];
     int32_t sl[U][KM];
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(kThreads) void combine_flat_kernel(const vec16* __r
                                                                 int k_arg, int cpr, int shift, vec16* __restrict__ y) {
     constexpr int KG = KK > 0 ? KK : 4;
     const int k = KK > 0 ? KK : k_arg;
-    const int64_t base = (int64_t)blockIdx.x * (kThreads * U) + threadIdx.x;
+    const int64_t base = (int64_t)linear_block() * (kThreads * U) + threadIdx.x;
     int tok[U], col[U];
     float acc[U][8];
 #pragma unroll
@@ -125,12 +125,12 @@ static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* sl
     vec16* out = static_cast<vec16*>(y);
     if (rows_by_wave(cpr)) {
         const int wpr = row_waves(cpr);
-        const dim3 grid((unsigned)ceil_div(S * (int64_t)wpr, kThreads / 64 * U)), block(kThreads);
+        const dim3 grid = grid_of(ceil_div(S * (int64_t)wpr, kThreads / 64 * U), kThreads), block(kThreads);
         combine_kernel<DT, KK, U, UNITW>
             <<<grid, block, 0, st>>>(r, K_rows, slot, topk_w, S, k, cpr, wpr, pow2_shift(wpr), out);
     } else {
         const int64_t total = S * (int64_t)cpr;
-        const dim3 grid((unsigned)ceil_div(total, kThreads * U)), block(kThreads);
+        const dim3 grid = grid_of(ceil_div(total, kThreads * U), kThreads), block(kThreads);
         combine_flat_kernel<DT, KK, U, UNITW>
             <<<grid, block, 0, st>>>(r, K_rows, slot, topk_w, total, k, cpr, pow2_shift(cpr), out);
     }
@@ -182,7 +182,8 @@ static int combine_entry(const char* fn, const void* recv, int64_t K_rows, const
     if (weighted && (rc = check_ptr(fn, "topk_w", topk_w, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, weighted ? "y" : "d_x", y, 16)) != TAMOE_OK) return rc;
     const int cpr = d * elem_bytes(dtype) / 16;  // 16-byte chunks per row
-    if (ceil_div(S * (int64_t)cpr, kThreads * 1) > 0x7fffffff)
+    if (ceil_div(S * (int64_t)cpr, kThreads * 1) > 0x7fffffff ||
+        (rows_by_wave(cpr) && ceil_div(S * (int64_t)row_waves(cpr), kThreads / 64) > 0x7fffffff))
         return fail(TAMOE_UNSUPPORTED, "%s: the output is too large for one launch", fn);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (weighted)

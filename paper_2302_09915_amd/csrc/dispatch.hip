@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void dispatch_copy_kernel(const vec16* __
                                                                  vec16* __restrict__ send) {
     constexpr int KM = KK > 0 ? KK : TAMOE_MAX_K;
     const int k = KK > 0 ? KK : k_arg;
-    const int64_t base = (int64_t)blockIdx.x * (kThreads * U) + threadIdx.x;
+    const int64_t base = (int64_t)linear_block() * (kThreads * U) + threadIdx.x;
     vec16 v[U];
     int32_t sl[U][KM];
     int col[U];
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kThreads) void dispatch_copy_kernel(const vec16* __
 template <int KK, int U>
 static void launch_copy(const void* x, const int32_t* slot, int64_t S, int k, int cpr, void* send, hipStream_t st) {
     const int64_t total = S * (int64_t)cpr;
-    const dim3 grid((unsigned)ceil_div(total, kThreads * U)), block(kThreads);
+    const dim3 grid = grid_of(ceil_div(total, kThreads * U), kThreads), block(kThreads);
     const vec16* src = static_cast<const vec16*>(x);
     vec16* dst = static_cast<vec16*>(send);
     const int shift = pow2_shift(cpr);

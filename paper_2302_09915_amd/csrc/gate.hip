@@ -33,7 +33,8 @@ __global__ __launch_bounds__(512) void select_kernel(const float* __restrict__ l
     __shared__ unsigned char rank[TOK * TAMOE_MAX_K];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t tile0 = (int64_t)blockIdx.x * TOK;
+    const int64_t tile0 = (int64_t)linear_block() * TOK;
+    if (tile0 >= S) return;   // past the last tile (grid_of)
     auto load_scores = [&](int tl, int q, auto& sc) {   // a token's lanes read consecutive pieces
         using SG = SelectGeom<NB, WAVES, TOK>;
         const int64_t t = tile0 + tl < S ? tile0 + tl : S - 1;
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(256) void gate_finalize_kernel(const float* __restr
 
 static void launch_select(int64_t blocks, hipStream_t st, const float* logits, int64_t S, int N, int k,
                           int32_t* topk_idx, float* topk_w, const GateStats& gs) {
-    const dim3 grid((unsigned)blocks), block(512);
+    const dim3 grid = grid_of(blocks, 512), block(512);
     TraceScope tr("select_kernel", st);
     if (N <= 32)
         select_kernel<1><<<grid, block, 0, st>>>(logits, S, N, k, topk_idx, topk_w, gs);

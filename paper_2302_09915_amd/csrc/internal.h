@@ -87,6 +87,16 @@ int check_select_outputs(const char* fn, int64_t S, int32_t* topk_idx, float* to
 constexpr int64_t kCacheResidentSendBytes = (int64_t)96 << 20;
 inline bool send_stays_in_cache(int64_t S, int k, int cpr) { return S * k * (int64_t)cpr * 16 <= kCacheResidentSendBytes; }
 
+// Workgroups of a launch as a grid.  HIP takes fewer than 2^32 threads along a dimension: 16 777 216 workgroups of
+// 256 are an invalid configuration, and of a few more only those run, without an error.  More go into rows
+// of 2^20 workgroups, the last of which may have workgroups without work.  blocks < 2^31.
+constexpr int kGridRowShift = 20;
+inline dim3 grid_of(int64_t blocks, int threads) {
+    if (blocks * threads < (int64_t)1 << 32) return dim3((unsigned)blocks);
+    return dim3(1u << kGridRowShift, (unsigned)ceil_div(blocks, (int64_t)1 << kGridRowShift));
+}
+__device__ __forceinline__ uint32_t linear_block() { return blockIdx.x + (blockIdx.y << kGridRowShift); }
+
 // log2(v) if v is a power of two, else -1.
 inline int pow2_shift(int v) {
     if (v <= 0 || (v & (v - 1)) != 0) return -1;

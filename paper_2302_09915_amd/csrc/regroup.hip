@@ -53,7 +53,7 @@ __device__ __forceinline__ void offset_tables(const Segments& sg, bool to_expert
         const int32_t i1 = wave_inclusive_scan(c[1]) + __builtin_amdgcn_readlane(i0, 63);
         const int32_t off[2] = {i0 - c[0], i1 - c[1]};
         int32_t* tab = wave == 0 ? from_off : to_off;
-        const bool write = expert_major && blockIdx.x == 0 && expert_offset != nullptr;
+        const bool write = expert_major && linear_block() == 0 && expert_offset != nullptr;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int h = lane + 64 * i;
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kThreads) void regroup_copy_kernel(const vec16* __r
                                                                 int32_t* __restrict__ expert_offset) {
     __shared__ int32_t from_off[kMaxSeg + 1], to_off[kMaxSeg + 1];
     const int lane = threadIdx.x & 63, n = sg.P * sg.E;
-    const uint32_t wave = blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wave = linear_block() * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     offset_tables(sg, to_expert_major, from_off, to_off, expert_offset);
     const int32_t f0 = lane < n ? from_off[lane] : 0x7fffffff, f1 = lane + 64 < n ? from_off[lane + 64] : 0x7fffffff;
     const int32_t rows = __builtin_amdgcn_readfirstlane(from_off[n]);
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kThreads) void regroup_flat_kernel(const vec16* __r
     offset_tables(sg, to_expert_major, from_off, to_off, expert_offset);
     const int64_t R = from_off[n] < cap_rows ? from_off[n] : cap_rows;
     const int64_t total = R * cpr;
-    const int64_t base = (int64_t)blockIdx.x * (kThreads * U) + threadIdx.x;
+    const int64_t base = (int64_t)linear_block() * (kThreads * U) + threadIdx.x;
     vec16 v[U];
     int64_t dst[U];
 #pragma unroll
@@ -188,7 +188,7 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
     const Segments sg{recv_count, P, E, (65536 + P - 1) / P, (65536 + E - 1) / E};
     const vec16* src = static_cast<const vec16*>(in);
     vec16* dst = static_cast<vec16*>(out);
-    const dim3 grid((unsigned)blocks), block(kThreads);
+    const dim3 grid = grid_of(blocks, kThreads), block(kThreads);
     TraceScope tr("regroup_copy_kernel", st);
 #define TAMOE_REGROUP(STREAM)                                                                                      \
     do {                                                                                                           \

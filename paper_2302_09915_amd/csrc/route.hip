@@ -60,7 +60,8 @@ __global__ __launch_bounds__(512) void route_rank_kernel(const int32_t* __restri
     __shared__ int32_t pairs[(TOK / 64) * TAMOE_MAX_K * NB * 32];
     __shared__ signed char sel[TOK * TAMOE_MAX_K];
     __shared__ unsigned char rank[TOK * TAMOE_MAX_K];
-    const int64_t tile0 = (int64_t)blockIdx.x * TOK;
+    const int64_t tile0 = (int64_t)linear_block() * TOK;
+    if (tile0 >= S) return;   // past the last tile (grid_of)
     const int n = (int)(S - tile0 < TOK ? S - tile0 : TOK) * k;
     for (int i = threadIdx.x; i < TOK * k; i += WAVES * 64) {
         const int32_t e = i < n ? idx[tile0 * k + i] : -1;
@@ -351,7 +352,8 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
     const vec16* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_pos,
     const int32_t* __restrict__ tile_table, const int32_t* __restrict__ cap, int32_t* __restrict__ slot,
     vec16* __restrict__ send, const RouteArgs a) {
-    if (blockIdx.x == 0) {
+    const uint32_t wg = linear_block();
+    if (wg == 0) {
         route_layer_outputs<TABLE>(a);
         return;
     }
@@ -361,8 +363,9 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
     const int N = a.N, cpr = a.cpr;
     const int lane = threadIdx.x & 63;
 
-    if ((int)blockIdx.x > a.copy_blocks) {   // zero rows e*C + kept[e] .. (e+1)*C - 1, a share of them
-        const int f = (int)blockIdx.x - 1 - a.copy_blocks;
+    if (wg > (uint32_t)a.copy_blocks) {   // zero rows e*C + kept[e] .. (e+1)*C - 1, a share of them
+        const int f = (int)(wg - 1 - (uint32_t)a.copy_blocks);
+        if (f >= N * a.fill_parts) return;   // past the last workgroup (grid_of)
         const int e = f / a.fill_parts, part = f - e * a.fill_parts;
         if constexpr (TABLE) scan_table<1>(a, 0, kept_w, nullptr, nullptr);
         const int32_t used = TABLE ? kept_w[TABLE ? e : 0] : a.kept_expert[e];
@@ -380,7 +383,7 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
     }
 
     const int k = KK > 0 ? KK : a.k;
-    const uint32_t blk = blockIdx.x - 1;
+    const uint32_t blk = wg - 1;
     const int64_t total = a.S * cpr;
     int tok[U], col[U], seg[U];
     bool inside[U];
@@ -509,14 +512,18 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
 
 constexpr int copy_units(int k) { return k == 1 ? 2 : 1; }   // chunks per thread
 
+// Workgroups that move rows.
+static int64_t copy_workgroups(int64_t S, int cpr, int k) {
+    const int U = copy_units(k);
+    return rows_by_wave(cpr) ? ceil_div(S * (int64_t)row_waves(cpr), kCopyThreads / 64 * U)
+                             : ceil_div(S * (int64_t)cpr, kCopyThreads * U);
+}
+
 // Fills in the launch geometry.
 static void plan_copy(RouteArgs& a) {
-    const int U = copy_units(a.k);
-    const bool rowu = rows_by_wave(a.cpr);
     a.wpr = row_waves(a.cpr);
-    a.shift = pow2_shift(rowu ? a.wpr : a.cpr);
-    a.copy_blocks = (int)(rowu ? ceil_div(a.S * (int64_t)a.wpr, kCopyThreads / 64 * U)
-                               : ceil_div(a.S * (int64_t)a.cpr, kCopyThreads * U));
+    a.shift = pow2_shift(rows_by_wave(a.cpr) ? a.wpr : a.cpr);
+    a.copy_blocks = (int)copy_workgroups(a.S, a.cpr, a.k);
     // about 4096 workgroups clear rows, at most one per 4 KiB of an expert's rows
     a.fill_parts = a.pad_C == 0 ? 0 : (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(4096, a.N),
                                                                      ceil_div((int64_t)a.pad_C * a.cpr, kCopyThreads)));
@@ -525,7 +532,7 @@ static void plan_copy(RouteArgs& a) {
 template <int KK>
 static void launch_route_copy(const RouteArgs& a, bool table, hipStream_t st) {
     constexpr int U = copy_units(KK);
-    const dim3 grid((unsigned)(1 + (int64_t)a.copy_blocks + (int64_t)a.N * a.fill_parts)), block(kCopyThreads);
+    const dim3 grid = grid_of(1 + (int64_t)a.copy_blocks + (int64_t)a.N * a.fill_parts, kCopyThreads), block(kCopyThreads);
     const int64_t rows = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : a.S * a.k;
     const bool stream = !send_stays_in_cache(rows, 1, a.cpr);
     const int32_t* caps = a.cap != nullptr ? a.cap : a.table;   // N entries at least
@@ -585,7 +592,8 @@ int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const i
                  int32_t* expert_offset, int32_t* send_count_dev, void* ws, const Workspace& lay, hipStream_t st) {
     int rc;
     const int cpr = d * elem_bytes(dtype) / 16;  // 16-byte chunks per row
-    if (S > 0 && ceil_div(S * (int64_t)cpr, kCopyThreads) >= 0x7fff0000)   // a few more workgroups are added
+    // a few more workgroups are added
+    if (S > 0 && std::max(ceil_div(S * (int64_t)cpr, kCopyThreads), copy_workgroups(S, cpr, k)) >= 0x7fff0000)
         return fail(TAMOE_UNSUPPORTED, "%s: x is too large for one launch", fn);
     const int tok = rank_tokens(S, N, k);
     const int64_t blocks = ceil_div(S, tok);
@@ -594,7 +602,7 @@ int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const i
     run.tile_tokens = tok;
     if (blocks > 0) {
         TraceScope tr("route_rank_kernel", st);
-        const dim3 grid((unsigned)blocks), block(512);
+        const dim3 grid = grid_of(blocks, 512), block(512);
 #define TAMOE_RANK(NB)                                                                                  \
     do {                                                                                                \
         if (tok == 128) route_rank_kernel<NB, 128><<<grid, block, 0, st>>>(topk_idx, S, N, k, run.stats); \
@@ -655,7 +663,8 @@ extern "C" int tamoe_gate_dispatch(const void* x, const void* w, int dtype, int6
     if ((rc = check_select_outputs(fn, S, topk_idx, topk_w, m, c_expert, c_device, ws, ws_bytes, lay)) != TAMOE_OK)
         return rc;
     const int cpr = d * elem_bytes(dtype) / 16;  // 16-byte chunks per row
-    if (S > 0 && ceil_div(S * (int64_t)cpr, kCopyThreads) >= 0x7fffffff)   // one more workgroup is added
+    // one more workgroup is added
+    if (S > 0 && std::max(ceil_div(S * (int64_t)cpr, kCopyThreads), copy_workgroups(S, cpr, k)) >= 0x7fffffff)
         return fail(TAMOE_UNSUPPORTED, "%s: x is too large for one launch", fn);
     hipStream_t st = static_cast<hipStream_t>(stream);
 

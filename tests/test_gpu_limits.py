@@ -125,3 +125,90 @@ def test_more_than_2_to_32_chunks(T):
     assert bad == 0
     del xh, send_a, fz
     torch.cuda.empty_cache()
+
+
+def test_launches_of_2_to_32_threads(T):
+    """Rows just over 1 KiB take two wavefronts each: 2^25 of them are 2^32 threads, more than a launch takes along
+    one dimension.  Few rows are kept, so that the reference stays small."""
+    dev = torch.device("cuda:0")
+    S, d, N, P, k = (1 << 25) + 5, 520, 8, 4, 2
+    row = d * 2
+    if torch.cuda.mem_get_info()[0] < 5 * S * row:
+        pytest.skip("needs 175 GB of free device memory")
+    g = torch.Generator(device=dev)
+    g.manual_seed(9)
+    x = torch.empty((S, d), dtype=torch.bfloat16, device=dev)
+    for s0 in range(0, S, 1 << 20):
+        n = min(1 << 20, S - s0)
+        x[s0:s0 + n] = torch.randn((n, d), generator=g, device=dev, dtype=torch.float32).to(torch.bfloat16)
+    w = (torch.randn((N, d), generator=g, device=dev) / d ** 0.5).to(torch.bfloat16)
+    cap = torch.full((N,), 1000, dtype=torch.int32, device=dev)
+    f = T.gate_dispatch(x, w, P, k, None, cap, want_logits=False)
+    torch.cuda.synchronize()
+    K = N * 1000
+    assert int(f["expert_offset"][-1]) == K and torch.equal(f["kept_expert"], cap)
+    assert int(f["c_expert"].sum()) == S * k
+
+    def check_slots(r):   # the first 1000 pairs of every expert, in the order of first choices, then second ones
+        for e in range(N):
+            t = torch.nonzero(r["topk_idx"][:, 0] == e).flatten()[:1000]
+            assert torch.equal(r["slot"][t, 0], torch.arange(e * 1000, e * 1000 + 1000, dtype=torch.int32, device=dev))
+            assert torch.equal(r["send"][e * 1000:e * 1000 + 1000].view(torch.int16), x[t].view(torch.int16))
+        assert int((r["slot"] >= 0).sum()) == K
+
+    check_slots(f)
+    send = f.pop("send")
+    f["send"] = send
+    send[:K] = 0
+    ws = T.workspace(S, d, N, P, k, T.BF16, dev)
+    slot, kept = torch.empty_like(f["slot"]), torch.empty_like(f["kept_expert"])
+    off, scd = torch.empty_like(f["expert_offset"]), torch.empty_like(f["send_count_dev"])
+    T.tamoe_dispatch(x, f["topk_idx"], cap, N, P, send, slot, kept, off, scd, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(slot, f["slot"])
+    check_slots(f)
+    # the last tokens too: y and the gradients of tokens with a kept pair, zeros elsewhere
+    slot[(slot >= 0) & (slot < 3) | (slot == K - 1)] = -1
+    slot[S - 3:] = torch.tensor([[0, 1], [2, -1], [-1, K - 1]], dtype=torch.int32, device=dev)
+    recv = send[:K].clone()
+    live = torch.nonzero((slot >= 0).any(1)).flatten()
+    rows = recv[slot[live].clamp(min=0).long()].float() * (slot[live] >= 0)[..., None]
+    wgt = f["topk_w"]
+    y = send[:S]
+    T.tamoe_combine(recv, K, slot, wgt, y)
+    assert torch.allclose(y[live].float(), (rows * wgt[live][..., None]).sum(1), rtol=2.0 ** -7, atol=1e-6)
+    y[live] = 0
+    assert not any(bool(y[s0:s0 + (1 << 20)].any()) for s0 in range(0, S, 1 << 20))
+    T.tamoe_dispatch_bwd(recv, K, slot, y)
+    assert torch.allclose(y[live].float(), rows.sum(1), rtol=2.0 ** -7, atol=1e-6)
+    y[live] = 0
+    assert not any(bool(y[s0:s0 + (1 << 20)].any()) for s0 in range(0, S, 1 << 20))
+    d_recv, d_w = torch.empty_like(recv), torch.full_like(wgt, 7.0)
+    T.tamoe_combine_bwd(x, recv, K, slot, wgt, d_recv, d_w)
+    dots = (rows * x[live].float()[:, None, :]).sum(2)
+    assert torch.allclose(d_w[live], dots, rtol=1e-4, atol=1e-3)
+    d_w[live] = 0
+    assert not bool(d_w.any())
+    t, j = torch.nonzero(slot >= 0, as_tuple=True)
+    assert t.numel() == K
+    want = wgt[t, j][:, None] * x[t].float()
+    assert torch.allclose(d_recv[slot[t, j].long()].float(), want, rtol=2.0 ** -7, atol=1e-6)
+    del d_w, slot, f, y
+    torch.cuda.empty_cache()
+
+    # two buffers of 2^26 rows
+    rows_in, rows_out = send, torch.empty_like(send)
+    rows_in[:K] = recv
+    cnt = torch.randint(0, 2 * K // 64, (8, 4), generator=g, device=dev, dtype=torch.int32)
+    R = int(cnt.sum())
+    assert 0 < R <= K
+    rows_out[:R + 5] = 3.0
+    off = torch.empty(5, dtype=torch.int32, device=dev)
+    T.tamoe_regroup(rows_in, cnt, True, rows_out, off, ws)
+    torch.cuda.synchronize()
+    c = cnt.cpu()
+    src = torch.cat([torch.zeros(1, dtype=torch.long), c.flatten().cumsum(0)])
+    order = torch.cat([torch.arange(int(src[s * 4 + e]), int(src[s * 4 + e + 1])) for e in range(4) for s in range(8)])
+    assert torch.equal(off.cpu().long(), torch.cat([torch.zeros(1, dtype=torch.long), c.sum(0).cumsum(0)]))
+    assert torch.equal(rows_out[:R].view(torch.int16), rows_in[order.to(dev)].view(torch.int16))
+    assert bool((rows_out[R:R + 5] == 3.0).all())
