@@ -43,7 +43,8 @@
  *    A token row must be a multiple of 16 bytes (d % 4 == 0 for F32, d % 8 == 0 otherwise) and
  *    x, W, send, recv, y must be 16-byte aligned.
  *  - Limits: 1 <= N <= TAMOE_MAX_EXPERTS, 1 <= k <= min(N, TAMOE_MAX_K), N % P == 0,
- *    S * k < 2^31.  S = 0 is accepted by every device function except tamoe_aux_loss.
+ *    S * k < 2^31, rows below 2 GiB (tamoe_gate: d < 2^31, fp32 d < 2^30).
+ *    S = 0 is accepted by every device function except tamoe_aux_loss.
  *  - Inputs must be finite.  NaN scores give unspecified (but in-range or -1) selections.
  *  - Every function returns a tamoe_status.  On failure nothing has been enqueued and
  *    tamoe_last_error() describes the reason (thread-local, valid until the next call).

@@ -312,7 +312,8 @@ extern "C" int tamoe_combine_bwd(const void* dy, const void* recv, int64_t K_row
     if (k <= 0) return fail(TAMOE_INVALID_ARG, "%s: k = %d must be positive", fn, k);
     if (k > TAMOE_MAX_K) return fail(TAMOE_UNSUPPORTED, "%s: k = %d exceeds the limit of %d", fn, k, TAMOE_MAX_K);
     if (S * (int64_t)k >= (int64_t)1 << 31) return fail(TAMOE_UNSUPPORTED, "%s: S*k does not fit int32", fn);
-    if ((rc = check_rows(fn, dtype, d)) != TAMOE_OK) return rc;
+    int cpr = 0;   // 16-byte chunks per row
+    if ((rc = check_rows(fn, dtype, d, &cpr)) != TAMOE_OK) return rc;
     if (S == 0) return TAMOE_OK;
     if ((rc = check_ptr(fn, "dy", dy, 16)) != TAMOE_OK) return rc;
     if (K_rows > 0 && (rc = check_ptr(fn, "recv", recv, 16)) != TAMOE_OK) return rc;
@@ -320,7 +321,6 @@ extern "C" int tamoe_combine_bwd(const void* dy, const void* recv, int64_t K_row
     if ((rc = check_ptr(fn, "slot", slot, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "topk_w", topk_w, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "d_topk_w", d_topk_w, 4)) != TAMOE_OK) return rc;
-    const int cpr = d * elem_bytes(dtype) / 16;
     if (S > 0x7fffffff) return fail(TAMOE_UNSUPPORTED, "%s: too many tokens for one launch", fn);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (dtype == TAMOE_F32)

@@ -175,13 +175,13 @@ static int combine_entry(const char* fn, const void* recv, int64_t K_rows, const
     if (k <= 0) return fail(TAMOE_INVALID_ARG, "%s: k = %d must be positive", fn, k);
     if (k > TAMOE_MAX_K) return fail(TAMOE_UNSUPPORTED, "%s: k = %d exceeds the limit of %d", fn, k, TAMOE_MAX_K);
     if (S * (int64_t)k >= (int64_t)1 << 31) return fail(TAMOE_UNSUPPORTED, "%s: S*k does not fit int32", fn);
-    if ((rc = check_rows(fn, dtype, d)) != TAMOE_OK) return rc;
+    int cpr = 0;   // 16-byte chunks per row
+    if ((rc = check_rows(fn, dtype, d, &cpr)) != TAMOE_OK) return rc;
     if (S == 0) return TAMOE_OK;
     if (K_rows > 0 && (rc = check_ptr(fn, weighted ? "recv" : "d_send", recv, 16)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "slot", slot, 4)) != TAMOE_OK) return rc;
     if (weighted && (rc = check_ptr(fn, "topk_w", topk_w, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, weighted ? "y" : "d_x", y, 16)) != TAMOE_OK) return rc;
-    const int cpr = d * elem_bytes(dtype) / 16;  // 16-byte chunks per row
     if (ceil_div(S * (int64_t)cpr, kThreads * 1) > 0x7fffffff ||
         (rows_by_wave(cpr) && ceil_div(S * (int64_t)row_waves(cpr), kThreads / 64) > 0x7fffffff))
         return fail(TAMOE_UNSUPPORTED, "%s: the output is too large for one launch", fn);

@@ -262,12 +262,11 @@ static void launch_dispatch_copy(const void* x, const int32_t* slot, int64_t S, 
 
 // tile_count: device scratch of k * count_tiles(S) * N ints; every entry is written by the count
 // kernel before it is read, so its content on entry does not matter.
-static int dispatch_in_scratch(const char* fn, const void* x, const int32_t* topk_idx, const int32_t* cap, int dtype,
-                               int64_t S, int d, int N, int P, int k, void* send, int32_t* slot, int32_t* kept_expert,
+static int dispatch_in_scratch(const char* fn, const void* x, const int32_t* topk_idx, const int32_t* cap, int64_t S,
+                               int cpr, int N, int P, int k, void* send, int32_t* slot, int32_t* kept_expert,
                                int32_t* expert_offset, int32_t* send_count_dev, int32_t* tile_count, void* stream) {
     int rc;
     const int64_t n_ct = count_tiles(S);
-    const int cpr = d * elem_bytes(dtype) / 16;  // 16-byte chunks per row
     if (S > 0 && ceil_div(S * (int64_t)cpr, kThreads * 1) > 0x7fffffff)
         return fail(TAMOE_UNSUPPORTED, "%s: x is too large for one launch", fn);
 
@@ -333,9 +332,9 @@ extern "C" int tamoe_dispatch_static(const void* x, const int32_t* topk_idx, con
                                      void* stream) {
     const char* fn = "tamoe_dispatch_static";
     clear_error();
-    int rc;
+    int rc, cpr = 0;   // 16-byte chunks per row
     if ((rc = check_shape(fn, S, N, P, k)) != TAMOE_OK) return rc;
-    if ((rc = check_rows(fn, dtype, d)) != TAMOE_OK) return rc;
+    if ((rc = check_rows(fn, dtype, d, &cpr)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "cap", cap, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "kept_expert", kept_expert, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "expert_offset", expert_offset, 4)) != TAMOE_OK) return rc;
@@ -354,7 +353,7 @@ extern "C" int tamoe_dispatch_static(const void* x, const int32_t* topk_idx, con
                     fn, kCountTile, (long long)entries, (int)(TAMOE_STATIC_SCRATCH_BYTES / sizeof(int32_t)));
     int32_t* tile_count = nullptr;
     if ((rc = static_scratch(fn, &tile_count)) != TAMOE_OK) return rc;
-    return dispatch_in_scratch(fn, x, topk_idx, cap, dtype, S, d, N, P, k, send, slot, kept_expert, expert_offset,
+    return dispatch_in_scratch(fn, x, topk_idx, cap, S, cpr, N, P, k, send, slot, kept_expert, expert_offset,
                                send_count_dev, tile_count, stream);
 }
 
@@ -364,9 +363,9 @@ extern "C" int tamoe_dispatch(const void* x, const int32_t* topk_idx, const int3
                               void* stream) {
     const char* fn = "tamoe_dispatch";
     clear_error();
-    int rc;
+    int rc, cpr = 0;   // 16-byte chunks per row
     if ((rc = check_shape(fn, S, N, P, k)) != TAMOE_OK) return rc;
-    if ((rc = check_rows(fn, dtype, d)) != TAMOE_OK) return rc;
+    if ((rc = check_rows(fn, dtype, d, &cpr)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "cap", cap, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "kept_expert", kept_expert, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "expert_offset", expert_offset, 4)) != TAMOE_OK) return rc;
@@ -381,7 +380,7 @@ extern "C" int tamoe_dispatch(const void* x, const int32_t* topk_idx, const int3
     const Workspace lay = workspace_layout(S, N, k);
     if (ws_bytes < lay.total)
         return fail(TAMOE_WORKSPACE_TOO_SMALL, "%s: workspace has %zu bytes, %zu needed", fn, ws_bytes, lay.total);
-    return run_dispatch(fn, x, topk_idx, cap, dtype, S, d, N, P, k, 0, send, slot, kept_expert, expert_offset,
+    return run_dispatch(fn, x, topk_idx, cap, S, cpr, N, P, k, 0, send, slot, kept_expert, expert_offset,
                         send_count_dev, ws, lay, static_cast<hipStream_t>(stream));
 }
 
@@ -390,9 +389,9 @@ extern "C" int tamoe_dispatch_padded(const void* x, const int32_t* topk_idx, con
                                      int32_t* kept_expert, void* ws, size_t ws_bytes, void* stream) {
     const char* fn = "tamoe_dispatch_padded";
     clear_error();
-    int rc;
+    int rc, cpr = 0;   // 16-byte chunks per row
     if ((rc = check_shape(fn, S, N, P, k)) != TAMOE_OK) return rc;
-    if ((rc = check_rows(fn, dtype, d)) != TAMOE_OK) return rc;
+    if ((rc = check_rows(fn, dtype, d, &cpr)) != TAMOE_OK) return rc;
     if (C <= 0 || (int64_t)N * C >= ((int64_t)1 << 31))
         return fail(TAMOE_INVALID_ARG, "%s: C = %d, N*C must lie in (0, 2^31)", fn, C);
     if (cap != nullptr && (rc = check_ptr(fn, "cap", cap, 4)) != TAMOE_OK) return rc;
@@ -407,6 +406,6 @@ extern "C" int tamoe_dispatch_padded(const void* x, const int32_t* topk_idx, con
     const Workspace lay = workspace_layout(S, N, k);
     if (ws_bytes < lay.total)
         return fail(TAMOE_WORKSPACE_TOO_SMALL, "%s: workspace has %zu bytes, %zu needed", fn, ws_bytes, lay.total);
-    return run_dispatch(fn, x, topk_idx, cap, dtype, S, d, N, P, k, C, send, slot, kept_expert, nullptr, nullptr, ws, lay,
+    return run_dispatch(fn, x, topk_idx, cap, S, cpr, N, P, k, C, send, slot, kept_expert, nullptr, nullptr, ws, lay,
                         static_cast<hipStream_t>(stream));
 }

@@ -76,6 +76,15 @@ int check_rows(const char* fn, int dtype, int d) {
     return TAMOE_OK;
 }
 
+int check_rows(const char* fn, int dtype, int d, int* cpr) {
+    const int rc = check_rows(fn, dtype, d);
+    if (rc != TAMOE_OK) return rc;
+    const int64_t chunks = (int64_t)d * elem_bytes(dtype) / 16;
+    if (chunks >= (int64_t)1 << 27) return fail(TAMOE_UNSUPPORTED, "%s: a row of d = %d elements has 2 GiB or more", fn, d);
+    *cpr = (int)chunks;
+    return TAMOE_OK;
+}
+
 int check_ptr(const char* fn, const char* name, const void* p, size_t align) {
     if (p == nullptr) return fail(TAMOE_INVALID_ARG, "%s: %s is NULL", fn, name);
     if (align > 1 && (reinterpret_cast<uintptr_t>(p) % align) != 0)

@@ -73,8 +73,8 @@ int run_select_stage(const char* fn, const float* logits, int64_t S, int N, int 
                      void* ws, const Workspace& lay, hipStream_t st, GateRun* run);
 // The dispatch of a routing that is given, arguments already checked: packed rows (pad_C == 0) or pad_C rows
 // per expert (then expert_offset and send_count_dev may be NULL).  ws: laid out as `lay`.
-int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const int32_t* cap, int dtype, int64_t S,
-                 int d, int N, int P, int k, int pad_C, void* send, int32_t* slot, int32_t* kept_expert,
+int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const int32_t* cap, int64_t S, int cpr, int N,
+                 int P, int k, int pad_C, void* send, int32_t* slot, int32_t* kept_expert,
                  int32_t* expert_offset, int32_t* send_count_dev, void* ws, const Workspace& lay, hipStream_t st);
 int check_select_outputs(const char* fn, int64_t S, int32_t* topk_idx, float* topk_w, float* m, int32_t* c_expert,
                          int32_t* c_device, void* ws, size_t ws_bytes, const Workspace& lay);
@@ -125,8 +125,8 @@ __device__ __forceinline__ void split_chunk(int64_t c, int64_t total, int cpr, i
 // last one with idle lanes unless the row is a multiple of 1 KiB.  A wavefront then has one token, whose
 // slots and weights go through the scalar unit, nothing is divided per lane, and a row is a buffer of its
 // own (RowBuffer).  A flat layout of chunks over lanes has none of this, and gains only where most of a
-// wavefront would idle (shorter rows).  (A buffer holds less than 2 GiB; longer rows go the flat way too.)
-inline bool rows_by_wave(int cpr) { return cpr >= 64 && cpr < (1 << 27); }
+// wavefront would idle (shorter rows).
+inline bool rows_by_wave(int cpr) { return cpr >= 64; }
 inline int row_waves(int cpr) { return (cpr + 63) / 64; }
 // Wavefront wv of a launch -> row and segment of 64 chunks in it.  shift: pow2_shift(wpr).  The rows of one
 // device's memory are fewer than 2^31 wavefronts.
@@ -157,18 +157,21 @@ struct RowBuffer {
     __device__ __forceinline__ RowBuffer(const void* row, int cpr, bool present)
         : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, present ? cpr * 16 : 0, 0x00020000)) {}
     __device__ __forceinline__ vec16 load(int col) const {                     // streaming
-        return __builtin_bit_cast(vec16, __builtin_amdgcn_raw_buffer_load_b128(rsrc, col * 16, 0, 2));
+        return __builtin_bit_cast(vec16, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)((uint32_t)col * 16u), 0, 2));
     }
     template <bool STREAM>
     __device__ __forceinline__ void store(int col, vec16 v) const {
         typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, col * 16, 0, STREAM ? 2 : 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, (int)((uint32_t)col * 16u), 0, STREAM ? 2 : 0);
     }
 };
 
 // Common argument checks.  Return TAMOE_OK or a failure already recorded with fail().
 int check_shape(const char* fn, int64_t S, int N, int P, int k);
 int check_rows(const char* fn, int dtype, int d);
+// check_rows for the row movers, with the number of 16-byte chunks per row: below 2^27 (a RowBuffer and its
+// byte offsets hold less than 2 GiB).
+int check_rows(const char* fn, int dtype, int d, int* cpr);
 int check_ptr(const char* fn, const char* name, const void* p, size_t align);
 int check_launch(const char* fn, const char* kernel);
 

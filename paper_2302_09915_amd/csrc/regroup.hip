@@ -161,7 +161,8 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
         return fail(TAMOE_UNSUPPORTED, "%s: P*E = %lld exceeds the limit of %d segments", fn, (long long)P * E, kMaxSeg);
     if (cap_rows < 0 || cap_rows >= ((int64_t)1 << 31))
         return fail(TAMOE_INVALID_ARG, "%s: cap_rows = %lld outside [0, 2^31)", fn, (long long)cap_rows);
-    if ((rc = check_rows(fn, dtype, d)) != TAMOE_OK) return rc;
+    int cpr = 0;   // 16-byte chunks per row
+    if ((rc = check_rows(fn, dtype, d, &cpr)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "recv_count", recv_count, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "ws", ws, 256)) != TAMOE_OK) return rc;
     const size_t need = 2 * (kMaxSeg + 1) * sizeof(int32_t);
@@ -171,7 +172,6 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
         if ((rc = check_ptr(fn, "out", out, 16)) != TAMOE_OK) return rc;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int cpr = d * elem_bytes(dtype) / 16;
     // two chunks per thread: the tables are made once per 8 KiB instead of once per 4 KiB
     // (2 GiB: 377 -> 341 us; four chunks: 350 us)
     constexpr int U = 2;

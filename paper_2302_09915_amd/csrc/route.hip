@@ -587,11 +587,10 @@ static int run_copy(const char* fn, const GateRun& run, RouteArgs a, const char*
     return check_launch(fn, "route_copy_kernel");
 }
 
-int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const int32_t* cap, int dtype, int64_t S,
-                 int d, int N, int P, int k, int pad_C, void* send, int32_t* slot, int32_t* kept_expert,
+int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const int32_t* cap, int64_t S, int cpr, int N,
+                 int P, int k, int pad_C, void* send, int32_t* slot, int32_t* kept_expert,
                  int32_t* expert_offset, int32_t* send_count_dev, void* ws, const Workspace& lay, hipStream_t st) {
     int rc;
-    const int cpr = d * elem_bytes(dtype) / 16;  // 16-byte chunks per row
     // a few more workgroups are added
     if (S > 0 && std::max(ceil_div(S * (int64_t)cpr, kCopyThreads), copy_workgroups(S, cpr, k)) >= 0x7fff0000)
         return fail(TAMOE_UNSUPPORTED, "%s: x is too large for one launch", fn);
@@ -644,9 +643,9 @@ extern "C" int tamoe_gate_dispatch(const void* x, const void* w, int dtype, int6
                                    int32_t* send_count_dev, void* ws, size_t ws_bytes, void* stream) {
     const char* fn = "tamoe_gate_dispatch";
     clear_error();
-    int rc;
+    int rc, cpr = 0;   // 16-byte chunks per row
     if ((rc = check_shape(fn, S, N, P, k)) != TAMOE_OK) return rc;
-    if ((rc = check_rows(fn, dtype, d)) != TAMOE_OK) return rc;
+    if ((rc = check_rows(fn, dtype, d, &cpr)) != TAMOE_OK) return rc;
     if (S > 0) {
         if ((rc = check_ptr(fn, "x", x, 16)) != TAMOE_OK) return rc;
         if ((rc = check_ptr(fn, "w", w, 16)) != TAMOE_OK) return rc;
@@ -662,7 +661,6 @@ extern "C" int tamoe_gate_dispatch(const void* x, const void* w, int dtype, int6
     const Workspace lay = workspace_layout(S, N, k);
     if ((rc = check_select_outputs(fn, S, topk_idx, topk_w, m, c_expert, c_device, ws, ws_bytes, lay)) != TAMOE_OK)
         return rc;
-    const int cpr = d * elem_bytes(dtype) / 16;  // 16-byte chunks per row
     // one more workgroup is added
     if (S > 0 && std::max(ceil_div(S * (int64_t)cpr, kCopyThreads), copy_workgroups(S, cpr, k)) >= 0x7fffffff)
         return fail(TAMOE_UNSUPPORTED, "%s: x is too large for one launch", fn);

@@ -256,6 +256,24 @@ def test_device_entry_points_reject_bad_shapes_without_a_gpu(T):
            T.WORKSPACE_TOO_SMALL, "needed")
 
 
+@pytest.mark.parametrize("dtype,d", [(1, 1 << 30), (2, (1 << 30) + 64), (0, 1 << 29), (1, 0x7ffffff8), (0, 0x7ffffffc)])
+def test_row_movers_refuse_rows_of_2_gib(T, dtype, d):
+    """The size of such a row in bytes is no 32-bit number; below it the rows are accepted."""
+    L, one, big = T.lib(), ctypes.c_void_p(256), 1 << 30
+    for rc in (L.tamoe_combine(one, 10, one, one, dtype, 3, d, 2, one, None),
+               L.tamoe_combine_bwd(one, one, 10, one, one, dtype, 3, d, 2, one, one, None),
+               L.tamoe_dispatch_bwd(one, 10, one, dtype, 3, d, 2, one, None),
+               L.tamoe_dispatch(one, one, one, dtype, 3, d, 8, 4, 2, one, one, one, one, one, one, big, None),
+               L.tamoe_dispatch_static(one, one, one, dtype, 3, d, 8, 4, 2, one, one, one, one, one, None),
+               L.tamoe_dispatch_padded(one, one, None, dtype, 3, d, 8, 4, 2, 2, one, one, one, one, big, None),
+               L.tamoe_gate_dispatch(one, one, dtype, 3, d, 8, 4, 2, None, one, None, one, one, one, one, one, one, one, one, one,
+                                     one, one, one, big, None),
+               L.tamoe_regroup(one, one, 4, 2, dtype, d, 3, 1, one, None, one, big, None)):
+        assert rc == T.UNSUPPORTED and "2 GiB" in T.tamoe_last_error(), (rc, T.tamoe_last_error())
+    # just below: the next check answers (S = 0 returns before anything else)
+    assert L.tamoe_combine(one, 10, one, one, dtype, 0, (1 << 29) - 4 if dtype == 0 else (1 << 30) - 8, 2, one, None) == T.OK
+
+
 def test_workspace_size_is_monotone_and_covers_the_configs(T):
     prev = 0
     for S in (0, 1, 100, 4096, 65536):
