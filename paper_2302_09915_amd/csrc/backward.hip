@@ -323,6 +323,7 @@ extern "C" int tamoe_combine_bwd(const void* dy, const void* recv, int64_t K_row
     if ((rc = check_ptr(fn, "d_topk_w", d_topk_w, 4)) != TAMOE_OK) return rc;
     if (S > 0x7fffffff) return fail(TAMOE_UNSUPPORTED, "%s: too many tokens for one launch", fn);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    K_rows = slot_bound(K_rows);
     if (dtype == TAMOE_F32)
         launch_combine_bwd<TAMOE_F32>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_topk_w, st);
     else if (dtype == TAMOE_F16)

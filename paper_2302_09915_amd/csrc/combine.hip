@@ -186,6 +186,7 @@ static int combine_entry(const char* fn, const void* recv, int64_t K_rows, const
         (rows_by_wave(cpr) && ceil_div(S * (int64_t)row_waves(cpr), kThreads / 64) > 0x7fffffff))
         return fail(TAMOE_UNSUPPORTED, "%s: the output is too large for one launch", fn);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    K_rows = slot_bound(K_rows);
     if (weighted)
         launch_combine_typed<false>(dtype, recv, K_rows, slot, topk_w, S, k, cpr, y, st);
     else   // unit weights (tamoe_dispatch_bwd)

@@ -147,6 +147,10 @@ __device__ __forceinline__ int32_t pair_limit(const int32_t* __restrict__ cap, i
     return pair_limit(cap != nullptr ? cap[e] : 0, cap != nullptr, pad_C);
 }
 
+// Rows that a slot can name: the kernels compare slots as unsigned numbers, so that one comparison leaves out a dropped
+// pair (-1) too, whatever bound the caller gives.
+inline int64_t slot_bound(int64_t K_rows) { return K_rows < (int64_t)1 << 31 ? K_rows : (int64_t)1 << 31; }
+
 // A row as a buffer resource: the hardware returns zeros for a load and drops a store outside its `cpr`
 // chunks, and a row that is not there (present == false) has none.  Lanes beyond the end of a row and
 // dropped pairs need no branch then, and cost no memory access.  With a branch around each load the k

@@ -120,6 +120,31 @@ def test_infinities_stay_with_their_pairs(T, dtype, k):
         assert torch.isfinite(y).all() and (y[:6] == 0).all()
 
 
+@pytest.mark.parametrize("chunks", [5, 64, 200])
+def test_dropped_pairs_under_any_bound(T, chunks):
+    """K_rows beyond the range of a slot (a caller without a bound): -1 and other negative slots stay dropped."""
+    S, k, d = 33, 3, chunks * 8
+    g = torch.Generator(device="cuda").manual_seed(chunks)
+    recv = torch.randn(S * k, d, generator=g, device="cuda").bfloat16()
+    dy = torch.randn(S, d, generator=g, device="cuda").bfloat16()
+    w = torch.rand(S, k, generator=g, device="cuda")
+    slot = torch.randperm(S * k, generator=g, device="cuda").int().reshape(S, k)
+    slot[::2, 1], slot[::3, 0], slot[5] = -1, -(1 << 31), -7
+
+    def run(K_rows):
+        y, dx, d_recv, d_w = torch.empty_like(dy), torch.empty_like(dy), torch.full_like(recv, 7.0), torch.empty_like(w)
+        L, st, p = T.lib(), torch.cuda.current_stream().cuda_stream, torch.Tensor.data_ptr
+        assert L.tamoe_combine(p(recv), K_rows, p(slot), p(w), T.BF16, S, d, k, p(y), st) == T.OK
+        assert L.tamoe_dispatch_bwd(p(recv), K_rows, p(slot), T.BF16, S, d, k, p(dx), st) == T.OK
+        assert L.tamoe_combine_bwd(p(dy), p(recv), K_rows, p(slot), p(w), T.BF16, S, d, k, p(d_recv), p(d_w), st) == T.OK
+        return y, dx, d_recv, d_w
+
+    want = run(S * k)
+    for bound in (1 << 31, 1 << 32, (1 << 32) + 5, (1 << 63) - 1):
+        for a, b in zip(run(bound), want):
+            assert torch.equal(a, b), bound
+
+
 @pytest.mark.parametrize("P,E,chunks,mean", [(1, 1, 1, 3), (3, 2, 63, 4), (64, 2, 64, 3), (2, 64, 65, 2), (5, 7, 128, 0.3), (128, 1, 8, 5),
                                              (16, 4, 129, 20)])
 @pytest.mark.parametrize("clip", [0, 7])
