@@ -39,7 +39,7 @@ def bench_sources():
 
 def _headers():
     return (glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
-            + glob.glob(os.path.join(BENCH_CSRC, "*.h")))
+            + glob.glob(os.path.join(BENCH_CSRC, "*.h")) + glob.glob(os.path.join(os.path.dirname(NATIVE_SRC), "*.h")))
 
 
 def _fresh(obj: str, src: str) -> bool:

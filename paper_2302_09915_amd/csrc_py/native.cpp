@@ -17,6 +17,7 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 
 #include "tamoe.h"
+#include "unlocked.h"
 
 namespace {
 
@@ -113,7 +114,9 @@ struct Out {
 
 struct Dict {
     PyObject* d = PyDict_New();
-    ~Dict() { Py_XDECREF(d); }
+    ~Dict() {
+        if (d != nullptr && PyGILState_Check()) Py_DECREF(d);   // not in a thread that the interpreter ends (unlocked)
+    }
     void put(const char* key, const at::Tensor& t) { put(key, THPVariable_Wrap(t)); }
     void none(const char* key) { put(key, Py_NewRef(Py_None)); }
     void put(const char* key, PyObject* v) {
@@ -128,17 +131,6 @@ struct Dict {
     }
 };
 
-// Runs a C entry point or an allocation without the interpreter lock, as ctypes and torch's own binding do (another
-// thread may need the lock to leave the allocator).
-template <class F>
-auto unlocked(F call) {
-    struct Release {
-        PyThreadState* state = PyEval_SaveThread();
-        ~Release() { PyEval_RestoreThread(state); }
-    } release;
-    return call();
-}
-
 // a workspace that is given, or a new one
 at::Tensor workspace(PyObject* ws, int64_t S, int d, int N, int P, int k, int dtype, const Out& o) {
     if (ws != Py_None) return tensor(ws, at::kByte);
@@ -150,6 +142,8 @@ PyObject* guarded(Py_ssize_t n, Py_ssize_t want, F body) {
     if (n == want && !at::impl::torch_function_mode_enabled() && !c10::impl::dispatch_mode_enabled()) {
         try {
             return body();
+        } catch (abi::__forced_unwind&) {   // the thread is being ended (unlocked)
+            throw;
         } catch (...) {   // Slow, or an error of the allocator: the Python path meets it again
         }
         PyErr_Clear();

@@ -1,4 +1,10 @@
 """The native half of the binding against the Python path: same results bit for bit, same errors."""
+import os
+import shutil
+import subprocess
+import sys
+import sysconfig
+
 import numpy as np
 import pytest
 import torch
@@ -30,6 +36,40 @@ def test_host_tensors_raise_as_before():
         with pytest.raises(T.TamoeError, match="must be a device tensor") as e:
             call()
         assert e.value.status == T.INVALID_ARG
+
+
+def test_daemon_threads_at_the_end_of_the_interpreter(tmp_path):
+    """Threads that are outside the interpreter lock when the program ends do not abort it."""
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("g++ not found")
+    src = tmp_path / "spin.cpp"
+    src.write_text('''
+#include "unlocked.h"
+#include <stdexcept>
+#include <unistd.h>
+static PyObject* spin(PyObject*, PyObject* fail) {
+    try {
+        unlocked([&] { usleep(2000); if (fail != Py_None) throw std::runtime_error(""); return 0; });
+    } catch (abi::__forced_unwind&) { throw;
+    } catch (...) { return PyLong_FromLong(1); }
+    Py_RETURN_NONE;
+}
+static PyMethodDef m[] = {{"spin", spin, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+static PyModuleDef d = {PyModuleDef_HEAD_INIT, "spin", nullptr, -1, m, nullptr, nullptr, nullptr, nullptr};
+PyMODINIT_FUNC PyInit_spin() { return PyModule_Create(&d); }
+''')
+    here = os.path.join(os.path.dirname(T.__file__), "csrc_py")
+    subprocess.run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-I", here, "-I", sysconfig.get_paths()["include"], str(src),
+                    "-o", str(tmp_path / "spin.so")], check=True)
+    prog = ("import threading, time, spin\n"
+            "assert spin.spin(None) is None and spin.spin(1) == 1\n"
+            "def f(x):\n    while True: spin.spin(x)\n"
+            "for i in range(8): threading.Thread(target=f, args=(None if i % 2 else 1,), daemon=True).start()\n"
+            "time.sleep(0.05)\n")
+    for _ in range(3):
+        r = subprocess.run([sys.executable, "-c", prog], cwd=tmp_path, capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr
 
 
 def _layer(dtype, S, d, N, P, k, stream=None):
