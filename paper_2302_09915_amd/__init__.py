@@ -8,13 +8,16 @@ not been built, importing the binding's functions raises.
 The helpers without the prefix (gate, dispatch, combine, ...) only allocate the output tensors
 with torch.empty and call the tamoe_* function.  Those of the layer (gate, aux_loss, dispatch, gate_dispatch,
 combine) and the entry points of its backward first try the same call in native code (csrc_py/native.cpp), which
-leaves anything out of the ordinary to the code here.
+leaves anything out of the ordinary to the code here.  That half is built for one Python and one torch; where it is
+missing or does not fit, a warning is given once and the code here does all the work.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 import threading
+import warnings
 from typing import Dict, Optional
 
 import numpy as np
@@ -178,20 +181,31 @@ def lib() -> ctypes.CDLL:
     return L
 
 
-_native_half = None
+_native_half = None     # the module, or False where there is none that fits
+
+
+def _load_native_half():
+    try:
+        native = importlib.import_module("._native", __name__)
+        if native.torch_version == torch.__version__:
+            return native
+        why = f"it was built for torch {native.torch_version}, this is {torch.__version__}"
+    except (ImportError, AttributeError) as e:
+        why = str(e)
+    warnings.warn(f"the native half of the binding is not used, calls take longer on the host: {why}", RuntimeWarning,
+                  stacklevel=3)
+    return False
 
 
 def _fast():
-    """The native half of the binding; None while bind() records a call."""
+    """The native half of the binding; None while bind() records a call, and where there is none."""
     global _native_half
     if getattr(_bind_state, "recorder", None) is not None:
         return None
     if _native_half is None:
         lib()
-        from . import _native
-
-        _native_half = _native
-    return _native_half
+        _native_half = _load_native_half()
+    return _native_half or None
 
 
 def _done(r):

@@ -16,9 +16,9 @@ LIB = os.path.join(HERE, "libtamoe.so")
 # yardstick kernels that only bench.py calls: a library of their own, nothing shared with libtamoe.so
 BENCH_CSRC = os.path.join(HERE, "csrc_bench")
 BENCH_LIB = os.path.join(HERE, "libtamoe_bench.so")
-# native half of the Python binding: host code over torch's C++ tensors that links libtamoe.so
+# native half of the Python binding: host code over torch's C++ tensors that links libtamoe.so, for this Python
 NATIVE_SRC = os.path.join(HERE, "csrc_py", "native.cpp")
-NATIVE_LIB = os.path.join(HERE, "_native.so")
+NATIVE_LIB = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -50,6 +50,12 @@ def _fresh(obj: str, src: str) -> bool:
     return all(os.path.getmtime(f) < t for f in [src, *_headers()])
 
 
+def _run(cmd, verbose: bool) -> subprocess.CompletedProcess:
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    return subprocess.run(cmd, capture_output=True, text=True)
+
+
 def _compile(hipcc: str, src: str, verbose: bool, incremental: bool = False):
     obj = os.path.join(OBJ_DIR, os.path.basename(src) + ".o")
     if incremental and _fresh(obj, src):
@@ -57,10 +63,7 @@ def _compile(hipcc: str, src: str, verbose: bool, incremental: bool = False):
     # .cpp files hold host code only but share the HIP headers
     inc = ["-I", BENCH_CSRC] if os.path.dirname(src) == BENCH_CSRC else ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     cmd = [hipcc, *HIPCC_FLAGS, *inc, "-x", "hip", "-c", src, "-o", obj]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    return obj, res
+    return obj, _run(cmd, verbose)
 
 
 def _torch_dir() -> str:
@@ -69,19 +72,48 @@ def _torch_dir() -> str:
     return os.path.dirname(torch.__file__)
 
 
+def _native_object() -> str:
+    """Named after everything outside the sources that the code in it depends on."""
+    import torch
+
+    abi = int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    return os.path.join(OBJ_DIR, f"native-{sys.implementation.cache_tag}-torch-{torch.__version__}-abi{abi}.o")
+
+
 def _compile_native(verbose: bool, incremental: bool = False):
     import torch
 
-    obj = os.path.join(OBJ_DIR, "native.cpp.o")
+    obj = _native_object()
     if incremental and _fresh(obj, NATIVE_SRC):
         return obj, subprocess.CompletedProcess([], 0, "", "")
     cmd = [shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-Wall",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DTAMOE_TORCH_VERSION="{torch.__version__}"', "-I", os.path.join(ROOT, "include"),
            "-isystem", os.path.join(_torch_dir(), "include"), "-isystem", sysconfig.get_paths()["include"],
            "-c", NATIVE_SRC, "-o", obj]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    return obj, subprocess.run(cmd, capture_output=True, text=True)
+    return obj, _run(cmd, verbose)
+
+
+def _link_native(obj: str, verbose: bool) -> subprocess.CompletedProcess:
+    return _run([shutil.which("g++") or "c++", "-shared", "-L", HERE, "-L", os.path.join(_torch_dir(), "lib"),
+                 "-Wl,-rpath,$ORIGIN", obj, "-ltamoe", "-ltorch_cpu", "-lc10", "-ltorch_python", "-o", NATIVE_LIB], verbose)
+
+
+def _finish_native(compiled, verbose: bool) -> None:
+    """Links the native half of the binding.  Without it the binding works, so what stands in the way of it (no g++,
+    no headers of torch or Python) is reported and does not fail the build; an older one does not stay behind."""
+    for old in (NATIVE_LIB, os.path.join(HERE, "_native.so")):   # the latter: any Python would load it
+        if os.path.exists(old):
+            os.remove(old)
+    try:
+        obj, res = compiled.result()
+        if res.returncode == 0:
+            res = _link_native(obj, verbose)
+        why = res.stdout + res.stderr if res.returncode != 0 else ""
+    except (ImportError, AttributeError, OSError) as e:
+        why = f"{type(e).__name__}: {e}\n"
+    if why:
+        sys.stderr.write(f"{why}the native half of the binding was not built\n")
 
 
 def build(verbose: bool = False, jobs: int = 0, incremental: bool = False) -> str:
@@ -97,28 +129,20 @@ def build(verbose: bool = False, jobs: int = 0, incremental: bool = False) -> st
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         native = pool.submit(_compile_native, verbose, incremental)
         done = list(pool.map(lambda src: _compile(hipcc, src, verbose, incremental), srcs))
-        done.append(native.result())
-    objs, bench_objs, native_objs = [], [], []
-    for src, (obj, res) in zip([*srcs, NATIVE_SRC], done):
+    objs, bench_objs = [], []
+    for src, (obj, res) in zip(srcs, done):
         if res.returncode != 0:
             sys.stderr.write(res.stdout + res.stderr)
-            raise RuntimeError(f"the compiler failed on {src}")
+            raise RuntimeError(f"hipcc failed compiling {src}")
         if verbose and res.stderr.strip():
             sys.stderr.write(res.stderr)
-        (native_objs if src == NATIVE_SRC else bench_objs if os.path.dirname(src) == BENCH_CSRC else objs).append(obj)
-    hip_link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"]
-    native_link = [shutil.which("g++") or "c++", "-shared", "-L", HERE, "-L", os.path.join(_torch_dir(), "lib"),
-                   "-Wl,-rpath,$ORIGIN"]
-    native_libs = ["-ltamoe", "-ltorch_cpu", "-lc10", "-ltorch_python"]
-    for out, linker, parts in ((LIB, hip_link, objs), (BENCH_LIB, hip_link, bench_objs),
-                               (NATIVE_LIB, native_link, [*native_objs, *native_libs])):
-        link = [*linker, *parts, "-o", out]
-        if verbose:
-            print(" ".join(link), flush=True)
-        res = subprocess.run(link, capture_output=True, text=True)
+        (bench_objs if os.path.dirname(src) == BENCH_CSRC else objs).append(obj)
+    for out, parts in ((LIB, objs), (BENCH_LIB, bench_objs)):
+        res = _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *parts, "-o", out], verbose)
         if res.returncode != 0:
             sys.stderr.write(res.stdout + res.stderr)
-            raise RuntimeError(f"linking {out} failed")
+            raise RuntimeError(f"hipcc failed linking {out}")
+    _finish_native(native, verbose)
     return LIB
 
 

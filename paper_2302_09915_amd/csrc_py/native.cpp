@@ -397,5 +397,7 @@ PyMODINIT_FUNC PyInit__native() {
     g_raw_stream = attribute("torch._C", "_cuda_getCurrentRawStream");
     g_device = attribute("torch._C", "_cuda_getDevice");
     PyErr_Clear();
-    return PyModule_Create(&g_module);
+    PyObject* m = PyModule_Create(&g_module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", TAMOE_TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
 }

@@ -4,6 +4,8 @@ import shutil
 import subprocess
 import sys
 import sysconfig
+import types
+import warnings
 
 import numpy as np
 import pytest
@@ -36,6 +38,40 @@ def test_host_tensors_raise_as_before():
         with pytest.raises(T.TamoeError, match="must be a device tensor") as e:
             call()
         assert e.value.status == T.INVALID_ARG
+
+
+@pytest.mark.parametrize("stand_in", [None, types.SimpleNamespace(torch_version="0.0"), types.SimpleNamespace()])
+def test_works_without_a_native_half_that_fits(stand_in, monkeypatch):
+    """Missing, of another torch or of an older build: one warning, then the Python path answers."""
+    monkeypatch.setitem(sys.modules, "paper_2302_09915_amd._native", stand_in)
+    monkeypatch.setattr(T, "_native_half", None)
+    with pytest.warns(RuntimeWarning, match="native half"):
+        assert T._fast() is None
+    f, i = torch.zeros(4, 4), torch.zeros(4, 2, dtype=torch.int32)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        for call in (lambda: T.gate(f, f, 2, 2, ws=f), lambda: T.aux_loss(f[0], i, None, 2, 4), lambda: T.dispatch(f, i, i, 4, 2, ws=f),
+                     lambda: T.combine(f, 4, i, f), lambda: T.tamoe_combine_bwd(f, f, 4, i, f, f, f)):
+            with pytest.raises(T.TamoeError, match="must be a device tensor"):
+                call()
+
+
+def test_build_without_a_host_compiler(tmp_path, monkeypatch):
+    """The library is built and a stale native half does not stay; its object depends on torch and Python."""
+    from concurrent.futures import Future
+
+    from paper_2302_09915_amd import build as B
+
+    assert torch.__version__ in B._native_object() and sys.implementation.cache_tag in B._native_object()
+    for name, path in (("HERE", str(tmp_path)), ("NATIVE_LIB", str(tmp_path / "_native.so.tagged"))):
+        monkeypatch.setattr(B, name, path)
+    for result in (("x.o", subprocess.CompletedProcess([], 1, "", "no headers\n")), FileNotFoundError("c++"), ImportError("torch")):
+        for stale in ("_native.so", "_native.so.tagged"):
+            (tmp_path / stale).write_text("old")
+        done = Future()
+        done.set_exception(result) if isinstance(result, Exception) else done.set_result(result)
+        B._finish_native(done, False)
+        assert os.listdir(tmp_path) == []
 
 
 def test_daemon_threads_at_the_end_of_the_interpreter(tmp_path):
