@@ -136,20 +136,37 @@ def _layer(dtype, S, d, N, P, k, stream=None):
     return out
 
 
+def _count_answers(monkeypatch):
+    """Calls of every native function that were not left to the Python path."""
+    native, answered = T._fast(), {name: 0 for name in CALLS}
+
+    class Proxy:
+        def __getattr__(self, name):
+            def call(*args):
+                r = getattr(native, name)(*args)
+                answered[name] += r is not NotImplemented
+                return r
+            return call
+
+    monkeypatch.setattr(T, "_fast", lambda: Proxy())
+    return answered
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", [(1, 8, 2, 2, 1), (333, 40, 12, 4, 3), (1024, 256, 64, 8, 2)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
 def test_same_as_the_python_path(dtype, shape, monkeypatch):
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
+    answered = _count_answers(monkeypatch)
     fast = [_layer(dtype, *shape), _layer(dtype, *shape, stream=side), _layer(dtype, *shape, stream=side.cuda_stream)]
     with torch.cuda.stream(side):
         fast.append(_layer(dtype, *shape))
+    assert answered == {name: 4 for name in CALLS}      # the native half made every call, four layers long
     seen = []
-    real = T._fast()
-    monkeypatch.setattr(T, "_fast", lambda: seen.append(real) or None)
+    monkeypatch.setattr(T, "_fast", lambda: seen.append(0) or None)
     slow = _layer(dtype, *shape)
-    assert len(seen) == len(CALLS)
+    assert len(seen) == len(CALLS) and answered == {name: 4 for name in CALLS}
     for out in fast:
         assert list(out) == list(slow)
         for n, v in slow.items():
