@@ -14,7 +14,7 @@ constexpr int kThreads = 256;
 
 // KK > 0: k is the compile-time constant KK; KK == 0: any k up to TAMOE_MAX_K.
 // UNITW: every weight is 1 (the transpose of the scatter: dx[t] = sum of the rows its slots name).
-// Rows by whole wavefronts (rows_by_wave), U segments of 64 chunks each: all slots, weights and rows of
+// Rows by whole wavefronts (combine_by_wave), U segments of 64 chunks each: all slots, weights and rows of
 // a token are requested without a branch between them.
 template <int DT, int KK, int U, bool UNITW>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restrict__ recv, int64_t K_rows,
@@ -60,6 +60,17 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restri
         for (int j = 0; j < KM; ++j) Chunk<DT>::fma(acc, wgt[u][j], v[u][j]);
         RowBuffer(y + (size_t)tok[u] * cpr, cpr, true).template store<true>(col[u], Chunk<DT>::pack(acc));
     }
+}
+
+// By wavefront or flat?  A row just over one or two wavefronts leaves most of its last one idle, and with few
+// choices that wavefront's look-ups and weights are the larger part of its work: 65536 rows of 1040 bytes, two choices
+// 40.5 us by wavefront, 38.2 flat (transpose 42.3, 37.8), of 2064 bytes 73.1 and 71.2, four choices 124.4 and 118.7.  With
+// 16 lanes in the last wavefront or other numbers of choices it is the other way round: 2304 bytes 76.7 and 80.3;
+// 1040 bytes, four choices 59.6 and 62.3; 2064 bytes, one choice 48.6 and 49.8; and four wavefronts with a poor last
+// one (3184 bytes) 64.0 and 67.3.
+static bool combine_by_wave(int cpr, int k) {
+    const int wpr = row_waves(cpr), last = cpr % 64;
+    return rows_by_wave(cpr) && !(wpr <= 3 && last > 0 && last < 16 && k >= wpr - 1 && k <= wpr + 1);
 }
 
 // Other rows: chunks flat over the lanes.  More than four choices (KK == 0) are taken four at a time: loads
@@ -123,7 +134,7 @@ static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* sl
                              int k, int cpr, void* y, hipStream_t st) {
     const vec16* r = static_cast<const vec16*>(recv);
     vec16* out = static_cast<vec16*>(y);
-    if (rows_by_wave(cpr)) {
+    if (combine_by_wave(cpr, k)) {
         const int wpr = row_waves(cpr);
         const dim3 grid = grid_of(ceil_div(S * (int64_t)wpr, kThreads / 64 * U), kThreads), block(kThreads);
         combine_kernel<DT, KK, U, UNITW>
