@@ -69,7 +69,7 @@ __device__ __forceinline__ void offset_tables(const Segments& sg, bool to_expert
     __syncthreads();
 }
 
-// Rows by whole wavefronts (rows_by_wave), U segments of 64 chunks each; a row's segment of the table is found
+// Rows by whole wavefronts, U segments of 64 chunks each; a row's segment of the table is found
 // by counting the offsets that do not exceed it (one ballot per 64).
 template <int U, bool STREAM>
 __global__ __launch_bounds__(kThreads) void regroup_copy_kernel(const vec16* __restrict__ in, const Segments sg,
@@ -175,7 +175,12 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
     // two chunks per thread: the tables are made once per 8 KiB instead of once per 4 KiB
     // (2 GiB: 377 -> 341 us; four chunks: 350 us)
     constexpr int U = 2;
-    const bool rowu = rows_by_wave(cpr);
+    // Rows that are no multiple of a line (128 bytes): flat, the wavefronts write whole lines across the ends of
+    // rows; by wavefront every row ends in a partial line and, but for a multiple of 1 KiB, in idle lanes.  200000
+    // x 1040 bytes, both ways: 166 us by wavefront, 145 flat; 60000 x 4112 174, 164; 40000 x 12016 321, 312.  Below 24 MiB
+    // latency counts, and the search for a chunk's segment is longer flat: 3000 x 3184 12.5, 14.0.  Whole
+    // lines go by wavefront at any size: 76288 x 7680 381, 406.
+    const bool rowu = rows_by_wave(cpr) && (cpr % 8 == 0 || cap_rows * cpr * 16 <= (int64_t)24 << 20);
     const int wpr = row_waves(cpr);
     int64_t blocks = rowu ? ceil_div(cap_rows * wpr, kThreads / 64 * U) : ceil_div(cap_rows * cpr, kThreads * U);
     if (blocks > 0x7fffffff) return fail(TAMOE_UNSUPPORTED, "%s: the buffer is too large for one launch", fn);

@@ -147,7 +147,7 @@ def test_dropped_pairs_under_any_bound(T, chunks):
 
 
 @pytest.mark.parametrize("P,E,chunks,mean", [(1, 1, 1, 3), (3, 2, 63, 4), (64, 2, 64, 3), (2, 64, 65, 2), (5, 7, 128, 0.3), (128, 1, 8, 5),
-                                             (16, 4, 129, 20)])
+                                             (16, 4, 129, 20), (16, 4, 65, 400), (8, 3, 321, 250), (16, 4, 136, 190)])
 @pytest.mark.parametrize("clip", [0, 7])
 def test_regroup_layouts(T, P, E, chunks, mean, clip):
     rng = np.random.default_rng(P * 100 + chunks)
