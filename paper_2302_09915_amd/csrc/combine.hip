@@ -62,15 +62,13 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restri
     }
 }
 
-// By wavefront or flat?  A row just over one or two wavefronts leaves most of its last one idle, and with few
-// choices that wavefront's look-ups and weights are the larger part of its work: 65536 rows of 1040 bytes, two choices
-// 40.5 us by wavefront, 38.2 flat (transpose 42.3, 37.8), of 2064 bytes 73.1 and 71.2, four choices 124.4 and 118.7.  With
-// 16 lanes in the last wavefront or other numbers of choices it is the other way round: 2304 bytes 76.7 and 80.3;
-// 1040 bytes, four choices 59.6 and 62.3; 2064 bytes, one choice 48.6 and 49.8; and four wavefronts with a poor last
-// one (3184 bytes) 64.0 and 67.3.
+// By wavefront or flat?  Flat with a poor last wavefront and about as many choices as wavefronts: 65536 rows of 1040
+// bytes, two choices 40.5 us by wavefront, 38.2 flat (transpose 42.3, 37.8), of 2064 bytes 73.1 and 71.2, four choices
+// 124.4 and 118.7.  With more lanes in the last wavefront or other numbers of choices it is the other way round:
+// 2304 bytes 76.7 and 80.3; 1040 bytes, four choices 59.6 and 62.3; 2064 bytes, one choice 48.6 and 49.8.
 static bool combine_by_wave(int cpr, int k) {
-    const int wpr = row_waves(cpr), last = cpr % 64;
-    return rows_by_wave(cpr) && !(wpr <= 3 && last > 0 && last < 16 && k >= wpr - 1 && k <= wpr + 1);
+    const int wpr = row_waves(cpr);
+    return rows_by_wave(cpr) && !(poor_last_wave(cpr) && k >= wpr - 1 && k <= wpr + 1);
 }
 
 // Other rows: chunks flat over the lanes.  More than four choices (KK == 0) are taken four at a time: loads

@@ -128,6 +128,8 @@ __device__ __forceinline__ void split_chunk(int64_t c, int64_t total, int cpr, i
 // wavefront would idle (shorter rows).
 inline bool rows_by_wave(int cpr) { return cpr >= 64; }
 inline int row_waves(int cpr) { return (cpr + 63) / 64; }
+// Rows just over one or two wavefronts: the last one has next to no lanes, and costs what the others cost.
+inline bool poor_last_wave(int cpr) { return row_waves(cpr) <= 3 && cpr % 64 > 0 && cpr % 64 < 12; }
 // Wavefront wv of a launch -> row and segment of 64 chunks in it.  shift: pow2_shift(wpr).  The rows of one
 // device's memory are fewer than 2^31 wavefronts.
 __device__ __forceinline__ void split_wave(uint32_t wv, int wpr, int shift, int& row, int& seg) {

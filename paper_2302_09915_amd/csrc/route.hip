@@ -341,7 +341,7 @@ __device__ __forceinline__ void route_layer_outputs(const RouteArgs& a) {
 // The scatter with the slot assignment folded in.  Workgroup 0 writes the layer's outputs and moves no rows:
 // as part of a copying workgroup that tail would end after every other workgroup of a short launch.
 // Then copy_blocks workgroups move rows, and N * fill_parts clear the unused rows of the fixed-size
-// layout.  ROWU: rows by whole wavefronts (rows_by_wave), U segments each; otherwise U chunks per
+// layout.  ROWU: rows by whole wavefronts (scatter_by_wave), U segments each; otherwise U chunks per
 // thread, flat.  STREAM: the rows are written with streaming stores.  TABLE: no route_expert_kernel ran;
 // the workgroup scans the table of pair counts itself.
 // (What the copying workgroups read comes as arguments of its own: only a pointer that is declared not to
@@ -512,17 +512,28 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
 
 constexpr int copy_units(int k) { return k == 1 ? 2 : 1; }   // chunks per thread
 
+// By wavefront or flat?  Flat with a poor last wavefront: 65536 rows of 2064 bytes, two choices 107.8 us by wavefront,
+// 100.7 flat, 1040 bytes 53.4 and 51.5, one choice 31.9 and 28.6, 8000 of them with two 11.4 and 9.9; from 12 lanes on
+// the other way round (2288 bytes 47.6 and 49.2, 3184 bytes 78.7 and 85.3).  And flat with more than four choices, for
+// which a wavefront keeps eight of everything, if a tenth of its lanes would idle: 16500 x 2064, eight choices 105.6
+// and 96.7, 11520 x 6368 166.9 and 161.7, 65536 x 1536 193.2 and 188.7; but 9000 x 4000, six choices (2 % idle) 2.9 us
+// less by wavefront.
+static bool scatter_by_wave(int cpr, int k) {
+    const int lanes = row_waves(cpr) * 64;
+    return rows_by_wave(cpr) && !poor_last_wave(cpr) && (k <= 4 || (lanes - cpr) * 10 <= lanes);
+}
+
 // Workgroups that move rows.
 static int64_t copy_workgroups(int64_t S, int cpr, int k) {
     const int U = copy_units(k);
-    return rows_by_wave(cpr) ? ceil_div(S * (int64_t)row_waves(cpr), kCopyThreads / 64 * U)
+    return scatter_by_wave(cpr, k) ? ceil_div(S * (int64_t)row_waves(cpr), kCopyThreads / 64 * U)
                              : ceil_div(S * (int64_t)cpr, kCopyThreads * U);
 }
 
 // Fills in the launch geometry.
 static void plan_copy(RouteArgs& a) {
     a.wpr = row_waves(a.cpr);
-    a.shift = pow2_shift(rows_by_wave(a.cpr) ? a.wpr : a.cpr);
+    a.shift = pow2_shift(scatter_by_wave(a.cpr, a.k) ? a.wpr : a.cpr);
     a.copy_blocks = (int)copy_workgroups(a.S, a.cpr, a.k);
     // about 4096 workgroups clear rows, at most one per 4 KiB of an expert's rows
     a.fill_parts = a.pad_C == 0 ? 0 : (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(4096, a.N),
@@ -545,7 +556,7 @@ static void launch_route_copy(const RouteArgs& a, bool table, hipStream_t st) {
             route_copy_kernel<KK, U, RU, ST, false><<<grid, block, 0, st>>>(             \
                 a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a);        \
     } while (0)
-    if (rows_by_wave(a.cpr)) {
+    if (scatter_by_wave(a.cpr, a.k)) {
         if (stream) TAMOE_ROUTE_COPY(true, true); else TAMOE_ROUTE_COPY(true, false);
     } else {
         if (stream) TAMOE_ROUTE_COPY(false, true); else TAMOE_ROUTE_COPY(false, false);

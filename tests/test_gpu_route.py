@@ -24,7 +24,9 @@ def T():
     (1, 8, 1, 1, 1), (511, 8, 3, 3, 1), (513, 520, 64, 8, 2), (1024, 512, 128, 64, 2), (1025, 512, 128, 64, 2),   # table / expert
     (4096, 512, 64, 64, 2), (4097, 512, 64, 64, 3), (3000, 16, 128, 2, 8), (70000, 8, 32, 4, 1),                   # blocks, tiles
     (2000, 1000, 48, 16, 4), (700, 512, 5, 5, 5), (9000, 1032, 128, 64, 8), (33, 4096, 16, 4, 6),
-    (257, 8, 6, 3, 3), (129, 64, 10, 5, 5), (16384, 8, 16, 4, 8), (16385, 8, 16, 4, 8), (20000, 24, 128, 4, 5)])    # tiles of the ranking
+    (257, 8, 6, 3, 3), (129, 64, 10, 5, 5), (16384, 8, 16, 4, 8), (16385, 8, 16, 4, 8), (20000, 24, 128, 4, 5),    # tiles of the ranking
+    (5000, 520, 16, 4, 1), (5000, 600, 16, 4, 2), (5000, 608, 16, 4, 2), (333, 1032, 16, 4, 3), (4000, 1112, 16, 4, 4),    # by wavefront
+    (4000, 1120, 16, 4, 1), (900, 800, 16, 4, 5), (900, 1024, 16, 4, 6), (300, 1544, 16, 4, 2)])                           # or flat
 def test_dispatch_stages(T, oracle, S, d, N, P, k):
     rng = np.random.default_rng(S + d + N)
     x_np = W.to_storage(rng.standard_normal((S, d)).astype(np.float32), W.BF16)
@@ -62,7 +64,8 @@ def test_dispatch_stages(T, oracle, S, d, N, P, k):
     np.testing.assert_array_equal(np.asarray(to_host(send, W.BF16)).view(np.uint16), rows)
 
 
-@pytest.mark.parametrize("S,d,N,P,k", [(1, 8, 1, 1, 1), (600, 64, 8, 8, 1), (2048, 512, 32, 8, 2), (2049, 512, 32, 8, 2), (130, 1032, 128, 64, 8)])
+@pytest.mark.parametrize("S,d,N,P,k", [(1, 8, 1, 1, 1), (600, 64, 8, 8, 1), (2048, 512, 32, 8, 2), (2049, 512, 32, 8, 2), (130, 1032, 128, 64, 8),
+                                        (5000, 520, 16, 4, 1), (9000, 1032, 64, 8, 2), (777, 1000, 24, 3, 6)])
 def test_fused_call_against_separate_calls(T, S, d, N, P, k):
     g = torch.Generator(device="cuda").manual_seed(S + d)
     x = torch.randn((S, d), generator=g, device="cuda").bfloat16()
