@@ -34,7 +34,7 @@
  *    started).  Scratch comes from the caller's workspace `ws` (device
  *    memory, 256-byte aligned, at least tamoe_workspace_bytes() bytes).  Its content is
  *    garbage on entry and on exit; two calls that share a workspace must be ordered on one
- *    stream.
+ *    stream, whichever they are (tamoe_dispatch uses the same parts of it as the gate).
  *  - Device functions only enqueue work on `stream` (a hipStream_t passed as void*; NULL is
  *    the default stream).  They never synchronise and are deterministic: same inputs, same
  *    bits.
@@ -178,6 +178,9 @@ size_t tamoe_workspace_bytes(int64_t S, int d, int N, int P, int k, int dtype);
  *   c_expert[e]   = number of (t, j) with topk_idx[t][j] == e        (before any capacity)
  *   c_device[j]   = sum of c_expert over the experts of device j
  *   m[e]          = (1/S) * sum_t G[t][e]                             (0 if S == 0)
+ * Infinities in x or w give the scores of IEEE arithmetic: an expert whose scores are -infinity has no probability
+ * and is chosen only when nothing else is left (then as -1).  A tile of tokens with such scores takes fp32
+ * about twice as long.
  * TAMOE_F32: a product of two values is formed from bfloat16 parts; what is left out of it is below 2^-22
  * of the product (of either sign), and values below 2^-108 in magnitude enter with fewer than 24 bits, those
  * below 2^-126 as zero.
@@ -363,7 +366,7 @@ int tamoe_dispatch_padded(const void* x, const int32_t* topk_idx, const int32_t*
  * cap_rows = number of rows both buffers can hold; only the first R = sum of the counts rows are
  * read and written (R is taken on the device; rows beyond cap_rows are dropped).  P*E <= 128.
  * in, out [cap_rows, d] `dtype`, recv_count [P*E], expert_offset: device.  ws: at least
- * tamoe_workspace_bytes(...) (any shape) bytes.
+ * tamoe_workspace_bytes(...) (any shape) bytes, as ever, although nothing in it is read or written.
  */
 int tamoe_regroup(const void* in, const int32_t* recv_count, int P, int E, int dtype, int d,
                   int64_t cap_rows, int to_expert_major, void* out, int32_t* expert_offset,

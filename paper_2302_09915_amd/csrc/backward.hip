@@ -16,8 +16,12 @@ constexpr int kThreads = 256;
 // One 16-byte chunk per thread, like the forward row movers: a thread requests its chunk of dy and of the
 // k source rows, then stores its k products.  A loop of such steps would wait for the stores of one step
 // before the loads of the next are back (stores and loads retire in one order): one wavefront per
-// token took 146 us where this takes 90 (bf16, 32768 x 768, k = 4; 34 -> 10 us for 65536 rows of 128 bytes).  d_w is a fixed-order sum: a
-// butterfly over the lanes of a row segment, then the row's segments in ascending order.
+// token took 146 us where this takes 90 (bf16, 32768 x 768, k = 4; 34 -> 10 us for 65536 rows of 128 bytes).  d_w is a
+// fixed-order sum: a butterfly over the lanes of a row segment, then the row's segments in ascending order.
+//
+// d_recv stays in the last-level cache when it fits (the rule of the scatter): with buffers that the call before
+// left there, this and dispatch_bwd take 49.8 us for the GPT-MoE layer where streaming stores took 52.8; on rows
+// that come from HBM it is 56.7 and 56.0, no gain.
 //
 // Rows of 64 chunks and more: a row takes whole wavefronts of one workgroup (ceil(cpr / 64) of them, at
 // most kRowWaves, each of which takes every kRowWaves-th segment of a longer row), several rows share a
@@ -151,7 +155,7 @@ __device__ __forceinline__ float lane_xor(float v) {
     return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), (MASK << 10) | 0x1f));
 }
 template <int LPT>
-__device__ __forceinline__ float group_max(float v) {
+__device__ __forceinline__ float butterfly_max(float v) {
     if constexpr (LPT > 1) v = fmaxf(v, lane_xor<1>(v));
     if constexpr (LPT > 2) v = fmaxf(v, lane_xor<2>(v));
     if constexpr (LPT > 4) v = fmaxf(v, lane_xor<4>(v));
@@ -160,7 +164,7 @@ __device__ __forceinline__ float group_max(float v) {
     return v;
 }
 template <int LPT>
-__device__ __forceinline__ float group_sum(float v) {
+__device__ __forceinline__ float butterfly_sum(float v) {
     if constexpr (LPT > 1) v += lane_xor<1>(v);
     if constexpr (LPT > 2) v += lane_xor<2>(v);
     if constexpr (LPT > 4) v += lane_xor<4>(v);
@@ -202,7 +206,7 @@ __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restr
 #pragma unroll
         for (int i = 0; i < 4; ++i) l[i] = (token_ok && e0 + i < N) ? row[e0 + i] : -INFINITY;
     }
-    float mx = group_max<LPT>(fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
+    float mx = butterfly_max<LPT>(fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
     if (!token_ok) mx = 0.f;
     float g[4], part = 0.f;
 #pragma unroll
@@ -210,7 +214,7 @@ __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restr
         g[i] = __builtin_amdgcn_exp2f((l[i] - mx) * 1.44269504088896340736f);
         part += g[i];
     }
-    const float den = group_sum<LPT>(part);
+    const float den = butterfly_sum<LPT>(part);
     const float inv = token_ok ? 1.0f / den : 0.f;
     float u[4];
 #pragma unroll
@@ -227,7 +231,7 @@ __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restr
     float ub = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) ub = __builtin_fmaf(u[i], g[i], ub);
-    const float ubar = group_sum<LPT>(ub);
+    const float ubar = butterfly_sum<LPT>(ub);
     if (token_ok) {
         float* out = d_logits + (size_t)token * N;
         if (VEC) {

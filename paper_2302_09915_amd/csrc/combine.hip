@@ -1,7 +1,8 @@
 // tamoe_combine: y[t] = sum over the kept choices j of topk_w[t][j] * recv[slot[t][j]]
 // (paper Section 3.1: the layer output aggregates the computed results).
 //
-// One 16-byte chunk of y per thread (two for k = 1), no loop and no LDS: a thread gathers the same chunk of the (up to k) source rows, accumulates in fp32 in
+// One 16-byte chunk of y per thread (two for k = 1), no LDS: a thread gathers the same chunk of the (up to k)
+// source rows (flat rows with more than four choices: four at a time, in a loop), accumulates in fp32 in
 // ascending j with one fused multiply-add per term, rounds once to the storage type and writes
 // the chunk of y.  Bound by HBM: d*b bytes read per kept pair, d*b written per token; the HBM
 // latency is covered by the number of independent wavefronts, as in a plain copy.

@@ -49,7 +49,7 @@ Workspace workspace_layout(int64_t S, int N, int k) {
     off = align_up(off + (size_t)pair_pitch(k, (int64_t)gb) * N * sizeof(int32_t), 256);
     w.local_pos = off;
     off = align_up(off + (size_t)S * k * sizeof(int32_t), 256);
-    w.total = off < 4096 ? 4096 : off;  // never less than the offset tables of tamoe_regroup
+    w.total = off < 4096 ? 4096 : off;  // never less than tamoe_regroup asks for
     return w;
 }
 

@@ -165,6 +165,7 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
     if ((rc = check_rows(fn, dtype, d, &cpr)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "recv_count", recv_count, 4)) != TAMOE_OK) return rc;
     if ((rc = check_ptr(fn, "ws", ws, 256)) != TAMOE_OK) return rc;
+    // the tables lie in LDS, ws is not touched; what it had to be when it held them is still asked for
     const size_t need = 2 * (kMaxSeg + 1) * sizeof(int32_t);
     if (ws_bytes < need) return fail(TAMOE_WORKSPACE_TOO_SMALL, "%s: workspace has %zu bytes, %zu needed", fn, ws_bytes, need);
     if (cap_rows > 0) {
