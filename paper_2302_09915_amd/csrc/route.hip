@@ -515,12 +515,12 @@ constexpr int copy_units(int k) { return k == 1 ? 2 : 1; }   // chunks per threa
 // By wavefront or flat?  Flat with a poor last wavefront: 65536 rows of 2064 bytes, two choices 107.8 us by wavefront,
 // 100.7 flat, 1040 bytes 53.4 and 51.5, one choice 31.9 and 28.6, 8000 of them with two 11.4 and 9.9; from 12 lanes on
 // the other way round (2288 bytes 47.6 and 49.2, 3184 bytes 78.7 and 85.3).  And flat with more than four choices, for
-// which a wavefront keeps eight of everything, if a tenth of its lanes would idle: 16500 x 2064, eight choices 105.6
-// and 96.7, 11520 x 6368 166.9 and 161.7, 65536 x 1536 193.2 and 188.7; but 9000 x 4000, six choices (2 % idle) 2.9 us
-// less by wavefront.
+// which a wavefront keeps eight of everything, if a tenth of its lanes would idle and rows are no whole lines: 16500 x
+// 2064, eight choices 105.6 and 96.7, 11520 x 6368 166.9 and 161.7; but 9000 x 4000, six choices (2 % idle) 2.9 us less
+// by wavefront, and 1536 bytes (whole lines, 25 % idle) 5 us less behind the gate, 5 more on its own.
 static bool scatter_by_wave(int cpr, int k) {
     const int lanes = row_waves(cpr) * 64;
-    return rows_by_wave(cpr) && !poor_last_wave(cpr) && (k <= 4 || (lanes - cpr) * 10 <= lanes);
+    return rows_by_wave(cpr) && !poor_last_wave(cpr) && (k <= 4 || cpr % 8 == 0 || (lanes - cpr) * 10 <= lanes);
 }
 
 // Workgroups that move rows.
