@@ -64,12 +64,13 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restri
 }
 
 // By wavefront or flat?  Flat with a poor last wavefront and about as many choices as wavefronts: 65536 rows of 1040
-// bytes, two choices 40.5 us by wavefront, 38.2 flat (transpose 42.3, 37.8), of 2064 bytes 73.1 and 71.2, four choices
-// 124.4 and 118.7.  With more lanes in the last wavefront or other numbers of choices it is the other way round:
-// 2304 bytes 76.7 and 80.3; 1040 bytes, four choices 59.6 and 62.3; 2064 bytes, one choice 48.6 and 49.8.
-static bool combine_by_wave(int cpr, int k) {
+// bytes, two choices 40.5 us by wavefront, 38.2 flat (transpose 42.3, 37.8), 8000 of them 6.4 and 5.6, 65536 of 2064 bytes
+// 73.1 and 71.2, four choices 124.4 and 118.7.  With more lanes in the last wavefront or other numbers of choices it is
+// the other way round: 8000 rows of 1120 bytes, three choices 6.7 and 7.9; 65536 of 2304 bytes 76.7 and 80.3, of 1040
+// bytes, four choices 59.6 and 62.3, of 2064 bytes, one choice 48.6 and 49.8.
+static bool combine_by_wave(int64_t S, int cpr, int k) {
     const int wpr = row_waves(cpr);
-    return rows_by_wave(cpr) && !(poor_last_wave(cpr) && k >= wpr - 1 && k <= wpr + 1);
+    return rows_by_wave(cpr) && !(poor_last_wave(S, cpr, 4) && k >= wpr - 1 && k <= wpr + 1);
 }
 
 // Other rows: chunks flat over the lanes.  More than four choices (KK == 0) are taken four at a time: loads
@@ -133,7 +134,7 @@ static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* sl
                              int k, int cpr, void* y, hipStream_t st) {
     const vec16* r = static_cast<const vec16*>(recv);
     vec16* out = static_cast<vec16*>(y);
-    if (combine_by_wave(cpr, k)) {
+    if (combine_by_wave(S, cpr, k)) {
         const int wpr = row_waves(cpr);
         const dim3 grid = grid_of(ceil_div(S * (int64_t)wpr, kThreads / 64 * U), kThreads), block(kThreads);
         combine_kernel<DT, KK, U, UNITW>

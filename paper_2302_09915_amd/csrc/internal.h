@@ -128,8 +128,12 @@ __device__ __forceinline__ void split_chunk(int64_t c, int64_t total, int cpr, i
 // wavefront would idle (shorter rows).
 inline bool rows_by_wave(int cpr) { return cpr >= 64; }
 inline int row_waves(int cpr) { return (cpr + 63) / 64; }
-// Rows just over one or two wavefronts: the last one has next to no lanes, and costs what the others cost.
-inline bool poor_last_wave(int cpr) { return row_waves(cpr) <= 3 && cpr % 64 > 0 && cpr % 64 < 12; }
+// S rows just over one or two wavefronts, the last of which has fewer than `lanes` lanes and costs what the others
+// cost, in a launch that is bound by that.  (Below 8192 wavefronts it is latency, and neither is better throughout: 2000
+// rows of 1040 bytes, dispatch with one choice 6.6 us by wavefront, 6.9 flat, with three 9.1 and 8.6.)
+inline bool poor_last_wave(int64_t S, int cpr, int lanes) {
+    return row_waves(cpr) <= 3 && cpr % 64 > 0 && cpr % 64 < lanes && S * row_waves(cpr) >= 8192;
+}
 // Wavefront wv of a launch -> row and segment of 64 chunks in it.  shift: pow2_shift(wpr).  The rows of one
 // device's memory are fewer than 2^31 wavefronts.
 __device__ __forceinline__ void split_wave(uint32_t wv, int wpr, int shift, int& row, int& seg) {

@@ -513,27 +513,30 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
 constexpr int copy_units(int k) { return k == 1 ? 2 : 1; }   // chunks per thread
 
 // By wavefront or flat?  Flat with a poor last wavefront: 65536 rows of 2064 bytes, two choices 107.8 us by wavefront,
-// 100.7 flat, 1040 bytes 53.4 and 51.5, one choice 31.9 and 28.6, 8000 of them with two 11.4 and 9.9; from 12 lanes on
-// the other way round (2288 bytes 47.6 and 49.2, 3184 bytes 78.7 and 85.3).  And flat with more than four choices, for
+// 100.7 flat, 1040 bytes 53.4 and 51.5, one choice 31.9 and 28.6, whole calls on 8000 x 1040
+// with two 14.9 and 13.4, on 8000 x 1184 with one 11.3 and 10.4; from 12 lanes on, or 4 behind two full wavefronts, the
+// other way round (2288 bytes 47.6 and 49.2, 3184 bytes 78.7 and 85.3, calls on 30000 x 2176 43.5 and 45.5).  And flat with more than four choices, for
 // which a wavefront keeps eight of everything, if a tenth of its lanes would idle and rows are no whole lines: 16500 x
 // 2064, eight choices 105.6 and 96.7, 11520 x 6368 166.9 and 161.7; but 9000 x 4000, six choices (2 % idle) 2.9 us less
 // by wavefront, and 1536 bytes (whole lines, 25 % idle) 5 us less behind the gate, 5 more on its own.
-static bool scatter_by_wave(int cpr, int k) {
+static bool scatter_by_wave(int64_t S, int cpr, int k) {
+    if (!rows_by_wave(cpr)) return false;
+    if (poor_last_wave(S, cpr, row_waves(cpr) == 2 ? 12 : 4)) return false;
     const int lanes = row_waves(cpr) * 64;
-    return rows_by_wave(cpr) && !poor_last_wave(cpr) && (k <= 4 || cpr % 8 == 0 || (lanes - cpr) * 10 <= lanes);
+    return k <= 4 || cpr % 8 == 0 || (lanes - cpr) * 10 <= lanes || S * row_waves(cpr) < 8192;
 }
 
 // Workgroups that move rows.
 static int64_t copy_workgroups(int64_t S, int cpr, int k) {
     const int U = copy_units(k);
-    return scatter_by_wave(cpr, k) ? ceil_div(S * (int64_t)row_waves(cpr), kCopyThreads / 64 * U)
+    return scatter_by_wave(S, cpr, k) ? ceil_div(S * (int64_t)row_waves(cpr), kCopyThreads / 64 * U)
                              : ceil_div(S * (int64_t)cpr, kCopyThreads * U);
 }
 
 // Fills in the launch geometry.
 static void plan_copy(RouteArgs& a) {
     a.wpr = row_waves(a.cpr);
-    a.shift = pow2_shift(scatter_by_wave(a.cpr, a.k) ? a.wpr : a.cpr);
+    a.shift = pow2_shift(scatter_by_wave(a.S, a.cpr, a.k) ? a.wpr : a.cpr);
     a.copy_blocks = (int)copy_workgroups(a.S, a.cpr, a.k);
     // about 4096 workgroups clear rows, at most one per 4 KiB of an expert's rows
     a.fill_parts = a.pad_C == 0 ? 0 : (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(4096, a.N),
@@ -556,7 +559,7 @@ static void launch_route_copy(const RouteArgs& a, bool table, hipStream_t st) {
             route_copy_kernel<KK, U, RU, ST, false><<<grid, block, 0, st>>>(             \
                 a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a);        \
     } while (0)
-    if (scatter_by_wave(a.cpr, a.k)) {
+    if (scatter_by_wave(a.S, a.cpr, a.k)) {
         if (stream) TAMOE_ROUTE_COPY(true, true); else TAMOE_ROUTE_COPY(true, false);
     } else {
         if (stream) TAMOE_ROUTE_COPY(false, true); else TAMOE_ROUTE_COPY(false, false);

@@ -26,7 +26,8 @@ def T():
     (2000, 1000, 48, 16, 4), (700, 512, 5, 5, 5), (9000, 1032, 128, 64, 8), (33, 4096, 16, 4, 6),
     (257, 8, 6, 3, 3), (129, 64, 10, 5, 5), (16384, 8, 16, 4, 8), (16385, 8, 16, 4, 8), (20000, 24, 128, 4, 5),    # tiles of the ranking
     (5000, 520, 16, 4, 1), (5000, 600, 16, 4, 2), (5000, 608, 16, 4, 2), (333, 1032, 16, 4, 3), (4000, 1112, 16, 4, 4),    # by wavefront
-    (4000, 1120, 16, 4, 1), (900, 800, 16, 4, 5), (900, 1024, 16, 4, 6), (300, 1544, 16, 4, 2)])                           # or flat
+    (4000, 1120, 16, 4, 1), (900, 800, 16, 4, 5), (900, 1024, 16, 4, 6), (300, 1544, 16, 4, 2), (4095, 520, 16, 4, 2),     # or flat
+    (4096, 520, 16, 4, 2), (2731, 1048, 16, 4, 2), (2731, 1056, 16, 4, 2), (4200, 808, 16, 4, 5), (4096, 936, 16, 4, 5), (2800, 1032, 16, 4, 6)])
 def test_dispatch_stages(T, oracle, S, d, N, P, k):
     rng = np.random.default_rng(S + d + N)
     x_np = W.to_storage(rng.standard_normal((S, d)).astype(np.float32), W.BF16)

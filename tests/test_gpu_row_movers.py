@@ -36,7 +36,8 @@ def _case(seed, S, d, dtype, k, K_rows):
 @pytest.mark.parametrize("S,chunks,k", [
     (1, 1, 1), (37, 3, 2), (130, 63, 3), (67, 64, 1), (66, 65, 2), (33, 125, 4), (31, 192, 5), (9, 256, 2), (65, 208, 8),
     (5, 1024, 2), (5, 1025, 3), (3, 2300, 1), (700, 8, 6), (257, 31, 4),
-    (131, 65, 1), (67, 65, 3), (66, 65, 4), (45, 79, 2), (45, 80, 2), (37, 129, 4), (33, 143, 1), (33, 129, 5), (29, 144, 2), (29, 193, 2)])
+    (131, 65, 1), (67, 65, 3), (66, 65, 4), (45, 79, 2), (45, 80, 2), (37, 129, 4), (33, 143, 1), (33, 129, 5), (29, 144, 2), (29, 193, 2),
+    (4095, 65, 2), (4096, 65, 2), (4100, 67, 1), (4100, 68, 3), (2731, 129, 2), (2731, 131, 4), (2731, 129, 1)])
 def test_combine_and_backward_layouts(T, oracle, dtype, S, chunks, k):
     d = chunks * (4 if dtype == W.F32 else 8)
     for K_rows in (0, max(1, (S * k * 2) // 3)):
