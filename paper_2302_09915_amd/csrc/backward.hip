@@ -19,17 +19,13 @@ constexpr int kThreads = 256;
 // token took 146 us where this takes 90 (bf16, 32768 x 768, k = 4; 34 -> 10 us for 65536 rows of 128 bytes).  d_w is a
 // fixed-order sum: a butterfly over the lanes of a row segment, then the row's segments in ascending order.
 //
-// d_recv stays in the last-level cache when it fits (the rule of the scatter): with buffers that the call before
-// left there, this and dispatch_bwd take 49.8 us for the GPT-MoE layer where streaming stores took 52.8; on rows
-// that come from HBM it is 56.7 and 56.0, no gain.
-//
 // Rows of 64 chunks and more: a row takes whole wavefronts of one workgroup (ceil(cpr / 64) of them, at
 // most kRowWaves, each of which takes every kRowWaves-th segment of a longer row), several rows share a
 // workgroup of four wavefronts.  KK > 0: k is the compile-time constant KK; KK == 0: any k.
-// STREAM: d_recv is too large to stay in the last-level cache and is written with streaming stores.
+// ST: how d_recv is stored (combine_bwd_store).
 constexpr int kRowWaves = 16;
 
-template <int DT, int KK, bool STREAM>
+template <int DT, int KK, int ST>
 __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
     const vec16* __restrict__ dy, const vec16* __restrict__ recv, int64_t K_rows, const int32_t* __restrict__ slot,
     const float* __restrict__ topk_w, int64_t S, int k_arg, int cpr, int row_waves, vec16* __restrict__ d_recv,
@@ -70,7 +66,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
             dot[j] = chunk_dot<DT>(g, r[j], dot[j]);
             float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             Chunk<DT>::fma(acc, w[j], g);
-            RowBuffer(d_recv + (size_t)s[j] * cpr, cpr, use[j]).template store<STREAM>(c, Chunk<DT>::pack(acc));
+            RowBuffer(d_recv + (size_t)s[j] * cpr, cpr, use[j]).template store<ST>(c, Chunk<DT>::pack(acc));
         }
     }
 #pragma unroll
@@ -94,7 +90,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
 
 // Other rows (fewer than 64 chunks): a row takes G consecutive lanes (the power of two that holds it).  More
 // than four choices (KK == 0) are taken four at a time, as in combine_flat_kernel.
-template <int DT, int KK, bool STREAM>
+template <int DT, int KK, int ST>
 __global__ __launch_bounds__(kThreads) void combine_bwd_short_kernel(
     const vec16* __restrict__ dy, const vec16* __restrict__ recv, int64_t K_rows, const int32_t* __restrict__ slot,
     const float* __restrict__ topk_w, int64_t S, int k_arg, int cpr, int g_shift, vec16* __restrict__ d_recv,
@@ -132,11 +128,7 @@ __global__ __launch_bounds__(kThreads) void combine_bwd_short_kernel(
             float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             Chunk<DT>::fma(acc, w[j], g);
             const vec16 o = Chunk<DT>::pack(acc);
-            vec16* dst = d_recv + (size_t)s[j] * cpr + c;
-            if (s[j] >= 0) {
-                if (STREAM) __builtin_nontemporal_store(o, dst);
-                else *dst = o;
-            }
+            if (s[j] >= 0) store_chunk<ST>(d_recv + (size_t)s[j] * cpr + c, o);
         }
 #pragma unroll
         for (int j = 0; j < KG; ++j) {
@@ -258,28 +250,47 @@ static void launch_gate_bwd(const float* logits, const int32_t* idx, const float
         gate_bwd_kernel<LPT, false><<<grid, block, 0, st>>>(logits, idx, d_w, penalty, c, scale, S, N, k, d_logits);
 }
 
-template <int DT, int KK>
-static void launch_combine_bwd_k(const vec16* dy, const vec16* recv, int64_t K_rows, const int32_t* slot,
+// d_recv is written straight through L2 at almost any size: the last-level cache keeps what fits of it for the kernel that
+// reads it next, and no dirty line is left for the end of this one.  combine_bwd and dispatch_bwd together: 58880
+// x 2 KiB, two choices (230 MiB) 159 us with ordinary stores, 194 streaming, 155 now; 128 rows of 8 KiB per MiB, 400 MiB
+// 276, 304, 272; 65536 x 8 KiB 782, 795, 770; 64527 x 1040 bytes 110, 110, 108.  Streaming is the better way only
+// for one choice and rows just over one wavefront, which two of them write (129055 x 1040: 154, 146, 151), ordinary
+// stores for the small buffers that the scatter left in L2 (a whole layer's pass of 1000 x 8 KiB, two choices 47.7 and
+// 49.5 through, 600 x 8 KiB, four 51.2 and 53.9; this and dispatch_bwd on their own 15.1 and 14.8).
+static int combine_bwd_store(int64_t S, int cpr, int k) {
+    const int64_t mib = S * k * (int64_t)cpr * 16 >> 20;
+    if (k == 1 && cpr > 64 && cpr < 68 && mib > 48) return kStoreStream;
+    return k > 1 && cpr >= 64 && cpr % 8 == 0 && mib >= 8 && mib < 24 ? kStoreBack : kStoreThrough;
+}
+
+template <int DT, int KK, int ST>
+static void launch_combine_bwd_s(const vec16* dy, const vec16* recv, int64_t K_rows, const int32_t* slot,
                                  const float* topk_w, int64_t S, int k, int cpr, vec16* d_recv, float* d_w,
                                  hipStream_t st) {
-    const bool stream = !send_stays_in_cache(S, k, cpr);
     if (rows_by_wave(cpr)) {
         const int rw = row_waves(cpr) < kRowWaves ? row_waves(cpr) : kRowWaves;
         const int rows = rw < 4 ? 4 / rw : 1;
         const dim3 grid = grid_of(ceil_div(S, rows), rows * rw * 64), block(rows * rw * 64);
-        if (stream)
-            combine_bwd_kernel<DT, KK, true><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, rw, d_recv, d_w);
-        else
-            combine_bwd_kernel<DT, KK, false><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, rw, d_recv, d_w);
+        combine_bwd_kernel<DT, KK, ST><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, rw, d_recv, d_w);
     } else {
         int g_shift = 0;
         while ((1 << g_shift) < cpr) ++g_shift;
         const dim3 grid = grid_of(ceil_div(S << g_shift, kThreads), kThreads), block(kThreads);
-        if (stream)
-            combine_bwd_short_kernel<DT, KK, true><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, g_shift, d_recv, d_w);
-        else
-            combine_bwd_short_kernel<DT, KK, false><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, g_shift, d_recv, d_w);
+        combine_bwd_short_kernel<DT, KK, ST><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, g_shift, d_recv, d_w);
     }
+}
+
+template <int DT, int KK>
+static void launch_combine_bwd_k(const vec16* dy, const vec16* recv, int64_t K_rows, const int32_t* slot,
+                                 const float* topk_w, int64_t S, int k, int cpr, vec16* d_recv, float* d_w,
+                                 hipStream_t st) {
+    const int policy = combine_bwd_store(S, cpr, k);
+    if (policy == kStoreThrough)
+        launch_combine_bwd_s<DT, KK, kStoreThrough>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
+    else if (policy == kStoreStream)
+        launch_combine_bwd_s<DT, KK, kStoreStream>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
+    else
+        launch_combine_bwd_s<DT, KK, kStoreBack>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
 }
 
 template <int DT>

@@ -17,7 +17,7 @@ constexpr int kThreads = 256;
 // UNITW: every weight is 1 (the transpose of the scatter: dx[t] = sum of the rows its slots name).
 // Rows by whole wavefronts (combine_by_wave), U segments of 64 chunks each: all slots, weights and rows of
 // a token are requested without a branch between them.
-template <int DT, int KK, int U, bool UNITW>
+template <int DT, int KK, int U, bool UNITW, int ST>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restrict__ recv, int64_t K_rows,
                                                            const int32_t* __restrict__ slot,
                                                            const float* __restrict__ topk_w, int64_t S, int k_arg,
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restri
         float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < KM; ++j) Chunk<DT>::fma(acc, wgt[u][j], v[u][j]);
-        RowBuffer(y + (size_t)tok[u] * cpr, cpr, true).template store<true>(col[u], Chunk<DT>::pack(acc));
+        RowBuffer(y + (size_t)tok[u] * cpr, cpr, true).template store<ST>(col[u], Chunk<DT>::pack(acc));
     }
 }
 
@@ -73,10 +73,18 @@ static bool combine_by_wave(int64_t S, int cpr, int k) {
     return rows_by_wave(cpr) && !(poor_last_wave(S, cpr, 4) && k >= wpr - 1 && k <= wpr + 1);
 }
 
+// y goes straight through L2 and is not kept: ordinary stores are written back behind the last wavefront, and streaming
+// ones still wait in L2 for their turn (the whole forward call on 16384 x 2 KiB, two choices: 47.8 us with ordinary
+// stores, 47.5 streaming, 46.5 straight through; 65536 x 8 KiB 663, 625, 626; 28835 x 2000 bytes 86.0 streaming, 84.5).  Not with
+// one choice and rows that are no whole lines (28050 x 4112: 113.8 streaming, 116.6; 12098 x 1040 24.3, 24.8).
+static bool combine_writes_out(int64_t S, int cpr, int k) {
+    return (k > 1 || cpr % 8 == 0) && S * (int64_t)cpr * 16 <= (int64_t)256 << 20;
+}
+
 // Other rows: chunks flat over the lanes.  More than four choices (KK == 0) are taken four at a time: loads
 // under a condition per lane hold registers across each other, and eight of them left room for one
 // wavefront per SIMD in fp32.
-template <int DT, int KK, int U, bool UNITW>
+template <int DT, int KK, int U, bool UNITW, int ST>
 __global__ __launch_bounds__(kThreads) void combine_flat_kernel(const vec16* __restrict__ recv, int64_t K_rows,
                                                                 const int32_t* __restrict__ slot,
                                                                 const float* __restrict__ topk_w, int64_t total_chunks,
@@ -125,26 +133,35 @@ __global__ __launch_bounds__(kThreads) void combine_flat_kernel(const vec16* __r
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t c = base + (int64_t)u * kThreads;
-        if (c < total_chunks) __builtin_nontemporal_store(Chunk<DT>::pack(acc[u]), y + c);
+        if (c < total_chunks) store_chunk<ST>(y + c, Chunk<DT>::pack(acc[u]));
     }
 }
 
-template <int DT, int KK, int U, bool UNITW>
-static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* slot, const float* topk_w, int64_t S,
+template <int DT, int KK, int U, bool UNITW, int ST>
+static void launch_combine_s(const void* recv, int64_t K_rows, const int32_t* slot, const float* topk_w, int64_t S,
                              int k, int cpr, void* y, hipStream_t st) {
     const vec16* r = static_cast<const vec16*>(recv);
     vec16* out = static_cast<vec16*>(y);
     if (combine_by_wave(S, cpr, k)) {
         const int wpr = row_waves(cpr);
         const dim3 grid = grid_of(ceil_div(S * (int64_t)wpr, kThreads / 64 * U), kThreads), block(kThreads);
-        combine_kernel<DT, KK, U, UNITW>
+        combine_kernel<DT, KK, U, UNITW, ST>
             <<<grid, block, 0, st>>>(r, K_rows, slot, topk_w, S, k, cpr, wpr, pow2_shift(wpr), out);
     } else {
         const int64_t total = S * (int64_t)cpr;
         const dim3 grid = grid_of(ceil_div(total, kThreads * U), kThreads), block(kThreads);
-        combine_flat_kernel<DT, KK, U, UNITW>
+        combine_flat_kernel<DT, KK, U, UNITW, ST>
             <<<grid, block, 0, st>>>(r, K_rows, slot, topk_w, total, k, cpr, pow2_shift(cpr), out);
     }
+}
+
+template <int DT, int KK, int U, bool UNITW>
+static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* slot, const float* topk_w, int64_t S,
+                             int k, int cpr, void* y, hipStream_t st) {
+    if (combine_writes_out(S, cpr, k))
+        launch_combine_s<DT, KK, U, UNITW, kStoreOut>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
+    else
+        launch_combine_s<DT, KK, U, UNITW, kStoreStream>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
 }
 
 template <int DT, bool UNITW>

@@ -235,7 +235,7 @@ static void launch_copy(const void* x, const int32_t* slot, int64_t S, int k, in
     const vec16* src = static_cast<const vec16*>(x);
     vec16* dst = static_cast<vec16*>(send);
     const int shift = pow2_shift(cpr);
-    const bool stream = !send_stays_in_cache(S, k, cpr);
+    const bool stream = S * k * (int64_t)cpr * 16 > (int64_t)96 << 20;   // beyond what the last-level cache keeps beside x
     if (cpr % 64 == 0) {
         if (stream)
             dispatch_copy_kernel<KK, U, true, true><<<grid, block, 0, st>>>(src, slot, total, k, cpr, shift, dst);

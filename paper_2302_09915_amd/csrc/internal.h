@@ -79,14 +79,6 @@ int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const i
 int check_select_outputs(const char* fn, int64_t S, int32_t* topk_idx, float* topk_w, float* m, int32_t* c_expert,
                          int32_t* c_device, void* ws, size_t ws_bytes, const Workspace& lay);
 
-// Rows written by the scatter stay in the last-level cache (ordinary stores) when the whole send buffer
-// fits well inside its 256 MB, so that whoever reads them next (the exchange, a local expert, the
-// combine of an identity layer) finds them there; larger buffers are written with streaming stores,
-// which do not push the token matrix out of that cache while the scatter still reads it.  Measured:
-// GPT-MoE layer (64 MiB of rows) 62.2 -> 60.6 us per step, skewed 59.8 -> 55.9, large (1 GiB) 648 -> 661.
-constexpr int64_t kCacheResidentSendBytes = (int64_t)96 << 20;
-inline bool send_stays_in_cache(int64_t S, int k, int cpr) { return S * k * (int64_t)cpr * 16 <= kCacheResidentSendBytes; }
-
 // Workgroups of a launch as a grid.  HIP takes fewer than 2^32 threads along a dimension: 16 777 216 workgroups of
 // 256 are an invalid configuration, and of a few more only those run, without an error.  More go into rows
 // of 2^20 workgroups, the last of which may have workgroups without work.  blocks < 2^31.
@@ -157,6 +149,25 @@ __device__ __forceinline__ int32_t pair_limit(const int32_t* __restrict__ cap, i
 // pair (-1) too, whatever bound the caller gives.
 inline int64_t slot_bound(int64_t K_rows) { return K_rows < (int64_t)1 << 31 ? K_rows : (int64_t)1 << 31; }
 
+// Cache policies of the row stores (the bits of a buffer store).  A line that is dirty in an L2 when the kernel ends is
+// written back then, with nothing to overlap, and evictions before that come in L2's order and not in that of the rows.
+// Each row mover has a rule of its own, with what it measured.
+enum StorePolicy {
+    kStoreBack = 0,      // ordinary: the line waits in L2 until it is evicted or the kernel ends
+    kStoreStream = 2,    // nt: the last-level cache does not keep the line
+    kStoreThrough = 16,  // sc1: straight through L2; the last-level cache keeps the line
+    kStoreOut = 19       // nt sc1 sc0: straight through L2, not kept
+};
+// A chunk by address, with one of these policies.  (s_nop: the instruction behind a store of more than 8 bytes must not
+// overwrite its data, and the compiler looks at its own stores only.)
+template <int ST>
+__device__ __forceinline__ void store_chunk(vec16* p, vec16 v) {
+    if constexpr (ST == kStoreThrough) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+    else if constexpr (ST == kStoreOut) asm volatile("global_store_dwordx4 %0, %1, off sc0 nt sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+    else if constexpr (ST == kStoreStream) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // A row as a buffer resource: the hardware returns zeros for a load and drops a store outside its `cpr`
 // chunks, and a row that is not there (present == false) has none.  Lanes beyond the end of a row and
 // dropped pairs need no branch then, and cost no memory access.  With a branch around each load the k
@@ -169,10 +180,10 @@ struct RowBuffer {
     __device__ __forceinline__ vec16 load(int col) const {                     // streaming
         return __builtin_bit_cast(vec16, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)((uint32_t)col * 16u), 0, 2));
     }
-    template <bool STREAM>
+    template <int ST>
     __device__ __forceinline__ void store(int col, vec16 v) const {
         typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, (int)((uint32_t)col * 16u), 0, STREAM ? 2 : 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, (int)((uint32_t)col * 16u), 0, ST);
     }
 };
 

@@ -71,7 +71,7 @@ __device__ __forceinline__ void offset_tables(const Segments& sg, bool to_expert
 
 // Rows by whole wavefronts, U segments of 64 chunks each; a row's segment of the table is found
 // by counting the offsets that do not exceed it (one ballot per 64).
-template <int U, bool STREAM>
+template <int U, int ST>
 __global__ __launch_bounds__(kThreads) void regroup_copy_kernel(const vec16* __restrict__ in, const Segments sg,
                                                                 int64_t cap_rows, int cpr, int wpr, int shift,
                                                                 int to_expert_major, vec16* __restrict__ out,
@@ -102,11 +102,11 @@ __global__ __launch_bounds__(kThreads) void regroup_copy_kernel(const vec16* __r
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        RowBuffer(out + (size_t)(drow[u] >= 0 ? drow[u] : 0) * cpr, cpr, drow[u] >= 0).template store<STREAM>(col[u], v[u]);
+        RowBuffer(out + (size_t)(drow[u] >= 0 ? drow[u] : 0) * cpr, cpr, drow[u] >= 0).template store<ST>(col[u], v[u]);
 }
 
 // Other rows: chunks flat over the lanes, a chunk's segment by binary search over the offsets in LDS.
-template <int U, bool STREAM>
+template <int U, int ST>
 __global__ __launch_bounds__(kThreads) void regroup_flat_kernel(const vec16* __restrict__ in, const Segments sg,
                                                                 int64_t cap_rows, int cpr, int shift, int to_expert_major,
                                                                 vec16* __restrict__ out,
@@ -140,10 +140,15 @@ __global__ __launch_bounds__(kThreads) void regroup_flat_kernel(const vec16* __r
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (dst[u] >= 0) {
-            if (STREAM) __builtin_nontemporal_store(v[u], out + dst[u]);
-            else out[dst[u]] = v[u];
-        }
+        if (dst[u] >= 0) store_chunk<ST>(out + dst[u], v[u]);
+}
+
+// Straight through L2 while the buffer fits the last-level cache, which keeps it for the experts (or the exchange), and
+// streaming beyond; rows that are no whole or half lines stream earlier.  Us of one call with ordinary / streaming / through stores:
+// 12288 x 512 bytes 10.3 / 10.1 / 9.8, 20480 x 2 KiB 28.3 / 30.1 / 27.0, 117760 x 2 KiB 146 / 142 / 139, 44800 x 8 KiB 230 /
+// 213 / 220; 20971 x 2000 32.0 / 32.8 / 30.8, 34000 x 2320 (75 MiB) - / 53.6 / 50.0, 47185 x 2000 64.3 / 63.2 / 64.7, 120586 x 2000 155 / 148 / 174.
+static bool regroup_streams(int64_t rows, int cpr) {
+    return rows * cpr * 16 > (int64_t)(cpr % 4 == 0 ? 256 : 80) << 20;
 }
 
 }  // namespace tamoe
@@ -189,23 +194,22 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
         if (expert_offset == nullptr) return TAMOE_OK;
         blocks = 1;
     }
-    // rows that fit the last-level cache stay there for the experts (or the exchange), as in the scatter
-    const bool stays = send_stays_in_cache(cap_rows, 1, cpr);
+    const bool streams = regroup_streams(cap_rows, cpr);
     const Segments sg{recv_count, P, E, (65536 + P - 1) / P, (65536 + E - 1) / E};
     const vec16* src = static_cast<const vec16*>(in);
     vec16* dst = static_cast<vec16*>(out);
     const dim3 grid = grid_of(blocks, kThreads), block(kThreads);
     TraceScope tr("regroup_copy_kernel", st);
-#define TAMOE_REGROUP(STREAM)                                                                                      \
+#define TAMOE_REGROUP(ST)                                                                                          \
     do {                                                                                                           \
         if (rowu)                                                                                                  \
-            regroup_copy_kernel<U, STREAM><<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, wpr, pow2_shift(wpr),    \
+            regroup_copy_kernel<U, ST>    <<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, wpr, pow2_shift(wpr),    \
                                                                    to_expert_major, dst, expert_offset);           \
         else                                                                                                       \
-            regroup_flat_kernel<U, STREAM><<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, pow2_shift(cpr),         \
+            regroup_flat_kernel<U, ST>    <<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, pow2_shift(cpr),         \
                                                                    to_expert_major, dst, expert_offset);           \
     } while (0)
-    if (stays) TAMOE_REGROUP(false); else TAMOE_REGROUP(true);
+    if (streams) TAMOE_REGROUP(kStoreStream); else TAMOE_REGROUP(kStoreThrough);
 #undef TAMOE_REGROUP
     return check_launch(fn, "regroup_copy_kernel");
 }

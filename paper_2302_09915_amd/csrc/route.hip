@@ -19,8 +19,7 @@
 //      with the row's first chunk writes them to slot[].  The first workgroup writes what
 //      describes the layer as a whole: expert offsets, rows per destination device, the loss; in the
 //      fixed-size layout the last ones clear every expert's unused rows.
-//      Rows are written with ordinary stores while the send buffer is small enough to stay in the
-//      last-level cache, with streaming stores beyond that.
+//      How rows are stored depends on what the caches can do for them (scatter_store).
 #include <algorithm>
 
 #include "gate_tile.h"
@@ -166,6 +165,7 @@ struct RouteArgs {
     int n_blocks, pitch, tile_shift;
     int pad_C;                  // rows per expert of the fixed-size layout, 0: packed
     int copy_blocks, fill_parts;
+    bool fill_streams;
     // outputs; m, c_expert, c_device and loss are NULL for a given routing, expert_offset and
     // send_count_dev in the fixed-size layout
     const float* penalty;
@@ -342,12 +342,12 @@ __device__ __forceinline__ void route_layer_outputs(const RouteArgs& a) {
 // as part of a copying workgroup that tail would end after every other workgroup of a short launch.
 // Then copy_blocks workgroups move rows, and N * fill_parts clear the unused rows of the fixed-size
 // layout.  ROWU: rows by whole wavefronts (scatter_by_wave), U segments each; otherwise U chunks per
-// thread, flat.  STREAM: the rows are written with streaming stores.  TABLE: no route_expert_kernel ran;
+// thread, flat.  ST: how rows are stored (scatter_store).  TABLE: no route_expert_kernel ran;
 // the workgroup scans the table of pair counts itself.
 // (What the copying workgroups read comes as arguments of its own: only a pointer that is declared not to
 // alias is read through the scalar unit.  cap is never NULL here: without capacities it is the table, whose
 // entries are then not looked at, so that no branch stands between the look-ups.)
-template <int KK, int U, bool ROWU, bool STREAM, bool TABLE>
+template <int KK, int U, bool ROWU, int ST, bool TABLE>
 __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
     const vec16* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_pos,
     const int32_t* __restrict__ tile_table, const int32_t* __restrict__ cap, int32_t* __restrict__ slot,
@@ -375,9 +375,10 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
         const int64_t i1 = i0 + per < n ? i0 + per : n;
         vec16* base = a.send + ((int64_t)e * a.pad_C + used) * cpr;
         const vec16 zero = {0u, 0u, 0u, 0u};
-        for (int64_t i = i0 + threadIdx.x; i < i1; i += kCopyThreads) {
-            if (STREAM) __builtin_nontemporal_store(zero, base + i);
-            else base[i] = zero;
+        if (a.fill_streams) {
+            for (int64_t i = i0 + threadIdx.x; i < i1; i += kCopyThreads) store_chunk<kStoreStream>(base + i, zero);
+        } else {
+            for (int64_t i = i0 + threadIdx.x; i < i1; i += kCopyThreads) store_chunk<ST>(base + i, zero);
         }
         return;
     }
@@ -498,13 +499,9 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
             const int32_t sl = use[u][j] ? off + pos[u][j] : -1;
             if (inside[u] && (KK > 0 || j < k) && seg[u] == 0 && (!ROWU || lane == 0)) slot[(int64_t)tok[u] * k + j] = sl;
             if constexpr (ROWU) {
-                RowBuffer(send + (size_t)(use[u][j] ? sl : 0) * cpr, cpr, use[u][j]).template store<STREAM>(col[u], v[u]);
+                RowBuffer(send + (size_t)(use[u][j] ? sl : 0) * cpr, cpr, use[u][j]).template store<ST>(col[u], v[u]);
             } else if (use[u][j]) {
-                vec16* dst = send + (size_t)sl * cpr + col[u];
-                if (STREAM)
-                    __builtin_nontemporal_store(v[u], dst);
-                else
-                    *dst = v[u];
+                store_chunk<ST>(send + (size_t)sl * cpr + col[u], v[u]);
             }
         }
     }
@@ -526,6 +523,37 @@ static bool scatter_by_wave(int64_t S, int cpr, int k) {
     return k <= 4 || cpr % 8 == 0 || (lanes - cpr) * 10 <= lanes || S * row_waves(cpr) < 8192;
 }
 
+// How `rows` rows of send are written.  What decides is whether the last-level cache (256 MB) keeps them for whoever reads
+// them next, and who merges the lines that a row shares with its neighbours.  Us of gate_dispatch and combine, N = 32,
+// with ordinary / streaming / through stores:
+//  - rows of whole lines go straight through L2 as long as they fit the last-level cache (30720 x 2 KiB, two choices 44.5 /
+//    46.4 / 43.7; 14720 x 8 KiB, two 133.9 / 140.7 / 134.0; 17280 x 8 KiB, two 181 / 174 / 181; 34560 x 8 KiB, one 238 /
+//    252 / 235).  Small buffers that nothing but the combine of an identity layer reads are
+//    partly in L2 then (6144 x 1 KiB, two 18.2 / 20.0 / 18.9; dispatch alone 20.9 and 19.6 with through stores), short rows
+//    of many choices gain on their own too (8192 x 512 bytes, eight 27.8 and 28.6);
+//  - rows that are no whole lines, by wavefront: through (9830 x 4000, two 45.8 / 46.1 / 44.9; 47185 x 2000, two 134.5 /
+//    137.6 / 132.2), with many choices from L2, which merges their lines (11320 x 6368, eight 273 / 287 / 286);
+//    rows of half lines stream (39321 x 1600, two 93 / 88 / 92, 9611 x 3008, four 70 / 67 / 69);
+//  - flat ones from L2 (57974 x 1040, four 111 / 136 / 121; 115651 x 272, two 61 / 65 / 65), one choice streaming beyond
+//    96 MiB;
+//  - the fixed-size layout streams beyond 96 MiB: its padding takes the place of rows (14117 x 7328, two, 237 MiB 131
+//    streaming, 149 through; 56000 x 1 KiB, three, 205 MiB 99 and 101).
+static int scatter_store(int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
+    const int64_t mib = rows * cpr * 16 >> 20;
+    if (padded && mib > 96) return kStoreStream;
+    if (cpr % 8 == 0) {
+        const int from = behind_gate && by_wave ? 8 : 0;
+        const int to = behind_gate ? (k <= 2 ? 16 : 24) : !by_wave && k > 4 ? 32 : 0;
+        if (mib >= from && mib < to) return kStoreBack;
+        return mib <= (k == 1 ? 360 : 240) ? kStoreThrough : kStoreStream;
+    }
+    if (!by_wave) return mib <= (k == 1 ? 96 : k == 2 ? 240 : 640) ? kStoreBack : kStoreStream;
+    if (mib <= 24) return kStoreThrough;
+    if (k <= 4 && cpr % 4 == 0) return kStoreStream;
+    if (k <= 4 && mib <= 240) return kStoreThrough;
+    return k > 2 && mib <= 640 ? kStoreBack : kStoreStream;
+}
+
 // Workgroups that move rows.
 static int64_t copy_workgroups(int64_t S, int cpr, int k) {
     const int U = copy_units(k);
@@ -538,6 +566,9 @@ static void plan_copy(RouteArgs& a) {
     a.wpr = row_waves(a.cpr);
     a.shift = pow2_shift(scatter_by_wave(a.S, a.cpr, a.k) ? a.wpr : a.cpr);
     a.copy_blocks = (int)copy_workgroups(a.S, a.cpr, a.k);
+    // zeros of a large buffer would take the place of its rows in the last-level cache: 53902 x 1536 bytes, half of them
+    // padding 86 us, streamed 78; 8192 x 8 KiB 66 and 61; but 6144 x 2 KiB (48 MiB) 28.7 and 29.2
+    a.fill_streams = (int64_t)a.N * a.pad_C * a.cpr * 16 > (int64_t)64 << 20;
     // about 4096 workgroups clear rows, at most one per 4 KiB of an expert's rows
     a.fill_parts = a.pad_C == 0 ? 0 : (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(4096, a.N),
                                                                      ceil_div((int64_t)a.pad_C * a.cpr, kCopyThreads)));
@@ -548,7 +579,6 @@ static void launch_route_copy(const RouteArgs& a, bool table, hipStream_t st) {
     constexpr int U = copy_units(KK);
     const dim3 grid = grid_of(1 + (int64_t)a.copy_blocks + (int64_t)a.N * a.fill_parts, kCopyThreads), block(kCopyThreads);
     const int64_t rows = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : a.S * a.k;
-    const bool stream = !send_stays_in_cache(rows, 1, a.cpr);
     const int32_t* caps = a.cap != nullptr ? a.cap : a.table;   // N entries at least
 #define TAMOE_ROUTE_COPY(RU, ST)                                                         \
     do {                                                                                 \
@@ -559,11 +589,16 @@ static void launch_route_copy(const RouteArgs& a, bool table, hipStream_t st) {
             route_copy_kernel<KK, U, RU, ST, false><<<grid, block, 0, st>>>(             \
                 a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a);        \
     } while (0)
-    if (scatter_by_wave(a.S, a.cpr, a.k)) {
-        if (stream) TAMOE_ROUTE_COPY(true, true); else TAMOE_ROUTE_COPY(true, false);
-    } else {
-        if (stream) TAMOE_ROUTE_COPY(false, true); else TAMOE_ROUTE_COPY(false, false);
-    }
+    const bool rowu = scatter_by_wave(a.S, a.cpr, a.k);
+    const int policy = scatter_store(rows, a.cpr, a.k, rowu, a.m_part != nullptr, a.pad_C > 0);
+#define TAMOE_ROUTE_COPY_ST(ST)                                                          \
+    do {                                                                                 \
+        if (rowu) TAMOE_ROUTE_COPY(true, ST); else TAMOE_ROUTE_COPY(false, ST);          \
+    } while (0)
+    if (policy == kStoreStream) TAMOE_ROUTE_COPY_ST(kStoreStream);
+    else if (policy == kStoreThrough) TAMOE_ROUTE_COPY_ST(kStoreThrough);
+    else TAMOE_ROUTE_COPY_ST(kStoreBack);
+#undef TAMOE_ROUTE_COPY_ST
 #undef TAMOE_ROUTE_COPY
 }
 

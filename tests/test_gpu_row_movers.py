@@ -184,3 +184,63 @@ def test_regroup_layouts(T, P, E, chunks, mean, clip):
         np.testing.assert_array_equal(back.view(torch.int16).cpu().numpy()[:R], x[:R])
         assert (back.view(torch.int16)[R:] == 9).all()
         np.testing.assert_array_equal(off.cpu().numpy(), exp[::P][:E + 1])
+
+
+@pytest.mark.parametrize("S,chunks,k", [
+    (2048, 128, 2), (4096, 128, 2), (5000, 64, 3), (30720, 256, 2), (30721, 256, 2), (23041, 1024, 1), (23040, 1024, 1),  # whole lines
+    (4000, 100, 2), (21000, 100, 2), (11000, 137, 2), (63100, 125, 2), (31500, 125, 4), (4000, 125, 6), (21000, 125, 8),   # by wavefront
+    (6000, 17, 3), (63000, 65, 1), (97000, 65, 1), (121000, 65, 2), (121900, 65, 2)])                                     # flat
+def test_store_policies(T, S, chunks, k):
+    """Rows written with every cache policy, on both sides of the sizes where one takes over from another: rows of
+    whole lines, half lines and others, small buffers, buffers of the size of the last-level cache, larger ones."""
+    g = torch.Generator(device="cuda").manual_seed(S + chunks)
+    x = torch.randint(-32768, 32767, (S, chunks * 8), generator=g, device="cuda", dtype=torch.int16).view(torch.bfloat16)
+    N = 16
+    idx = torch.rand((S, N), generator=g, device="cuda").topk(k, 1).indices.int().contiguous()
+    cap = torch.full((N,), S * k // N - 3, dtype=torch.int32, device="cuda")       # some pairs are dropped
+    q = T.dispatch(x, idx, cap, N, N)
+    slot, K = q["slot"], int(q["expert_offset"][-1])
+    t, j = torch.nonzero(slot >= 0, as_tuple=True)
+    assert t.numel() == K == int(q["kept_expert"].sum())
+    same = lambda a, b: torch.equal(a.view(torch.int16), b.view(torch.int16))       # noqa: E731
+    assert same(q["send"][slot[t, j].long()], x[t])
+    # one row each: the transposes of the copy are copies too
+    first = torch.full_like(slot, -1)
+    first[:, 0] = slot[:, 0]
+    there = first[:, 0] >= 0
+    x0 = torch.where(there[:, None], x, torch.zeros_like(x)).nan_to_num(0.0, 0.0, 0.0)
+    rows = q["send"].nan_to_num(0.0, 0.0, 0.0)
+    y, dx = T.combine(rows, K, first, torch.ones((S, k), device="cuda")), torch.empty_like(x)
+    T.tamoe_dispatch_bwd(rows, K, first, dx)
+    assert torch.equal(y, x0) and torch.equal(dx, x0)
+    d_recv, d_w = torch.full_like(rows, 7.0), torch.empty((S, k), device="cuda")
+    T.tamoe_combine_bwd(x0, rows, K, first, torch.ones((S, k), device="cuda"), d_recv, d_w)
+    want = torch.full_like(rows, 7.0)
+    want[first[there, 0].long()] = x0[there]
+    assert torch.equal(d_recv, want)
+    # regrouping there and back
+    cnt = torch.full((8, 2), S * k // 16, dtype=torch.int32, device="cuda")
+    R = int(cnt.sum())
+    by_expert, back = torch.empty_like(rows), torch.empty_like(rows)
+    ws = T.workspace(1, chunks * 8, 16, 8, 1, T.BF16)
+    T.tamoe_regroup(rows, cnt, True, by_expert, None, ws)
+    assert torch.equal(by_expert[:R].view(2, 8, -1), rows[:R].view(8, 2, -1).transpose(0, 1))
+    T.tamoe_regroup(by_expert, cnt, False, back, None, ws)
+    assert torch.equal(back[:R], rows[:R])
+
+
+@pytest.mark.parametrize("S,d,k,C", [(2000, 512, 2, 500), (9000, 1024, 1, 2100), (9000, 1000, 2, 2200)])
+def test_padding_policies(T, S, d, k, C):
+    """Unused rows of the fixed-size layout are cleared whatever the size of the buffer."""
+    g = torch.Generator(device="cuda").manual_seed(S + d)
+    x = torch.randn((S, d), generator=g, device="cuda").bfloat16()
+    N = 16
+    idx = torch.rand((S, N), generator=g, device="cuda").topk(k, 1).indices.int().contiguous()
+    cap = torch.full((N,), C, dtype=torch.int32, device="cuda")
+    send = torch.full((N * C, d), 3.0, dtype=torch.bfloat16, device="cuda")
+    slot, kept = torch.empty((S, k), dtype=torch.int32, device="cuda"), torch.empty(N, dtype=torch.int32, device="cuda")
+    T.tamoe_dispatch_padded(x, idx, cap, N, N, C, send, slot, kept, T.workspace(S, d, N, N, k, T.BF16))
+    want = torch.zeros_like(send)
+    t, j = torch.nonzero(slot >= 0, as_tuple=True)
+    want[slot[t, j].long()] = x[t]
+    assert t.numel() == int(kept.sum()) and torch.equal(send, want)
