@@ -131,13 +131,15 @@ int check_select_outputs(const char* fn, int64_t S, int32_t* topk_idx, float* to
     return TAMOE_OK;
 }
 
-GateStats stats_in(void* ws, const Workspace& lay, int k, int64_t blocks) {
+GateStats stats_in(void* ws, const Workspace& lay, int N, int k, int64_t blocks, bool compact) {
     GateStats gs{};
     gs.m_part = reinterpret_cast<float*>(static_cast<char*>(ws) + lay.m_part);
     gs.tile_pairs = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + lay.tile_pairs);
     gs.local_pos = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + lay.local_pos);
     gs.n_blocks = (int)blocks;
     gs.pitch = (int)pair_pitch(k, blocks);
+    gs.counts = compact ? reinterpret_cast<uint16_t*>(gs.tile_pairs) : nullptr;
+    gs.stride = count_stride(N, k);
     return gs;
 }
 
@@ -145,7 +147,7 @@ int run_select_stage(const char* fn, const float* logits, int64_t S, int N, int 
                      void* ws, const Workspace& lay, hipStream_t st, GateRun* run) {
     const int64_t blocks = ceil_div(S, kSelectTokens);
     if ((int64_t)k * blocks > 0x3fffffff) return fail(TAMOE_UNSUPPORTED, "%s: too many token tiles", fn);
-    run->stats = stats_in(ws, lay, k, blocks);
+    run->stats = stats_in(ws, lay, N, k, blocks, false);
     run->tile_tokens = kSelectTokens;
     if (blocks > 0) {
         launch_select(blocks, st, logits, S, N, k, topk_idx, topk_w, run->stats);
@@ -155,9 +157,9 @@ int run_select_stage(const char* fn, const float* logits, int64_t S, int N, int 
 }
 
 int run_gate_stage(const char* fn, const void* x, const void* w, int dtype, int64_t S, int d, int N, int k,
-                   float* logits, int32_t* topk_idx, float* topk_w, void* ws, const Workspace& lay, hipStream_t st,
-                   GateRun* run) {
-    run->stats = stats_in(ws, lay, k, 0);
+                   float* logits, int32_t* topk_idx, float* topk_w, bool compact, void* ws, const Workspace& lay,
+                   hipStream_t st, GateRun* run) {
+    run->stats = stats_in(ws, lay, N, k, 0, compact);
     run->tile_tokens = 32;
     if (S <= 0) return TAMOE_OK;
     const int tokens = gate_tile_tokens(S, N);
@@ -165,7 +167,7 @@ int run_gate_stage(const char* fn, const void* x, const void* w, int dtype, int6
     if ((int64_t)k * blocks > 0x3fffffff) return fail(TAMOE_UNSUPPORTED, "%s: too many token tiles", fn);
     // the tile code addresses rows in 2-byte units: an fp32 row of d values is a row of 2*d units
     if (dtype == TAMOE_F32 && d > 0x3fffffff) return fail(TAMOE_UNSUPPORTED, "%s: d = %d is too large", fn, d);
-    run->stats = stats_in(ws, lay, k, blocks);
+    run->stats = stats_in(ws, lay, N, k, blocks, compact);
     run->tile_tokens = tokens;
     GateLaunch g{};
     g.tile_tokens = tokens;
@@ -238,7 +240,7 @@ extern "C" int tamoe_gate(const void* x, const void* w, int dtype, int64_t S, in
         return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     GateRun run{};
-    if ((rc = run_gate_stage(fn, x, w, dtype, S, d, N, k, logits, topk_idx, topk_w, ws, lay, st, &run)) != TAMOE_OK)
+    if ((rc = run_gate_stage(fn, x, w, dtype, S, d, N, k, logits, topk_idx, topk_w, false, ws, lay, st, &run)) != TAMOE_OK)
         return rc;
     return finalize(fn, run, N, P, k, S, m, c_expert, c_device, st);
 }

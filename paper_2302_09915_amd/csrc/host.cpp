@@ -1,5 +1,6 @@
 // Host side of libtamoe: error reporting, argument checks, workspace layout and the setup-time
 // derivation of the target dispatch pattern.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -44,9 +45,10 @@ Workspace workspace_layout(int64_t S, int N, int k) {
     size_t off = 0;
     const size_t gb = (size_t)gate_blocks_max(S);
     w.m_part = off;
-    off = align_up(off + gb * N * sizeof(float), 256);
+    off = align_up(off + gb * sum_stride(N) * sizeof(float), 256);
     w.tile_pairs = off;
-    off = align_up(off + (size_t)pair_pitch(k, (int64_t)gb) * N * sizeof(int32_t), 256);
+    off = align_up(off + std::max((size_t)pair_pitch(k, (int64_t)gb) * N * sizeof(int32_t),
+                                  gb * count_stride(N, k) * sizeof(uint16_t)), 256);
     w.local_pos = off;
     off = align_up(off + (size_t)S * k * sizeof(int32_t), 256);
     w.total = off < 4096 ? 4096 : off;  // never less than tamoe_regroup asks for

@@ -42,8 +42,8 @@ inline int64_t pair_pitch(int k, int64_t blocks) { return (int64_t)align_up((siz
 
 struct Workspace {
     size_t m_part;      // float  [N][gate blocks]        per-workgroup sums of gate probabilities
-    size_t tile_pairs;  // int32  [N][pair_pitch]         pairs per (expert; choice, token tile), then (large
-                        //                                tables) their exclusive prefix in priority order
+    size_t tile_pairs;  // int32  [N][pair_pitch]         pairs per (expert; choice, token tile), then their
+                        //                                exclusive prefix in priority order; or GateStats::counts
     size_t local_pos;   // int32  [S][k]                  position of a pair among those of its token tile
     size_t total;
 };
@@ -56,19 +56,34 @@ struct GateStats {
     int32_t* local_pos;   // [S][k]             earlier pairs of the same workgroup with the same expert and choice
     int n_blocks;
     int pitch;
+    uint16_t* counts;     // [n_blocks][stride] instead of tile_pairs, if not NULL: the pairs of (e, j) at j*N + e;
+                          // m_part is then [n_blocks][sum_stride(N)]
+    int stride;           // count_stride(N, k)
 };
+// Entries per row of m_part then and of `counts`: whole pieces of 16 bytes, a power of two of them.
+__host__ __device__ constexpr int sum_stride(int N) {
+    int pieces = 1;
+    while (pieces * 4 < N) pieces *= 2;
+    return pieces * 4;
+}
+inline int count_stride(int N, int k) {
+    int pieces = 1;
+    while (pieces * 8 < N * k) pieces *= 2;
+    return pieces * 8;
+}
 
 // What the gate stage left in the workspace for the stages behind it.
 struct GateRun {
     GateStats stats;
     int tile_tokens;      // tokens per gate workgroup: token t belongs to workgroup t / tile_tokens
 };
-// The gate's kernels up to the per-workgroup partial results (no finalize).  Arguments are those of
+// The gate's kernels up to the per-workgroup partial results (no finalize).  compact: the pair counts go to
+// stats.counts, for a scatter that scans them itself.  Arguments are those of
 // tamoe_gate / tamoe_select, already checked.
 int run_gate_stage(const char* fn, const void* x, const void* w, int dtype, int64_t S, int d, int N, int k,
-                   float* logits, int32_t* topk_idx, float* topk_w, void* ws, const Workspace& lay, hipStream_t st,
-                   GateRun* run);
-GateStats stats_in(void* ws, const Workspace& lay, int k, int64_t blocks);
+                   float* logits, int32_t* topk_idx, float* topk_w, bool compact, void* ws, const Workspace& lay,
+                   hipStream_t st, GateRun* run);
+GateStats stats_in(void* ws, const Workspace& lay, int N, int k, int64_t blocks, bool compact);
 int run_select_stage(const char* fn, const float* logits, int64_t S, int N, int k, int32_t* topk_idx, float* topk_w,
                      void* ws, const Workspace& lay, hipStream_t st, GateRun* run);
 // The dispatch of a routing that is given, arguments already checked: packed rows (pad_C == 0) or pad_C rows

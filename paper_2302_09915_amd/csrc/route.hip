@@ -8,10 +8,10 @@
 //      number of pairs per (expert e, choice j) and for every pair its position among the pairs of
 //      (b, e, j);
 //   2. route_expert_kernel, one workgroup per expert: mean probability, count, the exclusive prefix of
-//      the expert's pair counts in priority order (choice-major, then token order), kept rows.  Only
-//      where the table of counts is large: a small one (kTableReads) is scanned by every
-//      workgroup of the next kernel by itself, and this launch is left out;
-//   3. route_copy_kernel: the scatter.  A pair's slot is offset[e] + prefix[e][j][b] + position, kept
+//      the expert's pair counts in priority order (choice-major, then token order), kept rows.  Not
+//      where the table of counts is small (table_units): every workgroup of the next kernel sums it by
+//      itself, and this launch is left out;
+//   3. route_copy_kernel or route_table_kernel: the scatter.  A pair's slot is offset[e] + prefix[e][j][b] + position, kept
 //      iff prefix + position < cap[e]; offset[e] is the sum of the kept rows of the experts before e,
 //      which every wavefront takes from the N kept counts by a scan of its own (two loads and a dozen
 //      lane shifts: cheaper than one more pass over the experts in front of the scatter); every
@@ -29,14 +29,6 @@
 namespace tamoe {
 
 constexpr int kCopyThreads = 256;
-
-// When the workgroups of the scatter scan the table of pair counts themselves: in one generation of
-// workgroups (kTableBlocks, all resident) that read kTableReads counts together.  The kernel that this
-// replaces takes 3 us and more on its own; the scan adds 0.6 us to 16 workgroups (512 x 64, 128 counts),
-// 1.1 us to 512 (1024 x 2 KiB, 4096 counts), 3.3 us to 1024 with 4096 counts (4096 x 1 KiB: no gain), and
-// 2.5 us to every generation of a longer launch (16384 x 4 KiB: 10 us).
-constexpr int64_t kTableBlocks = 1024;
-constexpr int64_t kTableReads = (int64_t)2 << 20;
 
 // ---- a routing that is given ------------------------------------------------------------------------
 // What the gate kernel leaves behind, from topk_idx: one workgroup of eight wavefronts per TOK tokens, of which each
@@ -154,7 +146,8 @@ struct RouteArgs {
     const vec16* x;
     const int32_t* topk_idx;
     const int32_t* local_pos;
-    const int32_t* table;       // pairs per (expert; choice, tile); their prefix once route_expert_kernel ran
+    const int32_t* table;       // prefix of the pairs per (expert; choice, tile), left by route_expert_kernel
+    const uint16_t* counts;     // or the pairs themselves: rows of `stride` per tile, (e, j) at j*N + e
     const int32_t* cap;         // may be NULL when pad_C > 0
     const float* m_part;        // [N][n_blocks] sums of gate probabilities, NULL for a given routing
     int32_t* slot;
@@ -163,6 +156,7 @@ struct RouteArgs {
     int N, P, k;
     int cpr, wpr, shift;        // chunks per row, wavefronts per row, log2 of wpr (flat: of cpr) or -1
     int n_blocks, pitch, tile_shift;
+    int stride, units;          // small tables: count_stride, chunks of 64 lanes per wavefront of the scatter
     int pad_C;                  // rows per expert of the fixed-size layout, 0: packed
     int copy_blocks, fill_parts;
     bool fill_streams;
@@ -213,54 +207,146 @@ __device__ __forceinline__ int32_t offset_of(const WaveOffsets& o, int e) {
     }
 }
 
-// Lanes that share an expert's row of a table: all 256 threads over N experts, at most a wavefront each.
-__device__ __forceinline__ int lanes_per_expert(int N) {
-    int l = 64;
-    while (l > 1 && l * N > kCopyThreads) l >>= 1;
-    return l;
+// ---- small tables -------------------------------------------------------------------------------------
+// Every workgroup of the scatter sums the pair counts itself: a row per token tile, read 16 bytes per lane, added
+// up two to a register, first over a lane's rows, then over the lanes and wavefronts with the same
+// columns.  Latency: one memory round trip (1.5 us after the 0.7 that a workgroup needs to its first request), beside which
+// the rows are on their way too, then 0.9 us.  What was measured to count is the length of the code, which a wavefront
+// runs once, from cold instruction caches: with bytes for counts (half the requests, three times the additions)
+// small_forward took 17.8 us, with the steps of sum_columns under a condition each 15.9, now 14.8.
+constexpr int kTableThreads = 512, kTableWaves = kTableThreads / 64;
+constexpr int kTableBatch = 8;   // rows per lane, requested together (one in the smallest tables)
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+struct TableLds {
+    uint32_t part[kTableWaves][64][8];                       // by wavefront and column: all tiles, tiles before blk0
+    int32_t before[TAMOE_MAX_K * TAMOE_MAX_EXPERTS];         // pairs of e that precede choice j of tile blk0, at j*N + e
+    int32_t total[TAMOE_MAX_K * TAMOE_MAX_EXPERTS];          // pairs of (e, j), where a thread has one choice
+    int32_t pairs[TAMOE_MAX_EXPERTS], kept[TAMOE_MAX_EXPERTS];
+};
+
+// Sums over the lanes of a wavefront that are a multiple of C (a power of two) apart, of each of M values 4 bytes wide.
+template <class T, int M>
+__device__ __forceinline__ void sum_columns(T (&v)[M], int C) {
+    const auto u = [](T t) { return __builtin_bit_cast(uint32_t, t); };
+    const auto h = [](uint32_t t) { return __builtin_bit_cast(T, t); };
+    if (C <= 32) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            const auto s = __builtin_amdgcn_permlane32_swap(u(v[i]), u(v[i]), false, false);
+            v[i] = h(s[0]) + h(s[1]);
+        }
+    }
+    if (C <= 16) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            const auto s = __builtin_amdgcn_permlane16_swap(u(v[i]), u(v[i]), false, false);
+            v[i] = h(s[0]) + h(s[1]);
+        }
+    }
+    if (C <= 8) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] += h((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u(v[i]), 0x128, 0xf, 0xf, true));   // row_ror:8
+    }
+    if (C <= 4) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] += h((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u(v[i]), 0x124, 0xf, 0xf, true));   // row_ror:4
+    }
+    if (C <= 2) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] += h((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u(v[i]), 0x122, 0xf, 0xf, true));   // row_ror:2
+    }
+    if (C <= 1) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] += h((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u(v[i]), 0x121, 0xf, 0xf, true));   // row_ror:1
+    }
 }
 
-// The workgroup's own scan of a small table: kept[e] = min(pairs of e, its limit), and before[j][e] = pairs
-// of e that precede choice j of token tile blk0.  kept, before (KM rows), total: LDS.  Every thread
-// calls; ends with a barrier.
-template <int KM>
-__device__ __forceinline__ void scan_table(const RouteArgs& a, int blk0, int32_t* kept, int32_t (*before)[TAMOE_MAX_EXPERTS],
-                                           int32_t* total) {
-    const int lpe = lanes_per_expert(a.N);
-    const int e = threadIdx.x / lpe, l = threadIdx.x & (lpe - 1);
-    const int entries = a.k * a.n_blocks;
-    if (e < a.N) {
-        const int32_t lim = pair_limit(a.cap, e, a.pad_C);
-        const int32_t* row = a.table + (size_t)e * a.pitch;
-        int32_t sum = 0, bef[KM];
+// Fills in t; also calls while_waiting(), between the requests for the counts and their use.  Every thread calls; ends
+// with a barrier.
+template <int KK, int B, class Body>
+__device__ __forceinline__ void scan_counts(const RouteArgs& a, int blk0, TableLds& t, Body while_waiting) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int C = a.stride >> 3, shift = 31 - __builtin_clz(C);
+    const int col = tid & (C - 1), r0 = tid >> shift, R = kTableThreads >> shift;
+    const __amdgpu_buffer_rsrc_t rows =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.counts), 0, a.n_blocks * a.stride * 2, 0x00020000);
+    const int32_t cap_e = WordBuffer(a.cap, a.cap != nullptr ? a.N : 0).load<int32_t>(tid);
+    vec16 v[B];
 #pragma unroll
-        for (int j = 0; j < KM; ++j) bef[j] = 0;
-#pragma unroll 4
-        for (int q = 4 * l; q < entries; q += 4 * lpe) {
-            const int4 v = *reinterpret_cast<const int4*>(row + q);   // rows are padded to 64 entries
-            const int32_t c[4] = {v.x, v.y, v.z, v.w};
+    for (int i = 0; i < B; ++i)   // rows past the end are zeros
+        v[i] = __builtin_bit_cast(vec16, __builtin_amdgcn_raw_buffer_load_b128(rows, (r0 + i * R) * a.stride * 2 + col * 16, 0, 0));
+    __builtin_amdgcn_sched_barrier(0);
+    while_waiting();
+    __builtin_amdgcn_sched_barrier(0);
+    u16x2 sums[8] = {};   // all tiles, tiles before blk0
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int32_t n = q + i < entries ? c[i] : 0;         // the padding holds anything
-                sum += n;
+    for (int i = 0; i < B; ++i) {
+        const uint32_t mask = r0 + i * R < blk0 ? 0xffffffffu : 0u;
 #pragma unroll
-                for (int j = 0; j < KM; ++j) bef[j] += q + i < j * a.n_blocks + blk0 ? n : 0;
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t w = v[i][q];
+            sums[q] += __builtin_bit_cast(u16x2, w);
+            sums[q + 4] += __builtin_bit_cast(u16x2, w & mask);
+        }
+    }
+    sum_columns(sums, C);
+    if (lane < C) {
+        uint4* dst = reinterpret_cast<uint4*>(t.part[wave][lane]);
+        auto bits = [](u16x2 x) { return __builtin_bit_cast(uint32_t, x); };
+        dst[0] = make_uint4(bits(sums[0]), bits(sums[1]), bits(sums[2]), bits(sums[3]));
+        dst[1] = make_uint4(bits(sums[4]), bits(sums[5]), bits(sums[6]), bits(sums[7]));
+    }
+    __syncthreads();
+    const int half = C > 64 ? 1 : 0;   // 128 columns: the even wavefronts have the first 64 of them
+    auto column = [&](int i, int32_t& all, int32_t& bef) {
+        const int c = i >> 3, q = (i & 7) >> 1, sh = (i & 1) * 16;
+        uint32_t n[kTableWaves], b[kTableWaves];
+#pragma unroll
+        for (int w = 0; w < kTableWaves; ++w) {
+            const uint32_t* at = t.part[(w << half & 7) | c >> 6][c & 63];
+            n[w] = w < kTableWaves >> half ? at[q] : 0u;
+            b[w] = w < kTableWaves >> half ? at[q + 4] : 0u;
+        }
+        all = bef = 0;
+#pragma unroll
+        for (int w = 0; w < kTableWaves; ++w) {
+            all += n[w] >> sh & 0xffffu;
+            bef += b[w] >> sh & 0xffffu;
+        }
+    };
+    if constexpr (KK == 0) {   // a thread per choice too: one after the other they take 2 us (404 x 768 bytes, six)
+        for (int i = tid; i < a.k * a.N; i += kTableThreads) column(i, t.total[i], t.before[i]);
+        __syncthreads();
+    }
+    if (tid < a.N) {
+        int32_t run = 0;
+        if constexpr (KK > 0) {
+#pragma unroll
+            for (int j = 0; j < KK; ++j) {
+                int32_t all, bef;
+                column(j * a.N + tid, all, bef);
+                t.before[j * a.N + tid] = run + bef;
+                run += all;
+            }
+        } else {
+            int32_t all[TAMOE_MAX_K], bef[TAMOE_MAX_K];
+#pragma unroll
+            for (int j = 0; j < TAMOE_MAX_K; ++j) {
+                const int i = (j < a.k ? j : 0) * a.N + tid;
+                all[j] = t.total[i];
+                bef[j] = t.before[i];
+            }
+#pragma unroll
+            for (int j = 0; j < TAMOE_MAX_K; ++j) {
+                if (j >= a.k) break;
+                t.before[j * a.N + tid] = run + bef[j];
+                run += all[j];
             }
         }
-        for (int sft = lpe >> 1; sft > 0; sft >>= 1) {
-            sum += __shfl_xor(sum, sft);
-#pragma unroll
-            for (int j = 0; j < KM; ++j) bef[j] += __shfl_xor(bef[j], sft);
-        }
-        if (l == 0) {
-            kept[e] = sum < lim ? sum : lim;
-            if (total != nullptr) total[e] = sum;
-            if (before != nullptr) {
-#pragma unroll
-                for (int j = 0; j < KM; ++j)
-                    if (j < a.k) before[j][e] = bef[j];
-            }
-        }
+        const int32_t lim = pair_limit(cap_e, a.cap != nullptr, a.pad_C);
+        t.pairs[tid] = run;
+        t.kept[tid] = run < lim ? run : lim;
     }
     __syncthreads();
 }
@@ -269,117 +355,150 @@ __device__ __forceinline__ void scan_table(const RouteArgs& a, int blk0, int32_t
 // (every thread calls): expert offsets (Section 4.3: what the size exchange carries), rows and pairs per
 // destination device, the loss; with TABLE also what route_expert_kernel would have written.  N <= 128
 // values: the first wavefront holds two experts per lane, scans and sums them with lane operations
-// (fixed order), and hands offsets to the threads that write the per-device numbers through LDS.
-template <bool TABLE>
-__device__ __forceinline__ void route_layer_outputs(const RouteArgs& a) {
-    __shared__ int32_t total[TAMOE_MAX_EXPERTS];
-    __shared__ int32_t kept[TAMOE_MAX_EXPERTS];
-    __shared__ float mean[TAMOE_MAX_EXPERTS];
-    __shared__ int32_t off[TAMOE_MAX_EXPERTS + 1];
+// (fixed order), and looks up the per-device numbers in LDS.
+template <bool TABLE, int KK, int B>
+__device__ __forceinline__ void route_layer_outputs(const RouteArgs& a, TableLds* t) {
+    __shared__ float4 sums[TABLE ? kTableWaves : 1][TAMOE_MAX_EXPERTS / 4];
+    __shared__ int32_t off[TAMOE_MAX_EXPERTS + 1], pairs_off[TAMOE_MAX_EXPERTS + 1];
     const int tid = threadIdx.x;
     const int N = a.N;
+    const int e0 = tid & 63, e1 = e0 + 64;
+    // requested before anything is waited for
+    const WordBuffer pen(a.penalty, a.penalty != nullptr ? N : 0);
+    const float p0 = pen.load<float>(e0), p1 = pen.load<float>(e1);
+    int32_t k0, k1, c0, c1;   // kept rows and pairs of the lane's experts, 0 beyond N
+    float m0 = 0.f, m1 = 0.f;
     if constexpr (TABLE) {
-        if (a.m != nullptr) {
-            const int lpe = lanes_per_expert(N);
-            const int e = tid / lpe, l = tid & (lpe - 1);
-            if (e < N) {
-                float s = 0.f;
-#pragma unroll 4
-                for (int b = l; b < a.n_blocks; b += lpe) s += a.m_part[(size_t)e * a.n_blocks + b];
-                for (int sft = lpe >> 1; sft > 0; sft >>= 1) s += __shfl_xor(s, sft);
-                if (l == 0) {
-                    mean[e] = a.S > 0 ? s / (float)a.S : 0.f;
-                    a.m[e] = mean[e];
+        // sums of gate probabilities, four experts of a tile per lane
+        const int P4 = sum_stride(N) / 4, R = kTableThreads / P4;
+        const int r0 = tid / P4, q = tid & (P4 - 1);
+        scan_counts<KK, B>(a, 0, *t, [&] {
+            if (a.m == nullptr) return;
+            const __amdgpu_buffer_rsrc_t rows =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.m_part), 0, a.n_blocks * P4 * 16, 0x00020000);
+            float acc[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int r = 0; r < a.n_blocks; r += 8 * R) {
+                float4 v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)   // tiles past the end are zeros
+                    v[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rows, ((r + r0 + i * R) * P4 + q) * 16, 0, 0));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    acc[0] += v[i].x;
+                    acc[1] += v[i].y;
+                    acc[2] += v[i].z;
+                    acc[3] += v[i].w;
                 }
             }
+            sum_columns(acc, P4);
+            if ((tid & 63) < P4) sums[tid >> 6][q] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        });
+        if (tid >= 64) return;
+        k0 = e0 < N ? t->kept[e0] : 0;
+        k1 = e1 < N ? t->kept[e1] : 0;
+        c0 = e0 < N ? t->pairs[e0] : 0;
+        c1 = e1 < N ? t->pairs[e1] : 0;
+        if (a.m != nullptr) {
+            const float* part = reinterpret_cast<const float*>(sums);
+#pragma unroll
+            for (int w = 0; w < kTableWaves; ++w) {
+                m0 += e0 < N ? part[w * TAMOE_MAX_EXPERTS + e0] : 0.f;
+                m1 += e1 < N ? part[w * TAMOE_MAX_EXPERTS + e1] : 0.f;
+            }
+            m0 = a.S > 0 ? m0 / (float)a.S : 0.f;
+            m1 = a.S > 0 ? m1 / (float)a.S : 0.f;
+            if (e0 < N) a.m[e0] = m0;
+            if (e1 < N) a.m[e1] = m1;
         }
-        scan_table<1>(a, 0, kept, nullptr, total);
-        if (tid < N) {
-            a.kept_expert[tid] = kept[tid];
-            if (a.c_expert != nullptr) a.c_expert[tid] = total[tid];
+        if (e0 < N) a.kept_expert[e0] = k0;
+        if (e1 < N) a.kept_expert[e1] = k1;
+        if (a.c_expert != nullptr) {
+            if (e0 < N) a.c_expert[e0] = c0;
+            if (e1 < N) a.c_expert[e1] = c1;
         }
     } else {
-        if (tid < N) {
-            kept[tid] = a.kept_expert[tid];
-            if (a.c_expert != nullptr) total[tid] = a.c_expert[tid];
-            if (a.m != nullptr) mean[tid] = a.m[tid];
-        }
-        __syncthreads();
+        if (tid >= 64) return;
+        const WordBuffer kept(a.kept_expert, N), pairs(a.c_expert, a.c_expert != nullptr ? N : 0), mean(a.m, a.m != nullptr ? N : 0);
+        k0 = kept.load<int32_t>(e0);
+        k1 = kept.load<int32_t>(e1);
+        c0 = pairs.load<int32_t>(e0);
+        c1 = pairs.load<int32_t>(e1);
+        m0 = mean.load<float>(e0);
+        m1 = mean.load<float>(e1);
     }
-    if (tid < 64) {
-        const int e0 = tid, e1 = tid + 64;
-        const int32_t k0 = e0 < N ? kept[e0] : 0, k1 = e1 < N ? kept[e1] : 0;
-        const int32_t i0 = wave_inclusive_scan(k0);
-        const int32_t i1 = wave_inclusive_scan(k1) + __builtin_amdgcn_readlane(i0, 63);
-        off[e0] = i0 - k0;
-        off[e1] = i1 - k1;
-        if (e0 == N - 1) off[N] = i0;
-        if (e1 == N - 1) off[N] = i1;
-        if (a.loss != nullptr) {
-            float t0 = 0.f, t1 = 0.f;
-            if (e0 < N) t0 = mean[e0] * (float)total[e0] * (a.penalty != nullptr ? a.penalty[e0] : 1.f);
-            if (e1 < N) t1 = mean[e1] * (float)total[e1] * (a.penalty != nullptr ? a.penalty[e1] : 1.f);
-            float term = t0 + t1;
+    // one wavefront from here on, no barriers
+    auto prefix = [&](int32_t v0, int32_t v1, int32_t* out) {   // out[N] is the total
+        const int32_t i0 = wave_inclusive_scan(v0);
+        const int32_t i1 = wave_inclusive_scan(v1) + __builtin_amdgcn_readlane(i0, 63);
+        out[e0] = i0 - v0;
+        out[e1] = i1 - v1;
+        if (e1 == TAMOE_MAX_EXPERTS - 1) out[TAMOE_MAX_EXPERTS] = i1;
+    };
+    prefix(k0, k1, off);
+    prefix(c0, c1, pairs_off);
+    if (a.loss != nullptr) {
+        const float t0 = m0 * (float)c0 * (a.penalty != nullptr ? p0 : 1.f);
+        const float t1 = m1 * (float)c1 * (a.penalty != nullptr ? p1 : 1.f);
+        const float term = wave_total((e0 < N ? t0 : 0.f) + (e1 < N ? t1 : 0.f));
+        if (tid == 0) a.loss[0] = term * a.loss_scale;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int E = N / a.P;
 #pragma unroll
-            for (int sft = 32; sft > 0; sft >>= 1) term += __shfl_xor(term, sft);
-            if (tid == 0) a.loss[0] = term * a.loss_scale;
+    for (int h = 0; h < 2; ++h) {
+        const int i = tid + 64 * h;
+        if (a.expert_offset != nullptr && i < N) a.expert_offset[i] = off[i];
+        if (i < a.P) {
+            if (a.send_count_dev != nullptr) a.send_count_dev[i] = off[(i + 1) * E] - off[i * E];
+            if (a.c_device != nullptr) a.c_device[i] = pairs_off[(i + 1) * E] - pairs_off[i * E];
         }
     }
-    __syncthreads();
-    if (a.expert_offset != nullptr && tid <= N) a.expert_offset[tid] = off[tid];
-    if (tid < a.P) {
-        const int E = N / a.P;
-        if (a.send_count_dev != nullptr) a.send_count_dev[tid] = off[(tid + 1) * E] - off[tid * E];
-        if (a.c_device != nullptr) {
-            int32_t c = 0;
-            for (int q = 0; q < E; ++q) c += total[tid * E + q];
-            a.c_device[tid] = c;
-        }
+    if (a.expert_offset != nullptr && tid == 0) a.expert_offset[N] = off[N];
+}
+
+// Clears rows e*C + kept[e] .. (e+1)*C - 1 of the fixed-size layout, share f of all (N * fill_parts shares).
+template <int ST>
+__device__ __forceinline__ void clear_unused(const RouteArgs& a, int f, const int32_t* kept, int threads) {
+    const int e = f / a.fill_parts, part = f - e * a.fill_parts;
+    const int32_t used = kept[e];
+    const int64_t n = (int64_t)(a.pad_C - used) * a.cpr;               // chunks to clear, >= 0
+    const int64_t per = (n + a.fill_parts - 1) / a.fill_parts;
+    const int64_t i0 = (int64_t)part * per;
+    const int64_t i1 = i0 + per < n ? i0 + per : n;
+    vec16* base = a.send + ((int64_t)e * a.pad_C + used) * a.cpr;
+    const vec16 zero = {0u, 0u, 0u, 0u};
+    if (a.fill_streams) {
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += threads) store_chunk<kStoreStream>(base + i, zero);
+    } else {
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += threads) store_chunk<ST>(base + i, zero);
     }
 }
 
-// The scatter with the slot assignment folded in.  Workgroup 0 writes the layer's outputs and moves no rows:
-// as part of a copying workgroup that tail would end after every other workgroup of a short launch.
-// Then copy_blocks workgroups move rows, and N * fill_parts clear the unused rows of the fixed-size
+// The scatter with the slot assignment folded in, behind route_expert_kernel.  Workgroup 0 writes the layer's outputs
+// and moves no rows: as part of a copying workgroup that tail would end after every other workgroup of a short
+// launch.  Then copy_blocks workgroups move rows, and N * fill_parts clear the unused rows of the fixed-size
 // layout.  ROWU: rows by whole wavefronts (scatter_by_wave), U segments each; otherwise U chunks per
-// thread, flat.  ST: how rows are stored (scatter_store).  TABLE: no route_expert_kernel ran;
-// the workgroup scans the table of pair counts itself.
+// thread, flat.  ST: how rows are stored (scatter_store).
 // (What the copying workgroups read comes as arguments of its own: only a pointer that is declared not to
 // alias is read through the scalar unit.  cap is never NULL here: without capacities it is the table, whose
 // entries are then not looked at, so that no branch stands between the look-ups.)
-template <int KK, int U, bool ROWU, int ST, bool TABLE>
+template <int KK, int U, bool ROWU, int ST>
 __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
     const vec16* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_pos,
     const int32_t* __restrict__ tile_table, const int32_t* __restrict__ cap, int32_t* __restrict__ slot,
     vec16* __restrict__ send, const RouteArgs a) {
     const uint32_t wg = linear_block();
     if (wg == 0) {
-        route_layer_outputs<TABLE>(a);
+        route_layer_outputs<false, KK, 1>(a, nullptr);
         return;
     }
     constexpr int KM = KK > 0 ? KK : TAMOE_MAX_K;
-    __shared__ int32_t kept_w[TABLE ? TAMOE_MAX_EXPERTS : 1];
-    __shared__ int32_t before_w[TABLE ? KM : 1][TABLE ? TAMOE_MAX_EXPERTS : 1];
     const int N = a.N, cpr = a.cpr;
     const int lane = threadIdx.x & 63;
 
-    if (wg > (uint32_t)a.copy_blocks) {   // zero rows e*C + kept[e] .. (e+1)*C - 1, a share of them
+    if (wg > (uint32_t)a.copy_blocks) {
         const int f = (int)(wg - 1 - (uint32_t)a.copy_blocks);
-        if (f >= N * a.fill_parts) return;   // past the last workgroup (grid_of)
-        const int e = f / a.fill_parts, part = f - e * a.fill_parts;
-        if constexpr (TABLE) scan_table<1>(a, 0, kept_w, nullptr, nullptr);
-        const int32_t used = TABLE ? kept_w[TABLE ? e : 0] : a.kept_expert[e];
-        const int64_t n = (int64_t)(a.pad_C - used) * cpr;             // chunks to clear, >= 0
-        const int64_t per = (n + a.fill_parts - 1) / a.fill_parts;
-        const int64_t i0 = (int64_t)part * per;
-        const int64_t i1 = i0 + per < n ? i0 + per : n;
-        vec16* base = a.send + ((int64_t)e * a.pad_C + used) * cpr;
-        const vec16 zero = {0u, 0u, 0u, 0u};
-        if (a.fill_streams) {
-            for (int64_t i = i0 + threadIdx.x; i < i1; i += kCopyThreads) store_chunk<kStoreStream>(base + i, zero);
-        } else {
-            for (int64_t i = i0 + threadIdx.x; i < i1; i += kCopyThreads) store_chunk<ST>(base + i, zero);
-        }
+        if (f < N * a.fill_parts) clear_unused<ST>(a, f, a.kept_expert, kCopyThreads);   // else past the last workgroup (grid_of)
         return;
     }
 
@@ -417,38 +536,7 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
                 pos[u][j] = __builtin_amdgcn_readfirstlane(pos[u][j]);
             }
         }
-    // A small launch requests the row itself at once, whether or not a choice of its token is kept: behind
-    // the two look-ups it would be a third memory round trip (5.9 -> 5.5 us for 1024 x 2 KiB).  A large one
-    // is bound by bytes and leaves out the rows of dropped tokens (65536 x 8 KiB: 258 us, at once 262; half
-    // the tokens of 16384 x 4 KiB dropped: 15.9 us, at once 17.2).
-    vec16 v[U];
-    if constexpr (TABLE) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if constexpr (ROWU)
-                v[u] = RowBuffer(x + (size_t)tok[u] * cpr, cpr, inside[u]).load(col[u]);
-            else
-                v[u] = __builtin_nontemporal_load(x + (size_t)tok[u] * cpr + col[u]);
-        }
-    }
-    KeptPair kp = {0, 0};
-    int blk0 = 0;
-    if constexpr (TABLE) {
-        // token tile of the workgroup's first token: the same value in every thread
-        int t0;
-        if constexpr (ROWU) {
-            int s0;
-            split_wave(blk * (kCopyThreads / 64) * U, a.wpr, a.shift, t0, s0);
-        } else {
-            int c0;
-            split_chunk((int64_t)blk * (kCopyThreads * U), total, cpr, a.shift, t0, c0);
-        }
-        blk0 = t0 >> a.tile_shift;
-        scan_table<KM>(a, blk0, kept_w, before_w, nullptr);
-        kp = load_kept(kept_w, N);
-    } else {
-        kp = load_kept(a.kept_expert, N);
-    }
+    const KeptPair kp = load_kept(a.kept_expert, N);
     // table entries and limits of all choices, requested together (expert 0 stands in for a missing one)
     bool use[U][KM], live[U];
 #pragma unroll
@@ -460,13 +548,7 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
             use[u][j] = inside[u] && (KK > 0 || j < k) && (uint32_t)e[u][j] < (uint32_t)N;
             e[u][j] = use[u][j] ? e[u][j] : 0;
             cap_e[j] = cap[e[u][j]];
-            if constexpr (TABLE) {
-                first[j] = before_w[j][e[u][j]];
-                for (int b = blk0; b < tile; ++b)   // tiles that begin inside this workgroup's tokens
-                    first[j] += tile_table[(size_t)e[u][j] * a.pitch + (size_t)(KK > 0 || j < k ? j : 0) * a.n_blocks + b];
-            } else {
-                first[j] = tile_table[(size_t)e[u][j] * a.pitch + (size_t)(KK > 0 || j < k ? j : 0) * a.n_blocks + tile];
-            }
+            first[j] = tile_table[(size_t)e[u][j] * a.pitch + (size_t)(KK > 0 || j < k ? j : 0) * a.n_blocks + tile];
             if constexpr (ROWU) first[j] = __builtin_amdgcn_readfirstlane(first[j]);
         }
         live[u] = false;
@@ -478,15 +560,16 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
             live[u] |= use[u][j];
         }
     }
-    if constexpr (!TABLE) {
+    // Rows of dropped tokens are left out: a launch of this size is bound by bytes (65536 x 8 KiB: 258 us, requested at
+    // once 262; half the tokens of 16384 x 4 KiB dropped: 15.9 us, at once 17.2).
+    vec16 v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if constexpr (ROWU) {
-                v[u] = RowBuffer(x + (size_t)tok[u] * cpr, cpr, live[u]).load(col[u]);
-            } else {
-                v[u] = vec16{0u, 0u, 0u, 0u};
-                if (live[u]) v[u] = __builtin_nontemporal_load(x + (size_t)tok[u] * cpr + col[u]);
-            }
+    for (int u = 0; u < U; ++u) {
+        if constexpr (ROWU) {
+            v[u] = RowBuffer(x + (size_t)tok[u] * cpr, cpr, live[u]).load(col[u]);
+        } else {
+            v[u] = vec16{0u, 0u, 0u, 0u};
+            if (live[u]) v[u] = __builtin_nontemporal_load(x + (size_t)tok[u] * cpr + col[u]);
         }
     }
     // every lane is here: the scan and, without ROWU, the lane exchange of offset_of need them all
@@ -504,6 +587,116 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
                 store_chunk<ST>(send + (size_t)sl * cpr + col[u], v[u]);
             }
         }
+    }
+}
+
+// The same for a small table of pair counts (table_units), which every workgroup sums up by itself: one launch less, 2.5 to
+// 4.7 us (gate_dispatch and combine, us before and now: 4096 x 1 KiB, 16 experts 16.7, 14.8; 16384 x 2 KiB, 64 experts 46.0,
+// 42.8; fp32 4096 x 4 KiB 34.8, 31.7).  A wavefront has U units (64 chunks of one row, ROWU, or 64 chunks
+// anywhere), whose rows it requests, kept or not, behind the counts and before it waits for them.  At most 128
+// registers: two workgroups share a compute unit.
+// ROWU: a lane has one of the wavefront's pairs (unit, choice) and works out its slot; the stores read the slots from
+// the lanes.
+template <int KK, int U, bool ROWU, int ST, int B>
+__global__ __launch_bounds__(kTableThreads, 4) void route_table_kernel(
+    const vec16* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_pos,
+    const uint16_t* __restrict__ counts, int32_t* __restrict__ slot, vec16* __restrict__ send, const RouteArgs a) {
+    constexpr int KM = KK > 0 ? KK : TAMOE_MAX_K;
+    __shared__ TableLds t;
+    const int wg = (int)blockIdx.x;   // one generation
+    if (wg == 0) {
+        route_layer_outputs<true, KK, B>(a, &t);
+        return;
+    }
+    const int N = a.N, cpr = a.cpr, k = KK > 0 ? KK : a.k;
+    if (wg > a.copy_blocks) {
+        scan_counts<KK, B>(a, 0, t, [] {});
+        clear_unused<ST>(a, wg - 1 - a.copy_blocks, t.kept, kTableThreads);
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    const uint32_t first_unit = (uint32_t)(wg - 1) * kTableWaves * U;
+    const uint32_t unit0 = first_unit + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * U;
+    const int64_t total = a.S * cpr;
+    // token tile of the workgroup's first token
+    int t0, c0;
+    if constexpr (ROWU) split_wave(first_unit, a.wpr, a.shift, t0, c0);
+    else split_chunk((int64_t)first_unit * 64, total, cpr, a.shift, t0, c0);
+    const int blk0 = t0 >> a.tile_shift;
+    // Slot of choice j of token tok, from its expert and position; -1: none, or dropped.  All lanes call.
+    auto slot_of = [&](const WaveOffsets& wo, int32_t e, int32_t pos, int tok, int j, bool there) {
+        const bool ok = there && (uint32_t)e < (uint32_t)N;
+        e = ok ? e : 0;
+        const int at = j * N + e, tile = tok >> a.tile_shift;
+        pos += t.before[at];
+        for (int b = blk0; b < tile; ++b) pos += counts[(size_t)b * a.stride + at];   // tiles that begin inside this workgroup
+        const int32_t off = a.pad_C > 0 ? e * a.pad_C : offset_of<false>(wo, e);
+        return ok && pos < t.kept[e] ? off + pos : -1;
+    };
+    vec16 v[U];
+    if constexpr (ROWU) {
+        static_assert(U * KM <= 64, "a lane per pair of the wavefront");
+        const int pu = lane / KM, pj = lane % KM;
+        int ptok, pseg;
+        split_wave(unit0 + (pu < U ? pu : 0), a.wpr, a.shift, ptok, pseg);
+        const bool there = pu < U && pj < k && ptok < a.S;
+        const int64_t p = there ? (int64_t)ptok * k + pj : 0;
+        const int32_t e = topk_idx[p], pos = local_pos[p];
+        int tok[U], seg[U];
+        split_wave(unit0, a.wpr, a.shift, tok[0], seg[0]);
+#pragma unroll
+        for (int u = 1; u < U; ++u) {
+            const bool next = seg[u - 1] + 1 == a.wpr;
+            tok[u] = tok[u - 1] + next;
+            seg[u] = next ? 0 : seg[u - 1] + 1;
+        }
+        scan_counts<KK, B>(a, blk0, t, [&] {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool in = tok[u] < a.S;
+                v[u] = RowBuffer(x + (size_t)(in ? tok[u] : 0) * cpr, cpr, in).load(seg[u] * 64 + lane);
+            }
+        });
+        const WaveOffsets wo = wave_offsets(load_kept(t.kept, N));
+        const int32_t sl = slot_of(wo, e, pos, there ? ptok : t0, pj < k ? pj : 0, there);
+        if (there && pseg == 0) slot[p] = sl;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < KM; ++j) {
+                const int32_t to = __builtin_amdgcn_readlane(sl, u * KM + j);   // -1 where there is no such choice
+                RowBuffer(send + (size_t)(to >= 0 ? to : 0) * cpr, cpr, to >= 0).template store<ST>(seg[u] * 64 + lane, v[u]);
+            }
+    } else {
+        int tok[U], col[U];
+        bool inside[U];
+        int32_t e[U][KM], pos[U][KM];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t c = (int64_t)(unit0 + u) * 64 + lane;
+            inside[u] = c < total;
+            split_chunk(inside[u] ? c : total - 1, total, cpr, a.shift, tok[u], col[u]);
+#pragma unroll
+            for (int j = 0; j < KM; ++j) {
+                const int64_t p = (int64_t)tok[u] * k + (KK > 0 || j < k ? j : k - 1);
+                e[u][j] = topk_idx[p];
+                pos[u][j] = local_pos[p];
+            }
+        }
+        scan_counts<KK, B>(a, blk0, t, [&] {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(x + (size_t)tok[u] * cpr + col[u]);
+        });
+        const WaveOffsets wo = wave_offsets(load_kept(t.kept, N));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < KM; ++j) {
+                const bool there = inside[u] && (KK > 0 || j < k);
+                const int32_t sl = slot_of(wo, e[u][j], pos[u][j], tok[u], KK > 0 || j < k ? j : 0, there);
+                if (there && col[u] == 0) slot[(int64_t)tok[u] * k + j] = sl;
+                if (sl >= 0) store_chunk<ST>(send + (size_t)sl * cpr + col[u], v[u]);
+            }
     }
 }
 
@@ -537,10 +730,11 @@ static bool scatter_by_wave(int64_t S, int cpr, int k) {
 //  - flat ones from L2 (57974 x 1040, four 111 / 136 / 121; 115651 x 272, two 61 / 65 / 65), one choice streaming beyond
 //    96 MiB;
 //  - the fixed-size layout streams beyond 96 MiB: its padding takes the place of rows (14117 x 7328, two, 237 MiB 131
-//    streaming, 149 through; 56000 x 1 KiB, three, 205 MiB 99 and 101).
+//    streaming, 149 through; 56000 x 1 KiB, three, 205 MiB 99 and 101), flat rows come from L2 (14488 x 768, two 28.0,
+//    through 28.5).
 static int scatter_store(int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
     const int64_t mib = rows * cpr * 16 >> 20;
-    if (padded && mib > 96) return kStoreStream;
+    if (padded && (mib > 96 || !by_wave)) return mib > 96 ? kStoreStream : kStoreBack;
     if (cpr % 8 == 0) {
         const int from = behind_gate && by_wave ? 8 : 0;
         const int to = behind_gate ? (k <= 2 ? 16 : 24) : !by_wave && k > 4 ? 32 : 0;
@@ -563,32 +757,28 @@ static int64_t copy_workgroups(int64_t S, int cpr, int k) {
 
 // Fills in the launch geometry.
 static void plan_copy(RouteArgs& a) {
+    const bool by_wave = scatter_by_wave(a.S, a.cpr, a.k);
     a.wpr = row_waves(a.cpr);
-    a.shift = pow2_shift(scatter_by_wave(a.S, a.cpr, a.k) ? a.wpr : a.cpr);
-    a.copy_blocks = (int)copy_workgroups(a.S, a.cpr, a.k);
+    a.shift = pow2_shift(by_wave ? a.wpr : a.cpr);
+    a.copy_blocks = a.units == 0 ? (int)copy_workgroups(a.S, a.cpr, a.k)
+                                 : (int)ceil_div(by_wave ? a.S * a.wpr : ceil_div(a.S * (int64_t)a.cpr, 64), kTableWaves * a.units);
     // zeros of a large buffer would take the place of its rows in the last-level cache: 53902 x 1536 bytes, half of them
     // padding 86 us, streamed 78; 8192 x 8 KiB 66 and 61; but 6144 x 2 KiB (48 MiB) 28.7 and 29.2
     a.fill_streams = (int64_t)a.N * a.pad_C * a.cpr * 16 > (int64_t)64 << 20;
-    // about 4096 workgroups clear rows, at most one per 4 KiB of an expert's rows
-    a.fill_parts = a.pad_C == 0 ? 0 : (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(4096, a.N),
-                                                                     ceil_div((int64_t)a.pad_C * a.cpr, kCopyThreads)));
+    // about 4096 workgroups clear rows (512 of the larger ones that sum the table), at most one per 16 bytes per thread
+    const int wgs = a.units == 0 ? 4096 : 512, threads = a.units == 0 ? kCopyThreads : kTableThreads;
+    a.fill_parts = a.pad_C == 0 ? 0 : (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(wgs, a.N),
+                                                                     ceil_div((int64_t)a.pad_C * a.cpr, threads)));
 }
 
 template <int KK>
-static void launch_route_copy(const RouteArgs& a, bool table, hipStream_t st) {
+static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
     constexpr int U = copy_units(KK);
     const dim3 grid = grid_of(1 + (int64_t)a.copy_blocks + (int64_t)a.N * a.fill_parts, kCopyThreads), block(kCopyThreads);
     const int64_t rows = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : a.S * a.k;
     const int32_t* caps = a.cap != nullptr ? a.cap : a.table;   // N entries at least
-#define TAMOE_ROUTE_COPY(RU, ST)                                                         \
-    do {                                                                                 \
-        if (table)                                                                       \
-            route_copy_kernel<KK, U, RU, ST, true><<<grid, block, 0, st>>>(              \
-                a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a);        \
-        else                                                                             \
-            route_copy_kernel<KK, U, RU, ST, false><<<grid, block, 0, st>>>(             \
-                a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a);        \
-    } while (0)
+#define TAMOE_ROUTE_COPY(RU, ST)                                                          \
+    route_copy_kernel<KK, U, RU, ST><<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
     const bool rowu = scatter_by_wave(a.S, a.cpr, a.k);
     const int policy = scatter_store(rows, a.cpr, a.k, rowu, a.m_part != nullptr, a.pad_C > 0);
 #define TAMOE_ROUTE_COPY_ST(ST)                                                          \
@@ -602,17 +792,73 @@ static void launch_route_copy(const RouteArgs& a, bool table, hipStream_t st) {
 #undef TAMOE_ROUTE_COPY
 }
 
+// Units (64 chunks) per wavefront with which the scatter sums the table itself (route_table_kernel); 0: with
+// route_expert_kernel and route_copy_kernel.
+// The table has to be one batch of scan_counts: a second one is a second memory round trip (5003 x 2000 bytes, 157 tiles
+// of 192 counts: 65.9 us for a training pass, 65.7 with the launch).  Units: as many as leave a workgroup per compute
+// unit, since each one sums the table (small_forward, 4096 units: with two 14.8, with one 17.5; gpt_moe_forward, 32768: with
+// eight 43.0, with four 45.3); beyond 65536 of them (64 MiB of x) the launch that is saved counts for little, and for a
+// routing that is given, behind which x does not come from the last-level cache, beyond 32768 (skewed_separate, 65536: 53.7 with the
+// launch, 54.7 without; fused, 16384 x 4 KiB, one choice 59.7 and 56.7).  Flat rows have
+// the work of a slot in every lane, and at most two units (57635 x 384 bytes, two choices 45.5 and 47.5).
+static int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool behind_gate) {
+    // the sums of a wavefront's share of the tiles fit 16 bits
+    if (S > 200000 || ceil_div(S, tile_tokens) * (count_stride(N, k) / 8) > kTableBatch * kTableThreads) return 0;
+    const bool by_wave = scatter_by_wave(S, cpr, k);
+    const int64_t units = by_wave ? S * row_waves(cpr) : ceil_div(S * (int64_t)cpr, 64);
+    if (units > (!by_wave ? 8192 : behind_gate ? 65536 : 32768)) return 0;
+    int U = 1;
+    while (U < (by_wave ? 8 : 2) && units >= kTableWaves * U * 2 * 256) U *= 2;
+    return U;
+}
+
+template <int KK, int U, bool ROWU>
+static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
+    const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(kTableThreads);
+    const int64_t rows = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : a.S * a.k;
+    const int policy = scatter_store(rows, a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
+    // the smallest tables in a kernel that is shorter by seven requests and their sums
+    const bool one = U == 1 && (int64_t)a.n_blocks * (a.stride / 8) <= kTableThreads;
+#define TAMOE_ROUTE_TABLE(ST)                                                                      \
+    do {                                                                                           \
+        if (one)                                                                                   \
+            route_table_kernel<KK, U, ROWU, ST, U == 1 ? 1 : kTableBatch>                          \
+                <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a); \
+        else                                                                                       \
+            route_table_kernel<KK, U, ROWU, ST, kTableBatch>                                       \
+                <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a); \
+    } while (0)
+    if (policy == kStoreStream) TAMOE_ROUTE_TABLE(kStoreStream);
+    else if (policy == kStoreThrough) TAMOE_ROUTE_TABLE(kStoreThrough);
+    else TAMOE_ROUTE_TABLE(kStoreBack);
+#undef TAMOE_ROUTE_TABLE
+}
+template <int KK>
+static void launch_route_table(const RouteArgs& a, hipStream_t st) {
+    if (!scatter_by_wave(a.S, a.cpr, a.k)) {
+        if (a.units == 1) launch_route_table_u<KK, 1, false>(a, st);
+        else launch_route_table_u<KK, 2, false>(a, st);
+    } else {
+        if (a.units == 1) launch_route_table_u<KK, 1, true>(a, st);
+        else if (a.units == 2) launch_route_table_u<KK, 2, true>(a, st);
+        else if (a.units == 4) launch_route_table_u<KK, 4, true>(a, st);
+        else launch_route_table_u<KK, 8, true>(a, st);
+    }
+}
+
 // Stages 2 and 3, for table and positions as `run` describes them.
 static int run_copy(const char* fn, const GateRun& run, RouteArgs a, const char* label, hipStream_t st) {
     int rc;
     a.local_pos = run.stats.local_pos;
     a.table = run.stats.tile_pairs;
+    a.counts = run.stats.counts;
+    a.stride = run.stats.stride;
     a.n_blocks = run.stats.n_blocks;
     a.pitch = run.stats.pitch;
     a.tile_shift = pow2_shift(run.tile_tokens);
+    const bool table = a.counts != nullptr;
+    a.units = table ? table_units(a.S, a.cpr, a.N, a.k, run.tile_tokens, a.m_part != nullptr) : 0;
     plan_copy(a);
-    const int64_t blocks = (int64_t)a.copy_blocks + (int64_t)a.N * a.fill_parts;
-    const bool table = a.S == 0 || (blocks <= kTableBlocks && blocks * a.N * a.k * a.n_blocks <= kTableReads);
     if (!table) {
         TraceScope tr("route_expert_kernel", st);
         route_expert_kernel<<<dim3(a.N), dim3(kExpertThreads), 0, st>>>(a.m_part, run.stats.tile_pairs, a.n_blocks,
@@ -622,18 +868,18 @@ static int run_copy(const char* fn, const GateRun& run, RouteArgs a, const char*
     }
     {
         TraceScope tr(label, st);
-        if (a.k == 1)
-            launch_route_copy<1>(a, table, st);
-        else if (a.k == 2)
-            launch_route_copy<2>(a, table, st);
-        else if (a.k == 3)
-            launch_route_copy<3>(a, table, st);
-        else if (a.k == 4)
-            launch_route_copy<4>(a, table, st);
-        else
-            launch_route_copy<0>(a, table, st);
+#define TAMOE_ROUTE(KK)                                                               \
+    do {                                                                              \
+        if (table) launch_route_table<KK>(a, st); else launch_route_copy<KK>(a, st);  \
+    } while (0)
+        if (a.k == 1) TAMOE_ROUTE(1);
+        else if (a.k == 2) TAMOE_ROUTE(2);
+        else if (a.k == 3) TAMOE_ROUTE(3);
+        else if (a.k == 4) TAMOE_ROUTE(4);
+        else TAMOE_ROUTE(0);
+#undef TAMOE_ROUTE
     }
-    return check_launch(fn, "route_copy_kernel");
+    return check_launch(fn, table ? "route_table_kernel" : "route_copy_kernel");
 }
 
 int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const int32_t* cap, int64_t S, int cpr, int N,
@@ -643,10 +889,11 @@ int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const i
     // a few more workgroups are added
     if (S > 0 && std::max(ceil_div(S * (int64_t)cpr, kCopyThreads), copy_workgroups(S, cpr, k)) >= 0x7fff0000)
         return fail(TAMOE_UNSUPPORTED, "%s: x is too large for one launch", fn);
+    const bool table = table_units(S, cpr, N, k, rank_tokens(S, N, k), false) > 0;
     const int tok = rank_tokens(S, N, k);
     const int64_t blocks = ceil_div(S, tok);
     GateRun run{};
-    run.stats = stats_in(ws, lay, k, blocks);
+    run.stats = stats_in(ws, lay, N, k, blocks, table);
     run.tile_tokens = tok;
     if (blocks > 0) {
         TraceScope tr("route_rank_kernel", st);
@@ -716,7 +963,8 @@ extern "C" int tamoe_gate_dispatch(const void* x, const void* w, int dtype, int6
     hipStream_t st = static_cast<hipStream_t>(stream);
 
     GateRun run{};
-    if ((rc = run_gate_stage(fn, x, w, dtype, S, d, N, k, logits, topk_idx, topk_w, ws, lay, st, &run)) != TAMOE_OK)
+    const bool table = table_units(S, cpr, N, k, gate_tile_tokens(S, N), true) > 0;
+    if ((rc = run_gate_stage(fn, x, w, dtype, S, d, N, k, logits, topk_idx, topk_w, table, ws, lay, st, &run)) != TAMOE_OK)
         return rc;
 
     RouteArgs a{};

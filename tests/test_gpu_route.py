@@ -87,3 +87,35 @@ def test_fused_call_against_separate_calls(T, S, d, N, P, k):
     # sums of S (then N) 32-bit terms of one sign in another order
     torch.testing.assert_close(f["m"], a["m"], rtol=1e-5, atol=1e-9)
     torch.testing.assert_close(f["loss"], loss, rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("S,d,N,P,k", [
+    (33, 8, 2, 2, 2), (1000, 64, 3, 3, 1), (4095, 512, 16, 16, 2), (4096, 512, 16, 16, 2), (8191, 512, 40, 8, 2),        # units per wavefront
+    (16390, 512, 40, 8, 1), (16384, 1024, 64, 64, 2), (16385, 1024, 33, 11, 3), (65536, 512, 16, 4, 2), (65537, 512, 16, 4, 2),   # and no more
+    (3000, 1000, 64, 8, 4), (4128, 264, 64, 8, 4), (2000, 1544, 128, 8, 4), (2000, 264, 128, 8, 5), (1000, 1544, 128, 8, 8), (16384, 256, 16, 4, 2), (16385, 256, 16, 4, 2), (200000, 8, 8, 8, 2), (200001, 8, 8, 8, 2),  # columns
+    (2047, 128, 64, 8, 8), (2049, 128, 64, 8, 8), (777, 136, 5, 5, 5), (513, 2056, 127, 127, 3)])
+def test_table_summed_by_the_scatter(T, S, d, N, P, k):
+    """The fused call and tamoe_dispatch on both sides of the rule that leaves out the per-expert launch, against
+    tamoe_dispatch_static; some capacities keep nothing, some everything."""
+    g = torch.Generator(device="cuda").manual_seed(S + d + N)
+    x = torch.randn((S, d), generator=g, device="cuda").bfloat16()
+    w = (torch.randn((N, d), generator=g, device="cuda") / d ** 0.5).bfloat16()
+    pen = torch.rand(N, generator=g, device="cuda")
+    cap = torch.randint(0, max(2, 2 * S * k // N), (N,), generator=g, device="cuda", dtype=torch.int32)
+    cap[0], cap[N - 1] = 0, S
+    f = T.gate_dispatch(x, w, P, k, pen, cap)
+    q = T.dispatch(x, f["topk_idx"], cap, N, P)
+    s = {key: torch.empty_like(v) for key, v in q.items()}
+    T.tamoe_dispatch_static(x, f["topk_idx"], cap, N, P, s["send"], s["slot"], s["kept_expert"], s["expert_offset"], s["send_count_dev"])
+    K = int(s["expert_offset"][-1])
+    for key in ("slot", "kept_expert", "expert_offset", "send_count_dev"):
+        assert torch.equal(q[key], s[key]), key
+        assert torch.equal(f[key], s[key]), key
+    assert torch.equal(q["send"][:K].view(torch.int16), s["send"][:K].view(torch.int16))
+    assert torch.equal(f["send"][:K].view(torch.int16), s["send"][:K].view(torch.int16))
+    count = torch.bincount(f["topk_idx"].reshape(-1).long(), minlength=N)
+    assert torch.equal(f["c_expert"].long(), count) and torch.equal(f["c_device"].long(), count.view(P, -1).sum(1))
+    # sums of S (then N) 32-bit terms of one sign
+    m = torch.softmax(f["logits"].double(), 1).mean(0)
+    torch.testing.assert_close(f["m"].double(), m, rtol=1e-5, atol=1e-9)
+    torch.testing.assert_close(f["loss"].double().reshape(()), N * P / S * (pen.double() * m * count).sum(), rtol=1e-5, atol=0)
