@@ -171,18 +171,21 @@ __device__ __forceinline__ float butterfly_sum(float v) {
 //   u[e]  = coef[e] + sum_j d_w[t][j] * [idx[t][j] == e],   coef[e] = scale * p[e] * c[e]
 //   dl[e] = G[e] * (u[e] - sum_e' u[e'] G[e'])
 // VEC: N is a multiple of 4, rows are 16-byte aligned and each lane moves one dwordx4.
-template <int LPT, bool VEC>
+// Latency at most sizes: a lane requests its scores, its four penalties and counts and the token's pairs before it waits
+// for anything.  (With the coefficients made once per workgroup in LDS behind a barrier, the pairs requested one after the
+// other and ordinary stores the three backward calls took, before and now: 16384 x 64, 64 experts, two choices and rows
+// of 2 KiB 48.2 us, 47.3, four choices and rows of 128 bytes 15.0, 13.7; 65536, 128 experts, eight 61.8, 55.1.)
+// KK > 0: k is the compile-time constant KK; KK == 0: any k.
+template <int LPT, bool VEC, int KK>
 __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restrict__ logits,
                                                             const int32_t* __restrict__ idx,
                                                             const float* __restrict__ d_w,
                                                             const float* __restrict__ penalty,
                                                             const int32_t* __restrict__ c, float scale, int64_t S,
-                                                            int N, int k, float* __restrict__ d_logits) {
-    __shared__ float coef[TAMOE_MAX_EXPERTS + 4];
+                                                            int N, int k_arg, float* __restrict__ d_logits) {
+    constexpr int KM = KK > 0 ? KK : TAMOE_MAX_K;
+    const int k = KK > 0 ? KK : k_arg;
     const int tid = threadIdx.x;
-    for (int e = tid; e < TAMOE_MAX_EXPERTS + 4; e += kThreads)
-        coef[e] = e < N ? scale * (penalty != nullptr ? penalty[e] : 1.0f) * (float)c[e] : 0.f;
-    __syncthreads();
     const int64_t token = ((int64_t)linear_block() * kThreads + tid) / LPT;
     const int e0 = (tid % LPT) * 4;
     const bool token_ok = token < S;
@@ -191,13 +194,29 @@ __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restr
 
     float l[4];
     if (VEC) {
-        const float4 q = (token_ok && e0 < N) ? *reinterpret_cast<const float4*>(row + e0)
-                                             : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        const float4 q = *reinterpret_cast<const float4*>(row + (e0 < N ? e0 : 0));
         l[0] = q.x; l[1] = q.y; l[2] = q.z; l[3] = q.w;
     } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) l[i] = (token_ok && e0 + i < N) ? row[e0 + i] : -INFINITY;
+        for (int i = 0; i < 4; ++i) l[i] = row[e0 + i < N ? e0 + i : 0];
     }
+    // zeros beyond N
+    const __amdgpu_buffer_rsrc_t cb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(c), 0, N * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t pb =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(penalty), 0, penalty != nullptr ? N * 4 : 0, 0x00020000);
+    const int4 cnt = __builtin_bit_cast(int4, __builtin_amdgcn_raw_buffer_load_b128(cb, e0 * 4, 0, 0));
+    const float4 pen = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(pb, e0 * 4, 0, 0));
+    int sel[KM];
+    float dw[KM];
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {
+        const int64_t p = tk * k + (KK > 0 || j < k ? j : k - 1);
+        sel[j] = idx[p];
+        dw[j] = d_w[p];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) l[i] = (token_ok && e0 + i < N) ? l[i] : -INFINITY;
+
     float mx = butterfly_max<LPT>(fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
     if (!token_ok) mx = 0.f;
     float g[4], part = 0.f;
@@ -208,17 +227,19 @@ __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restr
     }
     const float den = butterfly_sum<LPT>(part);
     const float inv = token_ok ? 1.0f / den : 0.f;
+    const float pe[4] = {pen.x, pen.y, pen.z, pen.w};
+    const int32_t ce[4] = {cnt.x, cnt.y, cnt.z, cnt.w};
     float u[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         g[i] *= inv;
-        u[i] = coef[e0 + i];
+        u[i] = scale * (penalty != nullptr ? pe[i] : 1.0f) * (float)ce[i];
     }
-    for (int j = 0; j < k; ++j) {
-        const int sel = token_ok ? idx[tk * k + j] : -1;
-        const float dwt = token_ok ? d_w[tk * k + j] : 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) u[i] += (sel == e0 + i) ? dwt : 0.f;
+    for (int j = 0; j < KM; ++j) {
+        const bool there = token_ok && (KK > 0 || j < k);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[i] += there && sel[j] == e0 + i ? dw[j] : 0.f;
     }
     float ub = 0.f;
 #pragma unroll
@@ -228,8 +249,9 @@ __global__ __launch_bounds__(kThreads) void gate_bwd_kernel(const float* __restr
         float* out = d_logits + (size_t)token * N;
         if (VEC) {
             if (e0 < N)
-                *reinterpret_cast<float4*>(out + e0) =
-                    make_float4(g[0] * (u[0] - ubar), g[1] * (u[1] - ubar), g[2] * (u[2] - ubar), g[3] * (u[3] - ubar));
+                store_chunk<kStoreThrough>(reinterpret_cast<vec16*>(out + e0),
+                                           vec16{__float_as_uint(g[0] * (u[0] - ubar)), __float_as_uint(g[1] * (u[1] - ubar)),
+                                                 __float_as_uint(g[2] * (u[2] - ubar)), __float_as_uint(g[3] * (u[3] - ubar))});
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -244,10 +266,17 @@ static void launch_gate_bwd(const float* logits, const int32_t* idx, const float
     const dim3 grid = grid_of(ceil_div(S * LPT, kThreads), kThreads), block(kThreads);
     const bool vec = N % 4 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0 &&
                      reinterpret_cast<uintptr_t>(d_logits) % 16 == 0;
-    if (vec)
-        gate_bwd_kernel<LPT, true><<<grid, block, 0, st>>>(logits, idx, d_w, penalty, c, scale, S, N, k, d_logits);
-    else
-        gate_bwd_kernel<LPT, false><<<grid, block, 0, st>>>(logits, idx, d_w, penalty, c, scale, S, N, k, d_logits);
+#define TAMOE_GATE_BWD(KK)                                                                                              \
+    do {                                                                                                                \
+        if (vec)                                                                                                        \
+            gate_bwd_kernel<LPT, true, KK><<<grid, block, 0, st>>>(logits, idx, d_w, penalty, c, scale, S, N, k, d_logits);  \
+        else                                                                                                            \
+            gate_bwd_kernel<LPT, false, KK><<<grid, block, 0, st>>>(logits, idx, d_w, penalty, c, scale, S, N, k, d_logits); \
+    } while (0)
+    if (k == 1) TAMOE_GATE_BWD(1);
+    else if (k == 2) TAMOE_GATE_BWD(2);
+    else TAMOE_GATE_BWD(0);
+#undef TAMOE_GATE_BWD
 }
 
 // d_recv is written straight through L2 at almost any size: the last-level cache keeps what fits of it for the kernel that

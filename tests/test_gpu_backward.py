@@ -85,6 +85,14 @@ def test_gate_bwd(T, oracle, S, N, P, k, use_penalty):
     assert (np.abs(got0 - ref0) <= dlogits_bound(oracle, lg, idx, np.zeros((S, k)), pen, c, 1000.0, P)).all()
 
 
+@pytest.mark.parametrize("S,N,P,k,use_penalty", [
+    (65, 30, 30, 1, True), (33, 31, 31, 2, False), (64, 5, 5, 5, True), (17, 126, 42, 3, True), (1, 128, 64, 2, False),
+    (1025, 4, 2, 4, True), (130, 62, 31, 8, True)])
+def test_gate_bwd_edges(T, oracle, S, N, P, k, use_penalty):
+    """Every number of choices that has code of its own, experts that do not fill their lanes, partly empty workgroups."""
+    test_gate_bwd(T, oracle, S, N, P, k, use_penalty)
+
+
 @pytest.mark.parametrize("dtype,S,d,k,frac", [
     (W.BF16, 3000, 136, 2, 0.8), (W.BF16, 700, 4096, 2, 1.0), (W.BF16, 5000, 512, 1, 0.5),
     (W.F32, 900, 36, 3, 0.7), (W.BF16, 333, 1032, 5, 0.6), (W.F32, 1, 4, 1, 1.0),
