@@ -726,7 +726,7 @@ static bool scatter_by_wave(int64_t S, int cpr, int k) {
 //    of many choices gain on their own too (8192 x 512 bytes, eight 27.8 and 28.6);
 //  - rows that are no whole lines, by wavefront: through (9830 x 4000, two 45.8 / 46.1 / 44.9; 47185 x 2000, two 134.5 /
 //    137.6 / 132.2), with many choices from L2, which merges their lines (11320 x 6368, eight 273 / 287 / 286);
-//    rows of half lines stream (39321 x 1600, two 93 / 88 / 92, 9611 x 3008, four 70 / 67 / 69);
+//    rows of half lines stream (39321 x 1600, two 93 / 88 / 92, 9611 x 3008, four 70 / 67 / 69; 4342 x 7744, six 111 from L2, 107);
 //  - flat ones from L2 (57974 x 1040, four 111 / 136 / 121; 115651 x 272, two 61 / 65 / 65), one choice streaming beyond
 //    96 MiB;
 //  - the fixed-size layout streams beyond 96 MiB: its padding takes the place of rows (14117 x 7328, two, 237 MiB 131
@@ -743,7 +743,7 @@ static int scatter_store(int64_t rows, int cpr, int k, bool by_wave, bool behind
     }
     if (!by_wave) return mib <= (k == 1 ? 96 : k == 2 ? 240 : 640) ? kStoreBack : kStoreStream;
     if (mib <= 24) return kStoreThrough;
-    if (k <= 4 && cpr % 4 == 0) return kStoreStream;
+    if (cpr % 4 == 0 && (k <= 4 || mib > 96)) return kStoreStream;
     if (k <= 4 && mib <= 240) return kStoreThrough;
     return k > 2 && mib <= 640 ? kStoreBack : kStoreStream;
 }
