@@ -721,7 +721,8 @@ static bool scatter_by_wave(int64_t S, int cpr, int k) {
 // with ordinary / streaming / through stores:
 //  - rows of whole lines go straight through L2 as long as they fit the last-level cache (30720 x 2 KiB, two choices 44.5 /
 //    46.4 / 43.7; 14720 x 8 KiB, two 133.9 / 140.7 / 134.0; 17280 x 8 KiB, two 181 / 174 / 181; 34560 x 8 KiB, one 238 /
-//    252 / 235).  Small buffers that nothing but the combine of an identity layer reads are
+//    252 / 235), and beyond past that too (nt sc1 sc0, against nt alone: 65536 x 8 KiB, two 623.2 and 625.0, 65536 x 4 KiB,
+//    three 393.1 and 395.7; other rows lose by it, 30000 x 6368 258.7 and 247.5).  Small buffers that nothing but the combine of an identity layer reads are
 //    partly in L2 then (6144 x 1 KiB, two 18.2 / 20.0 / 18.9; dispatch alone 20.9 and 19.6 with through stores), short rows
 //    of many choices gain on their own too (8192 x 512 bytes, eight 27.8 and 28.6);
 //  - rows that are no whole lines, by wavefront: through (9830 x 4000, two 45.8 / 46.1 / 44.9; 47185 x 2000, two 134.5 /
@@ -734,12 +735,12 @@ static bool scatter_by_wave(int64_t S, int cpr, int k) {
 //    through 28.5).
 static int scatter_store(int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
     const int64_t mib = rows * cpr * 16 >> 20;
-    if (padded && (mib > 96 || !by_wave)) return mib > 96 ? kStoreStream : kStoreBack;
+    if (padded && (mib > 96 || !by_wave)) return mib <= 96 ? kStoreBack : cpr % 8 == 0 ? kStoreOut : kStoreStream;
     if (cpr % 8 == 0) {
         const int from = behind_gate && by_wave ? 8 : 0;
         const int to = behind_gate ? (k <= 2 ? 16 : 24) : !by_wave && k > 4 ? 32 : 0;
         if (mib >= from && mib < to) return kStoreBack;
-        return mib <= (k == 1 ? 360 : 240) ? kStoreThrough : kStoreStream;
+        return mib <= (k == 1 ? 360 : 240) ? kStoreThrough : kStoreOut;
     }
     if (!by_wave) return mib <= (k == 1 ? 96 : k == 2 ? 240 : 640) ? kStoreBack : kStoreStream;
     if (mib <= 24) return kStoreThrough;
@@ -786,6 +787,7 @@ static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
         if (rowu) TAMOE_ROUTE_COPY(true, ST); else TAMOE_ROUTE_COPY(false, ST);          \
     } while (0)
     if (policy == kStoreStream) TAMOE_ROUTE_COPY_ST(kStoreStream);
+    else if (policy == kStoreOut) TAMOE_ROUTE_COPY_ST(kStoreOut);
     else if (policy == kStoreThrough) TAMOE_ROUTE_COPY_ST(kStoreThrough);
     else TAMOE_ROUTE_COPY_ST(kStoreBack);
 #undef TAMOE_ROUTE_COPY_ST
@@ -828,7 +830,7 @@ static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
             route_table_kernel<KK, U, ROWU, ST, kTableBatch>                                       \
                 <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a); \
     } while (0)
-    if (policy == kStoreStream) TAMOE_ROUTE_TABLE(kStoreStream);
+    if (policy == kStoreStream || policy == kStoreOut) TAMOE_ROUTE_TABLE(kStoreStream);
     else if (policy == kStoreThrough) TAMOE_ROUTE_TABLE(kStoreThrough);
     else TAMOE_ROUTE_TABLE(kStoreBack);
 #undef TAMOE_ROUTE_TABLE
