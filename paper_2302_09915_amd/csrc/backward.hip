@@ -281,8 +281,8 @@ static void launch_gate_bwd(const float* logits, const int32_t* idx, const float
 
 // d_recv is written straight through L2 at almost any size: the last-level cache keeps what fits of it for the kernel that
 // reads it next, and no dirty line is left for the end of this one.  combine_bwd and dispatch_bwd together: 58880
-// x 2 KiB, two choices (230 MiB) 159 us with ordinary stores, 194 streaming, 155 now; 128 rows of 8 KiB per MiB, 400 MiB
-// 276, 304, 272; 65536 x 8 KiB 782, 795, 770; 64527 x 1040 bytes 110, 110, 108.  Streaming is the better way only
+// x 2 KiB, two choices (230 MiB) 159 us with ordinary stores, 194 streaming, 155 now; 25600 x 8 KiB, two
+// 276, 304, 272; 65536 x 8 KiB, two 782, 795, 770; 64527 x 1040 bytes 110, 110, 108.  Streaming is the better way only
 // for one choice and rows just over one wavefront, which two of them write (129055 x 1040: 154, 146, 151), ordinary
 // stores for the small buffers that the scatter left in L2 (a whole layer's pass of 1000 x 8 KiB, two choices 47.7 and
 // 49.5 through, 600 x 8 KiB, four 51.2 and 53.9; this and dispatch_bwd on their own 15.1 and 14.8).
