@@ -173,12 +173,12 @@ enum StorePolicy {
     kStoreThrough = 16,  // sc1: straight through L2; the last-level cache keeps the line
     kStoreOut = 19       // nt sc1 sc0: straight through L2, not kept
 };
-// A chunk by address, with one of these policies.  (s_nop: the instruction behind a store of more than 8 bytes must not
-// overwrite its data, and the compiler looks at its own stores only.)
+// A chunk by address, with one of these policies.  (s_nop: a vector instruction must not overwrite the data of a store of
+// more than 8 bytes in the two wait states behind it, and the compiler looks at its own stores only.)
 template <int ST>
 __device__ __forceinline__ void store_chunk(vec16* p, vec16 v) {
-    if constexpr (ST == kStoreThrough) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
-    else if constexpr (ST == kStoreOut) asm volatile("global_store_dwordx4 %0, %1, off sc0 nt sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+    if constexpr (ST == kStoreThrough) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+    else if constexpr (ST == kStoreOut) asm volatile("global_store_dwordx4 %0, %1, off sc0 nt sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
     else if constexpr (ST == kStoreStream) __builtin_nontemporal_store(v, p);
     else *p = v;
 }
