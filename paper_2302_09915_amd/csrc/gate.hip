@@ -32,7 +32,6 @@ __global__ __launch_bounds__(512) void select_kernel(const float* __restrict__ l
     __shared__ float m_w[WAVES * ROWS];
     __shared__ int32_t pairs[TAMOE_MAX_K * ROWS];
     __shared__ signed char sel[TOK * TAMOE_MAX_K];
-    __shared__ unsigned char rank[TOK * TAMOE_MAX_K];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t tile0 = (int64_t)linear_block() * TOK;
@@ -48,7 +47,7 @@ __global__ __launch_bounds__(512) void select_kernel(const float* __restrict__ l
     };
     select_tokens<NB, WAVES, TOK>(load_scores, lane, wave, tile0, S, N, k, nullptr, topk_idx, topk_w, sel,
                                   m_w + wave * ROWS);
-    finish_block<NB, WAVES, TOK>(m_w, sel, rank, pairs, lane, wave, tile0, S, N, k, gs);
+    finish_block<NB, WAVES, TOK>(m_w, sel, nullptr, pairs, lane, wave, tile0, S, N, k, gs);
 }
 
 // Fixed-order sums of the per-workgroup partials: one workgroup per expert, then one per device (E experts).
