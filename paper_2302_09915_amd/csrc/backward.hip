@@ -279,19 +279,6 @@ static void launch_gate_bwd(const float* logits, const int32_t* idx, const float
 #undef TAMOE_GATE_BWD
 }
 
-// d_recv is written straight through L2 at almost any size: the last-level cache keeps what fits of it for the kernel that
-// reads it next, and no dirty line is left for the end of this one.  combine_bwd and dispatch_bwd together: 58880
-// x 2 KiB, two choices (230 MiB) 159 us with ordinary stores, 194 streaming, 155 now; 25600 x 8 KiB, two
-// 276, 304, 272; 65536 x 8 KiB, two 782, 795, 770; 64527 x 1040 bytes 110, 110, 108.  Streaming is the better way only
-// for one choice and rows just over one wavefront, which two of them write (129055 x 1040: 154, 146, 151), ordinary
-// stores for the small buffers that the scatter left in L2 (a whole layer's pass of 1000 x 8 KiB, two choices 47.7 and
-// 49.5 through, 600 x 8 KiB, four 51.2 and 53.9; this and dispatch_bwd on their own 15.1 and 14.8).
-static int combine_bwd_store(int64_t S, int cpr, int k) {
-    const int64_t mib = S * k * (int64_t)cpr * 16 >> 20;
-    if (k == 1 && cpr > 64 && cpr < 68 && mib > 48) return kStoreStream;
-    return k > 1 && cpr >= 64 && cpr % 8 == 0 && mib >= 8 && mib < 24 ? kStoreBack : kStoreThrough;
-}
-
 template <int DT, int KK, int ST>
 static void launch_combine_bwd_s(const vec16* dy, const vec16* recv, int64_t K_rows, const int32_t* slot,
                                  const float* topk_w, int64_t S, int k, int cpr, vec16* d_recv, float* d_w,
@@ -313,7 +300,7 @@ template <int DT, int KK>
 static void launch_combine_bwd_k(const vec16* dy, const vec16* recv, int64_t K_rows, const int32_t* slot,
                                  const float* topk_w, int64_t S, int k, int cpr, vec16* d_recv, float* d_w,
                                  hipStream_t st) {
-    const int policy = combine_bwd_store(S, cpr, k);
+    const StorePolicy policy = combine_bwd_store(row_lines(d_recv, cpr), S, cpr, k);
     if (policy == kStoreThrough)
         launch_combine_bwd_s<DT, KK, kStoreThrough>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
     else if (policy == kStoreStream)

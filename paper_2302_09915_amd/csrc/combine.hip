@@ -73,16 +73,6 @@ static bool combine_by_wave(int64_t S, int cpr, int k) {
     return rows_by_wave(cpr) && !(poor_last_wave(S, cpr, 4) && k >= wpr - 1 && k <= wpr + 1);
 }
 
-// y goes straight through L2 and is not kept: ordinary stores are written back behind the last wavefront, and streaming
-// ones still wait in L2 for their turn (the whole forward call on 16384 x 2 KiB, two choices: 47.8 us with ordinary
-// stores, 47.5 streaming, 46.5 straight through; 65536 x 8 KiB 663, 625, 626).  Rows that are no whole lines only with three
-// and more choices (18970 x 1520, four 75.2 streaming, 73.5; 23592 x 2000, four 109.3, 105.7); with two what is gained on rows
-// from the last-level cache is lost on others (28835 x 2000 86.0, 84.5; fixed-size layout, 24898 x 5488 169.8, 171.9), with
-// one all of it (28050 x 4112: 113.8, 116.6); and flat rows not at all (fixed-size layout, 15808 x 640, two 28.3, 28.8).
-static bool combine_writes_out(int64_t S, int cpr, int k) {
-    return combine_by_wave(S, cpr, k) && (k > 2 || cpr % 8 == 0) && S * (int64_t)cpr * 16 <= (int64_t)256 << 20;
-}
-
 // Other rows: chunks flat over the lanes.  More than four choices (KK == 0) are taken four at a time: loads
 // under a condition per lane hold registers across each other, and eight of them left room for one
 // wavefront per SIMD in fp32.
@@ -160,7 +150,7 @@ static void launch_combine_s(const void* recv, int64_t K_rows, const int32_t* sl
 template <int DT, int KK, int U, bool UNITW>
 static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* slot, const float* topk_w, int64_t S,
                              int k, int cpr, void* y, hipStream_t st) {
-    if (combine_writes_out(S, cpr, k))
+    if (combine_store(row_lines(y, cpr), S, cpr, k, combine_by_wave(S, cpr, k)) == kStoreOut)
         launch_combine_s<DT, KK, U, UNITW, kStoreOut>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
     else
         launch_combine_s<DT, KK, U, UNITW, kStoreStream>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);

@@ -8,6 +8,7 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "store_rules.h"
 #include "tamoe.h"
 
 namespace tamoe {
@@ -164,16 +165,7 @@ __device__ __forceinline__ int32_t pair_limit(const int32_t* __restrict__ cap, i
 // pair (-1) too, whatever bound the caller gives.
 inline int64_t slot_bound(int64_t K_rows) { return K_rows < (int64_t)1 << 31 ? K_rows : (int64_t)1 << 31; }
 
-// Cache policies of the row stores (the bits of a buffer store).  A line that is dirty in an L2 when the kernel ends is
-// written back then, with nothing to overlap, and evictions before that come in L2's order and not in that of the rows.
-// Each row mover has a rule of its own, with what it measured.
-enum StorePolicy {
-    kStoreBack = 0,      // ordinary: the line waits in L2 until it is evicted or the kernel ends
-    kStoreStream = 2,    // nt: the last-level cache does not keep the line
-    kStoreThrough = 16,  // sc1: straight through L2; the last-level cache keeps the line
-    kStoreOut = 19       // nt sc1 sc0: straight through L2, not kept
-};
-// A chunk by address, with one of these policies.  (s_nop: a vector instruction must not overwrite the data of a store of
+// A chunk by address, with one of the policies.  (s_nop: a vector instruction must not overwrite the data of a store of
 // more than 8 bytes in the two wait states behind it, and the compiler looks at its own stores only.)
 template <int ST>
 __device__ __forceinline__ void store_chunk(vec16* p, vec16 v) {

@@ -143,14 +143,6 @@ __global__ __launch_bounds__(kThreads) void regroup_flat_kernel(const vec16* __r
         if (dst[u] >= 0) store_chunk<ST>(out + dst[u], v[u]);
 }
 
-// Straight through L2 while the buffer fits the last-level cache, which keeps it for the experts (or the exchange), and
-// streaming beyond; rows that are no whole or half lines stream earlier.  Us of one call with ordinary / streaming / through stores:
-// 12288 x 512 bytes 10.3 / 10.1 / 9.8, 20480 x 2 KiB 28.3 / 30.1 / 27.0, 117760 x 2 KiB 146 / 142 / 139, 44800 x 8 KiB 230 /
-// 213 / 220; 20971 x 2000 32.0 / 32.8 / 30.8, 34000 x 2320 (75 MiB) - / 53.6 / 50.0, 47185 x 2000 64.3 / 63.2 / 64.7, 120586 x 2000 155 / 148 / 174.
-static bool regroup_streams(int64_t rows, int cpr) {
-    return rows * cpr * 16 > (int64_t)(cpr % 4 == 0 ? 256 : 80) << 20;
-}
-
 }  // namespace tamoe
 
 using namespace tamoe;
@@ -194,7 +186,7 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
         if (expert_offset == nullptr) return TAMOE_OK;
         blocks = 1;
     }
-    const bool streams = regroup_streams(cap_rows, cpr);
+    const StorePolicy policy = regroup_store(row_lines(out, cpr), cap_rows, cpr);
     const Segments sg{recv_count, P, E, (65536 + P - 1) / P, (65536 + E - 1) / E};
     const vec16* src = static_cast<const vec16*>(in);
     vec16* dst = static_cast<vec16*>(out);
@@ -209,7 +201,7 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
             regroup_flat_kernel<U, ST>    <<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, pow2_shift(cpr),         \
                                                                    to_expert_major, dst, expert_offset);           \
     } while (0)
-    if (streams) TAMOE_REGROUP(kStoreStream); else TAMOE_REGROUP(kStoreThrough);
+    if (policy == kStoreStream) TAMOE_REGROUP(kStoreStream); else TAMOE_REGROUP(kStoreThrough);
 #undef TAMOE_REGROUP
     return check_launch(fn, "regroup_copy_kernel");
 }

@@ -716,39 +716,6 @@ static bool scatter_by_wave(int64_t S, int cpr, int k) {
     return k <= 4 || cpr % 8 == 0 || (lanes - cpr) * 10 <= lanes || S * row_waves(cpr) < 8192;
 }
 
-// How `rows` rows of send are written.  What decides is whether the last-level cache (256 MB) keeps them for whoever reads
-// them next, and who merges the lines that a row shares with its neighbours.  Us of gate_dispatch and combine, N = 32,
-// with ordinary / streaming / through stores:
-//  - rows of whole lines go straight through L2 as long as they fit the last-level cache (30720 x 2 KiB, two choices 44.5 /
-//    46.4 / 43.7; 14720 x 8 KiB, two 133.9 / 140.7 / 134.0; 17280 x 8 KiB, two 181 / 174 / 181; 34560 x 8 KiB, one 238 /
-//    252 / 235), and beyond past that too (nt sc1 sc0, against nt alone: 65536 x 8 KiB, two 623.2 and 625.0, 65536 x 4 KiB,
-//    three 393.1 and 395.7; other rows lose by it, 30000 x 6368 258.7 and 247.5).  Small buffers that nothing but the combine of an identity layer reads are
-//    partly in L2 then (6144 x 1 KiB, two 18.2 / 20.0 / 18.9; dispatch alone 20.9 and 19.6 with through stores), short rows
-//    of many choices gain on their own too (8192 x 512 bytes, eight 27.8 and 28.6);
-//  - rows that are no whole lines, by wavefront: through (9830 x 4000, two 45.8 / 46.1 / 44.9; 47185 x 2000, two 134.5 /
-//    137.6 / 132.2), with many choices from L2, which merges their lines (11320 x 6368, eight 273 / 287 / 286);
-//    rows of half lines stream (39321 x 1600, two 93 / 88 / 92, 9611 x 3008, four 70 / 67 / 69; 4342 x 7744, six 111 from L2, 107);
-//  - flat ones from L2 (57974 x 1040, four 111 / 136 / 121; 115651 x 272, two 61 / 65 / 65), one choice streaming beyond
-//    96 MiB;
-//  - the fixed-size layout streams beyond 96 MiB: its padding takes the place of rows (14117 x 7328, two, 237 MiB 131
-//    streaming, 149 through; 56000 x 1 KiB, three, 205 MiB 99 and 101), flat rows come from L2 (14488 x 768, two 28.0,
-//    through 28.5).
-static int scatter_store(int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
-    const int64_t mib = rows * cpr * 16 >> 20;
-    if (padded && (mib > 96 || !by_wave)) return mib <= 96 ? kStoreBack : cpr % 8 == 0 ? kStoreOut : kStoreStream;
-    if (cpr % 8 == 0) {
-        const int from = behind_gate && by_wave ? 8 : 0;
-        const int to = behind_gate ? (k <= 2 ? 16 : 24) : !by_wave && k > 4 ? 32 : 0;
-        if (mib >= from && mib < to) return kStoreBack;
-        return mib <= (k == 1 ? 360 : 240) ? kStoreThrough : kStoreOut;
-    }
-    if (!by_wave) return mib <= (k == 1 ? 96 : k == 2 ? 240 : 640) ? kStoreBack : kStoreStream;
-    if (mib <= 24) return kStoreThrough;
-    if (cpr % 4 == 0 && (k <= 4 || mib > 96)) return kStoreStream;
-    if (k <= 4 && mib <= 240) return kStoreThrough;
-    return k > 2 && mib <= 640 ? kStoreBack : kStoreStream;
-}
-
 // Workgroups that move rows.
 static int64_t copy_workgroups(int64_t S, int cpr, int k) {
     const int U = copy_units(k);
@@ -781,7 +748,7 @@ static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
 #define TAMOE_ROUTE_COPY(RU, ST)                                                          \
     route_copy_kernel<KK, U, RU, ST><<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
     const bool rowu = scatter_by_wave(a.S, a.cpr, a.k);
-    const int policy = scatter_store(rows, a.cpr, a.k, rowu, a.m_part != nullptr, a.pad_C > 0);
+    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows, a.cpr, a.k, rowu, a.m_part != nullptr, a.pad_C > 0);
 #define TAMOE_ROUTE_COPY_ST(ST)                                                          \
     do {                                                                                 \
         if (rowu) TAMOE_ROUTE_COPY(true, ST); else TAMOE_ROUTE_COPY(false, ST);          \
@@ -818,7 +785,7 @@ template <int KK, int U, bool ROWU>
 static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
     const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(kTableThreads);
     const int64_t rows = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : a.S * a.k;
-    const int policy = scatter_store(rows, a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
+    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows, a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
     // the smallest tables in a kernel that is shorter by seven requests and their sums
     const bool one = U == 1 && (int64_t)a.n_blocks * (a.stride / 8) <= kTableThreads;
 #define TAMOE_ROUTE_TABLE(ST)                                                                      \

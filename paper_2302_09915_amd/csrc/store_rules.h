@@ -1,0 +1,94 @@
+// How the row movers store their rows: a cache policy by size, by how rows lie on lines and by what comes next.  Host
+// code without HIP: the rules can be compiled and looked at anywhere.
+#pragma once
+
+#include <cstdint>
+
+namespace tamoe {
+
+// Cache policies of the row stores (the bits of a buffer store).  A line that is dirty in an L2 when the kernel ends is
+// written back then, with nothing to overlap, and evictions before that come in L2's order and not in that of the rows.
+// Each row mover has a rule of its own, with what it measured.
+enum StorePolicy {
+    kStoreBack = 0,      // ordinary: the line waits in L2 until it is evicted or the kernel ends
+    kStoreStream = 2,    // nt: the last-level cache does not keep the line
+    kStoreThrough = 16,  // sc1: straight through L2; the last-level cache keeps the line
+    kStoreOut = 19       // nt sc1 sc0: straight through L2, not kept
+};
+
+// How rows of cpr chunks of 16 bytes that begin at base lie on the lines of 128 bytes.  A line that a row shares with
+// another is written in two parts, which only L2 can merge.  The length alone does not say it: buffers are aligned to 16
+// bytes.  (Rows of whole lines in buffers that begin 48 bytes into one, us of a pass stored as if they were aligned, and
+// now: regroup 17407 x 3200 bytes, four choices 171.8, 143.7, 10171 x 5632, two 92.8, 79.6; forward 11008 x 5376, eight
+// 281.4, 228.6, 48222 x 3584, two 215.0, 187.9; backward 15009 x 4 KiB, two 95.4, 93.9.)
+enum RowLines { kWholeLines, kHalfLines, kSharedLines };
+inline RowLines row_lines(const void* base, int cpr) {
+    const uintptr_t ends = reinterpret_cast<uintptr_t>(base) | (uintptr_t)cpr * 16;
+    return ends % 128 == 0 ? kWholeLines : ends % 64 == 0 ? kHalfLines : kSharedLines;
+}
+
+// The scatter: how `rows` rows of send are written.  What decides is whether the last-level cache (256 MB) keeps them for whoever reads
+// them next, and who merges the lines that a row shares with its neighbours.  Us of gate_dispatch and combine, N = 32,
+// with ordinary / streaming / through stores:
+//  - rows of whole lines go straight through L2 as long as they fit the last-level cache (30720 x 2 KiB, two choices 44.5 /
+//    46.4 / 43.7; 14720 x 8 KiB, two 133.9 / 140.7 / 134.0; 17280 x 8 KiB, two 181 / 174 / 181; 34560 x 8 KiB, one 238 /
+//    252 / 235), and beyond past that too (nt sc1 sc0, against nt alone: 65536 x 8 KiB, two 623.2 and 625.0, 65536 x 4 KiB,
+//    three 393.1 and 395.7; other rows lose by it, 30000 x 6368 258.7 and 247.5).  Small buffers that nothing but the combine of an identity layer reads are
+//    partly in L2 then (6144 x 1 KiB, two 18.2 / 20.0 / 18.9; dispatch alone 20.9 and 19.6 with through stores), short rows
+//    of many choices gain on their own too (8192 x 512 bytes, eight 27.8 and 28.6);
+//  - rows that are no whole lines, by wavefront: through (9830 x 4000, two 45.8 / 46.1 / 44.9; 47185 x 2000, two 134.5 /
+//    137.6 / 132.2), with many choices from L2, which merges their lines (11320 x 6368, eight 273 / 287 / 286);
+//    rows of half lines stream (39321 x 1600, two 93 / 88 / 92, 9611 x 3008, four 70 / 67 / 69; 4342 x 7744, six 111 from L2, 107);
+//  - flat ones from L2 (57974 x 1040, four 111 / 136 / 121; 115651 x 272, two 61 / 65 / 65), one choice streaming beyond
+//    96 MiB;
+//  - the fixed-size layout streams beyond 96 MiB: its padding takes the place of rows (14117 x 7328, two, 237 MiB 131
+//    streaming, 149 through; 56000 x 1 KiB, three, 205 MiB 99 and 101), flat rows come from L2 (14488 x 768, two 28.0,
+//    through 28.5).
+inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
+    const int64_t mib = rows * cpr * 16 >> 20;
+    if (padded && (mib > 96 || !by_wave)) return mib <= 96 ? kStoreBack : lines == kWholeLines ? kStoreOut : kStoreStream;
+    if (lines == kWholeLines) {
+        const int from = behind_gate && by_wave ? 8 : 0;
+        const int to = behind_gate ? (k <= 2 ? 16 : 24) : !by_wave && k > 4 ? 32 : 0;
+        if (mib >= from && mib < to) return kStoreBack;
+        return mib <= (k == 1 ? 360 : 240) ? kStoreThrough : kStoreOut;
+    }
+    if (!by_wave) return mib <= (k == 1 ? 96 : k == 2 ? 240 : 640) ? kStoreBack : kStoreStream;
+    if (mib <= 24) return kStoreThrough;
+    if (lines == kHalfLines && (k <= 4 || mib > 96)) return kStoreStream;
+    if (k <= 4 && mib <= 240) return kStoreThrough;
+    return k > 2 && mib <= 640 ? kStoreBack : kStoreStream;
+}
+
+// The combine and its transpose: y goes straight through L2 and is not kept: ordinary stores are written back behind the last wavefront, and streaming
+// ones still wait in L2 for their turn (the whole forward call on 16384 x 2 KiB, two choices: 47.8 us with ordinary
+// stores, 47.5 streaming, 46.5 straight through; 65536 x 8 KiB 663, 625, 626).  Rows that are no whole lines only with three
+// and more choices (18970 x 1520, four 75.2 streaming, 73.5; 23592 x 2000, four 109.3, 105.7); with two what is gained on rows
+// from the last-level cache is lost on others (28835 x 2000 86.0, 84.5; fixed-size layout, 24898 x 5488 169.8, 171.9), with
+// one all of it (28050 x 4112: 113.8, 116.6); and flat rows not at all (fixed-size layout, 15808 x 640, two 28.3, 28.8).
+inline StorePolicy combine_store(RowLines lines, int64_t S, int cpr, int k, bool by_wave) {
+    return by_wave && (k > 2 || lines == kWholeLines) && S * cpr * 16 <= (int64_t)256 << 20 ? kStoreOut : kStoreStream;
+}
+
+// combine_bwd: d_recv is written straight through L2 at almost any size: the last-level cache keeps what fits of it for the kernel that
+// reads it next, and no dirty line is left for the end of this one.  combine_bwd and dispatch_bwd together: 58880
+// x 2 KiB, two choices (230 MiB) 159 us with ordinary stores, 194 streaming, 155 now; 25600 x 8 KiB, two
+// 276, 304, 272; 65536 x 8 KiB, two 782, 795, 770; 64527 x 1040 bytes 110, 110, 108.  Streaming is the better way only
+// for one choice and rows just over one wavefront, which two of them write (129055 x 1040: 154, 146, 151), ordinary
+// stores for the small buffers that the scatter left in L2 (a whole layer's pass of 1000 x 8 KiB, two choices 47.7 and
+// 49.5 through, 600 x 8 KiB, four 51.2 and 53.9; this and dispatch_bwd on their own 15.1 and 14.8).
+inline StorePolicy combine_bwd_store(RowLines lines, int64_t S, int cpr, int k) {
+    const int64_t mib = S * k * (int64_t)cpr * 16 >> 20;
+    if (k == 1 && cpr > 64 && cpr < 68 && mib > 48) return kStoreStream;
+    return k > 1 && cpr >= 64 && lines == kWholeLines && mib >= 8 && mib < 24 ? kStoreBack : kStoreThrough;
+}
+
+// The regroup: straight through L2 while the buffer fits the last-level cache, which keeps it for the experts (or the exchange), and
+// streaming beyond; rows that are no whole or half lines stream earlier.  Us of one call with ordinary / streaming / through stores:
+// 12288 x 512 bytes 10.3 / 10.1 / 9.8, 20480 x 2 KiB 28.3 / 30.1 / 27.0, 117760 x 2 KiB 146 / 142 / 139, 44800 x 8 KiB 230 /
+// 213 / 220; 20971 x 2000 32.0 / 32.8 / 30.8, 34000 x 2320 (75 MiB) - / 53.6 / 50.0, 47185 x 2000 64.3 / 63.2 / 64.7, 120586 x 2000 155 / 148 / 174.
+inline StorePolicy regroup_store(RowLines lines, int64_t rows, int cpr) {
+    return rows * cpr * 16 > (int64_t)(lines == kSharedLines ? 80 : 256) << 20 ? kStoreStream : kStoreThrough;
+}
+
+}  // namespace tamoe

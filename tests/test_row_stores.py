@@ -1,4 +1,6 @@
-"""How rows are stored (csrc/internal.h): what the compiler makes of store_chunk."""
+"""How rows are stored: what the compiler makes of store_chunk (csrc/internal.h), and the rules that choose a cache
+policy (csrc/store_rules.h, host code)."""
+import ctypes
 import os
 import re
 import shutil
@@ -65,3 +67,54 @@ def test_data_of_a_store_is_not_overwritten_early(tmp_path):
     assert sorted(gaps) == [0, 2, 16, 19] and all(len(g) >= 3 for g in gaps.values()), gaps
     need = min(gaps[0])   # the compiler's own
     assert need >= 2 and all(min(g) >= need for g in gaps.values()), gaps
+
+
+BACK, STREAM, THROUGH, OUT = 0, 2, 16, 19
+MIB = 1 << 20
+RULES = """
+#include "store_rules.h"
+using namespace tamoe;
+extern "C" {
+int scatter(uint64_t base, int64_t rows, int cpr, int k, int by_wave, int behind_gate, int padded) {
+    return scatter_store(row_lines((const void*)base, cpr), rows, cpr, k, by_wave, behind_gate, padded);
+}
+int combine(uint64_t base, int64_t S, int cpr, int k, int by_wave) { return combine_store(row_lines((const void*)base, cpr), S, cpr, k, by_wave); }
+int combine_bwd(uint64_t base, int64_t S, int cpr, int k) { return combine_bwd_store(row_lines((const void*)base, cpr), S, cpr, k); }
+int regroup(uint64_t base, int64_t rows, int cpr) { return regroup_store(row_lines((const void*)base, cpr), rows, cpr); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not found")
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(RULES)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC, str(d / "rules.cpp"),
+                    "-o", str(d / "rules.so")], check=True, timeout=120)
+    lib = ctypes.CDLL(str(d / "rules.so"))
+    i64, u64, i32 = ctypes.c_int64, ctypes.c_uint64, ctypes.c_int
+    lib.scatter.argtypes = [u64, i64] + [i32] * 5
+    lib.combine.argtypes = [u64, i64] + [i32] * 3
+    lib.combine_bwd.argtypes = [u64, i64] + [i32] * 2
+    lib.regroup.argtypes = [u64, i64, i32]
+    return lib
+
+
+@pytest.mark.parametrize("cpr", [8, 64, 128, 256, 320])
+def test_rows_share_lines_where_the_buffer_is_not_aligned(rules, cpr):
+    """A whole number of lines per row is not enough: in a buffer that begins inside a line every row shares its first and
+    last with its neighbours, and is stored as rows of other lengths are."""
+    at, off = 1 << 20, (1 << 20) + 48
+    rows = 200 * MIB // (cpr * 16)
+    assert rules.regroup(at, rows, cpr) == THROUGH and rules.regroup(off, rows, cpr) == STREAM == rules.regroup(at, rows, cpr + 1)
+    for k in (1, 2, 4, 8):
+        S = rows // k
+        for by_wave in ((1, 0) if cpr >= 64 else (0,)):
+            for n in (rows // 6, rows, 3 * rows):
+                assert rules.scatter(off, n, cpr, k, by_wave, 1, 0) == rules.scatter(at, n * cpr // (cpr + 1), cpr + 1, k, by_wave, 1, 0)
+            assert rules.combine(off, S, cpr, k, by_wave) == rules.combine(at, S, cpr + 1, k, by_wave)
+        if cpr >= 64:
+            assert rules.combine(at, S, cpr, k, 1) == OUT and rules.combine(off, S, cpr, k, 1) == (OUT if k > 2 else STREAM)
+    assert rules.scatter(at + 64, rows, cpr, 2, 1, 1, 0) == rules.scatter(at, rows, cpr + 4, 2, 1, 1, 0)   # half lines
