@@ -70,17 +70,23 @@ inline StorePolicy combine_store(RowLines lines, int64_t S, int cpr, int k, bool
     return by_wave && (k > 2 || lines == kWholeLines) && S * cpr * 16 <= (int64_t)256 << 20 ? kStoreOut : kStoreStream;
 }
 
-// combine_bwd: d_recv is written straight through L2 at almost any size: the last-level cache keeps what fits of it for the kernel that
-// reads it next, and no dirty line is left for the end of this one.  combine_bwd and dispatch_bwd together: 58880
-// x 2 KiB, two choices (230 MiB) 159 us with ordinary stores, 194 streaming, 155 now; 25600 x 8 KiB, two
-// 276, 304, 272; 65536 x 8 KiB, two 782, 795, 770; 64527 x 1040 bytes 110, 110, 108.  Streaming is the better way only
-// for one choice and rows just over one wavefront, which two of them write (129055 x 1040: 154, 146, 151), ordinary
-// stores for the small buffers that the scatter left in L2 (a whole layer's pass of 1000 x 8 KiB, two choices 47.7 and
-// 49.5 through, 600 x 8 KiB, four 51.2 and 53.9; this and dispatch_bwd on their own 15.1 and 14.8).
+// combine_bwd: d_recv goes straight through L2, whose last-level cache keeps what fits of it for the kernel that reads it
+// next, and no dirty line is left for the end of this one.  Us of combine_bwd, dispatch_bwd and gate_bwd, rows with ordinary /
+// streaming / through stores: 58880 x 2 KiB, two choices (combine_bwd and dispatch_bwd) 159 / 194 / 155, 25600 x 8 KiB, two 276 / 304 /
+// 272, 65536 x 8 KiB, two 782 / 795 / 770; 1664 x 7296, two (23 MiB) 22.5 / 24.2 / 22.2, 2696 x 1536, four 16.7 / 16.8 / 16.4.  But
+//  - flat rows of whole lines that fill their group of lanes are merged in L2, in buffers of up to 16 MiB: 2624 x 512 bytes, six
+//    choices 14.6 / 15.6 / 15.4, 12838 x 512, two 15.2 / 15.7 / 15.6, 34682 x 256, two (17 MiB) 20.8 / 22.4 / 21.0; not 5760 x 640, two
+//    13.1 / - / 12.2, 5893 x 768, two 13.5 / 12.9 / 12.6, 17498 x 384, three (19 MiB) 20.8 / 20.4 / 19.7, nor 10752 x 336, three 18.0 /
+//    16.6 / 16.5;
+//  - with one choice rows of half lines of up to 1.5 KiB stream beyond 48 MiB (107142 x 1344 142.7 / 132.2 / 139.0, 450000 x
+//    320 168.1 / 154.2 / 165.7, but 58752 x 3520 182.9 / 186.1 / 180.1; two choices, 27200 x 3648 148.0 / 154.4 / 146.1), and so do
+//    rows just over one wavefront, which two wavefronts write (129055 x 1040 148.4 / 139.6 / 145.3, 60000 x 1040 75.2 / 71.0 /
+//    72.5, but 80000 x 1104 97.7 / 97.9 / 95.6).
 inline StorePolicy combine_bwd_store(RowLines lines, int64_t S, int cpr, int k) {
-    const int64_t mib = S * k * (int64_t)cpr * 16 >> 20;
-    if (k == 1 && cpr > 64 && cpr < 68 && mib > 48) return kStoreStream;
-    return k > 1 && cpr >= 64 && lines == kWholeLines && mib >= 8 && mib < 24 ? kStoreBack : kStoreThrough;
+    const int64_t bytes = S * k * cpr * 16;
+    if (cpr < 64 && (cpr & (cpr - 1)) == 0 && lines == kWholeLines && bytes <= (int64_t)16 << 20) return kStoreBack;
+    if (k == 1 && bytes > (int64_t)48 << 20 && (lines == kHalfLines ? cpr <= 96 : cpr > 64 && cpr < 68)) return kStoreStream;
+    return kStoreThrough;
 }
 
 // The regroup: straight through L2 while the buffer fits the last-level cache, which keeps it for the experts (or the exchange), and

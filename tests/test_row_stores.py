@@ -118,3 +118,14 @@ def test_rows_share_lines_where_the_buffer_is_not_aligned(rules, cpr):
         if cpr >= 64:
             assert rules.combine(at, S, cpr, k, 1) == OUT and rules.combine(off, S, cpr, k, 1) == (OUT if k > 2 else STREAM)
     assert rules.scatter(at + 64, rows, cpr, 2, 1, 1, 0) == rules.scatter(at, rows, cpr + 4, 2, 1, 1, 0)   # half lines
+
+
+@pytest.mark.parametrize("S,cpr,k,policy", [
+    (2624, 32, 6, BACK), (12838, 32, 2, BACK), (16 * MIB // (32 * 16 * 2), 32, 2, BACK),                        # flat, whole lines, small
+    (16 * MIB // (32 * 16 * 2) + 1, 32, 2, THROUGH), (5760, 40, 2, THROUGH), (10752, 21, 3, THROUGH), (5000, 36, 1, THROUGH),
+    (1000, 512, 2, THROUGH), (600, 512, 4, THROUGH), (1664, 456, 2, THROUGH), (65536, 512, 2, THROUGH),          # by wavefront
+    (107142, 84, 1, STREAM), (66666, 60, 2, THROUGH), (58752, 220, 1, THROUGH), (20000, 84, 1, THROUGH),         # half lines
+    (129055, 65, 1, STREAM), (60000, 67, 1, STREAM), (60000, 69, 1, THROUGH), (60000, 65, 2, THROUGH), (40000, 65, 1, THROUGH)])
+def test_gradient_rows(rules, S, cpr, k, policy):
+    """Where each policy of combine_bwd's rows begins and ends."""
+    assert rules.combine_bwd(1 << 20, S, cpr, k) == policy
