@@ -27,37 +27,39 @@ inline RowLines row_lines(const void* base, int cpr) {
     return ends % 128 == 0 ? kWholeLines : ends % 64 == 0 ? kHalfLines : kSharedLines;
 }
 
-// The scatter: how `rows` rows of send are written.  What decides is whether the last-level cache (256 MB) keeps them for whoever reads
-// them next, and who merges the lines that a row shares with its neighbours.  Us of gate_dispatch and combine, N = 32,
+// The scatter: how `rows` rows of send are written.  What decides is whether the last-level cache (256 MB) keeps them for whoever
+// reads them next, and who merges the lines that a row shares with its neighbours.  Us of a whole forward call (recv = send)
 // with ordinary / streaming / through stores:
-//  - rows of whole lines go straight through L2 as long as they fit the last-level cache (30720 x 2 KiB, two choices 44.5 /
-//    46.4 / 43.7; 14720 x 8 KiB, two 133.9 / 140.7 / 134.0; 17280 x 8 KiB, two 181 / 174 / 181; 34560 x 8 KiB, one 238 /
-//    252 / 235), and beyond past that too (nt sc1 sc0, against nt alone: 65536 x 8 KiB, two 623.2 and 625.0, 65536 x 4 KiB,
-//    three 393.1 and 395.7; other rows lose by it, 30000 x 6368 258.7 and 247.5).  Small buffers that nothing but the combine of an identity layer reads are
-//    partly in L2 then (6144 x 1 KiB, two 18.2 / 20.0 / 18.9; dispatch alone 20.9 and 19.6 with through stores), short rows
-//    of many choices gain on their own too (8192 x 512 bytes, eight 27.8 and 28.6);
-//  - rows that are no whole lines, by wavefront: through (9830 x 4000, two 45.8 / 46.1 / 44.9; 47185 x 2000, two 134.5 /
-//    137.6 / 132.2), with many choices from L2, which merges their lines (11320 x 6368, eight 273 / 287 / 286);
-//    rows of half lines stream (39321 x 1600, two 93 / 88 / 92, 9611 x 3008, four 70 / 67 / 69; 4342 x 7744, six 111 from L2, 107);
-//  - flat ones from L2 (57974 x 1040, four 111 / 136 / 121; 115651 x 272, two 61 / 65 / 65), one choice streaming beyond
-//    96 MiB;
+//  - rows of whole lines go straight through L2 as long as they fit the last-level cache (576 x 7680 bytes, two choices (8 MiB)
+//    25.8 / 25.1 / 25.3; 1919 x 3456, two 19.7 / 19.7 / 19.0; 30720 x 2 KiB, two 44.5 / 46.4 / 43.7; 23706 x 5504, two (249 MiB) - /
+//    134.1 / 124.0, 29440 x 4608, two (259) - / 186.3 / 195.1; one choice, which leaves x less room to need, up to 360 MiB: 44244
+//    x 7936 (335) - / 289.1 / 281.1), and beyond past that too (nt sc1 sc0, against nt alone: 65536 x 8 KiB, two 623.2 and
+//    625.0, 65536 x 4 KiB, three 393.1 and 395.7; other rows lose by it, 30000 x 6368 258.7 and 247.5).  Flat ones behind the gate come
+//    from L2 below 16 MiB (2123 x 256, four 14.2 / 15.0 / 14.4; 1280 x 384, four 15.0 / 15.9 / 16.2; 16640 x 640, two (20 MiB) 26.4 / 27.9 /
+//    25.8), behind a routing that is given they gain nothing by it;
+//  - rows of half lines stream beyond 16 MiB, also flat (9920 x 2112, four 64.5 / 60.7 / 63.3, 2880 x 2240, six 32.2 / 30.9 / 33.1;
+//    41280 x 576, two 46.4 / 43.7 / 45.3, 45504 x 832, three 79.6 / 72.2 / 78.4, 33344 x 1600, eight 230.9 / 215.8 / 228.9);
+//  - other rows by wavefront: through (9830 x 4000, two 45.8 / 46.1 / 44.9; 47185 x 2000, two 134.5 / 137.6 / 132.2), with many choices
+//    and for large buffers of three and more from L2, which merges their lines (2496 x 2032, six 26.1 / 27.4 / 26.8, 11320 x 6368,
+//    eight 273 / 287 / 286, 42567 x 4208, four (683 MiB) 384 / 397 / 390; 15440 x 5648, three, a training pass 337 / 349 / 336);
+//  - other flat ones from L2 (57974 x 1040, four 111 / 136 / 121; 115651 x 272, two 61 / 65 / 65; 131072 x 880, eight (880 MiB) 422 / 441 /
+//    453), streaming beyond 32 MiB with one choice (86016 x 544 57.7 / 54.3 /
+//    58.0, 131072 x 720 108.1 / 100.1 / 108.2) and beyond 240 with two (64384 x 2096 155.6 / 142.1 / -; 126256 x 688 (166 MiB) 133.9 / 141.2 /
+//    143.3).
 //  - the fixed-size layout streams beyond 96 MiB: its padding takes the place of rows (14117 x 7328, two, 237 MiB 131
 //    streaming, 149 through; 56000 x 1 KiB, three, 205 MiB 99 and 101), flat rows come from L2 (14488 x 768, two 28.0,
 //    through 28.5).
 inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
-    const int64_t mib = rows * cpr * 16 >> 20;
-    if (padded && (mib > 96 || !by_wave)) return mib <= 96 ? kStoreBack : lines == kWholeLines ? kStoreOut : kStoreStream;
+    const int64_t bytes = rows * cpr * 16, MiB = (int64_t)1 << 20;
+    if (padded && (bytes > 96 * MiB || !by_wave)) return bytes <= 96 * MiB ? kStoreBack : lines == kWholeLines ? kStoreOut : kStoreStream;
     if (lines == kWholeLines) {
-        const int from = behind_gate && by_wave ? 8 : 0;
-        const int to = behind_gate ? (k <= 2 ? 16 : 24) : !by_wave && k > 4 ? 32 : 0;
-        if (mib >= from && mib < to) return kStoreBack;
-        return mib <= (k == 1 ? 360 : 240) ? kStoreThrough : kStoreOut;
+        if (!by_wave && behind_gate && bytes < 16 * MiB) return kStoreBack;
+        return bytes <= (k == 1 ? 360 : 240) * MiB ? kStoreThrough : kStoreOut;
     }
-    if (!by_wave) return mib <= (k == 1 ? 96 : k == 2 ? 240 : 640) ? kStoreBack : kStoreStream;
-    if (mib <= 24) return kStoreThrough;
-    if (lines == kHalfLines && (k <= 4 || mib > 96)) return kStoreStream;
-    if (k <= 4 && mib <= 240) return kStoreThrough;
-    return k > 2 && mib <= 640 ? kStoreBack : kStoreStream;
+    if (lines == kHalfLines && bytes > 16 * MiB) return kStoreStream;
+    if (!by_wave) return (k == 1 && bytes > 32 * MiB) || (k == 2 && bytes > 240 * MiB) ? kStoreStream : kStoreBack;
+    if (bytes <= (k <= 4 ? 240 : 24) * MiB) return kStoreThrough;
+    return k > 2 ? kStoreBack : kStoreStream;
 }
 
 // The combine and its transpose: y goes straight through L2 and is not kept: ordinary stores are written back behind the last wavefront, and streaming

@@ -129,3 +129,22 @@ def test_rows_share_lines_where_the_buffer_is_not_aligned(rules, cpr):
 def test_gradient_rows(rules, S, cpr, k, policy):
     """Where each policy of combine_bwd's rows begins and ends."""
     assert rules.combine_bwd(1 << 20, S, cpr, k) == policy
+
+
+def _at(mib, cpr):
+    """Rows of cpr chunks in mib MiB."""
+    return mib * MIB // (cpr * 16)
+
+
+@pytest.mark.parametrize("mib,cpr,k,by_wave,behind_gate,policy", [
+    (8, 480, 2, 1, 1, THROUGH), (12, 216, 2, 1, 1, THROUGH), (20, 64, 4, 1, 1, THROUGH), (240, 256, 2, 1, 1, THROUGH),   # whole lines
+    (241, 256, 2, 1, 1, OUT), (360, 256, 1, 1, 1, THROUGH), (361, 256, 1, 1, 1, OUT), (240, 32, 8, 0, 1, THROUGH), (241, 32, 8, 0, 1, OUT),
+    (15, 32, 2, 0, 1, BACK), (16, 32, 2, 0, 1, THROUGH), (20, 32, 4, 0, 1, THROUGH), (2, 24, 4, 0, 1, BACK), (15, 32, 8, 0, 0, THROUGH),
+    (15, 132, 2, 1, 1, THROUGH), (17, 132, 2, 1, 1, STREAM), (30, 140, 6, 1, 1, STREAM), (300, 300, 4, 1, 1, STREAM),    # half lines
+    (15, 36, 2, 0, 1, BACK), (17, 36, 2, 0, 1, STREAM), (400, 100, 8, 0, 1, STREAM), (500, 220, 6, 0, 1, STREAM),
+    (20, 125, 8, 1, 1, THROUGH), (25, 125, 8, 1, 1, BACK), (100, 125, 2, 1, 1, THROUGH), (100, 125, 4, 1, 1, THROUGH),     # others, by wavefront
+    (241, 125, 2, 1, 1, STREAM), (241, 125, 3, 1, 1, BACK), (700, 263, 4, 1, 1, BACK), (700, 397, 8, 1, 1, BACK),
+    (31, 45, 1, 0, 1, BACK), (33, 45, 1, 0, 1, STREAM), (240, 45, 2, 0, 1, BACK), (257, 131, 2, 0, 1, STREAM), (880, 55, 8, 0, 1, BACK)])
+def test_scattered_rows(rules, mib, cpr, k, by_wave, behind_gate, policy):
+    """Where each policy of the scatter's rows begins and ends."""
+    assert rules.scatter(1 << 20, _at(mib, cpr), cpr, k, by_wave, behind_gate, 0) == policy
