@@ -723,6 +723,12 @@ static int64_t copy_workgroups(int64_t S, int cpr, int k) {
                              : ceil_div(S * (int64_t)cpr, kCopyThreads * U);
 }
 
+// Rows that the scatter writes at most.
+static int64_t rows_sent(const RouteArgs& a) {
+    const int64_t pairs = a.S * a.k, room = (int64_t)a.N * a.pad_C;
+    return a.pad_C > 0 && room < pairs ? room : pairs;
+}
+
 // Fills in the launch geometry.
 static void plan_copy(RouteArgs& a) {
     const bool by_wave = scatter_by_wave(a.S, a.cpr, a.k);
@@ -730,9 +736,7 @@ static void plan_copy(RouteArgs& a) {
     a.shift = pow2_shift(by_wave ? a.wpr : a.cpr);
     a.copy_blocks = a.units == 0 ? (int)copy_workgroups(a.S, a.cpr, a.k)
                                  : (int)ceil_div(by_wave ? a.S * a.wpr : ceil_div(a.S * (int64_t)a.cpr, 64), kTableWaves * a.units);
-    // zeros of a large buffer would take the place of its rows in the last-level cache: 53902 x 1536 bytes, half of them
-    // padding 86 us, streamed 78; 8192 x 8 KiB 66 and 61; but 6144 x 2 KiB (48 MiB) 28.7 and 29.2
-    a.fill_streams = (int64_t)a.N * a.pad_C * a.cpr * 16 > (int64_t)64 << 20;
+    a.fill_streams = fill_streams((int64_t)a.N * a.pad_C, rows_sent(a), a.cpr);
     // about 4096 workgroups clear rows (512 of the larger ones that sum the table), at most one per 16 bytes per thread
     const int wgs = a.units == 0 ? 4096 : 512, threads = a.units == 0 ? kCopyThreads : kTableThreads;
     a.fill_parts = a.pad_C == 0 ? 0 : (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(wgs, a.N),
@@ -743,12 +747,11 @@ template <int KK>
 static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
     constexpr int U = copy_units(KK);
     const dim3 grid = grid_of(1 + (int64_t)a.copy_blocks + (int64_t)a.N * a.fill_parts, kCopyThreads), block(kCopyThreads);
-    const int64_t rows = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : a.S * a.k;
     const int32_t* caps = a.cap != nullptr ? a.cap : a.table;   // N entries at least
 #define TAMOE_ROUTE_COPY(RU, ST)                                                          \
     route_copy_kernel<KK, U, RU, ST><<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
     const bool rowu = scatter_by_wave(a.S, a.cpr, a.k);
-    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows, a.cpr, a.k, rowu, a.m_part != nullptr, a.pad_C > 0);
+    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, rowu, a.m_part != nullptr, a.pad_C > 0);
 #define TAMOE_ROUTE_COPY_ST(ST)                                                          \
     do {                                                                                 \
         if (rowu) TAMOE_ROUTE_COPY(true, ST); else TAMOE_ROUTE_COPY(false, ST);          \
@@ -784,8 +787,7 @@ static int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool b
 template <int KK, int U, bool ROWU>
 static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
     const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(kTableThreads);
-    const int64_t rows = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : a.S * a.k;
-    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows, a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
+    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
     // the smallest tables in a kernel that is shorter by seven requests and their sums
     const bool one = U == 1 && (int64_t)a.n_blocks * (a.stride / 8) <= kTableThreads;
 #define TAMOE_ROUTE_TABLE(ST)                                                                      \

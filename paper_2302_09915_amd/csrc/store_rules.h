@@ -46,20 +46,36 @@ inline RowLines row_lines(const void* base, int cpr) {
 //    453), streaming beyond 32 MiB with one choice (86016 x 544 57.7 / 54.3 /
 //    58.0, 131072 x 720 108.1 / 100.1 / 108.2) and beyond 240 with two (64384 x 2096 155.6 / 142.1 / -; 126256 x 688 (166 MiB) 133.9 / 141.2 /
 //    143.3).
-//  - the fixed-size layout streams beyond 96 MiB: its padding takes the place of rows (14117 x 7328, two, 237 MiB 131
-//    streaming, 149 through; 56000 x 1 KiB, three, 205 MiB 99 and 101), flat rows come from L2 (14488 x 768, two 28.0,
-//    through 28.5).
+//  - the fixed-size layout goes by the rows that pairs can name (the padding between them is stored by fill_streams), which
+//    nobody reads in the calls that were timed: beyond 128 MiB they leave the last-level cache to others (10880 x 6400, three (199 MiB) - /
+//    112.0 / 115.0, 45284 x 2304, two (199) - / 127.5 / 130.4, 13248 x 2960, eight (299) 144.6 / 139.0 / -; 5333 x 4 KiB, two,
+//    three of four rows padding (42) 55.6 / 62.4 / 55.4, 7245 x 2304, two, as many (32) 44.1 / 49.7 / 43.7, 1920 x 7984, eight (117) 79.4 / 87.7 /
+//    82.0), and flat rows go through L2 from 4 to 24 MiB (3712 x 512, eight (14) 24.9 / 22.5 / 22.4, 12822 x 384, two
+//    20.2 / - / 19.1, 7552 x 416, four (12) 19.9 / 18.1 / 18.3; 320 x 512, eight (1) 15.7 / - / 16.5, 13376 x 256, eight (26) 27.8 / - / 29.0, 30531 x 512, two (30) 31.3 / - / 31.9).
 inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
     const int64_t bytes = rows * cpr * 16, MiB = (int64_t)1 << 20;
-    if (padded && (bytes > 96 * MiB || !by_wave)) return bytes <= 96 * MiB ? kStoreBack : lines == kWholeLines ? kStoreOut : kStoreStream;
+    const bool leave = padded && bytes > 128 * MiB;
+    if (padded && !by_wave && bytes <= 24 * MiB) return bytes < 4 * MiB ? kStoreBack : kStoreThrough;
     if (lines == kWholeLines) {
-        if (!by_wave && behind_gate && bytes < 16 * MiB) return kStoreBack;
-        return bytes <= (k == 1 ? 360 : 240) * MiB ? kStoreThrough : kStoreOut;
+        if (!by_wave && (padded ? !leave : behind_gate && bytes < 16 * MiB)) return kStoreBack;
+        return leave || bytes > (k == 1 ? 360 : 240) * MiB ? kStoreOut : kStoreThrough;
     }
     if (lines == kHalfLines && bytes > 16 * MiB) return kStoreStream;
-    if (!by_wave) return (k == 1 && bytes > 32 * MiB) || (k == 2 && bytes > 240 * MiB) ? kStoreStream : kStoreBack;
+    if (!by_wave) return !padded && ((k == 1 && bytes > 32 * MiB) || (k == 2 && bytes > 240 * MiB)) ? kStoreStream : kStoreBack;
+    if (leave) return kStoreStream;
     if (bytes <= (k <= 4 ? 240 : 24) * MiB) return kStoreThrough;
     return k > 2 ? kStoreBack : kStoreStream;
+}
+
+// Padding of the fixed-size layout: zeros stream where they would take the place of its rows in the last-level cache, which is in
+// buffers of more than 96 MiB, and beyond 64 if they are not most of it; elsewhere they are stored as the rows are.  Us of a call
+// streamed / as the rows: 1388 x 3840 bytes, 15 of 16 rows padding (81 MiB) 28.9 / 22.4, 673 x 3872, as many (80) 29.5 / 22.1, 25024 x
+// 384, three of four (73) 34.6 / 31.3, 9152 x 640, seven of eight (89) 32.0 / 27.6; 5120 x 4304, half (84) 41.5 / 43.2, 40250 x 304, a
+// fifth (87) 59.5 / 62.8, 8576 x 1920, half (94) 41.5 / 42.6; 2829 x 10 KiB, three of four (110) 43.7 / 49.6, 5333 x 4 KiB, three of
+// four (167) 55.4 / 74.9, 53902 x 1536, half 78 / 86.
+inline bool fill_streams(int64_t buffer_rows, int64_t rows, int cpr) {
+    const int64_t bytes = buffer_rows * cpr * 16, MiB = (int64_t)1 << 20;
+    return bytes > 96 * MiB || (bytes > 64 * MiB && 3 * rows > buffer_rows);
 }
 
 // The combine and its transpose: y goes straight through L2 and is not kept: ordinary stores are written back behind the last wavefront, and streaming

@@ -80,6 +80,7 @@ int scatter(uint64_t base, int64_t rows, int cpr, int k, int by_wave, int behind
 }
 int combine(uint64_t base, int64_t S, int cpr, int k, int by_wave) { return combine_store(row_lines((const void*)base, cpr), S, cpr, k, by_wave); }
 int combine_bwd(uint64_t base, int64_t S, int cpr, int k) { return combine_bwd_store(row_lines((const void*)base, cpr), S, cpr, k); }
+int fill(int64_t buffer_rows, int64_t rows, int cpr) { return fill_streams(buffer_rows, rows, cpr); }
 int regroup(uint64_t base, int64_t rows, int cpr) { return regroup_store(row_lines((const void*)base, cpr), rows, cpr); }
 }
 """
@@ -98,6 +99,7 @@ def rules(tmp_path_factory):
     lib.scatter.argtypes = [u64, i64] + [i32] * 5
     lib.combine.argtypes = [u64, i64] + [i32] * 3
     lib.combine_bwd.argtypes = [u64, i64] + [i32] * 2
+    lib.fill.argtypes = [i64, i64, i32]
     lib.regroup.argtypes = [u64, i64, i32]
     return lib
 
@@ -148,3 +150,23 @@ def _at(mib, cpr):
 def test_scattered_rows(rules, mib, cpr, k, by_wave, behind_gate, policy):
     """Where each policy of the scatter's rows begins and ends."""
     assert rules.scatter(1 << 20, _at(mib, cpr), cpr, k, by_wave, behind_gate, 0) == policy
+
+
+@pytest.mark.parametrize("mib,cpr,k,by_wave,policy", [
+    (3, 32, 8, 0, BACK), (4, 32, 8, 0, THROUGH), (24, 32, 2, 0, THROUGH), (25, 32, 2, 0, BACK), (128, 32, 8, 0, BACK), (129, 32, 8, 0, OUT),
+    (3, 256, 2, 1, THROUGH), (128, 256, 2, 1, THROUGH), (129, 256, 2, 1, OUT), (129, 256, 1, 1, OUT), (17, 132, 2, 1, STREAM), (300, 300, 6, 1, STREAM),
+    (24, 125, 8, 1, THROUGH), (25, 125, 8, 1, BACK), (128, 125, 8, 1, BACK), (129, 125, 8, 1, STREAM), (128, 125, 2, 1, THROUGH), (129, 125, 4, 1, STREAM),
+    (3, 53, 2, 0, BACK), (5, 53, 2, 0, THROUGH), (24, 53, 8, 0, THROUGH), (25, 53, 8, 0, BACK), (51, 53, 1, 0, BACK), (300, 45, 2, 0, BACK),
+    (20, 36, 2, 0, THROUGH), (25, 36, 2, 0, STREAM)])
+def test_rows_of_the_fixed_size_layout(rules, mib, cpr, k, by_wave, policy):
+    """The rows go by their own size, whatever the padding between them."""
+    assert rules.scatter(1 << 20, _at(mib, cpr), cpr, k, by_wave, 0, 1) == policy
+
+
+@pytest.mark.parametrize("mib,part,streams", [
+    (64, 1.0, 0), (65, 1.0, 1), (65, 0.5, 1), (96, 0.25, 0), (96, 1 / 16, 0), (97, 0.25, 1), (97, 0, 1), (10, 0, 0)])
+def test_padding(rules, mib, part, streams):
+    """Zeros stream in buffers beyond 96 MiB, and beyond 64 MiB unless most rows are padding."""
+    for cpr in (1, 60, 240, 512):
+        rows = _at(mib, cpr)
+        assert rules.fill(rows, int(part * rows), cpr) == streams
