@@ -201,7 +201,9 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
             regroup_flat_kernel<U, ST>    <<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, pow2_shift(cpr),         \
                                                                    to_expert_major, dst, expert_offset);           \
     } while (0)
-    if (policy == kStoreStream) TAMOE_REGROUP(kStoreStream); else TAMOE_REGROUP(kStoreThrough);
+    if (policy == kStoreStream) TAMOE_REGROUP(kStoreStream);
+    else if (policy == kStoreThrough) TAMOE_REGROUP(kStoreThrough);
+    else TAMOE_REGROUP(kStoreBack);
 #undef TAMOE_REGROUP
     return check_launch(fn, "regroup_copy_kernel");
 }

@@ -107,12 +107,16 @@ inline StorePolicy combine_bwd_store(RowLines lines, int64_t S, int cpr, int k) 
     return kStoreThrough;
 }
 
-// The regroup: straight through L2 while the buffer fits the last-level cache, which keeps it for the experts (or the exchange), and
-// streaming beyond; rows that are no whole or half lines stream earlier.  Us of one call with ordinary / streaming / through stores:
-// 12288 x 512 bytes 10.3 / 10.1 / 9.8, 20480 x 2 KiB 28.3 / 30.1 / 27.0, 117760 x 2 KiB 146 / 142 / 139, 44800 x 8 KiB 230 /
-// 213 / 220; 20971 x 2000 32.0 / 32.8 / 30.8, 34000 x 2320 (75 MiB) - / 53.6 / 50.0, 47185 x 2000 64.3 / 63.2 / 64.7, 120586 x 2000 155 / 148 / 174.
+// The regroup: straight through L2 while the buffer fits the last-level cache, which keeps it for the experts (or the exchange),
+// and streaming beyond; rows that share lines stream earlier.  Small buffers of flat rows are merged in L2 instead.  Us of one call
+// with ordinary / streaming / through stores: 20480 x 2 KiB 28.3 / 30.1 / 27.0, 117760 x 2 KiB 146 / 142 / 139, 44800 x 8 KiB 230 / 213 / 220;
+// 20971 x 2000 32.0 / 32.8 / 30.8, 34000 x 2320 (75 MiB) - / 53.6 / 50.0, 47185 x 2000 64.3 / 63.2 / 64.7, 120586 x 2000 155 / 148 / 174.  Both
+// ways: 1340 x 384 7.4 / 7.4 / 8.0, 4852 x 384 (2 MiB) 6.9 / 7.0 / 7.2, 5120 x 176 7.9 / 8.4 / 8.5; 10551 x 512 (5 MiB) 10.1 / 9.7 / 9.7, 6480 x 608 (4
+// MiB) 9.7 / - / 9.3, 27904 x 176 (5 MiB) 10.5 / - / 9.9, 19200 x 608 (11 MiB) 12.3 / 12.9 / 12.0.
 inline StorePolicy regroup_store(RowLines lines, int64_t rows, int cpr) {
-    return rows * cpr * 16 > (int64_t)(lines == kSharedLines ? 80 : 256) << 20 ? kStoreStream : kStoreThrough;
+    const int64_t bytes = rows * cpr * 16, MiB = (int64_t)1 << 20;
+    if (cpr < 64 && bytes <= 3 * MiB) return kStoreBack;
+    return bytes > (lines == kSharedLines ? 80 : 256) * MiB ? kStoreStream : kStoreThrough;
 }
 
 }  // namespace tamoe

@@ -170,3 +170,13 @@ def test_padding(rules, mib, part, streams):
     for cpr in (1, 60, 240, 512):
         rows = _at(mib, cpr)
         assert rules.fill(rows, int(part * rows), cpr) == streams
+
+
+@pytest.mark.parametrize("rows,cpr,off,policy", [
+    (1340, 24, 0, BACK), (6144, 32, 0, BACK), (6145, 32, 0, THROUGH), (5120, 11, 0, BACK), (16384, 26, 0, THROUGH),      # flat
+    (6000, 24, 48, BACK), (27810, 24, 48, THROUGH), (1024, 128, 0, THROUGH), (1000, 65, 0, THROUGH), (500, 128, 48, THROUGH),
+    (_at(256, 128), 128, 0, THROUGH), (_at(257, 128), 128, 0, STREAM), (_at(256, 100), 100, 0, THROUGH), (_at(80, 145), 145, 0, THROUGH),
+    (_at(81, 145), 145, 0, STREAM), (_at(81, 128), 128, 48, STREAM), (_at(300, 32), 32, 0, STREAM)])
+def test_regrouped_rows(rules, rows, cpr, off, policy):
+    """Where each policy of the regroup begins and ends."""
+    assert rules.regroup((1 << 20) + off, rows, cpr) == policy
