@@ -21,6 +21,7 @@
 //      fixed-size layout the last ones clear every expert's unused rows.
 //      How rows are stored depends on what the caches can do for them (scatter_store).
 #include <algorithm>
+#include <type_traits>
 
 #include "gate_tile.h"
 #include "internal.h"
@@ -157,6 +158,7 @@ struct RouteArgs {
     int cpr, wpr, shift;        // chunks per row, wavefronts per row, log2 of wpr (flat: of cpr) or -1
     int n_blocks, pitch, tile_shift;
     int stride, units;          // small tables: count_stride, chunks of 64 lanes per wavefront of the scatter
+    int threads;                // of the scatter
     int pad_C;                  // rows per expert of the fixed-size layout, 0: packed
     int copy_blocks, fill_parts;
     bool fill_streams;
@@ -214,12 +216,13 @@ __device__ __forceinline__ int32_t offset_of(const WaveOffsets& o, int e) {
 // the rows are on their way too, then 0.9 us.  What was measured to count is the length of the code, which a wavefront
 // runs once, from cold instruction caches: with bytes for counts (half the requests, three times the additions)
 // small_forward took 17.8 us, with the steps of sum_columns under a condition each 15.9, now 14.8.
-constexpr int kTableThreads = 512, kTableWaves = kTableThreads / 64;
+constexpr int kTableThreads = 512;   // or half as many (table_threads)
 constexpr int kTableBatch = 8;   // rows per lane, requested together (one in the smallest tables)
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
+template <int TH>
 struct TableLds {
-    uint32_t part[kTableWaves][64][8];                       // by wavefront and column: all tiles, tiles before blk0
+    uint32_t part[TH / 64][64][8];                           // by wavefront and column: all tiles, tiles before blk0
     int32_t before[TAMOE_MAX_K * TAMOE_MAX_EXPERTS];         // pairs of e that precede choice j of tile blk0, at j*N + e
     int32_t total[TAMOE_MAX_K * TAMOE_MAX_EXPERTS];          // pairs of (e, j), where a thread has one choice
     int32_t pairs[TAMOE_MAX_EXPERTS], kept[TAMOE_MAX_EXPERTS];
@@ -264,11 +267,12 @@ __device__ __forceinline__ void sum_columns(T (&v)[M], int C) {
 
 // Fills in t; also calls while_waiting(), between the requests for the counts and their use.  Every thread calls; ends
 // with a barrier.
-template <int KK, int B, class Body>
-__device__ __forceinline__ void scan_counts(const RouteArgs& a, int blk0, TableLds& t, Body while_waiting) {
+template <int TH, int KK, int B, class Body>
+__device__ __forceinline__ void scan_counts(const RouteArgs& a, int blk0, TableLds<TH>& t, Body while_waiting) {
+    constexpr int kWaves = TH / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int C = a.stride >> 3, shift = 31 - __builtin_clz(C);
-    const int col = tid & (C - 1), r0 = tid >> shift, R = kTableThreads >> shift;
+    const int col = tid & (C - 1), r0 = tid >> shift, R = TH >> shift;
     const __amdgpu_buffer_rsrc_t rows =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.counts), 0, a.n_blocks * a.stride * 2, 0x00020000);
     const int32_t cap_e = WordBuffer(a.cap, a.cap != nullptr ? a.N : 0).load<int32_t>(tid);
@@ -301,22 +305,22 @@ __device__ __forceinline__ void scan_counts(const RouteArgs& a, int blk0, TableL
     const int half = C > 64 ? 1 : 0;   // 128 columns: the even wavefronts have the first 64 of them
     auto column = [&](int i, int32_t& all, int32_t& bef) {
         const int c = i >> 3, q = (i & 7) >> 1, sh = (i & 1) * 16;
-        uint32_t n[kTableWaves], b[kTableWaves];
+        uint32_t n[kWaves], b[kWaves];
 #pragma unroll
-        for (int w = 0; w < kTableWaves; ++w) {
-            const uint32_t* at = t.part[(w << half & 7) | c >> 6][c & 63];
-            n[w] = w < kTableWaves >> half ? at[q] : 0u;
-            b[w] = w < kTableWaves >> half ? at[q + 4] : 0u;
+        for (int w = 0; w < kWaves; ++w) {
+            const uint32_t* at = t.part[(w << half & (kWaves - 1)) | c >> 6][c & 63];
+            n[w] = w < kWaves >> half ? at[q] : 0u;
+            b[w] = w < kWaves >> half ? at[q + 4] : 0u;
         }
         all = bef = 0;
 #pragma unroll
-        for (int w = 0; w < kTableWaves; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             all += n[w] >> sh & 0xffffu;
             bef += b[w] >> sh & 0xffffu;
         }
     };
     if constexpr (KK == 0) {   // a thread per choice too: one after the other they take 2 us (404 x 768 bytes, six)
-        for (int i = tid; i < a.k * a.N; i += kTableThreads) column(i, t.total[i], t.before[i]);
+        for (int i = tid; i < a.k * a.N; i += TH) column(i, t.total[i], t.before[i]);
         __syncthreads();
     }
     if (tid < a.N) {
@@ -356,9 +360,10 @@ __device__ __forceinline__ void scan_counts(const RouteArgs& a, int blk0, TableL
 // destination device, the loss; with TABLE also what route_expert_kernel would have written.  N <= 128
 // values: the first wavefront holds two experts per lane, scans and sums them with lane operations
 // (fixed order), and looks up the per-device numbers in LDS.
-template <bool TABLE, int KK, int B>
-__device__ __forceinline__ void route_layer_outputs(const RouteArgs& a, TableLds* t) {
-    __shared__ float4 sums[TABLE ? kTableWaves : 1][TAMOE_MAX_EXPERTS / 4];
+template <int TH, bool TABLE, int KK, int B>
+__device__ __forceinline__ void route_layer_outputs(const RouteArgs& a, TableLds<TH>* t) {
+    constexpr int kWaves = TH / 64;
+    __shared__ float4 sums[TABLE ? kWaves : 1][TAMOE_MAX_EXPERTS / 4];
     __shared__ int32_t off[TAMOE_MAX_EXPERTS + 1], pairs_off[TAMOE_MAX_EXPERTS + 1];
     const int tid = threadIdx.x;
     const int N = a.N;
@@ -370,9 +375,9 @@ __device__ __forceinline__ void route_layer_outputs(const RouteArgs& a, TableLds
     float m0 = 0.f, m1 = 0.f;
     if constexpr (TABLE) {
         // sums of gate probabilities, four experts of a tile per lane
-        const int P4 = sum_stride(N) / 4, R = kTableThreads / P4;
+        const int P4 = sum_stride(N) / 4, R = TH / P4;
         const int r0 = tid / P4, q = tid & (P4 - 1);
-        scan_counts<KK, B>(a, 0, *t, [&] {
+        scan_counts<TH, KK, B>(a, 0, *t, [&] {
             if (a.m == nullptr) return;
             const __amdgpu_buffer_rsrc_t rows =
                 __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.m_part), 0, a.n_blocks * P4 * 16, 0x00020000);
@@ -401,7 +406,7 @@ __device__ __forceinline__ void route_layer_outputs(const RouteArgs& a, TableLds
         if (a.m != nullptr) {
             const float* part = reinterpret_cast<const float*>(sums);
 #pragma unroll
-            for (int w = 0; w < kTableWaves; ++w) {
+            for (int w = 0; w < kWaves; ++w) {
                 m0 += e0 < N ? part[w * TAMOE_MAX_EXPERTS + e0] : 0.f;
                 m1 += e1 < N ? part[w * TAMOE_MAX_EXPERTS + e1] : 0.f;
             }
@@ -489,7 +494,7 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
     vec16* __restrict__ send, const RouteArgs a) {
     const uint32_t wg = linear_block();
     if (wg == 0) {
-        route_layer_outputs<false, KK, 1>(a, nullptr);
+        route_layer_outputs<kCopyThreads, false, KK, 1>(a, nullptr);
         return;
     }
     constexpr int KM = KK > 0 ? KK : TAMOE_MAX_K;
@@ -597,25 +602,25 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
 // registers: two workgroups share a compute unit.
 // ROWU: a lane has one of the wavefront's pairs (unit, choice) and works out its slot; the stores read the slots from
 // the lanes.
-template <int KK, int U, bool ROWU, int ST, int B>
-__global__ __launch_bounds__(kTableThreads, 4) void route_table_kernel(
+template <int TH, int KK, int U, bool ROWU, int ST, int B>
+__global__ __launch_bounds__(TH, 4) void route_table_kernel(
     const vec16* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_pos,
     const uint16_t* __restrict__ counts, int32_t* __restrict__ slot, vec16* __restrict__ send, const RouteArgs a) {
     constexpr int KM = KK > 0 ? KK : TAMOE_MAX_K;
-    __shared__ TableLds t;
+    __shared__ TableLds<TH> t;
     const int wg = (int)blockIdx.x;   // one generation
     if (wg == 0) {
-        route_layer_outputs<true, KK, B>(a, &t);
+        route_layer_outputs<TH, true, KK, B>(a, &t);
         return;
     }
     const int N = a.N, cpr = a.cpr, k = KK > 0 ? KK : a.k;
     if (wg > a.copy_blocks) {
-        scan_counts<KK, B>(a, 0, t, [] {});
-        clear_unused<ST>(a, wg - 1 - a.copy_blocks, t.kept, kTableThreads);
+        scan_counts<TH, KK, B>(a, 0, t, [] {});
+        clear_unused<ST>(a, wg - 1 - a.copy_blocks, t.kept, TH);
         return;
     }
     const int lane = threadIdx.x & 63;
-    const uint32_t first_unit = (uint32_t)(wg - 1) * kTableWaves * U;
+    const uint32_t first_unit = (uint32_t)(wg - 1) * (TH / 64) * U;
     const uint32_t unit0 = first_unit + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * U;
     const int64_t total = a.S * cpr;
     // token tile of the workgroup's first token
@@ -650,7 +655,7 @@ __global__ __launch_bounds__(kTableThreads, 4) void route_table_kernel(
             tok[u] = tok[u - 1] + next;
             seg[u] = next ? 0 : seg[u - 1] + 1;
         }
-        scan_counts<KK, B>(a, blk0, t, [&] {
+        scan_counts<TH, KK, B>(a, blk0, t, [&] {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const bool in = tok[u] < a.S;
@@ -683,7 +688,7 @@ __global__ __launch_bounds__(kTableThreads, 4) void route_table_kernel(
                 pos[u][j] = local_pos[p];
             }
         }
-        scan_counts<KK, B>(a, blk0, t, [&] {
+        scan_counts<TH, KK, B>(a, blk0, t, [&] {
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(x + (size_t)tok[u] * cpr + col[u]);
         });
@@ -716,6 +721,11 @@ static bool scatter_by_wave(int64_t S, int cpr, int k) {
     return k <= 4 || cpr % 8 == 0 || (lanes - cpr) * 10 <= lanes || S * row_waves(cpr) < 8192;
 }
 
+// Units of 64 chunks: of one row each, or anywhere (flat).
+static int64_t move_units(int64_t S, int cpr, int k) {
+    return scatter_by_wave(S, cpr, k) ? S * row_waves(cpr) : ceil_div(S * (int64_t)cpr, 64);
+}
+
 // Workgroups that move rows.
 static int64_t copy_workgroups(int64_t S, int cpr, int k) {
     const int U = copy_units(k);
@@ -735,12 +745,12 @@ static void plan_copy(RouteArgs& a) {
     a.wpr = row_waves(a.cpr);
     a.shift = pow2_shift(by_wave ? a.wpr : a.cpr);
     a.copy_blocks = a.units == 0 ? (int)copy_workgroups(a.S, a.cpr, a.k)
-                                 : (int)ceil_div(by_wave ? a.S * a.wpr : ceil_div(a.S * (int64_t)a.cpr, 64), kTableWaves * a.units);
+                                 : (int)ceil_div(move_units(a.S, a.cpr, a.k), a.threads / 64 * a.units);
     a.fill_streams = fill_streams((int64_t)a.N * a.pad_C, rows_sent(a), a.cpr);
     // about 4096 workgroups clear rows (512 of the larger ones that sum the table), at most one per 16 bytes per thread
-    const int wgs = a.units == 0 ? 4096 : 512, threads = a.units == 0 ? kCopyThreads : kTableThreads;
+    const int wgs = a.units == 0 ? 4096 : 512;
     a.fill_parts = a.pad_C == 0 ? 0 : (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(wgs, a.N),
-                                                                     ceil_div((int64_t)a.pad_C * a.cpr, threads)));
+                                                                     ceil_div((int64_t)a.pad_C * a.cpr, a.threads)));
 }
 
 template <int KK>
@@ -777,43 +787,61 @@ static int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool b
     // the sums of a wavefront's share of the tiles fit 16 bits
     if (S > 200000 || ceil_div(S, tile_tokens) * (count_stride(N, k) / 8) > kTableBatch * kTableThreads) return 0;
     const bool by_wave = scatter_by_wave(S, cpr, k);
-    const int64_t units = by_wave ? S * row_waves(cpr) : ceil_div(S * (int64_t)cpr, 64);
+    const int64_t units = move_units(S, cpr, k);
     if (units > (!by_wave ? 8192 : behind_gate ? 65536 : 32768)) return 0;
     int U = 1;
-    while (U < (by_wave ? 8 : 2) && units >= kTableWaves * U * 2 * 256) U *= 2;
+    while (U < (by_wave ? 8 : 2) && units >= kTableThreads / 64 * U * 2 * 256) U *= 2;
     return U;
 }
 
-template <int KK, int U, bool ROWU>
+// Threads of a workgroup that sums the table: half as many where workgroups of 512 would be fewer than the compute units, as
+// long as the table is one batch of theirs (forward calls, us with 512 and 256: 496 x 160 bytes, three choices 13.4, 12.9; 704 x 128, four 13.5, 12.5;
+// 1024 x 1 KiB, 72 experts 14.9, 14.5; 512 x 256, fp32, one 12.2, 12.1; 128 threads are no better: 1958 x 1792 13.8, 256 13.1).
+static int table_threads(int64_t S, int cpr, int k, int64_t pieces) {
+    constexpr int kHalf = kTableThreads / 2;
+    // a fourth of the tiles per wavefront: fits 16 bits, as in table_units
+    return move_units(S, cpr, k) < kTableThreads / 64 * 256 && S <= 100000 && pieces <= kTableBatch * kHalf ? kHalf : kTableThreads;
+}
+
+// Only the policies that scatter_store can answer at these sizes are there: a unit is 1 KiB of x at most, and U units per wavefront
+// go with fewer than 4096 * U of them (65536 for U = 8; 2048 with the smaller workgroups).
+template <int TH, int KK, int U, bool ROWU>
 static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
-    const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(kTableThreads);
+    const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(TH);
     const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
     // the smallest tables in a kernel that is shorter by seven requests and their sums
-    const bool one = U == 1 && (int64_t)a.n_blocks * (a.stride / 8) <= kTableThreads;
-#define TAMOE_ROUTE_TABLE(ST)                                                                      \
-    do {                                                                                           \
-        if (one)                                                                                   \
-            route_table_kernel<KK, U, ROWU, ST, U == 1 ? 1 : kTableBatch>                          \
-                <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a); \
-        else                                                                                       \
-            route_table_kernel<KK, U, ROWU, ST, kTableBatch>                                       \
-                <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a); \
-    } while (0)
-    if (policy == kStoreStream || policy == kStoreOut) TAMOE_ROUTE_TABLE(kStoreStream);
-    else if (policy == kStoreThrough) TAMOE_ROUTE_TABLE(kStoreThrough);
-    else TAMOE_ROUTE_TABLE(kStoreBack);
-#undef TAMOE_ROUTE_TABLE
+    const bool one = U == 1 && (int64_t)a.n_blocks * (a.stride / 8) <= TH;
+    const auto launch = [&](auto st_c) {
+        constexpr int ST = decltype(st_c)::value;
+        if (one)
+            route_table_kernel<TH, KK, U, ROWU, ST, U == 1 ? 1 : kTableBatch>
+                <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
+        else
+            route_table_kernel<TH, KK, U, ROWU, ST, kTableBatch>
+                <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
+    };
+    constexpr int kMiB = (U == 8 ? 64 : 4 * U) / (TH == kTableThreads ? 1 : 2) * (KK > 0 ? KK : TAMOE_MAX_K);   // of rows
+    if constexpr (kMiB > 16)   // half lines
+        if (policy == kStoreStream) return launch(std::integral_constant<int, kStoreStream>{});
+    if constexpr (!ROWU || (KK == 0 && kMiB > 24) || (KK == 4 && kMiB > 240))
+        if (policy == kStoreBack) return launch(std::integral_constant<int, kStoreBack>{});
+    if constexpr (ROWU && kMiB > 128)
+        if (policy == kStoreOut) return launch(std::integral_constant<int, kStoreOut>{});
+    launch(std::integral_constant<int, kStoreThrough>{});
 }
 template <int KK>
 static void launch_route_table(const RouteArgs& a, hipStream_t st) {
+    constexpr int TH = kTableThreads;
     if (!scatter_by_wave(a.S, a.cpr, a.k)) {
-        if (a.units == 1) launch_route_table_u<KK, 1, false>(a, st);
-        else launch_route_table_u<KK, 2, false>(a, st);
+        if (a.threads != TH) launch_route_table_u<TH / 2, KK, 1, false>(a, st);
+        else if (a.units == 1) launch_route_table_u<TH, KK, 1, false>(a, st);
+        else launch_route_table_u<TH, KK, 2, false>(a, st);
     } else {
-        if (a.units == 1) launch_route_table_u<KK, 1, true>(a, st);
-        else if (a.units == 2) launch_route_table_u<KK, 2, true>(a, st);
-        else if (a.units == 4) launch_route_table_u<KK, 4, true>(a, st);
-        else launch_route_table_u<KK, 8, true>(a, st);
+        if (a.threads != TH) launch_route_table_u<TH / 2, KK, 1, true>(a, st);
+        else if (a.units == 1) launch_route_table_u<TH, KK, 1, true>(a, st);
+        else if (a.units == 2) launch_route_table_u<TH, KK, 2, true>(a, st);
+        else if (a.units == 4) launch_route_table_u<TH, KK, 4, true>(a, st);
+        else launch_route_table_u<TH, KK, 8, true>(a, st);
     }
 }
 
@@ -829,6 +857,7 @@ static int run_copy(const char* fn, const GateRun& run, RouteArgs a, const char*
     a.tile_shift = pow2_shift(run.tile_tokens);
     const bool table = a.counts != nullptr;
     a.units = table ? table_units(a.S, a.cpr, a.N, a.k, run.tile_tokens, a.m_part != nullptr) : 0;
+    a.threads = table ? table_threads(a.S, a.cpr, a.k, (int64_t)a.n_blocks * (a.stride / 8)) : kCopyThreads;
     plan_copy(a);
     if (!table) {
         TraceScope tr("route_expert_kernel", st);

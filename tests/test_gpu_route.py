@@ -93,6 +93,8 @@ def test_fused_call_against_separate_calls(T, S, d, N, P, k):
     (33, 8, 2, 2, 2), (1000, 64, 3, 3, 1), (4095, 512, 16, 16, 2), (4096, 512, 16, 16, 2), (8191, 512, 40, 8, 2),        # units per wavefront
     (16390, 512, 40, 8, 1), (16384, 1024, 64, 64, 2), (16385, 1024, 33, 11, 3), (65536, 512, 16, 4, 2), (65537, 512, 16, 4, 2),   # and no more
     (3000, 1000, 64, 8, 4), (4128, 264, 64, 8, 4), (2000, 1544, 128, 8, 4), (2000, 264, 128, 8, 5), (1000, 1544, 128, 8, 8), (16384, 256, 16, 4, 2), (16385, 256, 16, 4, 2), (200000, 8, 8, 8, 2), (200001, 8, 8, 8, 2),  # columns
+    (2047, 512, 16, 16, 2), (2048, 512, 16, 16, 2), (16376, 64, 8, 8, 2), (16385, 64, 8, 8, 2), (1024, 96, 64, 8, 8), (1025, 96, 64, 8, 8), (1030, 96, 128, 8, 2),   # smaller workgroups
+    (256, 512, 128, 8, 4), (257, 512, 128, 8, 4), (31, 16, 128, 8, 8), (33, 64, 128, 8, 8),
     (2047, 128, 64, 8, 8), (2049, 128, 64, 8, 8), (777, 136, 5, 5, 5), (513, 2056, 127, 127, 3)])
 def test_table_summed_by_the_scatter(T, S, d, N, P, k):
     """The fused call and tamoe_dispatch on both sides of the rule that leaves out the per-expert launch, against

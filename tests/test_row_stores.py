@@ -180,3 +180,23 @@ def test_padding(rules, mib, part, streams):
 def test_regrouped_rows(rules, rows, cpr, off, policy):
     """Where each policy of the regroup begins and ends."""
     assert rules.regroup((1 << 20) + off, rows, cpr) == policy
+
+
+@pytest.mark.parametrize("units,U,by_wave", [(2047, 0.5, 1), (2047, 0.5, 0), (4095, 1, 1), (4095, 1, 0), (8191, 2, 1), (8192, 2, 0), (16383, 4, 1), (65536, 8, 1)])
+def test_policies_of_the_scatter_that_sums_the_table(rules, units, U, by_wave):
+    """launch_route_table_u leaves out the policies that no call of its size asks for: units of at most 1 KiB of x, times k."""
+    base = {0: 1 << 20, 1: (1 << 20) + 64, 2: (1 << 20) + 48}
+    for k in range(1, 9):
+        most = int((64 if U == 8 else 4 * U) * (k if k <= 4 else 8))   # MiB of rows that the launch reckons with
+        there = {THROUGH} | ({STREAM} if most > 16 else set())
+        if not by_wave or (k > 4 and most > 24) or (k == 4 and most > 240):
+            there.add(BACK)
+        if by_wave and most > 128:
+            there.add(OUT)
+        cprs = (64, 96, 100, 128, 200, 512) if by_wave else (1, 8, 24, 36, 60, 63)
+        for cpr in cprs:
+            waves = (cpr + 63) // 64 if by_wave else cpr / 64
+            for S in sorted({int(units / waves * f / 40) for f in range(1, 41)}):
+                for lines in base:
+                    for gate, padded in ((1, 0), (0, 0), (0, 1)):
+                        assert rules.scatter(base[lines], S * k, cpr, k, by_wave, gate, padded) in there, (k, cpr, S, lines, gate, padded)
