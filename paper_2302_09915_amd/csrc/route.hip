@@ -779,12 +779,15 @@ static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
 // The table has to be one batch of scan_counts: a second one is a second memory round trip (5003 x 2000 bytes, 157 tiles
 // of 192 counts: 65.9 us for a training pass, 65.7 with the launch).  Units: as many as leave a workgroup per compute
 // unit, since each one sums the table (small_forward, 4096 units: with two 14.8, with one 17.5; gpt_moe_forward, 32768: with
-// eight 43.0, with four 45.3); beyond 65536 of them (64 MiB of x) the launch that is saved counts for little, and for a
+// eight 43.0, with four 45.3; 6681 x 3456 bytes, eight choices, 26724: with eight 71.9, with two 75.0, with the launch 75.2); beyond 65536 of
+// them (64 MiB of x) the launch that is saved counts for little (31106 x 2304, three, 93318: 102.4 with it, 99.9 without), and for a
 // routing that is given, behind which x does not come from the last-level cache, beyond 32768 (skewed_separate, 65536: 53.7 with the
-// launch, 54.7 without; fused, 16384 x 4 KiB, one choice 59.7 and 56.7).  Flat rows have
-// the work of a slot in every lane, and at most two units (57635 x 384 bytes, two choices 45.5 and 47.5).
+// launch, 54.7 without; fused, 16384 x 4 KiB, one choice 59.7 and 56.7).  Flat rows have the work of a slot in every lane, and
+// at most two units (60623 x 256, one choice, 15156: 23.6 with the launch, 24.6 with two, 28.7 with one).
 static int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool behind_gate) {
-    // the sums of a wavefront's share of the tiles fit 16 bits
+    // 16 bits hold the sums of a wavefront's share of the tiles, whatever the routing: with R = 512 / C rows of C pieces requested at a
+    // time it has ceil(tiles / R) times max(1, 64 / C) tiles, (S + tile) / 8 + 64 * tile / C tokens at most, which are 57 832 for
+    // S = 200 000, C = 1 and tiles of 512, and a token counts once per expert and choice
     if (S > 200000 || ceil_div(S, tile_tokens) * (count_stride(N, k) / 8) > kTableBatch * kTableThreads) return 0;
     const bool by_wave = scatter_by_wave(S, cpr, k);
     const int64_t units = move_units(S, cpr, k);

@@ -95,6 +95,7 @@ def test_fused_call_against_separate_calls(T, S, d, N, P, k):
     (3000, 1000, 64, 8, 4), (4128, 264, 64, 8, 4), (2000, 1544, 128, 8, 4), (2000, 264, 128, 8, 5), (1000, 1544, 128, 8, 8), (16384, 256, 16, 4, 2), (16385, 256, 16, 4, 2), (200000, 8, 8, 8, 2), (200001, 8, 8, 8, 2),  # columns
     (2047, 512, 16, 16, 2), (2048, 512, 16, 16, 2), (16376, 64, 8, 8, 2), (16385, 64, 8, 8, 2), (1024, 96, 64, 8, 8), (1025, 96, 64, 8, 8), (1030, 96, 128, 8, 2),   # smaller workgroups
     (256, 512, 128, 8, 4), (257, 512, 128, 8, 4), (31, 16, 128, 8, 8), (33, 64, 128, 8, 8),
+    (16384, 512, 8, 8, 8), (16385, 512, 8, 8, 8), (8191, 512, 8, 8, 5), (8192, 512, 8, 8, 5), (16383, 512, 16, 4, 4), (16384, 512, 16, 4, 4), (9000, 1024, 16, 4, 3),   # a lane per pair
     (2047, 128, 64, 8, 8), (2049, 128, 64, 8, 8), (777, 136, 5, 5, 5), (513, 2056, 127, 127, 3)])
 def test_table_summed_by_the_scatter(T, S, d, N, P, k):
     """The fused call and tamoe_dispatch on both sides of the rule that leaves out the per-expert launch, against
@@ -121,3 +122,20 @@ def test_table_summed_by_the_scatter(T, S, d, N, P, k):
     m = torch.softmax(f["logits"].double(), 1).mean(0)
     torch.testing.assert_close(f["m"].double(), m, rtol=1e-5, atol=1e-9)
     torch.testing.assert_close(f["loss"].double().reshape(()), N * P / S * (pen.double() * m * count).sum(), rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("S,d,k", [(200000, 8, 1), (200000, 8, 2), (199997, 16, 1), (100000, 8, 1), (100000, 8, 3), (65536, 32, 2), (131071, 8, 1), (4096, 512, 2)])
+def test_all_tokens_to_the_same_experts(T, S, d, k):
+    """The largest sums of pair counts that the scatter adds up 16 bits wide."""
+    g = torch.Generator(device="cuda").manual_seed(S + k)
+    x = torch.randint(-32768, 32767, (S, d), generator=g, device="cuda", dtype=torch.int16).view(torch.bfloat16)
+    idx = torch.arange(k, device="cuda", dtype=torch.int32).flip(0).repeat(S, 1).contiguous()
+    cap = torch.full((8,), S - 5, dtype=torch.int32, device="cuda")
+    q = T.dispatch(x, idx, cap, 8, 8)
+    s = {key: torch.empty_like(v) for key, v in q.items()}
+    T.tamoe_dispatch_static(x, idx, cap, 8, 8, s["send"], s["slot"], s["kept_expert"], s["expert_offset"], s["send_count_dev"])
+    for key in ("slot", "kept_expert", "expert_offset", "send_count_dev"):
+        assert torch.equal(q[key], s[key]), key
+    assert q["kept_expert"].tolist() == [S - 5] * k + [0] * (8 - k)
+    K = k * (S - 5)
+    assert torch.equal(q["send"][:K].view(torch.int16), s["send"][:K].view(torch.int16))
