@@ -798,8 +798,9 @@ static int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool b
 }
 
 // Threads of a workgroup that sums the table: half as many where workgroups of 512 would be fewer than the compute units, as
-// long as the table is one batch of theirs (forward calls, us with 512 and 256: 496 x 160 bytes, three choices 13.4, 12.9; 704 x 128, four 13.5, 12.5;
-// 1024 x 1 KiB, 72 experts 14.9, 14.5; 512 x 256, fp32, one 12.2, 12.1; 128 threads are no better: 1958 x 1792 13.8, 256 13.1).
+// long as the table is one batch of theirs (forward calls, us with 512 and 256: 435 x 400 bytes, four choices 15.0, 14.4; 704 x 128,
+// four 13.5, 12.7; 1024 x 1 KiB, 72 experts 14.9, 14.5; fixed-size layout, 704 x 352, eight 17.1, 15.7; 128 threads are no better: 1958 x
+// 1792 13.8, 256 13.1).
 static int table_threads(int64_t S, int cpr, int k, int64_t pieces) {
     constexpr int kHalf = kTableThreads / 2;
     // a fourth of the tiles per wavefront: fits 16 bits, as in table_units

@@ -186,13 +186,28 @@ def test_regroup_layouts(T, P, E, chunks, mean, clip):
         np.testing.assert_array_equal(off.cpu().numpy(), exp[::P][:E + 1])
 
 
-@pytest.mark.parametrize("S,chunks,k", [
-    (2048, 128, 2), (4096, 128, 2), (5000, 64, 3), (30720, 256, 2), (30721, 256, 2), (23041, 1024, 1), (23040, 1024, 1),  # whole lines
-    (4000, 100, 2), (21000, 100, 2), (11000, 137, 2), (63100, 125, 2), (31500, 125, 4), (4000, 125, 6), (21000, 125, 8),   # by wavefront
-    (6000, 17, 3), (63000, 65, 1), (97000, 65, 1), (121000, 65, 2), (121900, 65, 2)])                                     # flat
+# (tokens, chunks per row, choices, whether the scatter takes the rows by wavefront, how it stores them): tests/test_row_stores.py
+# holds this list and the next against the rules
+BACK, STREAM, THROUGH, OUT = 0, 2, 16, 19
+STORE_SHAPES = [
+    (2048, 128, 2, 1, THROUGH), (5000, 64, 3, 1, THROUGH), (30720, 256, 2, 1, THROUGH), (30721, 256, 2, 1, OUT), (23040, 1024, 1, 1, THROUGH),
+    (23041, 1024, 1, 1, OUT), (3000, 32, 2, 0, THROUGH), (61440, 32, 8, 0, THROUGH), (61441, 32, 8, 0, OUT),                       # whole lines
+    (4000, 100, 2, 1, THROUGH), (21000, 100, 2, 1, STREAM), (60000, 84, 1, 1, STREAM), (10000, 36, 2, 0, BACK), (30000, 36, 2, 0, STREAM),   # half lines
+    (11000, 137, 2, 1, THROUGH), (62914, 125, 2, 1, THROUGH), (62915, 125, 2, 1, STREAM), (31457, 125, 4, 1, THROUGH), (31458, 125, 4, 1, BACK),
+    (2000, 125, 6, 1, THROUGH), (4000, 125, 6, 1, BACK), (21000, 125, 8, 1, BACK),                                                 # others, by wavefront
+    (6000, 17, 3, 0, BACK), (32000, 65, 1, 0, BACK), (33000, 65, 1, 0, STREAM), (120989, 65, 2, 0, BACK), (120990, 65, 2, 0, STREAM)]   # flat
+# (tokens, chunks, choices, rows per expert of 16, by wavefront, how rows are stored, whether padding streams)
+PADDING_SHAPES = [
+    (2000, 64, 2, 500, 1, THROUGH, 0), (9000, 128, 1, 2200, 1, THROUGH, 0), (20000, 128, 1, 2200, 1, THROUGH, 1), (9000, 128, 2, 3300, 1, THROUGH, 1),
+    (70000, 128, 1, 4500, 1, OUT, 1), (16000, 128, 8, 9000, 1, OUT, 1), (9000, 125, 2, 2300, 1, THROUGH, 1), (8000, 125, 6, 3300, 1, BACK, 1),
+    (70000, 125, 1, 4500, 1, STREAM, 1), (20000, 36, 2, 2600, 0, THROUGH, 0), (16000, 132, 4, 4100, 1, STREAM, 1), (1000, 8, 2, 200, 0, BACK, 0),
+    (20000, 16, 2, 2600, 0, THROUGH, 0), (60000, 32, 2, 8000, 0, BACK, 0), (140000, 32, 2, 18000, 0, OUT, 1), (40000, 36, 2, 5100, 0, STREAM, 0)]
+
+
+@pytest.mark.parametrize("S,chunks,k", [s[:3] for s in STORE_SHAPES])
 def test_store_policies(T, S, chunks, k):
-    """Rows written with every cache policy, on both sides of the sizes where one takes over from another: rows of
-    whole lines, half lines and others, small buffers, buffers of the size of the last-level cache, larger ones."""
+    """Rows scattered with every cache policy, on both sides of the sizes where one takes over from another, and what
+    the other movers make of them."""
     g = torch.Generator(device="cuda").manual_seed(S + chunks)
     x = torch.randint(-32768, 32767, (S, chunks * 8), generator=g, device="cuda", dtype=torch.int16).view(torch.bfloat16)
     N = 16
@@ -229,9 +244,9 @@ def test_store_policies(T, S, chunks, k):
     assert torch.equal(back[:R], rows[:R])
 
 
-@pytest.mark.parametrize("S,d,k,C", [(2000, 512, 2, 500), (9000, 1024, 1, 2100), (9000, 1000, 2, 2200)])
+@pytest.mark.parametrize("S,d,k,C", [(s[0], s[1] * 8, s[2], s[3]) for s in PADDING_SHAPES])
 def test_padding_policies(T, S, d, k, C):
-    """Unused rows of the fixed-size layout are cleared whatever the size of the buffer."""
+    """Rows of the fixed-size layout with every policy; unused rows are cleared whatever the size of the buffer."""
     g = torch.Generator(device="cuda").manual_seed(S + d)
     x = torch.randn((S, d), generator=g, device="cuda").bfloat16()
     N = 16

@@ -200,3 +200,23 @@ def test_policies_of_the_scatter_that_sums_the_table(rules, units, U, by_wave):
                 for lines in base:
                     for gate, padded in ((1, 0), (0, 0), (0, 1)):
                         assert rules.scatter(base[lines], S * k, cpr, k, by_wave, gate, padded) in there, (k, cpr, S, lines, gate, padded)
+
+
+def test_gpu_tests_reach_every_policy(rules):
+    """The shapes at which the GPU tests move rows are stored as they say, in every way there is."""
+    from test_gpu_row_movers import PADDING_SHAPES, STORE_SHAPES
+
+    for S, cpr, k, by_wave, policy in STORE_SHAPES:
+        assert rules.scatter(1 << 20, S * k, cpr, k, by_wave, 0, 0) == policy, (S, cpr, k)
+    for S, cpr, k, C, by_wave, policy, fill in PADDING_SHAPES:
+        assert rules.scatter(1 << 20, min(S * k, 16 * C), cpr, k, by_wave, 0, 1) == policy, (S, cpr, k, C)
+        assert rules.fill(16 * C, min(S * k, 16 * C), cpr) == fill, (S, cpr, k, C)
+    for shapes, at in ((STORE_SHAPES, 3), (PADDING_SHAPES, 4)):
+        for by_wave in (0, 1):
+            assert {s[at + 1] for s in shapes if s[at] == by_wave} == {BACK, STREAM, THROUGH, OUT}
+    for call, seen in (("combine", {OUT, STREAM}), ("combine_bwd", {BACK, STREAM, THROUGH}), ("regroup", {BACK, STREAM, THROUGH})):
+        got = set()
+        for S, cpr, k, by_wave, _ in STORE_SHAPES:
+            got.add({"combine": lambda: rules.combine(1 << 20, S, cpr, k, by_wave), "combine_bwd": lambda: rules.combine_bwd(1 << 20, S, cpr, k),
+                     "regroup": lambda: rules.regroup(1 << 20, S * k, cpr)}[call]())
+        assert got == seen, call
