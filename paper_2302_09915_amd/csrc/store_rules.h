@@ -51,11 +51,12 @@ inline RowLines row_lines(const void* base, int cpr) {
 //    112.0 / 115.0, 45284 x 2304, two (199) - / 127.5 / 130.4, 13248 x 2960, eight (299) 144.6 / 139.0 / -; 5333 x 4 KiB, two,
 //    three of four rows padding (42) 55.6 / 62.4 / 55.4, 7245 x 2304, two, as many (32) 44.1 / 49.7 / 43.7, 1920 x 7984, eight (117) 79.4 / 87.7 /
 //    82.0), and flat rows go through L2 from 4 to 24 MiB (3712 x 512, eight (14) 24.9 / 22.5 / 22.4, 12822 x 384, two
-//    20.2 / - / 19.1, 7552 x 416, four (12) 19.9 / 18.1 / 18.3; 320 x 512, eight (1) 15.7 / - / 16.5, 13376 x 256, eight (26) 27.8 / - / 29.0, 30531 x 512, two (30) 31.3 / - / 31.9).
+//    20.2 / - / 19.1, 7552 x 416, four (12) 19.9 / 18.1 / 18.3, those that share lines with more than four choices from 12 MiB: 2336 x
+//    880, six (15) 22.1 / 20.1 / 20.7, but 4008 x 272, six (6) 18.4 / - / 19.1; 320 x 512, eight (1) 15.7 / - / 16.5, 13376 x 256, eight (26) 27.8 / - / 29.0, 30531 x 512, two (30) 31.3 / - / 31.9).
 inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
     const int64_t bytes = rows * cpr * 16, MiB = (int64_t)1 << 20;
     const bool leave = padded && bytes > 128 * MiB;
-    if (padded && !by_wave && bytes <= 24 * MiB) return bytes < 4 * MiB ? kStoreBack : kStoreThrough;
+    if (padded && !by_wave && bytes <= 24 * MiB) return bytes < (k > 4 && lines == kSharedLines ? 12 : 4) * MiB ? kStoreBack : kStoreThrough;
     if (lines == kWholeLines) {
         if (!by_wave && (padded ? !leave : behind_gate && bytes < 16 * MiB)) return kStoreBack;
         return leave || bytes > (k == 1 ? 360 : 240) * MiB ? kStoreOut : kStoreThrough;

@@ -156,7 +156,7 @@ def test_scattered_rows(rules, mib, cpr, k, by_wave, behind_gate, policy):
     (3, 32, 8, 0, BACK), (4, 32, 8, 0, THROUGH), (24, 32, 2, 0, THROUGH), (25, 32, 2, 0, BACK), (128, 32, 8, 0, BACK), (129, 32, 8, 0, OUT),
     (3, 256, 2, 1, THROUGH), (128, 256, 2, 1, THROUGH), (129, 256, 2, 1, OUT), (129, 256, 1, 1, OUT), (17, 132, 2, 1, STREAM), (300, 300, 6, 1, STREAM),
     (24, 125, 8, 1, THROUGH), (25, 125, 8, 1, BACK), (128, 125, 8, 1, BACK), (129, 125, 8, 1, STREAM), (128, 125, 2, 1, THROUGH), (129, 125, 4, 1, STREAM),
-    (3, 53, 2, 0, BACK), (5, 53, 2, 0, THROUGH), (24, 53, 8, 0, THROUGH), (25, 53, 8, 0, BACK), (51, 53, 1, 0, BACK), (300, 45, 2, 0, BACK),
+    (3, 53, 2, 0, BACK), (5, 53, 4, 0, THROUGH), (11, 53, 6, 0, BACK), (13, 53, 6, 0, THROUGH), (5, 48, 6, 0, THROUGH), (24, 53, 8, 0, THROUGH), (25, 53, 8, 0, BACK), (51, 53, 1, 0, BACK), (300, 45, 2, 0, BACK),
     (20, 36, 2, 0, THROUGH), (25, 36, 2, 0, STREAM)])
 def test_rows_of_the_fixed_size_layout(rules, mib, cpr, k, by_wave, policy):
     """The rows go by their own size, whatever the padding between them."""
