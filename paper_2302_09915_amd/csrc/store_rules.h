@@ -43,16 +43,16 @@ inline RowLines row_lines(const void* base, int cpr) {
 //    and for large buffers of three and more from L2, which merges their lines (2496 x 2032, six 26.1 / 27.4 / 26.8, 11320 x 6368,
 //    eight 273 / 287 / 286, 42567 x 4208, four (683 MiB) 384 / 397 / 390; 15440 x 5648, three, a training pass 337 / 349 / 336);
 //  - other flat ones from L2 (57974 x 1040, four 111 / 136 / 121; 115651 x 272, two 61 / 65 / 65; 131072 x 880, eight (880 MiB) 422 / 441 /
-//    453), streaming beyond 32 MiB with one choice (86016 x 544 57.7 / 54.3 /
-//    58.0, 131072 x 720 108.1 / 100.1 / 108.2) and beyond 240 with two (64384 x 2096 155.6 / 142.1 / -; 126256 x 688 (166 MiB) 133.9 / 141.2 /
-//    143.3).
+//    453), streaming beyond 32 MiB with one choice (86016 x 544 57.7 / 54.3 / 58.0, 131072 x 720 108.1 / 100.1 / 108.2)
+//    and beyond 240 with two (64384 x 2096 155.6 / 142.1 / -; 126256 x 688 (166 MiB) 133.9 / 141.2 / 143.3);
 //  - the fixed-size layout goes by the rows that pairs can name (the padding between them is stored by fill_streams), which
 //    nobody reads in the calls that were timed: beyond 128 MiB they leave the last-level cache to others (10880 x 6400, three (199 MiB) - /
 //    112.0 / 115.0, 45284 x 2304, two (199) - / 127.5 / 130.4, 13248 x 2960, eight (299) 144.6 / 139.0 / -; 5333 x 4 KiB, two,
 //    three of four rows padding (42) 55.6 / 62.4 / 55.4, 7245 x 2304, two, as many (32) 44.1 / 49.7 / 43.7, 1920 x 7984, eight (117) 79.4 / 87.7 /
 //    82.0), and flat rows go through L2 from 4 to 24 MiB (3712 x 512, eight (14) 24.9 / 22.5 / 22.4, 12822 x 384, two
 //    20.2 / - / 19.1, 7552 x 416, four (12) 19.9 / 18.1 / 18.3, those that share lines with more than four choices from 12 MiB: 2336 x
-//    880, six (15) 22.1 / 20.1 / 20.7, but 4008 x 272, six (6) 18.4 / - / 19.1; 320 x 512, eight (1) 15.7 / - / 16.5, 13376 x 256, eight (26) 27.8 / - / 29.0, 30531 x 512, two (30) 31.3 / - / 31.9).
+//    880, six (15) 22.1 / 20.1 / 20.7, but 4008 x 272, six (6) 18.4 / - / 19.1; 320 x 512, eight (1) 15.7 / - / 16.5, 13376 x 256, eight (26) 27.8 / - /
+//    29.0, 30531 x 512, two (30) 31.3 / - / 31.9).
 inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, bool by_wave, bool behind_gate, bool padded) {
     const int64_t bytes = rows * cpr * 16, MiB = (int64_t)1 << 20;
     const bool leave = padded && bytes > 128 * MiB;
