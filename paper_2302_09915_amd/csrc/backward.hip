@@ -5,6 +5,8 @@
 //   tamoe_combine_bwd  transpose of the combine: d_recv (weighted scatter of dy) and d_topk_w
 //                      (one dot product per kept pair)
 // (tamoe_dispatch_bwd, the transpose of the scatter, is the combine kernel with unit weights.)
+#include <type_traits>
+
 #include "chunk.h"
 #include "internal.h"
 
@@ -25,7 +27,7 @@ constexpr int kThreads = 256;
 // ST: how d_recv is stored (combine_bwd_store).
 constexpr int kRowWaves = 16;
 
-template <int DT, int KK, int ST>
+template <int DT, int KK, int ST, int LD>
 __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
     const vec16* __restrict__ dy, const vec16* __restrict__ recv, int64_t K_rows, const int32_t* __restrict__ slot,
     const float* __restrict__ topk_w, int64_t S, int k_arg, int cpr, int row_waves, vec16* __restrict__ d_recv,
@@ -57,10 +59,10 @@ __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
     const RowBuffer gy(dy + (size_t)t * cpr, cpr, live);
     for (int seg = seg0; seg * 64 < cpr; seg += row_waves) {
         const int c = seg * 64 + lane;
-        const vec16 g = gy.load(c);
+        const vec16 g = gy.template load<LD>(c);
         vec16 r[KM];
 #pragma unroll
-        for (int j = 0; j < KM; ++j) r[j] = RowBuffer(recv + (size_t)s[j] * cpr, cpr, use[j]).load(c);
+        for (int j = 0; j < KM; ++j) r[j] = RowBuffer(recv + (size_t)s[j] * cpr, cpr, use[j]).template load<LD>(c);
 #pragma unroll
         for (int j = 0; j < KM; ++j) {
             dot[j] = chunk_dot<DT>(g, r[j], dot[j]);
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void combine_bwd_kernel(
 
 // Other rows (fewer than 64 chunks): a row takes G consecutive lanes (the power of two that holds it).  More
 // than four choices (KK == 0) are taken four at a time, as in combine_flat_kernel.
-template <int DT, int KK, int ST>
+template <int DT, int KK, int ST, int LD>
 __global__ __launch_bounds__(kThreads) void combine_bwd_short_kernel(
     const vec16* __restrict__ dy, const vec16* __restrict__ recv, int64_t K_rows, const int32_t* __restrict__ slot,
     const float* __restrict__ topk_w, int64_t S, int k_arg, int cpr, int g_shift, vec16* __restrict__ d_recv,
@@ -103,7 +105,7 @@ __global__ __launch_bounds__(kThreads) void combine_bwd_short_kernel(
     const int t = (int)(live ? i >> g_shift : S - 1);
     const bool inside = live && c < cpr;
     vec16 g = vec16{0u, 0u, 0u, 0u};
-    if (inside) g = __builtin_nontemporal_load(dy + (size_t)t * cpr + c);
+    if (inside) g = load_chunk<LD>(dy + (size_t)t * cpr + c);
 #pragma unroll 1
     for (int j0 = 0; j0 < k; j0 += KG) {
         int32_t s[KG];
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(kThreads) void combine_bwd_short_kernel(
         for (int j = 0; j < KG; ++j) {
             s[j] = (inside && s[j] >= 0 && (int64_t)s[j] < K_rows) ? s[j] : -1;
             r[j] = vec16{0u, 0u, 0u, 0u};
-            if (s[j] >= 0) r[j] = __builtin_nontemporal_load(recv + (size_t)s[j] * cpr + c);
+            if (s[j] >= 0) r[j] = load_chunk<LD>(recv + (size_t)s[j] * cpr + c);
         }
 #pragma unroll
         for (int j = 0; j < KG; ++j) {
@@ -279,7 +281,7 @@ static void launch_gate_bwd(const float* logits, const int32_t* idx, const float
 #undef TAMOE_GATE_BWD
 }
 
-template <int DT, int KK, int ST>
+template <int DT, int KK, int ST, int LD>
 static void launch_combine_bwd_s(const vec16* dy, const vec16* recv, int64_t K_rows, const int32_t* slot,
                                  const float* topk_w, int64_t S, int k, int cpr, vec16* d_recv, float* d_w,
                                  hipStream_t st) {
@@ -287,12 +289,13 @@ static void launch_combine_bwd_s(const vec16* dy, const vec16* recv, int64_t K_r
         const int rw = row_waves(cpr) < kRowWaves ? row_waves(cpr) : kRowWaves;
         const int rows = rw < 4 ? 4 / rw : 1;
         const dim3 grid = grid_of(ceil_div(S, rows), rows * rw * 64), block(rows * rw * 64);
-        combine_bwd_kernel<DT, KK, ST><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, rw, d_recv, d_w);
+        combine_bwd_kernel<DT, KK, ST, LD><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, rw, d_recv, d_w);
     } else {
         int g_shift = 0;
         while ((1 << g_shift) < cpr) ++g_shift;
         const dim3 grid = grid_of(ceil_div(S << g_shift, kThreads), kThreads), block(kThreads);
-        combine_bwd_short_kernel<DT, KK, ST><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, g_shift, d_recv, d_w);
+        combine_bwd_short_kernel<DT, KK, ST, LD>
+            <<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, g_shift, d_recv, d_w);
     }
 }
 
@@ -301,12 +304,15 @@ static void launch_combine_bwd_k(const vec16* dy, const vec16* recv, int64_t K_r
                                  const float* topk_w, int64_t S, int k, int cpr, vec16* d_recv, float* d_w,
                                  hipStream_t st) {
     const StorePolicy policy = combine_bwd_store(row_lines(d_recv, cpr), S, cpr, k);
-    if (policy == kStoreThrough)
-        launch_combine_bwd_s<DT, KK, kStoreThrough>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
-    else if (policy == kStoreStream)
-        launch_combine_bwd_s<DT, KK, kStoreStream>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
-    else
-        launch_combine_bwd_s<DT, KK, kStoreBack>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
+    const bool keep = combine_bwd_load(row_lines(recv, cpr), S, cpr, k) == kLoadKeep;
+    const auto launch = [&](auto st_c) {
+        constexpr int ST = decltype(st_c)::value;
+        if (keep) launch_combine_bwd_s<DT, KK, ST, kLoadKeep>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
+        else launch_combine_bwd_s<DT, KK, ST, kLoadStream>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
+    };
+    if (policy == kStoreThrough) launch(std::integral_constant<int, kStoreThrough>{});
+    else if (policy == kStoreBack) launch(std::integral_constant<int, kStoreBack>{});
+    else if constexpr (KK == 1) launch(std::integral_constant<int, kStoreStream>{});   // one choice alone
 }
 
 template <int DT>

@@ -17,7 +17,7 @@ constexpr int kThreads = 256;
 // UNITW: every weight is 1 (the transpose of the scatter: dx[t] = sum of the rows its slots name).
 // Rows by whole wavefronts (combine_by_wave), U segments of 64 chunks each: all slots, weights and rows of
 // a token are requested without a branch between them.
-template <int DT, int KK, int U, bool UNITW, int ST>
+template <int DT, int KK, int U, bool UNITW, int ST, int LD>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restrict__ recv, int64_t K_rows,
                                                            const int32_t* __restrict__ slot,
                                                            const float* __restrict__ topk_w, int64_t S, int k_arg,
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const vec16* __restri
 #pragma unroll
         for (int j = 0; j < KM; ++j) {
             const bool use = (KK > 0 || j < k) && (uint32_t)sl[u][j] < (uint64_t)K_rows;   // a dropped pair is -1
-            v[u][j] = RowBuffer(recv + (size_t)(use ? sl[u][j] : 0) * cpr, cpr, use).load(col[u]);
+            v[u][j] = RowBuffer(recv + (size_t)(use ? sl[u][j] : 0) * cpr, cpr, use).template load<LD>(col[u]);
             wgt[u][j] = use ? wgt[u][j] : 0.f;   // adds 0 * 0: the same bits as leaving it out
         }
 #pragma unroll
@@ -76,7 +76,7 @@ static bool combine_by_wave(int64_t S, int cpr, int k) {
 // Other rows: chunks flat over the lanes.  More than four choices (KK == 0) are taken four at a time: loads
 // under a condition per lane hold registers across each other, and eight of them left room for one
 // wavefront per SIMD in fp32.
-template <int DT, int KK, int U, bool UNITW, int ST>
+template <int DT, int KK, int U, bool UNITW, int ST, int LD>
 __global__ __launch_bounds__(kThreads) void combine_flat_kernel(const vec16* __restrict__ recv, int64_t K_rows,
                                                                 const int32_t* __restrict__ slot,
                                                                 const float* __restrict__ topk_w, int64_t total_chunks,
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kThreads) void combine_flat_kernel(const vec16* __r
                 const bool use = sl[u][j] >= 0 && (int64_t)sl[u][j] < K_rows;
                 wgt[u][j] = use ? wgt[u][j] : 0.f;
                 v[u][j] = vec16{0u, 0u, 0u, 0u};
-                if (use) v[u][j] = __builtin_nontemporal_load(recv + (size_t)sl[u][j] * cpr + col[u]);
+                if (use) v[u][j] = load_chunk<LD>(recv + (size_t)sl[u][j] * cpr + col[u]);
             }
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void combine_flat_kernel(const vec16* __r
     }
 }
 
-template <int DT, int KK, int U, bool UNITW, int ST>
+template <int DT, int KK, int U, bool UNITW, int ST, int LD>
 static void launch_combine_s(const void* recv, int64_t K_rows, const int32_t* slot, const float* topk_w, int64_t S,
                              int k, int cpr, void* y, hipStream_t st) {
     const vec16* r = static_cast<const vec16*>(recv);
@@ -137,12 +137,12 @@ static void launch_combine_s(const void* recv, int64_t K_rows, const int32_t* sl
     if (combine_by_wave(S, cpr, k)) {
         const int wpr = row_waves(cpr);
         const dim3 grid = grid_of(ceil_div(S * (int64_t)wpr, kThreads / 64 * U), kThreads), block(kThreads);
-        combine_kernel<DT, KK, U, UNITW, ST>
+        combine_kernel<DT, KK, U, UNITW, ST, LD>
             <<<grid, block, 0, st>>>(r, K_rows, slot, topk_w, S, k, cpr, wpr, pow2_shift(wpr), out);
     } else {
         const int64_t total = S * (int64_t)cpr;
         const dim3 grid = grid_of(ceil_div(total, kThreads * U), kThreads), block(kThreads);
-        combine_flat_kernel<DT, KK, U, UNITW, ST>
+        combine_flat_kernel<DT, KK, U, UNITW, ST, LD>
             <<<grid, block, 0, st>>>(r, K_rows, slot, topk_w, total, k, cpr, pow2_shift(cpr), out);
     }
 }
@@ -150,10 +150,20 @@ static void launch_combine_s(const void* recv, int64_t K_rows, const int32_t* sl
 template <int DT, int KK, int U, bool UNITW>
 static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* slot, const float* topk_w, int64_t S,
                              int k, int cpr, void* y, hipStream_t st) {
-    if (combine_store(row_lines(y, cpr), S, cpr, k, combine_by_wave(S, cpr, k)) == kStoreOut)
-        launch_combine_s<DT, KK, U, UNITW, kStoreOut>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
-    else
-        launch_combine_s<DT, KK, U, UNITW, kStoreStream>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
+    const bool by_wave = combine_by_wave(S, cpr, k);
+    const bool out = combine_store(row_lines(y, cpr), S, cpr, k, by_wave) == kStoreOut;
+    if constexpr (UNITW) {
+        // what dispatch_bwd_load keeps has two choices at most and shares lines, which combine_store streams
+        if constexpr (KK == 1 || KK == 2) {
+            if (dispatch_bwd_load(row_lines(recv, cpr), S, cpr, k, by_wave) == kLoadKeep && !out)
+                return launch_combine_s<DT, KK, U, true, kStoreStream, kLoadKeep>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
+        }
+    } else if (combine_load(S, cpr, k) == kLoadKeep) {
+        if (out) return launch_combine_s<DT, KK, U, false, kStoreOut, kLoadKeep>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
+        return launch_combine_s<DT, KK, U, false, kStoreStream, kLoadKeep>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
+    }
+    if (out) launch_combine_s<DT, KK, U, UNITW, kStoreOut, kLoadStream>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
+    else launch_combine_s<DT, KK, U, UNITW, kStoreStream, kLoadStream>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
 }
 
 template <int DT, bool UNITW>

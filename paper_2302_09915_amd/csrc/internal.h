@@ -175,6 +175,13 @@ __device__ __forceinline__ void store_chunk(vec16* p, vec16 v) {
     else *p = v;
 }
 
+// A chunk by address, with one of the policies.
+template <int LD>
+__device__ __forceinline__ vec16 load_chunk(const vec16* p) {
+    if constexpr (LD == kLoadStream) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
 // A row as a buffer resource: the hardware returns zeros for a load and drops a store outside its `cpr`
 // chunks, and a row that is not there (present == false) has none.  Lanes beyond the end of a row and
 // dropped pairs need no branch then, and cost no memory access.  With a branch around each load the k
@@ -184,8 +191,9 @@ struct RowBuffer {
     __amdgpu_buffer_rsrc_t rsrc;
     __device__ __forceinline__ RowBuffer(const void* row, int cpr, bool present)
         : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, present ? cpr * 16 : 0, 0x00020000)) {}
-    __device__ __forceinline__ vec16 load(int col) const {                     // streaming
-        return __builtin_bit_cast(vec16, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)((uint32_t)col * 16u), 0, 2));
+    template <int LD>
+    __device__ __forceinline__ vec16 load(int col) const {
+        return __builtin_bit_cast(vec16, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)((uint32_t)col * 16u), 0, LD));
     }
     template <int ST>
     __device__ __forceinline__ void store(int col, vec16 v) const {

@@ -71,7 +71,7 @@ __device__ __forceinline__ void offset_tables(const Segments& sg, bool to_expert
 
 // Rows by whole wavefronts, U segments of 64 chunks each; a row's segment of the table is found
 // by counting the offsets that do not exceed it (one ballot per 64).
-template <int U, int ST>
+template <int U, int ST, int LD>
 __global__ __launch_bounds__(kThreads) void regroup_copy_kernel(const vec16* __restrict__ in, const Segments sg,
                                                                 int64_t cap_rows, int cpr, int wpr, int shift,
                                                                 int to_expert_major, vec16* __restrict__ out,
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kThreads) void regroup_copy_kernel(const vec16* __r
             drow[u] = __builtin_amdgcn_readfirstlane(to_off[other_order(sg, g, to_expert_major)] + (row - from_off[g]));
         }
         if (drow[u] >= cap_rows) drow[u] = -1;
-        v[u] = RowBuffer(in + (size_t)(drow[u] >= 0 ? row : 0) * cpr, cpr, drow[u] >= 0).load(col[u]);
+        v[u] = RowBuffer(in + (size_t)(drow[u] >= 0 ? row : 0) * cpr, cpr, drow[u] >= 0).template load<LD>(col[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kThreads) void regroup_copy_kernel(const vec16* __r
 }
 
 // Other rows: chunks flat over the lanes, a chunk's segment by binary search over the offsets in LDS.
-template <int U, int ST>
+template <int U, int ST, int LD>
 __global__ __launch_bounds__(kThreads) void regroup_flat_kernel(const vec16* __restrict__ in, const Segments sg,
                                                                 int64_t cap_rows, int cpr, int shift, int to_expert_major,
                                                                 vec16* __restrict__ out,
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kThreads) void regroup_flat_kernel(const vec16* __r
             const int64_t drow = (int64_t)to_off[other_order(sg, lo, to_expert_major)] + (row - from_off[lo]);
             if (drow < cap_rows) {
                 dst[u] = drow * cpr + col;
-                v[u] = __builtin_nontemporal_load(in + c);
+                v[u] = load_chunk<LD>(in + c);
             }
         }
     }
@@ -192,18 +192,19 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
     vec16* dst = static_cast<vec16*>(out);
     const dim3 grid = grid_of(blocks, kThreads), block(kThreads);
     TraceScope tr("regroup_copy_kernel", st);
-#define TAMOE_REGROUP(ST)                                                                                          \
+#define TAMOE_REGROUP(ST, LD)                                                                                      \
     do {                                                                                                           \
         if (rowu)                                                                                                  \
-            regroup_copy_kernel<U, ST>    <<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, wpr, pow2_shift(wpr),    \
+            regroup_copy_kernel<U, ST, LD><<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, wpr, pow2_shift(wpr),    \
                                                                    to_expert_major, dst, expert_offset);           \
         else                                                                                                       \
-            regroup_flat_kernel<U, ST>    <<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, pow2_shift(cpr),         \
+            regroup_flat_kernel<U, ST, LD><<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, pow2_shift(cpr),         \
                                                                    to_expert_major, dst, expert_offset);           \
     } while (0)
-    if (policy == kStoreStream) TAMOE_REGROUP(kStoreStream);
-    else if (policy == kStoreThrough) TAMOE_REGROUP(kStoreThrough);
-    else TAMOE_REGROUP(kStoreBack);
+    if (policy == kStoreStream) TAMOE_REGROUP(kStoreStream, kLoadStream);
+    else if (policy == kStoreBack) TAMOE_REGROUP(kStoreBack, kLoadStream);
+    else if (regroup_load(cap_rows, cpr) == kLoadKeep) TAMOE_REGROUP(kStoreThrough, kLoadKeep);
+    else TAMOE_REGROUP(kStoreThrough, kLoadStream);
 #undef TAMOE_REGROUP
     return check_launch(fn, "regroup_copy_kernel");
 }

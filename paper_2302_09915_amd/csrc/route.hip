@@ -487,7 +487,7 @@ __device__ __forceinline__ void clear_unused(const RouteArgs& a, int f, const in
 // (What the copying workgroups read comes as arguments of its own: only a pointer that is declared not to
 // alias is read through the scalar unit.  cap is never NULL here: without capacities it is the table, whose
 // entries are then not looked at, so that no branch stands between the look-ups.)
-template <int KK, int U, bool ROWU, int ST>
+template <int KK, int U, bool ROWU, int ST, int LD>
 __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
     const vec16* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_pos,
     const int32_t* __restrict__ tile_table, const int32_t* __restrict__ cap, int32_t* __restrict__ slot,
@@ -571,10 +571,10 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         if constexpr (ROWU) {
-            v[u] = RowBuffer(x + (size_t)tok[u] * cpr, cpr, live[u]).load(col[u]);
+            v[u] = RowBuffer(x + (size_t)tok[u] * cpr, cpr, live[u]).template load<LD>(col[u]);
         } else {
             v[u] = vec16{0u, 0u, 0u, 0u};
-            if (live[u]) v[u] = __builtin_nontemporal_load(x + (size_t)tok[u] * cpr + col[u]);
+            if (live[u]) v[u] = load_chunk<LD>(x + (size_t)tok[u] * cpr + col[u]);
         }
     }
     // every lane is here: the scan and, without ROWU, the lane exchange of offset_of need them all
@@ -602,7 +602,7 @@ __global__ __launch_bounds__(kCopyThreads) void route_copy_kernel(
 // registers: two workgroups share a compute unit.
 // ROWU: a lane has one of the wavefront's pairs (unit, choice) and works out its slot; the stores read the slots from
 // the lanes.
-template <int TH, int KK, int U, bool ROWU, int ST, int B>
+template <int TH, int KK, int U, bool ROWU, int ST, int LD, int B>
 __global__ __launch_bounds__(TH, 4) void route_table_kernel(
     const vec16* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_pos,
     const uint16_t* __restrict__ counts, int32_t* __restrict__ slot, vec16* __restrict__ send, const RouteArgs a) {
@@ -659,7 +659,7 @@ __global__ __launch_bounds__(TH, 4) void route_table_kernel(
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const bool in = tok[u] < a.S;
-                v[u] = RowBuffer(x + (size_t)(in ? tok[u] : 0) * cpr, cpr, in).load(seg[u] * 64 + lane);
+                v[u] = RowBuffer(x + (size_t)(in ? tok[u] : 0) * cpr, cpr, in).template load<LD>(seg[u] * 64 + lane);
             }
         });
         const WaveOffsets wo = wave_offsets(load_kept(t.kept, N));
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(TH, 4) void route_table_kernel(
         }
         scan_counts<TH, KK, B>(a, blk0, t, [&] {
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(x + (size_t)tok[u] * cpr + col[u]);
+            for (int u = 0; u < U; ++u) v[u] = load_chunk<LD>(x + (size_t)tok[u] * cpr + col[u]);
         });
         const WaveOffsets wo = wave_offsets(load_kept(t.kept, N));
 #pragma unroll
@@ -758,19 +758,25 @@ static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
     constexpr int U = copy_units(KK);
     const dim3 grid = grid_of(1 + (int64_t)a.copy_blocks + (int64_t)a.N * a.fill_parts, kCopyThreads), block(kCopyThreads);
     const int32_t* caps = a.cap != nullptr ? a.cap : a.table;   // N entries at least
-#define TAMOE_ROUTE_COPY(RU, ST)                                                          \
-    route_copy_kernel<KK, U, RU, ST><<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
-    const bool rowu = scatter_by_wave(a.S, a.cpr, a.k);
-    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, rowu, a.m_part != nullptr, a.pad_C > 0);
-#define TAMOE_ROUTE_COPY_ST(ST)                                                          \
-    do {                                                                                 \
-        if (rowu) TAMOE_ROUTE_COPY(true, ST); else TAMOE_ROUTE_COPY(false, ST);          \
+    const bool rowu = scatter_by_wave(a.S, a.cpr, a.k), behind_gate = a.m_part != nullptr;
+    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, rowu, behind_gate, a.pad_C > 0);
+    const bool keep = scatter_load(a.S, rows_sent(a), a.cpr, behind_gate) == kLoadKeep;
+#define TAMOE_ROUTE_COPY(RU, ST, LD)                                                          \
+    route_copy_kernel<KK, U, RU, ST, LD><<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
+#define TAMOE_ROUTE_COPY_LD(ST, LD)                                                          \
+    do {                                                                                     \
+        if (rowu) TAMOE_ROUTE_COPY(true, ST, LD); else TAMOE_ROUTE_COPY(false, ST, LD);      \
     } while (0)
-    if (policy == kStoreStream) TAMOE_ROUTE_COPY_ST(kStoreStream);
-    else if (policy == kStoreOut) TAMOE_ROUTE_COPY_ST(kStoreOut);
+#define TAMOE_ROUTE_COPY_ST(ST)                                                              \
+    do {                                                                                     \
+        if (keep) TAMOE_ROUTE_COPY_LD(ST, kLoadKeep); else TAMOE_ROUTE_COPY_LD(ST, kLoadStream); \
+    } while (0)
+    if (policy == kStoreOut) TAMOE_ROUTE_COPY_LD(kStoreOut, kLoadStream);   // more than scatter_load keeps
+    else if (policy == kStoreStream) TAMOE_ROUTE_COPY_ST(kStoreStream);
     else if (policy == kStoreThrough) TAMOE_ROUTE_COPY_ST(kStoreThrough);
     else TAMOE_ROUTE_COPY_ST(kStoreBack);
 #undef TAMOE_ROUTE_COPY_ST
+#undef TAMOE_ROUTE_COPY_LD
 #undef TAMOE_ROUTE_COPY
 }
 
@@ -813,18 +819,27 @@ template <int TH, int KK, int U, bool ROWU>
 static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
     const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(TH);
     const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
+    constexpr int kX = (U == 8 ? 64 : 4 * U) / (TH == kTableThreads ? 1 : 2);   // MiB of x
+    constexpr int kMiB = kX * (KK > 0 ? KK : TAMOE_MAX_K);                       // of rows
+    constexpr bool kKeepsAll = kX + kMiB <= kKeepGiven;
+    const bool keep = kKeepsAll || scatter_load(a.S, rows_sent(a), a.cpr, a.m_part != nullptr) == kLoadKeep;
     // the smallest tables in a kernel that is shorter by seven requests and their sums
     const bool one = U == 1 && (int64_t)a.n_blocks * (a.stride / 8) <= TH;
-    const auto launch = [&](auto st_c) {
-        constexpr int ST = decltype(st_c)::value;
+    const auto launch_ld = [&](auto st_c, auto ld_c) {
+        constexpr int ST = decltype(st_c)::value, LD = decltype(ld_c)::value;
         if (one)
-            route_table_kernel<TH, KK, U, ROWU, ST, U == 1 ? 1 : kTableBatch>
+            route_table_kernel<TH, KK, U, ROWU, ST, LD, U == 1 ? 1 : kTableBatch>
                 <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
         else
-            route_table_kernel<TH, KK, U, ROWU, ST, kTableBatch>
+            route_table_kernel<TH, KK, U, ROWU, ST, LD, kTableBatch>
                 <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
     };
-    constexpr int kMiB = (U == 8 ? 64 : 4 * U) / (TH == kTableThreads ? 1 : 2) * (KK > 0 ? KK : TAMOE_MAX_K);   // of rows
+    const auto launch = [&](auto st_c) {
+        constexpr bool kOut = decltype(st_c)::value == kStoreOut;   // more than scatter_load keeps
+        if constexpr (kOut || !kKeepsAll)
+            if (kOut || !keep) return launch_ld(st_c, std::integral_constant<int, kLoadStream>{});
+        if constexpr (!kOut) launch_ld(st_c, std::integral_constant<int, kLoadKeep>{});
+    };
     if constexpr (kMiB > 16)   // half lines
         if (policy == kStoreStream) return launch(std::integral_constant<int, kStoreStream>{});
     if constexpr (!ROWU || (KK == 0 && kMiB > 24) || (KK == 4 && kMiB > 240))

@@ -1,4 +1,4 @@
-// How the row movers store their rows: a cache policy by size, by how rows lie on lines and by what comes next.  Host
+// How the row movers store their rows, and how they load them: a cache policy by size, by how rows lie on lines and by what comes next.  Host
 // code without HIP: the rules can be compiled and looked at anywhere.
 #pragma once
 
@@ -14,6 +14,12 @@ enum StorePolicy {
     kStoreStream = 2,    // nt: the last-level cache does not keep the line
     kStoreThrough = 16,  // sc1: straight through L2; the last-level cache keeps the line
     kStoreOut = 19       // nt sc1 sc0: straight through L2, not kept
+};
+
+// Cache policies of the row loads.
+enum LoadPolicy {
+    kLoadKeep = 0,    // ordinary
+    kLoadStream = 2   // nt: the caches let go of the line first
 };
 
 // How rows of cpr chunks of 16 bytes that begin at base lie on the lines of 128 bytes.  A line that a row shares with
@@ -68,6 +74,20 @@ inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, b
     return k > 2 ? kStoreBack : kStoreStream;
 }
 
+// Where a mover finds everything it touches in the last-level cache, rows are loaded so that they stay there; beyond, what is read
+// makes room for the rest.  Us of whole calls over the buffers of three layers in turn, with streaming / ordinary loads of the
+// one mover.
+// The scatter, x.  Behind the gate, which has just read x, in forward calls: 34176 x 288 bytes, one choice (19 MiB with the rows) 27.0 /
+// 26.1, 2528 x 7232, eight (24) 42.7 / 39.0, 9486 x 2432, two (66) 41.6 / 39.8, 1007 x 8176, eight (71) 58.9 / 50.6, 15950 x 2432, two
+// (111) 56.7 / 54.8; beyond 128 MiB either way (63985 x 768, two (141) 63.6 / 62.5, 6784 x 7552, two (147) 76.3 / 77.4, 65536 x 8 KiB, two 625
+// / 637).  Of a routing that is given, in the fixed-size layout with ordinary loads of the combine: 39168 x 256, two (27) 24.3 / 22.6, 20098 x
+// 512, three (39) 26.2 / 24.9, 3648 x 4608, two (48) 27.8 / 26.0; streaming ones there: 8926 x 2432, two (62) 34.8 / 36.1, 3693 x 8960, one (63) 38.5 /
+// 41.4, 28736 x 1536, two (126) 59.5 / 62.6.
+constexpr int kKeepBehindGate = 128, kKeepGiven = 48;   // MiB of x and the rows sent
+inline LoadPolicy scatter_load(int64_t S, int64_t rows, int cpr, bool behind_gate) {
+    return (S + rows) * cpr * 16 <= (int64_t)(behind_gate ? kKeepBehindGate : kKeepGiven) << 20 ? kLoadKeep : kLoadStream;
+}
+
 // Padding of the fixed-size layout: zeros stream where they would take the place of its rows in the last-level cache, which is in
 // buffers of more than 96 MiB, and beyond 64 if they are not most of it; elsewhere they are stored as the rows are.  Us of a call
 // streamed / as the rows: 1388 x 3840 bytes, 15 of 16 rows padding (81 MiB) 28.9 / 22.4, 673 x 3872, as many (80) 29.5 / 22.1, 25024 x
@@ -89,6 +109,19 @@ inline StorePolicy combine_store(RowLines lines, int64_t S, int cpr, int k, bool
     return by_wave && (k > 2 || lines == kWholeLines) && S * cpr * 16 <= (int64_t)256 << 20 ? kStoreOut : kStoreStream;
 }
 
+// The combine, the rows it reads (with what it writes): 768 x 7216, two choices (16 MiB) forward 18.6 / 17.5, 1664 x 4912, four (39)
+// forward 34.4 / 32.5, 20098 x 512, three (39) fixed-size layout 26.8 / 24.9; forward 16159 x 1792, two (83) 34.8 / 34.6, 31936 x 640, four (98) 50.6 /
+// 54.6, fixed-size layout 8926 x 2432, two (62) 34.8 / 36.1, 3693 x 8960, one (63) 38.5 / 42.7.
+inline LoadPolicy combine_load(int64_t S, int cpr, int k) {
+    return S * (k + 1) * cpr * 16 <= (int64_t)48 << 20 ? kLoadKeep : kLoadStream;
+}
+// Its transpose reads what combine_bwd has left there either way.  Rows that share lines gain, as the line is wanted again: us of the three
+// backward calls on 16448 x 2224, two (35 MiB of rows per choice) 50.5 / 46.9, 5696 x 15968, one 79.3 / 76.9, 23808 x 3824, two (182 in all) 89.6 /
+// 85.4; but 9168 x 8928, eight (625) 411 / 471, and rows of whole lines 18911 x 1792, three 68.0 / 71.3, 25000 x 1536, two 45.5 / 45.6.
+inline LoadPolicy dispatch_bwd_load(RowLines lines, int64_t S, int cpr, int k, bool by_wave) {
+    return by_wave && k <= 2 && lines == kSharedLines && S * k * cpr * 16 <= (int64_t)192 << 20 ? kLoadKeep : kLoadStream;
+}
+
 // combine_bwd: d_recv goes straight through L2, whose last-level cache keeps what fits of it for the kernel that reads it
 // next, and no dirty line is left for the end of this one.  Us of combine_bwd, dispatch_bwd and gate_bwd, rows with ordinary /
 // streaming / through stores: 58880 x 2 KiB, two choices (combine_bwd and dispatch_bwd) 159 / 194 / 155, 25600 x 8 KiB, two 276 / 304 /
@@ -108,6 +141,14 @@ inline StorePolicy combine_bwd_store(RowLines lines, int64_t S, int cpr, int k) 
     return kStoreThrough;
 }
 
+// combine_bwd, dy and recv (with the rows it writes), us of the three backward calls: 7762 x 768, two (28 MiB) 13.25 / 12.3, 6920 x 512, eight
+// (57) 24.7 / 22.5, 12736 x 1152, two (70) 24.2 / 23.6; beyond 72 MiB either way (31931 x 640, two, 12 experts (97) 34.4 / 32.3, 32448 x 512, two, 128 experts,
+// whose scores take as much again (79) 32.4 / 33.9, 11494 x 2304, two (126) 40.1 / 41.8, 19489 x 2048, four (343) 74.5 / 77.7).  Not short rows
+// that share lines: 59392 x 224, two (63) 30.2 / 31.4.
+inline LoadPolicy combine_bwd_load(RowLines lines, int64_t S, int cpr, int k) {
+    return S * (2 * k + 1) * cpr * 16 <= (int64_t)72 << 20 && (cpr >= 64 || lines != kSharedLines) ? kLoadKeep : kLoadStream;
+}
+
 // The regroup: straight through L2 while the buffer fits the last-level cache, which keeps it for the experts (or the exchange),
 // and streaming beyond; rows that share lines stream earlier.  Small buffers of flat rows are merged in L2 instead.  Us of one call
 // with ordinary / streaming / through stores: 20480 x 2 KiB 28.3 / 30.1 / 27.0, 117760 x 2 KiB 146 / 142 / 139, 44800 x 8 KiB 230 / 213 / 220;
@@ -118,6 +159,14 @@ inline StorePolicy regroup_store(RowLines lines, int64_t rows, int cpr) {
     const int64_t bytes = rows * cpr * 16, MiB = (int64_t)1 << 20;
     if (cpr < 64 && bytes <= 3 * MiB) return kStoreBack;
     return bytes > (lines == kSharedLines ? 80 : 256) * MiB ? kStoreStream : kStoreThrough;
+}
+
+// Its loads, us there and back streaming / ordinary: 1115 x 1280, four (5 MiB) 7.9 / 7.9, 4958 x 896, two (8.5) 11.3 / 10.3, 3328 x 1776, four (22.5)
+// 21.8 / 17.7, 22.9 MiB of 1280 bytes 18.9 / 17.3; 31 MiB of 1 KiB 23.0 / 23.0, 40 of 512 bytes 32.1 / 32.8, 52 of 4864 bytes 33.9 / 38.0; 1893 x
+// 256, six (3) 7.7 / 8.0.
+inline LoadPolicy regroup_load(int64_t rows, int cpr) {
+    const int64_t bytes = rows * cpr * 16, MiB = (int64_t)1 << 20;
+    return bytes > 4 * MiB && bytes <= 24 * MiB ? kLoadKeep : kLoadStream;
 }
 
 }  // namespace tamoe

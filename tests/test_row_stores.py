@@ -82,6 +82,11 @@ int combine(uint64_t base, int64_t S, int cpr, int k, int by_wave) { return comb
 int combine_bwd(uint64_t base, int64_t S, int cpr, int k) { return combine_bwd_store(row_lines((const void*)base, cpr), S, cpr, k); }
 int fill(int64_t buffer_rows, int64_t rows, int cpr) { return fill_streams(buffer_rows, rows, cpr); }
 int regroup(uint64_t base, int64_t rows, int cpr) { return regroup_store(row_lines((const void*)base, cpr), rows, cpr); }
+int scatter_ld(int64_t S, int64_t rows, int cpr, int behind_gate) { return scatter_load(S, rows, cpr, behind_gate); }
+int combine_ld(int64_t S, int cpr, int k) { return combine_load(S, cpr, k); }
+int dispatch_bwd_ld(uint64_t base, int64_t S, int cpr, int k, int by_wave) { return dispatch_bwd_load(row_lines((const void*)base, cpr), S, cpr, k, by_wave); }
+int combine_bwd_ld(uint64_t base, int64_t S, int cpr, int k) { return combine_bwd_load(row_lines((const void*)base, cpr), S, cpr, k); }
+int regroup_ld(int64_t rows, int cpr) { return regroup_load(rows, cpr); }
 }
 """
 
@@ -101,6 +106,11 @@ def rules(tmp_path_factory):
     lib.combine_bwd.argtypes = [u64, i64] + [i32] * 2
     lib.fill.argtypes = [i64, i64, i32]
     lib.regroup.argtypes = [u64, i64, i32]
+    lib.scatter_ld.argtypes = [i64, i64, i32, i32]
+    lib.combine_ld.argtypes = [i64, i32, i32]
+    lib.dispatch_bwd_ld.argtypes = [u64, i64, i32, i32, i32]
+    lib.combine_bwd_ld.argtypes = [u64, i64, i32, i32]
+    lib.regroup_ld.argtypes = [i64, i32]
     return lib
 
 
@@ -220,3 +230,40 @@ def test_gpu_tests_reach_every_policy(rules):
             got.add({"combine": lambda: rules.combine(1 << 20, S, cpr, k, by_wave), "combine_bwd": lambda: rules.combine_bwd(1 << 20, S, cpr, k),
                      "regroup": lambda: rules.regroup(1 << 20, S * k, cpr)}[call]())
         assert got == seen, call
+
+
+KEEP = 0   # rows are loaded with ordinary loads; STREAM: with streaming ones
+
+
+@pytest.mark.parametrize("cpr", [1, 16, 64, 125, 512])
+def test_loaded_rows(rules, cpr):
+    """Where the movers cease to load rows for the caches to keep, in MiB of what they touch."""
+    for k in (1, 2, 3, 8):
+        S = lambda mib, per: mib * MIB // (per * cpr * 16)   # noqa: E731  tokens of per rows each
+        for gate, most in ((1, 128), (0, 48)):
+            assert [rules.scatter_ld(S(m, k + 1), S(m, k + 1) * k, cpr, gate) for m in (most, most + 1)] == [KEEP, STREAM]
+        assert [rules.combine_ld(S(m, k + 1), cpr, k) for m in (1, 48, 49)] == [KEEP, KEEP, STREAM]
+        at, off = 1 << 20, (1 << 20) + 48
+        short = cpr < 64
+        assert [rules.combine_bwd_ld(at, S(m, 2 * k + 1), cpr, k) for m in (72, 73)] == [STREAM if short and cpr % 4 else KEEP, STREAM]
+        assert rules.combine_bwd_ld(off, S(72, 2 * k + 1), cpr, k) == (STREAM if short else KEEP)
+        for m, by_wave in ((192, 1), (193, 1), (100, 0)):
+            shared = KEEP if by_wave and k <= 2 and m <= 192 else STREAM
+            assert rules.dispatch_bwd_ld(off, S(m, k), cpr, k, by_wave) == shared
+            assert rules.dispatch_bwd_ld(at, S(m, k), cpr, k, by_wave) == (STREAM if cpr % 4 == 0 else shared)
+    assert [rules.regroup_ld(_at(m, cpr), cpr) for m in (3, 5, 24, 25)] == [STREAM, KEEP, KEEP, STREAM]
+
+
+def test_gpu_tests_reach_every_load_policy(rules):
+    from test_gpu_row_movers import STORE_SHAPES
+
+    seen = {"scatter": set(), "combine": set(), "dispatch_bwd": set(), "combine_bwd": set(), "regroup": set()}
+    for S, cpr, k, by_wave, _ in STORE_SHAPES:
+        seen["scatter"].add((by_wave, rules.scatter_ld(S, S * k, cpr, 0)))
+        seen["combine"].add((by_wave, rules.combine_ld(S, cpr, k)))
+        seen["combine_bwd"].add((by_wave, rules.combine_bwd_ld(1 << 20, S, cpr, k)))
+        seen["dispatch_bwd"].add((by_wave, rules.dispatch_bwd_ld(1 << 20, S, cpr, k, by_wave)))
+        seen["regroup"].add((by_wave, rules.regroup_ld(S * k, cpr)))
+    both = {(b, p) for b in (0, 1) for p in (KEEP, STREAM)}
+    assert seen.pop("dispatch_bwd") == both - {(0, KEEP)}
+    assert all(s == both for s in seen.values()), seen
