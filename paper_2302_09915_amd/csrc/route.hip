@@ -739,6 +739,11 @@ static int64_t rows_sent(const RouteArgs& a) {
     return a.pad_C > 0 && room < pairs ? room : pairs;
 }
 
+// How x is loaded: by what it and the rows take, the unused ones of the fixed-size layout too.
+static bool keeps_x(const RouteArgs& a) {
+    return scatter_load(a.S, a.pad_C > 0 ? (int64_t)a.N * a.pad_C : rows_sent(a), a.cpr, a.m_part != nullptr) == kLoadKeep;
+}
+
 // Fills in the launch geometry.
 static void plan_copy(RouteArgs& a) {
     const bool by_wave = scatter_by_wave(a.S, a.cpr, a.k);
@@ -760,7 +765,7 @@ static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
     const int32_t* caps = a.cap != nullptr ? a.cap : a.table;   // N entries at least
     const bool rowu = scatter_by_wave(a.S, a.cpr, a.k), behind_gate = a.m_part != nullptr;
     const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, rowu, behind_gate, a.pad_C > 0);
-    const bool keep = scatter_load(a.S, rows_sent(a), a.cpr, behind_gate) == kLoadKeep;
+    const bool keep = keeps_x(a);
 #define TAMOE_ROUTE_COPY(RU, ST, LD)                                                          \
     route_copy_kernel<KK, U, RU, ST, LD><<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
 #define TAMOE_ROUTE_COPY_LD(ST, LD)                                                          \
@@ -821,8 +826,9 @@ static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
     const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
     constexpr int kX = (U == 8 ? 64 : 4 * U) / (TH == kTableThreads ? 1 : 2);   // MiB of x
     constexpr int kMiB = kX * (KK > 0 ? KK : TAMOE_MAX_K);                       // of rows
-    constexpr bool kKeepsAll = kX + kMiB <= kKeepGiven;
-    const bool keep = kKeepsAll || scatter_load(a.S, rows_sent(a), a.cpr, a.m_part != nullptr) == kLoadKeep;
+    constexpr bool kKeepsAll = U == 1;   // but for much padding, where 4 MiB of x do not matter
+    static_assert(!kKeepsAll || kX + kMiB <= kKeepGiven, "nothing of its size streams");
+    const bool keep = kKeepsAll || keeps_x(a);
     // the smallest tables in a kernel that is shorter by seven requests and their sums
     const bool one = U == 1 && (int64_t)a.n_blocks * (a.stride / 8) <= TH;
     const auto launch_ld = [&](auto st_c, auto ld_c) {

@@ -82,7 +82,8 @@ inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, b
 // (111) 56.7 / 54.8; beyond 128 MiB either way (63985 x 768, two (141) 63.6 / 62.5, 6784 x 7552, two (147) 76.3 / 77.4, 65536 x 8 KiB, two 625
 // / 637).  Of a routing that is given, in the fixed-size layout with ordinary loads of the combine: 39168 x 256, two (27) 24.3 / 22.6, 20098 x
 // 512, three (39) 26.2 / 24.9, 3648 x 4608, two (48) 27.8 / 26.0; streaming ones there: 8926 x 2432, two (62) 34.8 / 36.1, 3693 x 8960, one (63) 38.5 /
-// 41.4, 28736 x 1536, two (126) 59.5 / 62.6.
+// 41.4, 28736 x 1536, two (126) 59.5 / 62.6.  The rows are those of the buffer: 6144 x 2 KiB, two, half of 48 MiB padding 25.65 / 26.2, 11776 x 1 KiB, two,
+// as much 31.6 / 34.2, 9856 x 1 KiB, two (47) 27.3 / 24.9.
 constexpr int kKeepBehindGate = 128, kKeepGiven = 48;   // MiB of x and the rows sent
 inline LoadPolicy scatter_load(int64_t S, int64_t rows, int cpr, bool behind_gate) {
     return (S + rows) * cpr * 16 <= (int64_t)(behind_gate ? kKeepBehindGate : kKeepGiven) << 20 ? kLoadKeep : kLoadStream;
@@ -111,9 +112,11 @@ inline StorePolicy combine_store(RowLines lines, int64_t S, int cpr, int k, bool
 
 // The combine, the rows it reads (with what it writes): 768 x 7216, two choices (16 MiB) forward 18.6 / 17.5, 1664 x 4912, four (39)
 // forward 34.4 / 32.5, 20098 x 512, three (39) fixed-size layout 26.8 / 24.9; forward 16159 x 1792, two (83) 34.8 / 34.6, 31936 x 640, four (98) 50.6 /
-// 54.6, fixed-size layout 8926 x 2432, two (62) 34.8 / 36.1, 3693 x 8960, one (63) 38.5 / 42.7.
-inline LoadPolicy combine_load(int64_t S, int cpr, int k) {
-    return S * (k + 1) * cpr * 16 <= (int64_t)48 << 20 ? kLoadKeep : kLoadStream;
+// 54.6, fixed-size layout 8926 x 2432, two (62) 34.8 / 36.1, 3693 x 8960, one (63) 38.5 / 42.7.  The buffer they lie in
+// counts too: 6144 x 2 KiB, two, half of 48 MiB padding 26.2 / 25.4, 21193 x 768, two, half of 62 MiB 34.8 / 37.5.
+inline LoadPolicy combine_load(int64_t S, int64_t buffer_rows, int cpr, int k) {
+    const int64_t row = cpr * 16, MiB = (int64_t)1 << 20;
+    return S * (k + 1) * row <= 48 * MiB && buffer_rows <= (60 * MiB) / row ? kLoadKeep : kLoadStream;
 }
 // Its transpose reads what combine_bwd has left there either way.  Rows that share lines gain, as the line is wanted again: us of the three
 // backward calls on 16448 x 2224, two (35 MiB of rows per choice) 50.5 / 46.9, 5696 x 15968, one 79.3 / 76.9, 23808 x 3824, two (182 in all) 89.6 /

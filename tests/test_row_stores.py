@@ -83,7 +83,7 @@ int combine_bwd(uint64_t base, int64_t S, int cpr, int k) { return combine_bwd_s
 int fill(int64_t buffer_rows, int64_t rows, int cpr) { return fill_streams(buffer_rows, rows, cpr); }
 int regroup(uint64_t base, int64_t rows, int cpr) { return regroup_store(row_lines((const void*)base, cpr), rows, cpr); }
 int scatter_ld(int64_t S, int64_t rows, int cpr, int behind_gate) { return scatter_load(S, rows, cpr, behind_gate); }
-int combine_ld(int64_t S, int cpr, int k) { return combine_load(S, cpr, k); }
+int combine_ld(int64_t S, int64_t rows, int cpr, int k) { return combine_load(S, rows, cpr, k); }
 int dispatch_bwd_ld(uint64_t base, int64_t S, int cpr, int k, int by_wave) { return dispatch_bwd_load(row_lines((const void*)base, cpr), S, cpr, k, by_wave); }
 int combine_bwd_ld(uint64_t base, int64_t S, int cpr, int k) { return combine_bwd_load(row_lines((const void*)base, cpr), S, cpr, k); }
 int regroup_ld(int64_t rows, int cpr) { return regroup_load(rows, cpr); }
@@ -107,7 +107,7 @@ def rules(tmp_path_factory):
     lib.fill.argtypes = [i64, i64, i32]
     lib.regroup.argtypes = [u64, i64, i32]
     lib.scatter_ld.argtypes = [i64, i64, i32, i32]
-    lib.combine_ld.argtypes = [i64, i32, i32]
+    lib.combine_ld.argtypes = [i64, i64, i32, i32]
     lib.dispatch_bwd_ld.argtypes = [u64, i64, i32, i32, i32]
     lib.combine_bwd_ld.argtypes = [u64, i64, i32, i32]
     lib.regroup_ld.argtypes = [i64, i32]
@@ -242,7 +242,8 @@ def test_loaded_rows(rules, cpr):
         S = lambda mib, per: mib * MIB // (per * cpr * 16)   # noqa: E731  tokens of per rows each
         for gate, most in ((1, 128), (0, 48)):
             assert [rules.scatter_ld(S(m, k + 1), S(m, k + 1) * k, cpr, gate) for m in (most, most + 1)] == [KEEP, STREAM]
-        assert [rules.combine_ld(S(m, k + 1), cpr, k) for m in (1, 48, 49)] == [KEEP, KEEP, STREAM]
+        assert [rules.combine_ld(S(m, k + 1), S(m, k + 1) * k, cpr, k) for m in (1, 48, 49)] == [KEEP, KEEP, STREAM]
+        assert [rules.combine_ld(100, rows, cpr, k) for rows in (0, _at(60, cpr), _at(61, cpr), 1 << 31)] == [KEEP, KEEP, STREAM, STREAM]
         at, off = 1 << 20, (1 << 20) + 48
         short = cpr < 64
         assert [rules.combine_bwd_ld(at, S(m, 2 * k + 1), cpr, k) for m in (72, 73)] == [STREAM if short and cpr % 4 else KEEP, STREAM]
@@ -260,7 +261,7 @@ def test_gpu_tests_reach_every_load_policy(rules):
     seen = {"scatter": set(), "combine": set(), "dispatch_bwd": set(), "combine_bwd": set(), "regroup": set()}
     for S, cpr, k, by_wave, _ in STORE_SHAPES:
         seen["scatter"].add((by_wave, rules.scatter_ld(S, S * k, cpr, 0)))
-        seen["combine"].add((by_wave, rules.combine_ld(S, cpr, k)))
+        seen["combine"].add((by_wave, rules.combine_ld(S, S * k, cpr, k)))
         seen["combine_bwd"].add((by_wave, rules.combine_bwd_ld(1 << 20, S, cpr, k)))
         seen["dispatch_bwd"].add((by_wave, rules.dispatch_bwd_ld(1 << 20, S, cpr, k, by_wave)))
         seen["regroup"].add((by_wave, rules.regroup_ld(S * k, cpr)))
