@@ -28,6 +28,12 @@ def T():
     (33, 512, 64, 64, 2), (8192, 72, 33, 3, 4), (8193, 128, 64, 8, 1), (16385, 24, 48, 16, 2),   # 32, 64, 128
     (32, 8, 128, 64, 8), (8191, 136, 65, 5, 2), (8257, 64, 128, 32, 5), (16500, 32, 96, 8, 2),   # 32, 64, 128
     (32769, 24, 128, 64, 2), (33000, 64, 100, 4, 8),                                         # 256
+    # steps of the small tiles: fewer, as many and more than wavefronts that share a row, a part of a step left over
+    (1, 8, 1, 1, 1), (33, 64, 16, 4, 2), (95, 136, 16, 16, 8), (40, 256, 9, 3, 3), (40, 520, 16, 4, 2), (70, 1032, 16, 4, 2),
+    (40, 1000, 17, 1, 2), (33, 1032, 32, 8, 2), (33, 2056, 32, 8, 2), (40, 128, 64, 8, 2), (40, 136, 33, 3, 2), (33, 1024, 48, 16, 4),
+    (40, 1032, 64, 8, 2), (33, 3000, 64, 8, 2), (40, 512, 65, 5, 2), (33, 1016, 128, 8, 8), (33, 1040, 128, 8, 2),
+    (8300, 64, 16, 4, 2), (8300, 264, 10, 5, 2), (16400, 40, 16, 4, 2), (8300, 72, 32, 8, 2), (8300, 600, 16, 4, 1),
+    (8300, 504, 16, 4, 2), (8300, 512, 16, 4, 2), (16500, 520, 9, 3, 2), (32768, 136, 32, 8, 2), (8300, 128, 20, 4, 2),
 ])
 def test_tile_edges(T, oracle, dtype, S, d, N, P, k):
     oracle.set_threads(oracle.max_threads())
