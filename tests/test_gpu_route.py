@@ -27,6 +27,8 @@ def T():
     (257, 8, 6, 3, 3), (129, 64, 10, 5, 5), (16384, 8, 16, 4, 8), (16385, 8, 16, 4, 8), (20000, 24, 128, 4, 5),    # tiles of the ranking
     (5000, 520, 16, 4, 1), (5000, 600, 16, 4, 2), (5000, 608, 16, 4, 2), (333, 1032, 16, 4, 3), (4000, 1112, 16, 4, 4),    # by wavefront
     (4000, 1120, 16, 4, 1), (900, 800, 16, 4, 5), (900, 1024, 16, 4, 6), (300, 1544, 16, 4, 2), (4095, 520, 16, 4, 2),     # or flat
+    (8192, 64, 64, 64, 1), (8193, 64, 64, 64, 1), (4096, 64, 8, 8, 1), (4097, 64, 8, 8, 1), (1024, 72, 128, 64, 8), (1025, 72, 128, 64, 8),   # a routing ranked
+    (512, 64, 128, 64, 8), (513, 64, 5, 5, 5), (1365, 56, 16, 4, 6), (1366, 128, 16, 4, 3), (2730, 1032, 10, 5, 3), (4096, 1024, 16, 4, 2), (8190, 512, 16, 4, 1), (2000, 32, 16, 4, 2),   # by the scatter
     (4096, 520, 16, 4, 2), (2731, 1048, 16, 4, 2), (2731, 1056, 16, 4, 2), (4200, 808, 16, 4, 5), (4096, 936, 16, 4, 5), (2800, 1032, 16, 4, 6)])
 def test_dispatch_stages(T, oracle, S, d, N, P, k):
     rng = np.random.default_rng(S + d + N)
