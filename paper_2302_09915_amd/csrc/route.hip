@@ -170,9 +170,10 @@ static int64_t rows_sent(const RouteArgs& a) {
     return a.pad_C > 0 && room < pairs ? room : pairs;
 }
 
-// How x is loaded: by what it and the rows take, the unused ones of the fixed-size layout too.
-static bool keeps_x(const RouteArgs& a) {
-    return scatter_load(a.S, a.pad_C > 0 ? (int64_t)a.N * a.pad_C : rows_sent(a), a.cpr, a.m_part != nullptr) == kLoadKeep;
+// How x is loaded: by what it and the rows take, the unused ones of the fixed-size layout too.  The packed dispatch follows a
+// gate on the same x.
+static bool keeps_x(const RouteArgs& a, bool ranks = false) {
+    return scatter_load(a.S, a.pad_C > 0 ? (int64_t)a.N * a.pad_C : rows_sent(a), a.cpr, a.pad_C == 0, ranks) == kLoadKeep;
 }
 
 // Fills in the launch geometry.
@@ -243,13 +244,13 @@ static int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool b
 // Units per wavefront with which the scatter counts a given routing itself, and its threads; 0: behind a launch that ranks it.
 // A launch is 2.4 us on the host and 3 or more on the device.  Renormalisation, dispatch_padded and combine, us with it and without:
 // 4096 x 128 bytes, two choices 14.6, 11.4, 4096 x 1 KiB, two 17.6, 11.2, 1024 x 1 KiB, eight 15.1, 12.8, 8192 x 512, two 17.7, 13.4, 6144 x 2 KiB, two, half of
-// it padding 26.2, 22.4, 4096 x 4 KiB, two 28.7, 23.3; separate calls of 8192 x 256, two 37.5, 33.0.  Every workgroup reads all pairs:
+// it padding 26.2, 22.4, 4096 x 4 KiB, two 28.7, 23.3; separate calls of 8192 x 256, two 37.5, 33.0, 16384 x 4 KiB, one 68.2, 61.8, 8192 x 8 KiB, two 91.3, 86.8.  Every workgroup reads all pairs:
 // beyond kGivenPairs that takes longer than the launch (with 30000, 10000 x 256, three 15.8, 23.5).  It should be one of at most
 // 256, as many units to a wavefront as that takes (5003 x 2000, three: 626 workgroups 23.0, 313 21.1; 3200 x 1 KiB, five 19.0, 16.1).
 static int given_units(int64_t S, int cpr, int N, int k, int* threads) {
     const int64_t units = move_units(S, cpr, k);
     const bool by_wave = scatter_by_wave(S, cpr, k);
-    if (S <= 0 || S * k > kGivenPairs || units > (by_wave ? 32768 : 8192)) return 0;
+    if (S <= 0 || S * k > kGivenPairs || units > (by_wave ? 131072 : 8192)) return 0;
     const bool half = units < kTableThreads / 64 * 256 && S * k <= kGivenBatch * kTableThreads / 2;
     *threads = half ? kTableThreads / 2 : kTableThreads;
     int U = 1;
@@ -384,13 +385,12 @@ int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const i
     if ((a.units = given_units(S, cpr, N, k, &a.threads)) > 0) {
         const bool by_wave = scatter_by_wave(S, cpr, k);
         const StorePolicy policy = scatter_store(row_lines(send, cpr), rows_sent(a), cpr, k, by_wave, false, pad_C > 0);
-        // beyond 96 MiB rows would be better loaded otherwise (scatter_load), and the launch is little of it
-        if ((S + rows_sent(a)) * cpr * 16 <= (int64_t)96 << 20 && (policy == kStoreThrough || (policy == kStoreBack && !by_wave))) {
+        if (policy == kStoreThrough || (policy == kStoreBack && !by_wave)) {   // what there are instances for
             plan_copy(a, true);
             a.k_magic = k > 1 ? (uint32_t)((((uint64_t)1 << 32) + k - 1) / k) : 0;
             {
                 TraceScope tr("dispatch_copy_kernel", st);
-                launch_route_given(a, by_wave, policy == kStoreThrough, st);
+                launch_route_given(a, by_wave, policy == kStoreThrough, keeps_x(a, true), st);
             }
             return check_launch(fn, "route_table_kernel");
         }

@@ -5,11 +5,16 @@
 namespace tamoe {
 
 template <int TH, int KK, int U, bool ROWU>
-static void launch_u(const RouteArgs& a, bool through, hipStream_t st) {
+static void launch_u(const RouteArgs& a, bool through, bool keep, hipStream_t st) {
     const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(TH);
     const auto launch = [&](auto st_c) {
-        route_table_kernel<TH, KK, U, ROWU, decltype(st_c)::value, kLoadKeep, 0>
-            <<<grid, block, 0, st>>>(a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
+        constexpr int ST = decltype(st_c)::value;
+        if constexpr (ROWU && U >= 4)   // 8 MiB of x and more; less is loaded to stay whatever the padding
+            if (!keep) {
+                route_table_kernel<TH, KK, U, ROWU, ST, kLoadStream, 0><<<grid, block, 0, st>>>(a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
+                return;
+            }
+        route_table_kernel<TH, KK, U, ROWU, ST, kLoadKeep, 0><<<grid, block, 0, st>>>(a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
     };
     if constexpr (!ROWU)   // rows by wavefront of these sizes go through L2
         if (!through) return launch(std::integral_constant<int, kStoreBack>{});
@@ -17,27 +22,27 @@ static void launch_u(const RouteArgs& a, bool through, hipStream_t st) {
 }
 
 template <int KK>
-static void launch_k(const RouteArgs& a, bool by_wave, bool through, hipStream_t st) {
+static void launch_k(const RouteArgs& a, bool by_wave, bool through, bool keep, hipStream_t st) {
     constexpr int TH = kTableThreads;
     if (!by_wave) {
-        if (a.threads != TH) launch_u<TH / 2, KK, 1, false>(a, through, st);
-        else if (a.units == 1) launch_u<TH, KK, 1, false>(a, through, st);
-        else launch_u<TH, KK, 2, false>(a, through, st);
+        if (a.threads != TH) launch_u<TH / 2, KK, 1, false>(a, through, keep, st);
+        else if (a.units == 1) launch_u<TH, KK, 1, false>(a, through, keep, st);
+        else launch_u<TH, KK, 2, false>(a, through, keep, st);
     } else {
-        if (a.threads != TH) launch_u<TH / 2, KK, 1, true>(a, through, st);
-        else if (a.units == 1) launch_u<TH, KK, 1, true>(a, through, st);
-        else if (a.units == 2) launch_u<TH, KK, 2, true>(a, through, st);
-        else if (a.units == 4) launch_u<TH, KK, 4, true>(a, through, st);
-        else launch_u<TH, KK, 8, true>(a, through, st);
+        if (a.threads != TH) launch_u<TH / 2, KK, 1, true>(a, through, keep, st);
+        else if (a.units == 1) launch_u<TH, KK, 1, true>(a, through, keep, st);
+        else if (a.units == 2) launch_u<TH, KK, 2, true>(a, through, keep, st);
+        else if (a.units == 4) launch_u<TH, KK, 4, true>(a, through, keep, st);
+        else launch_u<TH, KK, 8, true>(a, through, keep, st);
     }
 }
 
-void launch_route_given(const RouteArgs& a, bool by_wave, bool through, hipStream_t st) {
-    if (a.k == 1) launch_k<1>(a, by_wave, through, st);
-    else if (a.k == 2) launch_k<2>(a, by_wave, through, st);
-    else if (a.k == 3) launch_k<3>(a, by_wave, through, st);
-    else if (a.k == 4) launch_k<4>(a, by_wave, through, st);
-    else launch_k<0>(a, by_wave, through, st);
+void launch_route_given(const RouteArgs& a, bool by_wave, bool through, bool keep, hipStream_t st) {
+    if (a.k == 1) launch_k<1>(a, by_wave, through, keep, st);
+    else if (a.k == 2) launch_k<2>(a, by_wave, through, keep, st);
+    else if (a.k == 3) launch_k<3>(a, by_wave, through, keep, st);
+    else if (a.k == 4) launch_k<4>(a, by_wave, through, keep, st);
+    else launch_k<0>(a, by_wave, through, keep, st);
 }
 
 }  // namespace tamoe

@@ -696,6 +696,7 @@ __global__ __launch_bounds__(TH, 4) void route_table_kernel(
     }
 }
 
-// The scatter that ranks a given routing itself (route_given.hip): a is complete, `through` says how rows are stored.
-void launch_route_given(const RouteArgs& a, bool by_wave, bool through, hipStream_t st);
+// The scatter that ranks a given routing itself (route_given.hip): a is complete, rows are stored through L2 or from it, x is loaded
+// to stay in the caches or not.
+void launch_route_given(const RouteArgs& a, bool by_wave, bool through, bool keep, hipStream_t st);
 }  // namespace tamoe

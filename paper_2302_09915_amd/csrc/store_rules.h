@@ -84,9 +84,13 @@ inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, b
 // 512, three (39) 26.2 / 24.9, 3648 x 4608, two (48) 27.8 / 26.0; streaming ones there: 8926 x 2432, two (62) 34.8 / 36.1, 3693 x 8960, one (63) 38.5 /
 // 41.4, 28736 x 1536, two (126) 59.5 / 62.6.  The rows are those of the buffer: 6144 x 2 KiB, two, half of 48 MiB padding 25.65 / 26.2, 11776 x 1 KiB, two,
 // as much 31.6 / 34.2, 9856 x 1 KiB, two (47) 27.3 / 24.9.
-constexpr int kKeepBehindGate = 128, kKeepGiven = 48;   // MiB of x and the rows sent
-inline LoadPolicy scatter_load(int64_t S, int64_t rows, int cpr, bool behind_gate) {
-    return (S + rows) * cpr * 16 <= (int64_t)(behind_gate ? kKeepBehindGate : kKeepGiven) << 20 ? kLoadKeep : kLoadStream;
+// Ranked by the scatter itself, which waits for the counts meanwhile: 8192 x 4 KiB, one (72) 31.4 / 27.9, 3770 x 5888, two (62)
+// 29.9 / 26.4, 1150 x 16 KiB, two, half padding (92) 32.2 / 29.0; 8192 x 4 KiB, two (96) 40.9 / 44.7, 5300 x 7 KiB, two (118) 46.4 / 49.2, 16384 x 4 KiB, one (140) 52.7 / 56.4; some of 57 to 66
+// MiB, half padding, lose (6144 x 2 KiB, two (60) 21.6 / 22.5).
+constexpr int kKeepBehindGate = 128, kKeepRanking = 88, kKeepGiven = 48;   // MiB of x and the rows sent
+inline LoadPolicy scatter_load(int64_t S, int64_t rows, int cpr, bool behind_gate, bool ranks = false) {
+    const int most = behind_gate ? kKeepBehindGate : ranks ? kKeepRanking : kKeepGiven;
+    return (S + rows) * cpr * 16 <= (int64_t)most << 20 ? kLoadKeep : kLoadStream;
 }
 
 // Padding of the fixed-size layout: zeros stream where they would take the place of its rows in the last-level cache, which is in

@@ -82,7 +82,7 @@ int combine(uint64_t base, int64_t S, int cpr, int k, int by_wave) { return comb
 int combine_bwd(uint64_t base, int64_t S, int cpr, int k) { return combine_bwd_store(row_lines((const void*)base, cpr), S, cpr, k); }
 int fill(int64_t buffer_rows, int64_t rows, int cpr) { return fill_streams(buffer_rows, rows, cpr); }
 int regroup(uint64_t base, int64_t rows, int cpr) { return regroup_store(row_lines((const void*)base, cpr), rows, cpr); }
-int scatter_ld(int64_t S, int64_t rows, int cpr, int behind_gate) { return scatter_load(S, rows, cpr, behind_gate); }
+int scatter_ld(int64_t S, int64_t rows, int cpr, int kind) { return scatter_load(S, rows, cpr, kind == 1, kind == 2); }
 int combine_ld(int64_t S, int64_t rows, int cpr, int k) { return combine_load(S, rows, cpr, k); }
 int dispatch_bwd_ld(uint64_t base, int64_t S, int cpr, int k, int by_wave) { return dispatch_bwd_load(row_lines((const void*)base, cpr), S, cpr, k, by_wave); }
 int combine_bwd_ld(uint64_t base, int64_t S, int cpr, int k) { return combine_bwd_load(row_lines((const void*)base, cpr), S, cpr, k); }
@@ -240,7 +240,7 @@ def test_loaded_rows(rules, cpr):
     """Where the movers cease to load rows for the caches to keep, in MiB of what they touch."""
     for k in (1, 2, 3, 8):
         S = lambda mib, per: mib * MIB // (per * cpr * 16)   # noqa: E731  tokens of per rows each
-        for gate, most in ((1, 128), (0, 48)):
+        for gate, most in ((1, 128), (0, 48), (2, 88)):   # behind a gate, behind a ranking, ranking itself
             assert [rules.scatter_ld(S(m, k + 1), S(m, k + 1) * k, cpr, gate) for m in (most, most + 1)] == [KEEP, STREAM]
         assert [rules.combine_ld(S(m, k + 1), S(m, k + 1) * k, cpr, k) for m in (1, 48, 49)] == [KEEP, KEEP, STREAM]
         assert [rules.combine_ld(100, rows, cpr, k) for rows in (0, _at(60, cpr), _at(61, cpr), 1 << 31)] == [KEEP, KEEP, STREAM, STREAM]
