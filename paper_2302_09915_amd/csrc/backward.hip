@@ -271,9 +271,9 @@ static void launch_gate_bwd(const float* logits, const int32_t* idx, const float
 #define TAMOE_GATE_BWD(KK)                                                                                              \
     do {                                                                                                                \
         if (vec)                                                                                                        \
-            gate_bwd_kernel<LPT, true, KK><<<grid, block, 0, st>>>(logits, idx, d_w, penalty, c, scale, S, N, k, d_logits);  \
+            launch_kernel(gate_bwd_kernel<LPT, true, KK>, grid, block, st, logits, idx, d_w, penalty, c, scale, S, N, k, d_logits);  \
         else                                                                                                            \
-            gate_bwd_kernel<LPT, false, KK><<<grid, block, 0, st>>>(logits, idx, d_w, penalty, c, scale, S, N, k, d_logits); \
+            launch_kernel(gate_bwd_kernel<LPT, false, KK>, grid, block, st, logits, idx, d_w, penalty, c, scale, S, N, k, d_logits); \
     } while (0)
     if (k == 1) TAMOE_GATE_BWD(1);
     else if (k == 2) TAMOE_GATE_BWD(2);
@@ -289,13 +289,12 @@ static void launch_combine_bwd_s(const vec16* dy, const vec16* recv, int64_t K_r
         const int rw = row_waves(cpr) < kRowWaves ? row_waves(cpr) : kRowWaves;
         const int rows = rw < 4 ? 4 / rw : 1;
         const dim3 grid = grid_of(ceil_div(S, rows), rows * rw * 64), block(rows * rw * 64);
-        combine_bwd_kernel<DT, KK, ST, LD><<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, rw, d_recv, d_w);
+        launch_kernel(combine_bwd_kernel<DT, KK, ST, LD>, grid, block, st, dy, recv, K_rows, slot, topk_w, S, k, cpr, rw, d_recv, d_w);
     } else {
         int g_shift = 0;
         while ((1 << g_shift) < cpr) ++g_shift;
         const dim3 grid = grid_of(ceil_div(S << g_shift, kThreads), kThreads), block(kThreads);
-        combine_bwd_short_kernel<DT, KK, ST, LD>
-            <<<grid, block, 0, st>>>(dy, recv, K_rows, slot, topk_w, S, k, cpr, g_shift, d_recv, d_w);
+        launch_kernel(combine_bwd_short_kernel<DT, KK, ST, LD>, grid, block, st, dy, recv, K_rows, slot, topk_w, S, k, cpr, g_shift, d_recv, d_w);
     }
 }
 

@@ -137,13 +137,11 @@ static void launch_combine_s(const void* recv, int64_t K_rows, const int32_t* sl
     if (combine_by_wave(S, cpr, k)) {
         const int wpr = row_waves(cpr);
         const dim3 grid = grid_of(ceil_div(S * (int64_t)wpr, kThreads / 64 * U), kThreads), block(kThreads);
-        combine_kernel<DT, KK, U, UNITW, ST, LD>
-            <<<grid, block, 0, st>>>(r, K_rows, slot, topk_w, S, k, cpr, wpr, pow2_shift(wpr), out);
+        launch_kernel(combine_kernel<DT, KK, U, UNITW, ST, LD>, grid, block, st, r, K_rows, slot, topk_w, S, k, cpr, wpr, pow2_shift(wpr), out);
     } else {
         const int64_t total = S * (int64_t)cpr;
         const dim3 grid = grid_of(ceil_div(total, kThreads * U), kThreads), block(kThreads);
-        combine_flat_kernel<DT, KK, U, UNITW, ST, LD>
-            <<<grid, block, 0, st>>>(r, K_rows, slot, topk_w, total, k, cpr, pow2_shift(cpr), out);
+        launch_kernel(combine_flat_kernel<DT, KK, U, UNITW, ST, LD>, grid, block, st, r, K_rows, slot, topk_w, total, k, cpr, pow2_shift(cpr), out);
     }
 }
 

@@ -238,14 +238,14 @@ static void launch_copy(const void* x, const int32_t* slot, int64_t S, int k, in
     const bool stream = S * k * (int64_t)cpr * 16 > (int64_t)96 << 20;   // beyond what the last-level cache keeps beside x
     if (cpr % 64 == 0) {
         if (stream)
-            dispatch_copy_kernel<KK, U, true, true><<<grid, block, 0, st>>>(src, slot, total, k, cpr, shift, dst);
+            launch_kernel(dispatch_copy_kernel<KK, U, true, true>, grid, block, st, src, slot, total, k, cpr, shift, dst);
         else
-            dispatch_copy_kernel<KK, U, true, false><<<grid, block, 0, st>>>(src, slot, total, k, cpr, shift, dst);
+            launch_kernel(dispatch_copy_kernel<KK, U, true, false>, grid, block, st, src, slot, total, k, cpr, shift, dst);
     } else {
         if (stream)
-            dispatch_copy_kernel<KK, U, false, true><<<grid, block, 0, st>>>(src, slot, total, k, cpr, shift, dst);
+            launch_kernel(dispatch_copy_kernel<KK, U, false, true>, grid, block, st, src, slot, total, k, cpr, shift, dst);
         else
-            dispatch_copy_kernel<KK, U, false, false><<<grid, block, 0, st>>>(src, slot, total, k, cpr, shift, dst);
+            launch_kernel(dispatch_copy_kernel<KK, U, false, false>, grid, block, st, src, slot, total, k, cpr, shift, dst);
     }
 }
 
@@ -274,21 +274,21 @@ static int dispatch_in_scratch(const char* fn, const void* x, const int32_t* top
 
     if (n_ct > 0) {
         TraceScope tr("dispatch_count_kernel", st);
-        dispatch_count_kernel<<<dim3((unsigned)n_ct), dim3(kThreads), 0, st>>>(topk_idx, S, N, k, (int)n_ct,
+        launch_kernel(dispatch_count_kernel, dim3((unsigned)n_ct), dim3(kThreads), st, topk_idx, S, N, k, (int)n_ct,
                                                                                 tile_count);
         if ((rc = check_launch(fn, "dispatch_count_kernel")) != TAMOE_OK) return rc;
     }
     {
         TraceScope tr("dispatch_scan_kernel", st);
-        dispatch_scan_kernel<<<dim3(1), dim3(kScanThreads), 0, st>>>(tile_count, cap, N, P, (int)(k * n_ct),
+        launch_kernel(dispatch_scan_kernel, dim3(1), dim3(kScanThreads), st, tile_count, cap, N, P, (int)(k * n_ct),
                                                                       kept_expert, expert_offset, send_count_dev);
     }
     if ((rc = check_launch(fn, "dispatch_scan_kernel")) != TAMOE_OK) return rc;
     if (S > 0) {
         {
             TraceScope tr("dispatch_slot_kernel", st);
-            dispatch_slot_kernel<<<dim3((unsigned)ceil_div(S, kSlotTile)), dim3(kThreads), 0, st>>>(
-                topk_idx, cap, tile_count, expert_offset, S, N, k, (int)n_ct, slot);
+            launch_kernel(dispatch_slot_kernel, dim3((unsigned)ceil_div(S, kSlotTile)), dim3(kThreads), st,
+                          topk_idx, cap, tile_count, expert_offset, S, N, k, (int)n_ct, slot);
         }
         if ((rc = check_launch(fn, "dispatch_slot_kernel")) != TAMOE_OK) return rc;
         launch_dispatch_copy(x, slot, S, k, cpr, send, st);

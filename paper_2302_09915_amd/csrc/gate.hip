@@ -107,11 +107,11 @@ static void launch_select(int64_t blocks, hipStream_t st, const float* logits, i
     const dim3 grid = grid_of(blocks, 512), block(512);
     TraceScope tr("select_kernel", st);
     if (N <= 32)
-        select_kernel<1><<<grid, block, 0, st>>>(logits, S, N, k, topk_idx, topk_w, gs);
+        launch_kernel(select_kernel<1>, grid, block, st, logits, S, N, k, topk_idx, topk_w, gs);
     else if (N <= 64)
-        select_kernel<2><<<grid, block, 0, st>>>(logits, S, N, k, topk_idx, topk_w, gs);
+        launch_kernel(select_kernel<2>, grid, block, st, logits, S, N, k, topk_idx, topk_w, gs);
     else
-        select_kernel<4><<<grid, block, 0, st>>>(logits, S, N, k, topk_idx, topk_w, gs);
+        launch_kernel(select_kernel<4>, grid, block, st, logits, S, N, k, topk_idx, topk_w, gs);
 }
 
 int check_select_outputs(const char* fn, int64_t S, int32_t* topk_idx, float* topk_w, float* m, int32_t* c_expert,
@@ -195,7 +195,7 @@ static int finalize(const char* fn, const GateRun& run, int N, int P, int k, int
                     int32_t* c_device, hipStream_t st) {
     {
         TraceScope tr("gate_finalize_kernel", st);
-        gate_finalize_kernel<<<dim3(N + P), dim3(256), 0, st>>>(run.stats.m_part, run.stats.tile_pairs, run.stats.n_blocks,
+        launch_kernel(gate_finalize_kernel, dim3(N + P), dim3(256), st, run.stats.m_part, run.stats.tile_pairs, run.stats.n_blocks,
                                                             k * run.stats.n_blocks, run.stats.pitch, N, N / P, S, m,
                                                             c_expert, c_device);
     }

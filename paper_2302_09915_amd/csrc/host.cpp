@@ -94,8 +94,14 @@ int check_ptr(const char* fn, const char* name, const void* p, size_t align) {
     return TAMOE_OK;
 }
 
+static thread_local hipError_t g_launch_error = hipSuccess;
+void note_launch_error(hipError_t e) {
+    (void)hipGetLastError();   // it is reported here and to nobody else
+    if (g_launch_error == hipSuccess) g_launch_error = e;
+}
 int check_launch(const char* fn, const char* kernel) {
-    hipError_t e = hipGetLastError();
+    const hipError_t e = g_launch_error;
+    g_launch_error = hipSuccess;
     if (e != hipSuccess)
         return fail(TAMOE_HIP_ERROR, "%s: launch of %s failed: %s", fn, kernel, hipGetErrorString(e));
     return TAMOE_OK;

@@ -49,7 +49,7 @@ extern "C" int tamoe_aux_loss(const float* m, const int32_t* c_expert, const flo
     hipStream_t st = static_cast<hipStream_t>(stream);
     {
         TraceScope tr("aux_loss_kernel", st);
-        aux_loss_kernel<<<dim3(1), dim3(TAMOE_MAX_EXPERTS), 0, st>>>(m, c_expert, penalty, N, scale, loss);
+        launch_kernel(aux_loss_kernel, dim3(1), dim3(TAMOE_MAX_EXPERTS), st, m, c_expert, penalty, N, scale, loss);
     }
     return check_launch(fn, "aux_loss_kernel");
 }

@@ -195,10 +195,10 @@ extern "C" int tamoe_regroup(const void* in, const int32_t* recv_count, int P, i
 #define TAMOE_REGROUP(ST, LD)                                                                                      \
     do {                                                                                                           \
         if (rowu)                                                                                                  \
-            regroup_copy_kernel<U, ST, LD><<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, wpr, pow2_shift(wpr),    \
+            launch_kernel(regroup_copy_kernel<U, ST, LD>, grid, block, st, src, sg, cap_rows, cpr, wpr, pow2_shift(wpr),    \
                                                                    to_expert_major, dst, expert_offset);           \
         else                                                                                                       \
-            regroup_flat_kernel<U, ST, LD><<<grid, block, 0, st>>>(src, sg, cap_rows, cpr, pow2_shift(cpr),         \
+            launch_kernel(regroup_flat_kernel<U, ST, LD>, grid, block, st, src, sg, cap_rows, cpr, pow2_shift(cpr),         \
                                                                    to_expert_major, dst, expert_offset);           \
     } while (0)
     if (policy == kStoreStream) TAMOE_REGROUP(kStoreStream, kLoadStream);

@@ -200,7 +200,7 @@ static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
     const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, rowu, behind_gate, a.pad_C > 0);
     const bool keep = keeps_x(a);
 #define TAMOE_ROUTE_COPY(RU, ST, LD)                                                          \
-    route_copy_kernel<KK, U, RU, ST, LD><<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
+    launch_kernel(route_copy_kernel<KK, U, RU, ST, LD>, grid, block, st, a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
 #define TAMOE_ROUTE_COPY_LD(ST, LD)                                                          \
     do {                                                                                     \
         if (rowu) TAMOE_ROUTE_COPY(true, ST, LD); else TAMOE_ROUTE_COPY(false, ST, LD);      \
@@ -287,11 +287,9 @@ static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
     const auto launch_ld = [&](auto st_c, auto ld_c) {
         constexpr int ST = decltype(st_c)::value, LD = decltype(ld_c)::value;
         if (one)
-            route_table_kernel<TH, KK, U, ROWU, ST, LD, U == 1 ? 1 : kTableBatch>
-                <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
+            launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, LD, U == 1 ? 1 : kTableBatch>, grid, block, st, a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
         else
-            route_table_kernel<TH, KK, U, ROWU, ST, LD, kTableBatch>
-                <<<grid, block, 0, st>>>(a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
+            launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, LD, kTableBatch>, grid, block, st, a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
     };
     const auto launch = [&](auto st_c) {
         constexpr bool kOut = decltype(st_c)::value == kStoreOut;   // more than scatter_load keeps
@@ -339,7 +337,7 @@ static int run_copy(const char* fn, const GateRun& run, RouteArgs a, const char*
     plan_copy(a);
     if (!table) {
         TraceScope tr("route_expert_kernel", st);
-        route_expert_kernel<<<dim3(a.N), dim3(kExpertThreads), 0, st>>>(a.m_part, run.stats.tile_pairs, a.n_blocks,
+        launch_kernel(route_expert_kernel, dim3(a.N), dim3(kExpertThreads), st, a.m_part, run.stats.tile_pairs, a.n_blocks,
                                                                         a.k * a.n_blocks, a.pitch, a.S, a.cap, a.pad_C,
                                                                         a.m, a.c_expert, a.kept_expert);
         if ((rc = check_launch(fn, "route_expert_kernel")) != TAMOE_OK) return rc;
@@ -406,9 +404,9 @@ int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const i
         const dim3 grid = grid_of(blocks, 512), block(512);
 #define TAMOE_RANK(NB)                                                                                  \
     do {                                                                                                \
-        if (tok == 128) route_rank_kernel<NB, 128><<<grid, block, 0, st>>>(topk_idx, S, N, k, run.stats); \
-        else if (tok == 256) route_rank_kernel<NB, 256><<<grid, block, 0, st>>>(topk_idx, S, N, k, run.stats); \
-        else route_rank_kernel<NB, 512><<<grid, block, 0, st>>>(topk_idx, S, N, k, run.stats);           \
+        if (tok == 128) launch_kernel(route_rank_kernel<NB, 128>, grid, block, st, topk_idx, S, N, k, run.stats); \
+        else if (tok == 256) launch_kernel(route_rank_kernel<NB, 256>, grid, block, st, topk_idx, S, N, k, run.stats); \
+        else launch_kernel(route_rank_kernel<NB, 512>, grid, block, st, topk_idx, S, N, k, run.stats);           \
     } while (0)
         if (N <= 32) TAMOE_RANK(1);
         else if (N <= 64) TAMOE_RANK(2);

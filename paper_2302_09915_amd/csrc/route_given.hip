@@ -11,10 +11,10 @@ static void launch_u(const RouteArgs& a, bool through, bool keep, hipStream_t st
         constexpr int ST = decltype(st_c)::value;
         if constexpr (ROWU && U >= 4)   // 8 MiB of x and more; less is loaded to stay whatever the padding
             if (!keep) {
-                route_table_kernel<TH, KK, U, ROWU, ST, kLoadStream, 0><<<grid, block, 0, st>>>(a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
+                launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, kLoadStream, 0>, grid, block, st, a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
                 return;
             }
-        route_table_kernel<TH, KK, U, ROWU, ST, kLoadKeep, 0><<<grid, block, 0, st>>>(a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
+        launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, kLoadKeep, 0>, grid, block, st, a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
     };
     if constexpr (!ROWU)   // rows by wavefront of these sizes go through L2
         if (!through) return launch(std::integral_constant<int, kStoreBack>{});

@@ -75,11 +75,11 @@ extern "C" int tamoe_renorm_topk(const float* topk_w, int64_t S, int k, float* o
     {
         TraceScope tr("renorm_topk_kernel", st);
         if (k == 1)
-            renorm_topk_kernel<1><<<grid, block, 0, st>>>(topk_w, S, k, out);
+            launch_kernel(renorm_topk_kernel<1>, grid, block, st, topk_w, S, k, out);
         else if (k == 2)
-            renorm_topk_kernel<2><<<grid, block, 0, st>>>(topk_w, S, k, out);
+            launch_kernel(renorm_topk_kernel<2>, grid, block, st, topk_w, S, k, out);
         else
-            renorm_topk_kernel<0><<<grid, block, 0, st>>>(topk_w, S, k, out);
+            launch_kernel(renorm_topk_kernel<0>, grid, block, st, topk_w, S, k, out);
     }
     return check_launch(fn, "renorm_topk_kernel");
 }
@@ -99,11 +99,11 @@ extern "C" int tamoe_renorm_topk_bwd(const float* topk_w, const float* d_out, in
     {
         TraceScope tr("renorm_topk_bwd_kernel", st);
         if (k == 1)
-            renorm_topk_bwd_kernel<1><<<grid, block, 0, st>>>(topk_w, d_out, S, k, d_topk_w);
+            launch_kernel(renorm_topk_bwd_kernel<1>, grid, block, st, topk_w, d_out, S, k, d_topk_w);
         else if (k == 2)
-            renorm_topk_bwd_kernel<2><<<grid, block, 0, st>>>(topk_w, d_out, S, k, d_topk_w);
+            launch_kernel(renorm_topk_bwd_kernel<2>, grid, block, st, topk_w, d_out, S, k, d_topk_w);
         else
-            renorm_topk_bwd_kernel<0><<<grid, block, 0, st>>>(topk_w, d_out, S, k, d_topk_w);
+            launch_kernel(renorm_topk_bwd_kernel<0>, grid, block, st, topk_w, d_out, S, k, d_topk_w);
     }
     return check_launch(fn, "renorm_topk_bwd_kernel");
 }
