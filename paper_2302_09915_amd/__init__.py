@@ -107,6 +107,10 @@ def bind(entry, *args, **kwargs) -> BoundCall:
     if len(rec.calls) != 1:
         raise TamoeError(INVALID_ARG, "bind() takes one of the tamoe_* device entry points")
     name, cargs = rec.calls[0]
+    native = _fast()
+    call = native.bind(name, tuple(cargs)) if native is not None and hasattr(native, "bind") else NotImplemented
+    if call is not NotImplemented:   # its arguments are part of it
+        return BoundCall(call, (), (args, kwargs))
     return BoundCall(getattr(real, name), cargs, (args, kwargs))
 
 

@@ -72,6 +72,11 @@ def _torch_dir() -> str:
     return os.path.dirname(torch.__file__)
 
 
+def _rocm_dir() -> str:
+    hipcc = shutil.which("hipcc")
+    return os.path.dirname(os.path.dirname(os.path.realpath(hipcc))) if hipcc else "/opt/rocm"
+
+
 def _native_object() -> str:
     """Named after everything outside the sources that the code in it depends on."""
     import torch
@@ -90,13 +95,13 @@ def _compile_native(verbose: bool, incremental: bool = False):
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            f'-DTAMOE_TORCH_VERSION="{torch.__version__}"', "-I", os.path.join(ROOT, "include"),
            "-isystem", os.path.join(_torch_dir(), "include"), "-isystem", sysconfig.get_paths()["include"],
-           "-c", NATIVE_SRC, "-o", obj]
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-isystem", os.path.join(_rocm_dir(), "include"), "-c", NATIVE_SRC, "-o", obj]
     return obj, _run(cmd, verbose)
 
 
 def _link_native(obj: str, verbose: bool) -> subprocess.CompletedProcess:
     return _run([shutil.which("g++") or "c++", "-shared", "-L", HERE, "-L", os.path.join(_torch_dir(), "lib"),
-                 "-Wl,-rpath,$ORIGIN", obj, "-ltamoe", "-ltorch_cpu", "-lc10", "-ltorch_python", "-o", NATIVE_LIB], verbose)
+                 "-Wl,-rpath,$ORIGIN", obj, "-ltamoe", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-ltorch_python", "-o", NATIVE_LIB], verbose)
 
 
 def _finish_native(compiled, verbose: bool) -> None:

@@ -3,7 +3,8 @@
 //
 // A layer of a few thousand tokens is a handful of launches of 3 to 10 us each.  Checking and converting some
 // forty tensors and allocating eighteen outputs in Python took longer than that.  Host time, whatever the sizes:
-// gate + aux_loss + dispatch + combine 79 -> 38 us, the three backward entry points 29 -> 13 us.
+// gate + aux_loss + dispatch + combine 79 -> 38 us, the three backward entry points 29 -> 13 us.  Without
+// the dispatcher for each output, Python for the stream and ctypes for bound calls: gate_dispatch 17.0 -> 14.7, a bound call of one launch 3.0 -> 2.75.
 //
 // Every function returns NotImplemented when anything about its arguments is out of the ordinary (a type, a
 // layout, a device, a subclass, a mode that watches torch's functions, an exception on the way); the caller
@@ -13,8 +14,15 @@
 
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <Python.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPStream.h>
+
+#include <memory>
+#include <tuple>
+#include <type_traits>
+#include <utility>
 
 #include "tamoe.h"
 #include "unlocked.h"
@@ -23,8 +31,6 @@ namespace {
 
 PyObject* g_tensor = nullptr;          // torch.Tensor
 PyObject* g_parameter = nullptr;       // torch.nn.Parameter
-PyObject* g_raw_stream = nullptr;      // torch._C._cuda_getCurrentRawStream, or null
-PyObject* g_device = nullptr;          // torch._C._cuda_getDevice, or null
 
 struct Slow {};                        // thrown where the Python path has to decide
 
@@ -87,11 +93,7 @@ void holds_rows(const at::Tensor& t, int64_t rows, int64_t d) {
 void* stream_of(PyObject* stream) {
     PyObject* v;
     if (stream == Py_None) {
-        if (g_device == nullptr || g_raw_stream == nullptr) throw Slow{};
-        PyObject* dev = PyObject_CallNoArgs(g_device);
-        if (dev == nullptr) throw Slow{};
-        v = PyObject_CallOneArg(g_raw_stream, dev);
-        Py_DECREF(dev);
+        return c10::hip::getCurrentHIPStream().stream();
     } else if (PyLong_CheckExact(stream)) {
         v = Py_NewRef(stream);
     } else {
@@ -112,15 +114,41 @@ struct Out {
           i32(f32.dtype(at::kInt)), u8(f32.dtype(at::kByte)), x(f32.dtype(t.scalar_type())) {}
 };
 
+// at::empty without the dispatcher (a fourth of its time), which nothing watches here (guarded); with it where torch fills new tensors.
+at::Tensor empty(at::IntArrayRef sizes, const at::TensorOptions& o) {
+    if (at::globalContext().deterministicAlgorithms()) return at::empty(sizes, o);
+    return at::detail::empty_cuda(sizes, c10::typeMetaToScalarType(o.dtype()), o.device(), std::nullopt);
+}
+
+PyObject* interned(const char* text) { return PyUnicode_InternFromString(text); }
+// Keys of the results, made once.
+#define KEY(name) PyObject* const k_##name = interned(#name)
+struct Keys {
+    KEY(topk_idx);
+    KEY(topk_w);
+    KEY(m);
+    KEY(c_expert);
+    KEY(c_device);
+    KEY(logits);
+    KEY(loss);
+    KEY(send);
+    KEY(slot);
+    KEY(kept_expert);
+    KEY(expert_offset);
+    KEY(send_count_dev);
+};
+#undef KEY
+const Keys* g_keys = nullptr;
+
 struct Dict {
     PyObject* d = PyDict_New();
     ~Dict() {
         if (d != nullptr && PyGILState_Check()) Py_DECREF(d);   // not in a thread that the interpreter ends (unlocked)
     }
-    void put(const char* key, const at::Tensor& t) { put(key, THPVariable_Wrap(t)); }
-    void none(const char* key) { put(key, Py_NewRef(Py_None)); }
-    void put(const char* key, PyObject* v) {
-        const bool bad = d == nullptr || v == nullptr || PyDict_SetItemString(d, key, v) != 0;
+    void put(PyObject* key, const at::Tensor& t) { put(key, THPVariable_Wrap(t)); }
+    void none(PyObject* key) { put(key, Py_NewRef(Py_None)); }
+    void put(PyObject* key, PyObject* v) {
+        const bool bad = d == nullptr || v == nullptr || key == nullptr || PyDict_SetItem(d, key, v) != 0;
         Py_XDECREF(v);
         if (bad) throw Slow{};
     }
@@ -134,7 +162,7 @@ struct Dict {
 // a workspace that is given, or a new one
 at::Tensor workspace(PyObject* ws, int64_t S, int d, int N, int P, int k, int dtype, const Out& o) {
     if (ws != Py_None) return tensor(ws, at::kByte);
-    return unlocked([&] { return at::empty({(int64_t)tamoe_workspace_bytes(S, d, N, P, k, dtype)}, o.u8); });
+    return unlocked([&] { return empty({(int64_t)tamoe_workspace_bytes(S, d, N, P, k, dtype)}, o.u8); });
 }
 
 template <class F>
@@ -169,32 +197,32 @@ struct Gate {   // what the gate and the fused call share
 struct GateOut {
     at::Tensor idx, wgt, m, ce, cd, lg;
     GateOut(const Gate& g, bool logits)
-        : idx(at::empty({g.S, g.k}, g.o.i32)), wgt(at::empty({g.S, g.k}, g.o.f32)), m(at::empty({g.N}, g.o.f32)),
-          ce(at::empty({g.N}, g.o.i32)), cd(at::empty({g.P}, g.o.i32)) {
-        if (logits) lg = at::empty({g.S, g.N}, g.o.f32);
+        : idx(empty({g.S, g.k}, g.o.i32)), wgt(empty({g.S, g.k}, g.o.f32)), m(empty({g.N}, g.o.f32)),
+          ce(empty({g.N}, g.o.i32)), cd(empty({g.P}, g.o.i32)) {
+        if (logits) lg = empty({g.S, g.N}, g.o.f32);
     }
     float* logits() const { return lg.defined() ? ptr<float>(lg) : nullptr; }
     void fill(Dict& r) const {
-        r.put("topk_idx", idx);
-        r.put("topk_w", wgt);
-        r.put("m", m);
-        r.put("c_expert", ce);
-        r.put("c_device", cd);
-        if (lg.defined()) r.put("logits", lg);
-        else r.none("logits");
+        r.put(g_keys->k_topk_idx, idx);
+        r.put(g_keys->k_topk_w, wgt);
+        r.put(g_keys->k_m, m);
+        r.put(g_keys->k_c_expert, ce);
+        r.put(g_keys->k_c_device, cd);
+        if (lg.defined()) r.put(g_keys->k_logits, lg);
+        else r.none(g_keys->k_logits);
     }
 };
 struct DispatchOut {
     at::Tensor send, slot, kept, off, cnt;
     DispatchOut(const Out& o, int64_t S, int64_t k, int64_t d, int64_t N, int64_t P)
-        : send(at::empty({S * k, d}, o.x)), slot(at::empty({S, k}, o.i32)), kept(at::empty({N}, o.i32)),
-          off(at::empty({N + 1}, o.i32)), cnt(at::empty({P}, o.i32)) {}
+        : send(empty({S * k, d}, o.x)), slot(empty({S, k}, o.i32)), kept(empty({N}, o.i32)),
+          off(empty({N + 1}, o.i32)), cnt(empty({P}, o.i32)) {}
     void fill(Dict& r) const {
-        r.put("send", send);
-        r.put("slot", slot);
-        r.put("kept_expert", kept);
-        r.put("expert_offset", off);
-        r.put("send_count_dev", cnt);
+        r.put(g_keys->k_send, send);
+        r.put(g_keys->k_slot, slot);
+        r.put(g_keys->k_kept_expert, kept);
+        r.put(g_keys->k_expert_offset, off);
+        r.put(g_keys->k_send_count_dev, cnt);
     }
 };
 
@@ -224,14 +252,22 @@ PyObject* n_gate_dispatch(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const float* pen = ptr_or_null<float>(a[4], at::kFloat);
         const int32_t* cap = ptr<int32_t>(a[5], at::kInt);
         const bool logits = truth(a[6]);
-        const GateOut q = unlocked([&] { return GateOut(g, logits); });
-        const at::Tensor loss = unlocked([&] { return at::empty({1}, g.o.f32); });
-        const DispatchOut p = unlocked([&] { return DispatchOut(g.o, g.S, g.k, g.d, g.N, g.P); });
+        struct Outputs {
+            GateOut q;
+            at::Tensor loss;
+            DispatchOut p;
+        };
+        const Outputs all = unlocked([&] {
+            return Outputs{GateOut(g, logits), empty({1}, g.o.f32), DispatchOut(g.o, g.S, g.k, g.d, g.N, g.P)};
+        });
+        const GateOut& q = all.q;
+        const at::Tensor& loss = all.loss;
+        const DispatchOut& p = all.p;
         const at::Tensor ws = workspace(a[7], g.S, g.d, g.N, g.P, g.k, g.dt, g.o);
         void* st = stream_of(a[8]);
         Dict r;
         q.fill(r);
-        r.put("loss", loss);
+        r.put(g_keys->k_loss, loss);
         p.fill(r);
         const int rc = unlocked([&] {
             return tamoe_gate_dispatch(ptr(g.x), ptr(g.w), g.dt, g.S, g.d, g.N, g.P, g.k, pen, cap, q.logits(),
@@ -254,7 +290,7 @@ PyObject* n_aux_loss(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int64_t S = integer(a[4]);
         if (m.dim() < 1) throw Slow{};
         const int N = dim32(m.size(0));
-        const at::Tensor loss = unlocked([&] { return at::empty({1}, Out(m).f32); });
+        const at::Tensor loss = unlocked([&] { return empty({1}, Out(m).f32); });
         void* st = stream_of(a[5]);
         const int rc = unlocked([&] { return tamoe_aux_loss(ptr<float>(m), ce, pen, N, P, S, ptr<float>(loss), st); });
         return rc == TAMOE_OK ? THPVariable_Wrap(loss) : PyLong_FromLong(rc);
@@ -301,7 +337,7 @@ PyObject* n_combine(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int d = dim32(a[4] == Py_None ? recv.size(1) : integer(a[4])), k = dim32(slot.size(1));
         if (d < 0) throw Slow{};
         holds_rows(recv, K, d);
-        const at::Tensor y = unlocked([&] { return at::empty({S, d}, Out(recv).x); });
+        const at::Tensor y = unlocked([&] { return empty({S, d}, Out(recv).x); });
         const int dt = storage(y);
         void* st = stream_of(a[5]);
         const int rc = unlocked([&] { return tamoe_combine(ptr(recv), K, ptr<int32_t>(slot), w, dt, S, d, k, ptr(y), st); });
@@ -375,9 +411,80 @@ PyObject* n_gate_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
+// ---- bound calls ----
+// A C entry point with its arguments, called without any.
+template <class T>
+T unmarshal(PyObject* o) {   // what ctypes would be given
+    if constexpr (std::is_pointer_v<T>) {
+        if (o == Py_None) return nullptr;
+        PyObject* v = PyLong_Check(o) ? Py_NewRef(o) : PyObject_GetAttrString(o, "value");   // ctypes.c_void_p
+        if (v == nullptr) throw Slow{};
+        void* p = v == Py_None ? nullptr : PyLong_Check(v) ? PyLong_AsVoidPtr(v) : nullptr;
+        const bool bad = (v != Py_None && !PyLong_Check(v)) || PyErr_Occurred() != nullptr;
+        Py_DECREF(v);
+        if (bad) throw Slow{};
+        return static_cast<T>(p);
+    } else if constexpr (std::is_floating_point_v<T>) {
+        if (!PyFloat_CheckExact(o)) throw Slow{};
+        return (T)PyFloat_AS_DOUBLE(o);
+    } else {
+        const int64_t v = integer(o);
+        if ((int64_t)(T)v != v || (std::is_unsigned_v<T> && v < 0)) throw Slow{};
+        return (T)v;
+    }
+}
+template <auto Fn>
+struct Bound;
+template <class... A, int (*Fn)(A...)>
+struct Bound<Fn> {
+    using Args = std::tuple<A...>;
+    static constexpr const char* kName = "tamoe bound call";
+    static PyObject* call(PyObject* self, PyObject*) {
+        const Args* a = static_cast<const Args*>(PyCapsule_GetPointer(self, kName));
+        if (a == nullptr) return nullptr;
+        return PyLong_FromLong(unlocked([&] { return std::apply(Fn, *a); }));
+    }
+    static void drop(PyObject* self) { delete static_cast<Args*>(PyCapsule_GetPointer(self, kName)); }
+    template <size_t... I>
+    static PyObject* make(PyObject* args, std::index_sequence<I...>) {
+        if (PyTuple_GET_SIZE(args) != (Py_ssize_t)sizeof...(A)) throw Slow{};
+        auto a = std::make_unique<Args>(Args{unmarshal<A>(PyTuple_GET_ITEM(args, I))...});
+        static PyMethodDef def = {"bound", call, METH_NOARGS, nullptr};
+        PyObject* self = PyCapsule_New(a.get(), kName, drop);
+        if (self == nullptr) throw Slow{};
+        a.release();
+        PyObject* f = PyCFunction_New(&def, self);
+        Py_DECREF(self);
+        if (f == nullptr) throw Slow{};
+        return f;
+    }
+    static PyObject* make(PyObject* args) { return make(args, std::index_sequence_for<A...>{}); }
+};
+struct Entry {
+    const char* name;
+    PyObject* (*make)(PyObject*);
+};
+#define ENTRY(name) {#name, Bound<name>::make}
+const Entry g_entries[] = {ENTRY(tamoe_gate),           ENTRY(tamoe_select),          ENTRY(tamoe_aux_loss),    ENTRY(tamoe_dispatch),
+                           ENTRY(tamoe_dispatch_padded), ENTRY(tamoe_dispatch_static), ENTRY(tamoe_gate_dispatch), ENTRY(tamoe_combine),
+                           ENTRY(tamoe_combine_bwd),    ENTRY(tamoe_dispatch_bwd),    ENTRY(tamoe_gate_bwd),    ENTRY(tamoe_regroup),
+                           ENTRY(tamoe_renorm_topk),    ENTRY(tamoe_renorm_topk_bwd)};
+
+// bind(name, marshalled arguments) -> a function without arguments that returns the status
+PyObject* n_bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    try {
+        if (n == 2 && PyUnicode_Check(a[0]) && PyTuple_CheckExact(a[1]))
+            for (const Entry& e : g_entries)
+                if (PyUnicode_CompareWithASCIIString(a[0], e.name) == 0) return e.make(a[1]);
+    } catch (...) {   // the caller keeps its own way of calling
+    }
+    PyErr_Clear();
+    return Py_NewRef(Py_NotImplemented);
+}
+
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(n_##name)), METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {FAST(gate),        FAST(gate_dispatch), FAST(aux_loss),     FAST(dispatch), FAST(combine),
-                           FAST(combine_bwd), FAST(dispatch_bwd),  FAST(gate_bwd),     {nullptr, nullptr, 0, nullptr}};
+                           FAST(combine_bwd), FAST(dispatch_bwd),  FAST(gate_bwd),     FAST(bind),     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 
 PyObject* attribute(const char* module, const char* name) {
@@ -394,9 +501,8 @@ PyMODINIT_FUNC PyInit__native() {
     g_tensor = attribute("torch", "Tensor");
     g_parameter = attribute("torch.nn", "Parameter");
     if (g_tensor == nullptr || g_parameter == nullptr) return nullptr;
-    g_raw_stream = attribute("torch._C", "_cuda_getCurrentRawStream");
-    g_device = attribute("torch._C", "_cuda_getDevice");
-    PyErr_Clear();
+    static const Keys keys;
+    g_keys = &keys;
     PyObject* m = PyModule_Create(&g_module);
     if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", TAMOE_TORCH_VERSION) != 0) Py_CLEAR(m);
     return m;

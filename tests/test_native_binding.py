@@ -30,6 +30,26 @@ def test_leaves_the_unusual_to_python(name):
         assert native(*[torch.zeros(2, 2)] * count) is NotImplemented
 
 
+def test_bound_arguments():
+    """What ctypes would be given, and nothing else; a status comes back, which the caller turns into an error."""
+    import ctypes
+
+    bind, null = T._fast().bind, ctypes.c_void_p(None)
+    good = (null, 0, ctypes.c_void_p(16), None, T.F32, -1, 8, 1, null, ctypes.c_void_p(0))
+    call = bind("tamoe_combine", good)
+    assert call() == T.INVALID_ARG and call() == T.INVALID_ARG
+    with pytest.raises(TypeError):
+        call(1)
+    for name, args in (("tamoe_version", ()), ("tamoe_combine", good[:-1]), ("tamoe_combine", good + (None,)), ("tamoe_combine", list(good)),
+                       ("tamoe_combine", (1.5,) + good[1:]), ("tamoe_combine", good[:4] + (1 << 40,) + good[5:]),
+                       ("tamoe_combine", good[:1] + (1 << 70,) + good[2:]), ("tamoe_combine", good[:1] + (None,) + good[2:]),
+                       ("tamoe_renorm_topk", (None, 1, True, None, None)), ("tamoe_gate_bwd", (None,) * 5 + (1, 1, 2, 2, 1, None, None))):
+        assert bind(name, args) is NotImplemented, (name, args)
+    assert bind() is NotImplemented and bind("tamoe_combine") is NotImplemented and bind(1, good) is NotImplemented
+    zero = bind("tamoe_gate_bwd", (None,) * 5 + (0.5, 0, 2, 2, 1, None, None))   # no tokens: nothing is launched
+    assert zero() == T.OK
+
+
 def test_host_tensors_raise_as_before():
     f, i = torch.zeros(4, 4), torch.zeros(4, 2, dtype=torch.int32)
     for call in (lambda: T.gate(f, f, 2, 2, ws=f), lambda: T.aux_loss(f[0], i, None, 2, 4), lambda: T.dispatch(f, i, i, 4, 2, ws=f),
