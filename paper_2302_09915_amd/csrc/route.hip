@@ -170,10 +170,13 @@ static int64_t rows_sent(const RouteArgs& a) {
     return a.pad_C > 0 && room < pairs ? room : pairs;
 }
 
-// How x is loaded: by what it and the rows take, the unused ones of the fixed-size layout too.  The packed dispatch follows a
-// gate on the same x.
-static bool keeps_x(const RouteArgs& a, bool ranks = false) {
-    return scatter_load(a.S, a.pad_C > 0 ? (int64_t)a.N * a.pad_C : rows_sent(a), a.cpr, a.pad_C == 0, ranks) == kLoadKeep;
+// How rows are moved and x is loaded: by what it and the rows take, the unused ones of the fixed-size layout too.  The packed dispatch
+// follows a gate on the same x.
+static RowPolicies row_policies(const RouteArgs& a, bool ranks = false) {
+    const bool by_wave = scatter_by_wave(a.S, a.cpr, a.k);
+    const int64_t rows = rows_sent(a), buffer = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : rows;
+    return RowPolicies{by_wave, scatter_load(a.S, buffer, a.cpr, a.pad_C == 0, ranks) == kLoadKeep,
+                       scatter_store(row_lines(a.send, a.cpr), rows, a.cpr, a.k, by_wave, a.m_part != nullptr, a.pad_C > 0)};
 }
 
 // Fills in the launch geometry.
@@ -192,13 +195,12 @@ static void plan_copy(RouteArgs& a, bool given = false) {
 }
 
 template <int KK>
-static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
+static void launch_route_copy(const RouteArgs& a, const RowPolicies& how, hipStream_t st) {
     constexpr int U = copy_units(KK);
     const dim3 grid = grid_of(1 + (int64_t)a.copy_blocks + (int64_t)a.N * a.fill_parts, kCopyThreads), block(kCopyThreads);
     const int32_t* caps = a.cap != nullptr ? a.cap : a.table;   // N entries at least
-    const bool rowu = scatter_by_wave(a.S, a.cpr, a.k), behind_gate = a.m_part != nullptr;
-    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, rowu, behind_gate, a.pad_C > 0);
-    const bool keep = keeps_x(a);
+    const bool rowu = how.by_wave, keep = how.keep;
+    const StorePolicy policy = how.store;
 #define TAMOE_ROUTE_COPY(RU, ST, LD)                                                          \
     launch_kernel(route_copy_kernel<KK, U, RU, ST, LD>, grid, block, st, a.x, a.topk_idx, a.local_pos, a.table, caps, a.slot, a.send, a)
 #define TAMOE_ROUTE_COPY_LD(ST, LD)                                                          \
@@ -221,7 +223,9 @@ static void launch_route_copy(const RouteArgs& a, hipStream_t st) {
 // Units (64 chunks) per wavefront with which the scatter sums the table itself (route_table_kernel); 0: with
 // route_expert_kernel and route_copy_kernel.
 // The table has to be one batch of scan_counts: a second one is a second memory round trip (5003 x 2000 bytes, 157 tiles
-// of 192 counts: 65.9 us for a training pass, 65.7 with the launch).  Units: as many as leave a workgroup per compute
+// of 192 counts: 65.9 us for a training pass, 65.7 with the launch).  A batch of twice the pieces takes nearly all registers, which pays by wavefront
+// while all workgroups are resident (forward calls with the launch and without: that size 29.8, 28.4, 3000 x 1 KiB, four choices, 126 experts 19.6,
+// 18.2, 8192 x 2 KiB, four 39.0, 37.3; 32768 units 48.5, 49.0, 65536 of them 128.6, 134.0, flat 6000 x 512 18.1, 18.2).  Units: as many as leave a workgroup per compute
 // unit, since each one sums the table (small_forward, 4096 units: with two 14.8, with one 17.5; gpt_moe_forward, 32768: with
 // eight 43.0, with four 45.3; 6681 x 3456 bytes, eight choices, 26724: with eight 71.9, with two 75.0, with the launch 75.2); beyond 65536 of
 // them (64 MiB of x) the launch that is saved counts for little (31106 x 2304, three, 93318: 102.4 with it, 99.9 without), and for a
@@ -232,12 +236,14 @@ static int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool b
     // 16 bits hold the sums of a wavefront's share of the tiles, whatever the routing: with R = 512 / C rows of C pieces requested at a
     // time it has ceil(tiles / R) times max(1, 64 / C) tiles, (S + tile) / 8 + 64 * tile / C tokens at most, which are 57 832 for
     // S = 200 000, C = 1 and tiles of 512, and a token counts once per expert and choice
-    if (S > 200000 || ceil_div(S, tile_tokens) * (count_stride(N, k) / 8) > kTableBatch * kTableThreads) return 0;
+    const int64_t pieces = ceil_div(S, tile_tokens) * (count_stride(N, k) / 8);
+    if (S > 200000 || pieces > 2 * kTableBatch * kTableThreads) return 0;
     const bool by_wave = scatter_by_wave(S, cpr, k);
     const int64_t units = move_units(S, cpr, k);
     if (units > (!by_wave ? 8192 : behind_gate ? 65536 : 32768)) return 0;
     int U = 1;
     while (U < (by_wave ? 8 : 2) && units >= kTableThreads / 64 * U * 2 * 256) U *= 2;
+    if (pieces > kTableBatch * kTableThreads && (!by_wave || units >= 32768)) return 0;
     return U;
 }
 
@@ -271,56 +277,6 @@ static int table_threads(int64_t S, int cpr, int k, int64_t pieces) {
     return move_units(S, cpr, k) < kTableThreads / 64 * 256 && S <= 100000 && pieces <= kTableBatch * kHalf ? kHalf : kTableThreads;
 }
 
-// Only the policies that scatter_store can answer at these sizes are there: a unit is 1 KiB of x at most, and U units per wavefront
-// go with fewer than 4096 * U of them (65536 for U = 8; 2048 with the smaller workgroups).
-template <int TH, int KK, int U, bool ROWU>
-static void launch_route_table_u(const RouteArgs& a, hipStream_t st) {
-    const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(TH);
-    const StorePolicy policy = scatter_store(row_lines(a.send, a.cpr), rows_sent(a), a.cpr, a.k, ROWU, a.m_part != nullptr, a.pad_C > 0);
-    constexpr int kX = (U == 8 ? 64 : 4 * U) / (TH == kTableThreads ? 1 : 2);   // MiB of x
-    constexpr int kMiB = kX * (KK > 0 ? KK : TAMOE_MAX_K);                       // of rows
-    constexpr bool kKeepsAll = U == 1;   // but for much padding, where 4 MiB of x do not matter
-    static_assert(!kKeepsAll || kX + kMiB <= kKeepGiven, "nothing of its size streams");
-    const bool keep = kKeepsAll || keeps_x(a);
-    // the smallest tables in a kernel that is shorter by seven requests and their sums
-    const bool one = U == 1 && (int64_t)a.n_blocks * (a.stride / 8) <= TH;
-    const auto launch_ld = [&](auto st_c, auto ld_c) {
-        constexpr int ST = decltype(st_c)::value, LD = decltype(ld_c)::value;
-        if (one)
-            launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, LD, U == 1 ? 1 : kTableBatch>, grid, block, st, a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
-        else
-            launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, LD, kTableBatch>, grid, block, st, a.x, a.topk_idx, a.local_pos, a.counts, a.slot, a.send, a);
-    };
-    const auto launch = [&](auto st_c) {
-        constexpr bool kOut = decltype(st_c)::value == kStoreOut;   // more than scatter_load keeps
-        if constexpr (kOut || !kKeepsAll)
-            if (kOut || !keep) return launch_ld(st_c, std::integral_constant<int, kLoadStream>{});
-        if constexpr (!kOut) launch_ld(st_c, std::integral_constant<int, kLoadKeep>{});
-    };
-    if constexpr (kMiB > 16)   // half lines
-        if (policy == kStoreStream) return launch(std::integral_constant<int, kStoreStream>{});
-    if constexpr (!ROWU || (KK == 0 && kMiB > 24) || (KK == 4 && kMiB > 240))
-        if (policy == kStoreBack) return launch(std::integral_constant<int, kStoreBack>{});
-    if constexpr (ROWU && kMiB > 128)
-        if (policy == kStoreOut) return launch(std::integral_constant<int, kStoreOut>{});
-    launch(std::integral_constant<int, kStoreThrough>{});
-}
-template <int KK>
-static void launch_route_table(const RouteArgs& a, hipStream_t st) {
-    constexpr int TH = kTableThreads;
-    if (!scatter_by_wave(a.S, a.cpr, a.k)) {
-        if (a.threads != TH) launch_route_table_u<TH / 2, KK, 1, false>(a, st);
-        else if (a.units == 1) launch_route_table_u<TH, KK, 1, false>(a, st);
-        else launch_route_table_u<TH, KK, 2, false>(a, st);
-    } else {
-        if (a.threads != TH) launch_route_table_u<TH / 2, KK, 1, true>(a, st);
-        else if (a.units == 1) launch_route_table_u<TH, KK, 1, true>(a, st);
-        else if (a.units == 2) launch_route_table_u<TH, KK, 2, true>(a, st);
-        else if (a.units == 4) launch_route_table_u<TH, KK, 4, true>(a, st);
-        else launch_route_table_u<TH, KK, 8, true>(a, st);
-    }
-}
-
 // Stages 2 and 3, for table and positions as `run` describes them.
 static int run_copy(const char* fn, const GateRun& run, RouteArgs a, const char* label, hipStream_t st) {
     int rc;
@@ -344,16 +300,14 @@ static int run_copy(const char* fn, const GateRun& run, RouteArgs a, const char*
     }
     {
         TraceScope tr(label, st);
-#define TAMOE_ROUTE(KK)                                                               \
-    do {                                                                              \
-        if (table) launch_route_table<KK>(a, st); else launch_route_copy<KK>(a, st);  \
-    } while (0)
-        if (a.k == 1) TAMOE_ROUTE(1);
-        else if (a.k == 2) TAMOE_ROUTE(2);
-        else if (a.k == 3) TAMOE_ROUTE(3);
-        else if (a.k == 4) TAMOE_ROUTE(4);
-        else TAMOE_ROUTE(0);
-#undef TAMOE_ROUTE
+        const RowPolicies how = row_policies(a);
+        if (table && a.k <= 2) launch_route_table_few(a, how, st);
+        else if (table) launch_route_table_many(a, how, st);
+        else if (a.k == 1) launch_route_copy<1>(a, how, st);
+        else if (a.k == 2) launch_route_copy<2>(a, how, st);
+        else if (a.k == 3) launch_route_copy<3>(a, how, st);
+        else if (a.k == 4) launch_route_copy<4>(a, how, st);
+        else launch_route_copy<0>(a, how, st);
     }
     return check_launch(fn, table ? "route_table_kernel" : "route_copy_kernel");
 }
@@ -381,14 +335,13 @@ int run_dispatch(const char* fn, const void* x, const int32_t* topk_idx, const i
     a.expert_offset = expert_offset;
     a.send_count_dev = send_count_dev;
     if ((a.units = given_units(S, cpr, N, k, &a.threads)) > 0) {
-        const bool by_wave = scatter_by_wave(S, cpr, k);
-        const StorePolicy policy = scatter_store(row_lines(send, cpr), rows_sent(a), cpr, k, by_wave, false, pad_C > 0);
-        if (policy == kStoreThrough || (policy == kStoreBack && !by_wave)) {   // what there are instances for
+        const RowPolicies how = row_policies(a, true);
+        if (how.store == kStoreThrough || (how.store == kStoreBack && !how.by_wave)) {   // what there are instances for
             plan_copy(a, true);
             a.k_magic = k > 1 ? (uint32_t)((((uint64_t)1 << 32) + k - 1) / k) : 0;
             {
                 TraceScope tr("dispatch_copy_kernel", st);
-                launch_route_given(a, by_wave, policy == kStoreThrough, keeps_x(a, true), st);
+                launch_route_given(a, how, st);
             }
             return check_launch(fn, "route_table_kernel");
         }

@@ -5,44 +5,44 @@
 namespace tamoe {
 
 template <int TH, int KK, int U, bool ROWU>
-static void launch_u(const RouteArgs& a, bool through, bool keep, hipStream_t st) {
+static void launch_u(const RouteArgs& a, const RowPolicies& how, hipStream_t st) {
     const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(TH);
     const auto launch = [&](auto st_c) {
         constexpr int ST = decltype(st_c)::value;
         if constexpr (ROWU && U >= 4)   // 8 MiB of x and more; less is loaded to stay whatever the padding
-            if (!keep) {
+            if (!how.keep) {
                 launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, kLoadStream, 0>, grid, block, st, a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
                 return;
             }
         launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, kLoadKeep, 0>, grid, block, st, a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
     };
     if constexpr (!ROWU)   // rows by wavefront of these sizes go through L2
-        if (!through) return launch(std::integral_constant<int, kStoreBack>{});
+        if (how.store == kStoreBack) return launch(std::integral_constant<int, kStoreBack>{});
     launch(std::integral_constant<int, kStoreThrough>{});
 }
 
 template <int KK>
-static void launch_k(const RouteArgs& a, bool by_wave, bool through, bool keep, hipStream_t st) {
+static void launch_k(const RouteArgs& a, const RowPolicies& how, hipStream_t st) {
     constexpr int TH = kTableThreads;
-    if (!by_wave) {
-        if (a.threads != TH) launch_u<TH / 2, KK, 1, false>(a, through, keep, st);
-        else if (a.units == 1) launch_u<TH, KK, 1, false>(a, through, keep, st);
-        else launch_u<TH, KK, 2, false>(a, through, keep, st);
+    if (!how.by_wave) {
+        if (a.threads != TH) launch_u<TH / 2, KK, 1, false>(a, how, st);
+        else if (a.units == 1) launch_u<TH, KK, 1, false>(a, how, st);
+        else launch_u<TH, KK, 2, false>(a, how, st);
     } else {
-        if (a.threads != TH) launch_u<TH / 2, KK, 1, true>(a, through, keep, st);
-        else if (a.units == 1) launch_u<TH, KK, 1, true>(a, through, keep, st);
-        else if (a.units == 2) launch_u<TH, KK, 2, true>(a, through, keep, st);
-        else if (a.units == 4) launch_u<TH, KK, 4, true>(a, through, keep, st);
-        else launch_u<TH, KK, 8, true>(a, through, keep, st);
+        if (a.threads != TH) launch_u<TH / 2, KK, 1, true>(a, how, st);
+        else if (a.units == 1) launch_u<TH, KK, 1, true>(a, how, st);
+        else if (a.units == 2) launch_u<TH, KK, 2, true>(a, how, st);
+        else if (a.units == 4) launch_u<TH, KK, 4, true>(a, how, st);
+        else launch_u<TH, KK, 8, true>(a, how, st);
     }
 }
 
-void launch_route_given(const RouteArgs& a, bool by_wave, bool through, bool keep, hipStream_t st) {
-    if (a.k == 1) launch_k<1>(a, by_wave, through, keep, st);
-    else if (a.k == 2) launch_k<2>(a, by_wave, through, keep, st);
-    else if (a.k == 3) launch_k<3>(a, by_wave, through, keep, st);
-    else if (a.k == 4) launch_k<4>(a, by_wave, through, keep, st);
-    else launch_k<0>(a, by_wave, through, keep, st);
+void launch_route_given(const RouteArgs& a, const RowPolicies& how, hipStream_t st) {
+    if (a.k == 1) launch_k<1>(a, how, st);
+    else if (a.k == 2) launch_k<2>(a, how, st);
+    else if (a.k == 3) launch_k<3>(a, how, st);
+    else if (a.k == 4) launch_k<4>(a, how, st);
+    else launch_k<0>(a, how, st);
 }
 
 }  // namespace tamoe

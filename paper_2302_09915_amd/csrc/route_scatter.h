@@ -88,7 +88,7 @@ __device__ __forceinline__ int32_t offset_of(const WaveOffsets& o, int e) {
 // runs once, from cold instruction caches: with bytes for counts (half the requests, three times the additions)
 // small_forward took 17.8 us, with the steps of sum_columns under a condition each 15.9, now 14.8.
 constexpr int kTableThreads = 512;   // or half as many (table_threads)
-constexpr int kTableBatch = 8;   // rows per lane, requested together (one in the smallest tables)
+constexpr int kTableBatch = 8;   // rows per lane, requested together (one in the smallest tables, twice as many in large ones)
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 // Of a scatter that ranks a given routing itself: most pairs, those a thread requests at a time, most tokens of a workgroup.
@@ -696,7 +696,15 @@ __global__ __launch_bounds__(TH, 4) void route_table_kernel(
     }
 }
 
-// The scatter that ranks a given routing itself (route_given.hip): a is complete, rows are stored through L2 or from it, x is loaded
-// to stay in the caches or not.
-void launch_route_given(const RouteArgs& a, bool by_wave, bool through, bool keep, hipStream_t st);
+// How rows are moved: by whole wavefronts or flat, x loaded for the caches to keep or not, and how rows are stored.
+struct RowPolicies {
+    bool by_wave, keep;
+    StorePolicy store;
+};
+// Launches for complete arguments, each in a translation unit of its own: with a table of pair counts, by choices, and with a
+// routing that the scatter ranks itself (through L2, or flat rows from it).
+void launch_route_table_few(const RouteArgs& a, const RowPolicies& how, hipStream_t st);
+void launch_route_table_many(const RouteArgs& a, const RowPolicies& how, hipStream_t st);
+void launch_route_given(const RouteArgs& a, const RowPolicies& how, hipStream_t st);
+
 }  // namespace tamoe
