@@ -2,8 +2,8 @@
 // (paper Section 3.1: gate network G with softmax, top-k experts per token, c_ie, m_i;
 // Section 4.1: per-destination-device volume).
 //
-// gate_bf16_kernel / gate_f16_kernel / gate_f32_kernel (one tile code, three element types): the one
-// dense contraction of the path, on the matrix cores.  v_mfma_f32_32x32x16_bf16 (or _f16; fp32 operands
+// gate_bf16_kernel / gate_f16_kernel / gate_f32_kernel (one tile code, three element types), and gate_direct_kernel for
+// small tiles (launch_gate_small): the one dense contraction of the path, on the matrix cores.  v_mfma_f32_32x32x16_bf16 (or _f16; fp32 operands
 // are split into three bf16 parts each) with A = a 32-expert block of W and B = 32 tokens of x,
 // both from LDS tiles filled by coalesced loads of 128-byte K chunks.  The scores of a workgroup's tokens
 // end in an LDS tile; softmax and top-k read it with a token over 4 to 16 lanes, so that all

@@ -4,8 +4,8 @@
 // tamoe_dispatch.  tamoe_dispatch and tamoe_dispatch_padded take the same stages behind a kernel that ranks
 // a routing that is given (run_dispatch).
 //
-//   1. the gate kernel (gate_tile.h), or route_rank_kernel for a given routing (few pairs are ranked by the scatter: route_given.hip), leaves per token tile b the
-//      number of pairs per (expert e, choice j) and for every pair its position among the pairs of
+//   1. the gate kernel (gate_tile.h), or route_rank_kernel for a given routing (of few pairs: the scatter itself,
+//      count_given), leaves per token tile b the number of pairs per (expert e, choice j) and for every pair its position among the pairs of
 //      (b, e, j);
 //   2. route_expert_kernel, one workgroup per expert: mean probability, count, the exclusive prefix of
 //      the expert's pair counts in priority order (choice-major, then token order), kept rows.  Not
@@ -19,7 +19,9 @@
 //      with the row's first chunk writes them to slot[].  The first workgroup writes what
 //      describes the layer as a whole: expert offsets, rows per destination device, the loss; in the
 //      fixed-size layout the last ones clear every expert's unused rows.
-//      How rows are stored depends on what the caches can do for them (scatter_store).
+//      How rows are loaded and stored depends on what the caches can do for them (scatter_load, scatter_store).
+// The scatter's kernels are in route_scatter.h, their instances for small tables in route_table.hip and
+// route_table_k.hip, those for few pairs in route_given.hip.
 #include <algorithm>
 
 #include "route_scatter.h"
