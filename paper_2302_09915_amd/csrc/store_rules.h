@@ -118,9 +118,11 @@ inline StorePolicy combine_store(RowLines lines, int64_t S, int cpr, int k, bool
 // forward 34.4 / 32.5, 20098 x 512, three (39) fixed-size layout 26.8 / 24.9; forward 16159 x 1792, two (83) 34.8 / 34.6, 31936 x 640, four (98) 50.6 /
 // 54.6, fixed-size layout 8926 x 2432, two (62) 34.8 / 36.1, 3693 x 8960, one (63) 38.5 / 42.7.  The buffer they lie in
 // counts too: 6144 x 2 KiB, two, half of 48 MiB padding 26.2 / 25.4, 21193 x 768, two, half of 62 MiB 34.8 / 37.5.
+// Above 40 MiB only with up to four choices (streaming / kept, us): training pass of 5003 x 2000, four (48) 62.1 / 59.2; gate,
+// dispatch and combine of 2752 x 1920, eight (45) 35.4 / 38.0.
 inline LoadPolicy combine_load(int64_t S, int64_t buffer_rows, int cpr, int k) {
     const int64_t row = cpr * 16, MiB = (int64_t)1 << 20;
-    return S * (k + 1) * row <= 48 * MiB && buffer_rows <= (60 * MiB) / row ? kLoadKeep : kLoadStream;
+    return S * (k + 1) * row <= (k > 4 ? 40 : 48) * MiB && buffer_rows <= (60 * MiB) / row ? kLoadKeep : kLoadStream;
 }
 // Its transpose reads what combine_bwd has left there either way.  Rows that share lines gain, as the line is wanted again: us of the three
 // backward calls on 16448 x 2224, two (35 MiB of rows per choice) 50.5 / 46.9, 5696 x 15968, one 79.3 / 76.9, 23808 x 3824, two (182 in all) 89.6 /
@@ -151,9 +153,10 @@ inline StorePolicy combine_bwd_store(RowLines lines, int64_t S, int cpr, int k) 
 // combine_bwd, dy and recv (with the rows it writes), us of the three backward calls: 7762 x 768, two (28 MiB) 13.25 / 12.3, 6920 x 512, eight
 // (57) 24.7 / 22.5, 12736 x 1152, two (70) 24.2 / 23.6; beyond 72 MiB either way (31931 x 640, two, 12 experts (97) 34.4 / 32.3, 32448 x 512, two, 128 experts,
 // whose scores take as much again (79) 32.4 / 33.9, 11494 x 2304, two (126) 40.1 / 41.8, 19489 x 2048, four (343) 74.5 / 77.7).  Not short rows
-// that share lines: 59392 x 224, two (63) 30.2 / 31.4.
+// that share lines: 59392 x 224, two (63) 30.2 / 31.4; and flat rows, which have more scores to them, only up to 60 MiB: 57472 x 256,
+// two, 72 experts (70) 31.7 / 32.0.
 inline LoadPolicy combine_bwd_load(RowLines lines, int64_t S, int cpr, int k) {
-    return S * (2 * k + 1) * cpr * 16 <= (int64_t)72 << 20 && (cpr >= 64 || lines != kSharedLines) ? kLoadKeep : kLoadStream;
+    return S * (2 * k + 1) * cpr * 16 <= (int64_t)(cpr < 64 ? 60 : 72) << 20 && (cpr >= 64 || lines != kSharedLines) ? kLoadKeep : kLoadStream;
 }
 
 // The regroup: straight through L2 while the buffer fits the last-level cache, which keeps it for the experts (or the exchange),

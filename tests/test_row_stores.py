@@ -242,12 +242,14 @@ def test_loaded_rows(rules, cpr):
         S = lambda mib, per: mib * MIB // (per * cpr * 16)   # noqa: E731  tokens of per rows each
         for gate, most in ((1, 128), (0, 48), (2, 88)):   # behind a gate, behind a ranking, ranking itself
             assert [rules.scatter_ld(S(m, k + 1), S(m, k + 1) * k, cpr, gate) for m in (most, most + 1)] == [KEEP, STREAM]
-        assert [rules.combine_ld(S(m, k + 1), S(m, k + 1) * k, cpr, k) for m in (1, 48, 49)] == [KEEP, KEEP, STREAM]
+        most = 40 if k > 4 else 48
+        assert [rules.combine_ld(S(m, k + 1), S(m, k + 1) * k, cpr, k) for m in (1, most, most + 1)] == [KEEP, KEEP, STREAM]
         assert [rules.combine_ld(100, rows, cpr, k) for rows in (0, _at(60, cpr), _at(61, cpr), 1 << 31)] == [KEEP, KEEP, STREAM, STREAM]
         at, off = 1 << 20, (1 << 20) + 48
         short = cpr < 64
-        assert [rules.combine_bwd_ld(at, S(m, 2 * k + 1), cpr, k) for m in (72, 73)] == [STREAM if short and cpr % 4 else KEEP, STREAM]
-        assert rules.combine_bwd_ld(off, S(72, 2 * k + 1), cpr, k) == (STREAM if short else KEEP)
+        most = 60 if short else 72
+        assert [rules.combine_bwd_ld(at, S(m, 2 * k + 1), cpr, k) for m in (most, most + 1)] == [STREAM if short and cpr % 4 else KEEP, STREAM]
+        assert rules.combine_bwd_ld(off, S(most, 2 * k + 1), cpr, k) == (STREAM if short else KEEP)
         for m, by_wave in ((192, 1), (193, 1), (100, 0)):
             shared = KEEP if by_wave and k <= 2 and m <= 192 else STREAM
             assert rules.dispatch_bwd_ld(off, S(m, k), cpr, k, by_wave) == shared
