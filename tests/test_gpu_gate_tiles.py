@@ -85,6 +85,40 @@ def test_fp32_products_keep_their_bits(T, S, N, d):
     assert err.norm() / math.sqrt(err.numel()) <= math.sqrt(d / 8) * 2.0 ** -24 / 3 + 2.0 ** -24
 
 
+def _bf16_parts(v):
+    """A 32-bit value as the sum of three bfloat16 values, each rounded to nearest."""
+    parts, rest = [], v.clone()
+    for _ in range(3):
+        parts.append(rest.bfloat16().float())
+        rest = rest - parts[-1]
+    assert (rest == 0).all()
+    return [p.double() for p in parts]
+
+
+@pytest.mark.parametrize("S,N,d", [(33, 8, 64), (40, 16, 136), (40, 16, 1032), (100, 32, 512), (100, 31, 1032), (8300, 4, 256), (8300, 16, 264), (16500, 16, 1024),
+                                   (8300, 32, 64), (16500, 20, 520), (40000, 32, 64), (20000, 64, 128), (33000, 128, 64)])
+def test_fp32_terms_left_out(T, S, N, d):
+    """What a product leaves out are its terms of the third order of parts that are rounded to nearest, of x and of W: seen in the
+    difference of a product and its own value rounded to 32 bits, of which 24 bits cancel.  (Not in tiles of 32 tokens with
+    more than 32 experts, where W's middle part is cut.)"""
+    g = torch.Generator().manual_seed(S + d)
+    e = torch.arange(N)
+    tail = 2.0 ** -16 - 2.0 ** -23                            # of a middle part: 2^-16 once rounded, nothing when cut
+    b = torch.where(e % 2 == 0, 1 + 2.0 ** -9 + tail + (e // 2) * 2.0 ** -15, 1 + torch.rand(N, generator=g))
+    for a in (1 + 2.0 ** -8 - 2.0 ** -22, 1.0 + float(torch.rand(1, generator=g))):
+        a = torch.tensor(a, dtype=torch.float32)
+        x, w = torch.zeros((S, d)), torch.zeros((N, d))
+        x[:, d - 2], x[:, d - 1] = a, 1.0
+        w[:, d - 2], w[:, d - 1] = b, -(a.double() * b.double()).float()
+        (_, am, al), (_, bm, bl) = _bf16_parts(a), _bf16_parts(b)
+        left = am * bl + al * bm + al * bl
+        exact = a.double() * b.double() + w[:, d - 1].double()
+        got = T.gate(x.cuda(), w.cuda(), 1, 1)["logits"].cpu().double()
+        # the products of first parts have 16 bits and their sum is exact; what they leave and the other terms are below
+        # 2^-6, and a sum of those in 32 bits is off by 2^-31 at each of a dozen additions
+        assert (got - (exact - left)).abs().max() <= 16 * 2.0 ** -30
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
 @pytest.mark.parametrize("S,N,d", [(40, 8, 40), (40, 8, 64), (40, 8, 192), (9000, 20, 72), (40, 64, 64), (9000, 48, 136), (20000, 64, 72),
                                    (40, 128, 192), (9000, 100, 200), (20000, 128, 40), (33000, 128, 72), (33000, 65, 128),
