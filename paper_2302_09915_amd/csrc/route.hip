@@ -227,7 +227,7 @@ static void launch_route_copy(const RouteArgs& a, const RowPolicies& how, hipStr
 // The table has to be one batch of scan_counts: a second one is a second memory round trip (5003 x 2000 bytes, 157 tiles
 // of 192 counts: 65.9 us for a training pass, 65.7 with the launch).  A batch of twice the pieces takes nearly all registers, which pays by wavefront
 // while all workgroups are resident (forward calls with the launch and without: that size 29.8, 28.4, 3000 x 1 KiB, four choices, 126 experts 19.6,
-// 18.2, 8192 x 2 KiB, four 39.0, 37.3; 32768 units 48.5, 49.0, 65536 of them 128.6, 134.0, flat 6000 x 512 18.1, 18.2).  Units: as many as leave a workgroup per compute
+// 18.2, 8192 x 2 KiB, four 39.0, 37.3 (36.3 with every register in its place); 32768 units 48.5, 49.0, 65536 of them 128.6, 134.0, flat 6000 x 512 18.1, 18.2).  Units: as many as leave a workgroup per compute
 // unit, since each one sums the table (small_forward, 4096 units: with two 14.8, with one 17.5; gpt_moe_forward, 32768: with
 // eight 43.0, with four 45.3; 6681 x 3456 bytes, eight choices, 26724: with eight 71.9, with two 75.0, with the launch 75.2); beyond 65536 of
 // them (64 MiB of x) the launch that is saved counts for little (31106 x 2304, three, 93318: 102.4 with it, 99.9 without), and for a

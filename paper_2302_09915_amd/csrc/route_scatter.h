@@ -265,9 +265,13 @@ __device__ __forceinline__ void count_given(const RouteArgs& a, int t0, int t1, 
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     for (int from = 0;;) {
+        int p0 = from + tid;
+        // With more than four choices the compiler would keep all sixteen sums with i * TH, in scratch memory in part (71 registers
+        // so, 128 without); with fewer they fit and save time (8192 x 512 bytes, two: 12.6 us, 13.7 so).
+        if constexpr (KK == 0) asm("" : "+v"(p0));
 #pragma unroll
         for (int i = 0; i < kGivenBatch; ++i) {
-            const int p = from + tid + i * TH;
+            const int p = p0 + i * TH;
             if (p < n && (uint32_t)v[i] < (uint32_t)N) {
                 const int tok = KK > 0 ? p / (KK > 0 ? KK : 1) : (int)__umulhi((uint32_t)p, a.k_magic);
                 const int j = p - tok * k;
@@ -646,11 +650,14 @@ __global__ __launch_bounds__(TH, 4) void route_table_kernel(
             tok[u] = tok[u - 1] + next;
             seg[u] = next ? 0 : seg[u - 1] + 1;
         }
+        // A unit's 64 chunks are a buffer of their own: one offset serves all units.  An offset each is U registers, for which
+        // there is no room beside 16 rows of the table, or 16 indices and eight choices: a row went to scratch memory as soon as it
+        // was there, ahead of the sums (8192 x 2 KiB, four choices, 64 experts 37.7 us, now 36.7; 2048 x 8 KiB, eight, separate calls 76.7, 71.9).
         count_pairs<TH, KK, B>(a, blk0, t0, t1, t, [&] {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const bool in = tok[u] < a.S;
-                v[u] = RowBuffer(x + (size_t)(in ? tok[u] : 0) * cpr, cpr, in).template load<LD>(seg[u] * 64 + lane);
+                v[u] = RowBuffer(x + (size_t)(in ? tok[u] : 0) * cpr + seg[u] * 64, cpr - seg[u] * 64, in).template load<LD>(lane);
             }
         });
         const WaveOffsets wo = wave_offsets(load_kept(t.kept, N));
@@ -661,7 +668,7 @@ __global__ __launch_bounds__(TH, 4) void route_table_kernel(
 #pragma unroll
             for (int j = 0; j < KM; ++j) {
                 const int32_t to = __builtin_amdgcn_readlane(sl, u * KM + j);   // -1 where there is no such choice
-                RowBuffer(send + (size_t)(to >= 0 ? to : 0) * cpr, cpr, to >= 0).template store<ST>(seg[u] * 64 + lane, v[u]);
+                RowBuffer(send + (size_t)(to >= 0 ? to : 0) * cpr + seg[u] * 64, cpr - seg[u] * 64, to >= 0).template store<ST>(lane, v[u]);
             }
     } else {
         int tok[U], col[U];

@@ -309,3 +309,41 @@ def test_bind_notes_one_call_and_restores_the_library(T):
     call = T.bind(T.tamoe_version)                              # a call whose result is not a status of 0
     with pytest.raises(T.TamoeError):
         call()
+
+
+def _kernels(path):
+    """Metadata of every gfx950 kernel in a library that was built here: the notes of its code objects."""
+    import struct
+
+    import msgpack
+
+    data = open(path, "rb").read()
+    at = data.find(b"__CLANG_OFFLOAD_BUNDLE__")
+    while at >= 0:
+        pos = at + 32
+        for _ in range(struct.unpack_from("<Q", data, at + 24)[0]):
+            offset, size, length = struct.unpack_from("<QQQ", data, pos)
+            target = data[pos + 24:pos + 24 + length]
+            pos += 24 + length
+            if b"gfx950" not in target or size == 0:
+                continue
+            elf = data[at + offset:at + offset + size]
+            table, count = struct.unpack_from("<Q", elf, 0x28)[0], struct.unpack_from("<H", elf, 0x3c)[0]
+            for i in range(count):
+                _, kind, _, _, note, length = struct.unpack_from("<IIQQQQ", elf, table + 64 * i)
+                end = note + length if kind == 7 else note                     # SHT_NOTE
+                while note < end:
+                    name, desc, what = struct.unpack_from("<III", elf, note)
+                    note += 12 + (name + 3) // 4 * 4
+                    if what == 32:                                             # NT_AMDGPU_METADATA
+                        yield from msgpack.unpackb(elf[note:note + desc])["amdhsa.kernels"]
+                    note += (desc + 3) // 4 * 4
+        at = data.find(b"__CLANG_OFFLOAD_BUNDLE__", at + 24)
+
+
+def test_row_movers_fit_their_registers(T):
+    """No kernel that moves rows keeps registers in scratch memory, whatever its instance."""
+    kernels = {k[".name"]: k[".private_segment_fixed_size"] for k in _kernels(T.LIB_PATH)}
+    movers = {n: size for n, size in kernels.items() if re.search("route|copy|combine|regroup|dispatch", n)}
+    assert len(movers) > 100 and any("route_table_kernel" in n for n in movers)
+    assert {n: size for n, size in movers.items() if size > 0} == {}
