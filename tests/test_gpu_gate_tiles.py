@@ -34,6 +34,7 @@ def T():
     (40, 1032, 64, 8, 2), (33, 3000, 64, 8, 2), (40, 512, 65, 5, 2), (33, 1016, 128, 8, 8), (33, 1040, 128, 8, 2),
     (8300, 64, 16, 4, 2), (8300, 264, 10, 5, 2), (16400, 40, 16, 4, 2), (8300, 72, 32, 8, 2), (8300, 600, 16, 4, 1),
     (8300, 504, 16, 4, 2), (8300, 512, 16, 4, 2), (16500, 520, 9, 3, 2), (32768, 136, 32, 8, 2), (8300, 128, 20, 4, 2),
+    (40, 524296, 16, 4, 2), (33, 524352, 20, 4, 2),                                          # rows of more than 1 MiB
 ])
 def test_tile_edges(T, oracle, dtype, S, d, N, P, k):
     oracle.set_threads(oracle.max_threads())
@@ -96,7 +97,8 @@ def _bf16_parts(v):
 
 
 @pytest.mark.parametrize("S,N,d", [(33, 8, 64), (40, 16, 136), (40, 16, 1032), (100, 32, 512), (100, 31, 1032), (8300, 4, 256), (8300, 16, 264), (16500, 16, 1024),
-                                   (8300, 32, 64), (16500, 20, 520), (40000, 32, 64), (20000, 64, 128), (33000, 128, 64)])
+                                   (8300, 32, 64), (16500, 20, 520), (40000, 32, 64), (20000, 64, 128), (33000, 128, 64),
+                                   (40, 16, 262152), (33, 32, 262400)])                      # rows of more than 1 MiB
 def test_fp32_terms_left_out(T, S, N, d):
     """What a product leaves out are its terms of the third order of parts that are rounded to nearest, of x and of W: seen in the
     difference of a product and its own value rounded to 32 bits, of which 24 bits cancel.  (Not in tiles of 32 tokens with
