@@ -309,9 +309,10 @@ static void launch_combine_bwd_k(const vec16* dy, const vec16* recv, int64_t K_r
         if (keep) launch_combine_bwd_s<DT, KK, ST, kLoadKeep>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
         else launch_combine_bwd_s<DT, KK, ST, kLoadStream>(dy, recv, K_rows, slot, topk_w, S, k, cpr, d_recv, d_w, st);
     };
-    if (policy == kStoreThrough) launch(std::integral_constant<int, kStoreThrough>{});
-    else if (policy == kStoreBack) launch(std::integral_constant<int, kStoreBack>{});
-    else if constexpr (KK == 1) launch(std::integral_constant<int, kStoreStream>{});   // one choice alone
+    if constexpr (KK == 1)   // one choice alone
+        if (policy == kStoreStream) return launch(std::integral_constant<int, kStoreStream>{});
+    if (policy == kStoreBack) launch(std::integral_constant<int, kStoreBack>{});
+    else launch(std::integral_constant<int, kStoreThrough>{});
 }
 
 template <int DT>
