@@ -19,6 +19,7 @@ static void launch_route_table_u(const RouteArgs& a, const RowPolicies& how, hip
     // the smallest tables in a kernel that is shorter by seven requests and their sums
     const int64_t pieces = (int64_t)a.n_blocks * (a.stride / 8);
     const bool one = U == 1 && pieces <= TH;
+    const bool large = pieces > kTableBatch * TH;   // fewer than 32768 units then (table_units)
     const auto launch_ld = [&](auto st_c, auto ld_c) {
         constexpr int ST = decltype(st_c)::value, LD = decltype(ld_c)::value;
         const auto go = [&](auto b) {
@@ -27,8 +28,8 @@ static void launch_route_table_u(const RouteArgs& a, const RowPolicies& how, hip
         };
         if constexpr (U == 1)
             if (one) return go(std::integral_constant<int, 1>{});
-        if constexpr (TH == kTableThreads && ROWU)
-            if (pieces > kTableBatch * TH) return go(std::integral_constant<int, 2 * kTableBatch>{});
+        if constexpr (TH == kTableThreads && ROWU && (KK != 4 || ST == kStoreThrough || ST == kStoreStream))
+            if (large) return go(std::integral_constant<int, 2 * kTableBatch>{});
         go(std::integral_constant<int, kTableBatch>{});
     };
     const auto launch = [&](auto st_c) {
@@ -39,10 +40,11 @@ static void launch_route_table_u(const RouteArgs& a, const RowPolicies& how, hip
     };
     if constexpr (kMiB > 16)   // half lines
         if (policy == kStoreStream) return launch(std::integral_constant<int, kStoreStream>{});
+    const bool beyond = KK != 4 || !large;   // 240 MiB with four choices are more units than go with a large table
     if constexpr (!ROWU || (KK == 0 && kMiB > 24) || (KK == 4 && kMiB > 240))
-        if (policy == kStoreBack) return launch(std::integral_constant<int, kStoreBack>{});
-    if constexpr (ROWU && kMiB > 128)
-        if (policy == kStoreOut) return launch(std::integral_constant<int, kStoreOut>{});
+        if (policy == kStoreBack && beyond) return launch(std::integral_constant<int, kStoreBack>{});
+    if constexpr (ROWU && kMiB > 240)
+        if (policy == kStoreOut && beyond) return launch(std::integral_constant<int, kStoreOut>{});
     launch(std::integral_constant<int, kStoreThrough>{});
 }
 template <int KK>
