@@ -4,7 +4,8 @@
 // A layer of a few thousand tokens is a handful of launches of 3 to 10 us each.  Checking and converting some
 // forty tensors and allocating eighteen outputs in Python took longer than that.  Host time, whatever the sizes:
 // gate + aux_loss + dispatch + combine 79 -> 38 us, the three backward entry points 29 -> 13 us.  Without
-// the dispatcher for each output, Python for the stream and ctypes for bound calls: gate_dispatch 17.0 -> 14.7, a bound call of one launch 3.0 -> 2.75.
+// the dispatcher for each output, unless something watches torch, Python for the stream and ctypes for bound calls: gate_dispatch 17.0 -> 14.7,
+// a bound call of one launch 3.0 -> 2.75.
 //
 // Every function returns NotImplemented when anything about its arguments is out of the ordinary (a type, a
 // layout, a device, a subclass, a mode that watches torch's functions, an exception on the way); the caller
@@ -15,7 +16,9 @@
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <ATen/record_function.h>
 #include <Python.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 
@@ -114,9 +117,13 @@ struct Out {
           i32(f32.dtype(at::kInt)), u8(f32.dtype(at::kByte)), x(f32.dtype(t.scalar_type())) {}
 };
 
-// at::empty without the dispatcher (a fourth of its time), which nothing watches here (guarded); with it where torch fills new tensors.
+// Does something in torch look at operators or replace them: a profiler, a tracer, a transform of torch.func?
+bool watched() {
+    return at::hasCallbacks() || !(c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty();
+}
+// at::empty without the dispatcher (a fourth of its time) where nothing depends on it: not watched, and new tensors are not filled.
 at::Tensor empty(at::IntArrayRef sizes, const at::TensorOptions& o) {
-    if (at::globalContext().deterministicAlgorithms()) return at::empty(sizes, o);
+    if (at::globalContext().deterministicAlgorithms() || watched()) return at::empty(sizes, o);
     return at::detail::empty_cuda(sizes, c10::typeMetaToScalarType(o.dtype()), o.device(), std::nullopt);
 }
 

@@ -232,3 +232,22 @@ def test_takes_ordinary_calls_and_leaves_the_others():
     assert loss.item() == 7.0
     call()
     assert torch.equal(loss, T.aux_loss(m, c, None, 2, 8))
+
+
+@pytest.mark.gpu
+def test_new_tensors_are_seen_by_what_watches_torch():
+    """A profiler and a tracer see the outputs being made, and under a transform, where new tensors are wrapped and have no
+    address, the helpers refuse."""
+    x, w = torch.randn(64, 32, device="cuda"), torch.randn(8, 32, device="cuda")
+    plain = T.gate(x, w, 2, 2)
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as prof:
+        profiled = T.gate(x, w, 2, 2)
+    assert {e.key: e.count for e in prof.key_averages()}.get("aten::empty", 0) >= len(plain)
+    assert all(torch.equal(profiled[n], v) for n, v in plain.items())
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        traced = torch.jit.trace(lambda v: T.gate(v, w, 2, 2)["topk_w"], (x,), check_trace=False)
+    assert "aten::empty" in str(traced.graph)
+    with pytest.raises(RuntimeError):
+        torch.func.grad(lambda v: v.sum() + T.gate(x, w, 2, 2)["topk_w"].sum())(torch.ones(2, device="cuda"))
+    assert torch.equal(T.gate(x, w, 2, 2)["topk_w"], plain["topk_w"])
