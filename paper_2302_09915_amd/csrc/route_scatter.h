@@ -650,14 +650,18 @@ __global__ __launch_bounds__(TH, 4) void route_table_kernel(
             tok[u] = tok[u - 1] + next;
             seg[u] = next ? 0 : seg[u - 1] + 1;
         }
-        // A unit's 64 chunks are a buffer of their own: one offset serves all units.  An offset each is U registers, for which
-        // there is no room beside 16 rows of the table, or 16 indices and eight choices: a row went to scratch memory as soon as it
-        // was there, ahead of the sums (8192 x 2 KiB, four choices, 64 experts 37.7 us, now 36.7; 2048 x 8 KiB, eight, separate calls 76.7, 71.9).
+        // An offset for each unit is U registers, for which there is no room beside 16 rows of the table, or 16 indices and eight choices: a
+        // row went to scratch memory as soon as it was there, ahead of the sums (8192 x 2 KiB, four choices, 64 experts 37.7 us, now
+        // 36.7; 2048 x 8 KiB, eight, separate calls 76.7, 71.9).  There a unit's 64 chunks are a buffer of their own, with one offset
+        // for all (elsewhere that is slower: separate calls of 16384 x 4 KiB, one choice 50.2, 50.4).
+        constexpr bool kOwnBuffer = B > kTableBatch || (B == 0 && KK == 0);
+        const auto begin = [&](int u) { return kOwnBuffer ? seg[u] * 64 : 0; };
+        const auto col = [&](int u) { return kOwnBuffer ? lane : seg[u] * 64 + lane; };
         count_pairs<TH, KK, B>(a, blk0, t0, t1, t, [&] {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const bool in = tok[u] < a.S;
-                v[u] = RowBuffer(x + (size_t)(in ? tok[u] : 0) * cpr + seg[u] * 64, cpr - seg[u] * 64, in).template load<LD>(lane);
+                v[u] = RowBuffer(x + (size_t)(in ? tok[u] : 0) * cpr + begin(u), cpr - begin(u), in).template load<LD>(col(u));
             }
         });
         const WaveOffsets wo = wave_offsets(load_kept(t.kept, N));
@@ -668,7 +672,7 @@ __global__ __launch_bounds__(TH, 4) void route_table_kernel(
 #pragma unroll
             for (int j = 0; j < KM; ++j) {
                 const int32_t to = __builtin_amdgcn_readlane(sl, u * KM + j);   // -1 where there is no such choice
-                RowBuffer(send + (size_t)(to >= 0 ? to : 0) * cpr + seg[u] * 64, cpr - seg[u] * 64, to >= 0).template store<ST>(lane, v[u]);
+                RowBuffer(send + (size_t)(to >= 0 ? to : 0) * cpr + begin(u), cpr - begin(u), to >= 0).template store<ST>(col(u), v[u]);
             }
     } else {
         int tok[U], col[U];
