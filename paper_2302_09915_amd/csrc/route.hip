@@ -172,12 +172,13 @@ static int64_t rows_sent(const RouteArgs& a) {
     return a.pad_C > 0 && room < pairs ? room : pairs;
 }
 
-// How rows are moved and x is loaded: by what it and the rows take, the unused ones of the fixed-size layout too.  The packed dispatch
-// follows a gate on the same x.
+// How rows are moved and x is loaded: by what it and the rows take, the unused ones of the fixed-size layout too, and by what the
+// combine of as many rows will do.  The packed dispatch follows a gate on the same x.
 static RowPolicies row_policies(const RouteArgs& a, bool ranks = false) {
     const bool by_wave = scatter_by_wave(a.S, a.cpr, a.k);
     const int64_t rows = rows_sent(a), buffer = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : rows;
-    return RowPolicies{by_wave, scatter_load(a.S, buffer, a.cpr, a.pad_C == 0, ranks) == kLoadKeep,
+    const bool combine_keeps = combine_load(a.S, buffer, a.cpr, a.k) == kLoadKeep;
+    return RowPolicies{by_wave, scatter_load(a.S, buffer, a.cpr, a.pad_C == 0, ranks, combine_keeps) == kLoadKeep,
                        scatter_store(row_lines(a.send, a.cpr), rows, a.cpr, a.k, by_wave, a.m_part != nullptr, a.pad_C > 0)};
 }
 

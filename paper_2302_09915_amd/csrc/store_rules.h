@@ -85,11 +85,14 @@ inline StorePolicy scatter_store(RowLines lines, int64_t rows, int cpr, int k, b
 // 41.4, 28736 x 1536, two (126) 59.5 / 62.6.  The rows are those of the buffer: 6144 x 2 KiB, two, half of 48 MiB padding 25.65 / 26.2, 11776 x 1 KiB, two,
 // as much 31.6 / 34.2, 9856 x 1 KiB, two (47) 27.3 / 24.9.
 // Ranked by the scatter itself, which waits for the counts meanwhile: 8192 x 4 KiB, one (72) 31.4 / 27.9, 3770 x 5888, two (62)
-// 29.9 / 26.4, 1150 x 16 KiB, two, half padding (92) 32.2 / 29.0; 8192 x 4 KiB, two (96) 40.9 / 44.7, 5300 x 7 KiB, two (118) 46.4 / 49.2, 16384 x 4 KiB, one (140) 52.7 / 56.4; some of 57 to 66
-// MiB, half padding, lose (6144 x 2 KiB, two (60) 21.6 / 22.5).
-constexpr int kKeepBehindGate = 128, kKeepRanking = 88, kKeepGiven = 48;   // MiB of x and the rows sent
-inline LoadPolicy scatter_load(int64_t S, int64_t rows, int cpr, bool behind_gate, bool ranks = false) {
-    const int most = behind_gate ? kKeepBehindGate : ranks ? kKeepRanking : kKeepGiven;
+// 29.9 / 26.4, 1150 x 16 KiB, two, half padding (92) 32.2 / 29.0; 8192 x 4 KiB, two (96) 40.9 / 44.7, 5300 x 7 KiB, two (118) 46.4 / 49.2, 16384 x 4 KiB, one (140) 52.7 / 56.4.  Where
+// the combine keeps the rows that come back, which lie in another buffer (combine_load), there is room for less beside them: streaming / ordinary
+// 3481 x 4 KiB, two, half padding (68) 22.8 / 27.2, 7130 x 2000, two, half (68) 25.4 / 29.3, 5802 x 4 KiB, one, half (68) 24.7 / 26.9, 1820 x 4 KiB, four,
+// half (64) 22.9 / 25.0, 3072 x 4 KiB, two, half (60) 20.3 / 21.5; 4437 x 4 KiB, one, half (52) 21.7 / 19.4, 2218 x 8 KiB, one, half (52) 21.4 / 19.5,
+// 1331 x 8 KiB, two, half (52) 18.2 / 18.8.
+constexpr int kKeepBehindGate = 128, kKeepRanking = 88, kKeepBoth = 54, kKeepGiven = 48;   // MiB of x and the rows sent
+inline LoadPolicy scatter_load(int64_t S, int64_t rows, int cpr, bool behind_gate, bool ranks = false, bool combine_keeps = false) {
+    const int most = behind_gate ? kKeepBehindGate : !ranks ? kKeepGiven : combine_keeps ? kKeepBoth : kKeepRanking;
     return (S + rows) * cpr * 16 <= (int64_t)most << 20 ? kLoadKeep : kLoadStream;
 }
 

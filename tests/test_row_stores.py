@@ -270,3 +270,22 @@ def test_gpu_tests_reach_every_load_policy(rules):
     both = {(b, p) for b in (0, 1) for p in (KEEP, STREAM)}
     assert seen.pop("dispatch_bwd") == both - {(0, KEEP)}
     assert all(s == both for s in seen.values()), seen
+
+
+def test_x_is_kept_beside_what_the_combine_keeps(rules, tmp_path):
+    """A scatter that ranks the routing itself keeps x up to 88 MiB, or up to 54 where the combine keeps rows as well."""
+    src, so = tmp_path / "both.cpp", tmp_path / "both.so"
+    src.write_text("""#include "store_rules.h"
+extern "C" int both(int64_t S, int64_t rows, int cpr, int keeps) { return tamoe::scatter_load(S, rows, cpr, false, true, keeps); }""")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(so)], check=True)
+    both = ctypes.CDLL(str(so)).both
+    both.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    for cpr, k in ((64, 1), (125, 2), (512, 4)):
+        S = lambda mib: mib * MIB // ((k + 1) * cpr * 16)   # noqa: E731
+        for keeps, most in ((0, 88), (1, 54)):
+            assert [both(S(m), S(m) * k, cpr, keeps) for m in (most, most + 1)] == [KEEP, STREAM]
+        # half of the rows padding: what the combine reads decides
+        for m in (50, 60, 80, 90):
+            s = m * MIB // ((2 * k + 1) * cpr * 16)
+            keeps = rules.combine_ld(s, 2 * s * k, cpr, k) == KEEP
+            assert both(s, 2 * s * k, cpr, keeps) == (KEEP if m <= (54 if keeps else 88) else STREAM), (m, k)
