@@ -156,7 +156,7 @@ static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* sl
             if (dispatch_bwd_load(row_lines(recv, cpr), S, cpr, k, by_wave) == kLoadKeep && !out)
                 return launch_combine_s<DT, KK, U, true, kStoreStream, kLoadKeep>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
         }
-    } else if (combine_load(S, K_rows, cpr, k) == kLoadKeep) {
+    } else if (combine_load(S, K_rows, cpr, k, row_lines(recv, cpr)) == kLoadKeep) {
         if (out) return launch_combine_s<DT, KK, U, false, kStoreOut, kLoadKeep>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
         return launch_combine_s<DT, KK, U, false, kStoreStream, kLoadKeep>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
     }

@@ -177,9 +177,10 @@ static int64_t rows_sent(const RouteArgs& a) {
 static RowPolicies row_policies(const RouteArgs& a, bool ranks = false) {
     const bool by_wave = scatter_by_wave(a.S, a.cpr, a.k);
     const int64_t rows = rows_sent(a), buffer = a.pad_C > 0 ? (int64_t)a.N * a.pad_C : rows;
-    const bool combine_keeps = combine_load(a.S, buffer, a.cpr, a.k) == kLoadKeep;
+    const RowLines lines = row_lines(a.send, a.cpr);
+    const bool combine_keeps = combine_load(a.S, buffer, a.cpr, a.k, lines) == kLoadKeep;
     return RowPolicies{by_wave, scatter_load(a.S, buffer, a.cpr, a.pad_C == 0, ranks, combine_keeps) == kLoadKeep,
-                       scatter_store(row_lines(a.send, a.cpr), rows, a.cpr, a.k, by_wave, a.m_part != nullptr, a.pad_C > 0)};
+                       scatter_store(lines, rows, a.cpr, a.k, by_wave, a.m_part != nullptr, a.pad_C > 0)};
 }
 
 // Fills in the launch geometry.

@@ -121,15 +121,22 @@ inline StorePolicy combine_store(RowLines lines, int64_t S, int cpr, int k, bool
 // forward 34.4 / 32.5, 20098 x 512, three (39) fixed-size layout 26.8 / 24.9; forward 16159 x 1792, two (83) 34.8 / 34.6, 31936 x 640, four (98) 50.6 /
 // 54.6, fixed-size layout 8926 x 2432, two (62) 34.8 / 36.1, 3693 x 8960, one (63) 38.5 / 42.7.  The buffer they lie in
 // counts too: 6144 x 2 KiB, two, half of 48 MiB padding 26.2 / 25.4, 21193 x 768, two, half of 62 MiB 34.8 / 37.5.
-// Above 40 MiB only with up to four choices (streaming / kept, us): training pass of 5003 x 2000, four (48) 62.1 / 59.2; gate,
-// dispatch and combine of 2752 x 1920, eight (45) 35.4 / 38.0.
-inline LoadPolicy combine_load(int64_t S, int64_t buffer_rows, int cpr, int k) {
-    const int64_t row = cpr * 16, MiB = (int64_t)1 << 20;
-    return S * (k + 1) * row <= (k > 4 ? 40 : 48) * MiB && buffer_rows <= (60 * MiB) / row ? kLoadKeep : kLoadStream;
+// Above 40 MiB it depends on how the rows lie (42 to 47 MiB, streaming / kept): those that share lines gain whatever the call, as the
+// line is wanted again (forward 6484 x 1520, four 30.0 / 26.8, 2737 x 2000, eight 29.9 / 28.0; separate calls 10807 x 1520, two 40.3 / 37.6, 2464 x 4000,
+// four 37.6 / 35.0; training passes 6160 x 2000, three 59.1 / 56.4); others gain with up to three choices in training and with padding, and lose less
+// in separate calls (14336 x 1 KiB, two 48.2 / 47.0; 10752 x 1 KiB, three, a fifth padding 27.1 / 25.9; 5312 x 2 KiB, three 31.1 / 32.1); with four
+// and more those lose (8499 x 1 KiB, four 35.2 / 37.0, 2124 x 4 KiB, four 30.7 / 32.7, 1180 x 4 KiB, eight 32.4 / 36.4) what padding gains (8499 x 1 KiB,
+// four 28.8 / 28.0).  And buffers beyond 48 MiB lose (half padding, 3788 x 4 KiB, two (59) 24.3 / 26.1, 30037 x 512, two (59) 34.4 / 36.3; 3520 x 2000, six, a
+// fifth (50) 30.5 / 31.6).
+inline LoadPolicy combine_load(int64_t S, int64_t buffer_rows, int cpr, int k, RowLines lines = kWholeLines) {
+    const int64_t row = cpr * 16, MiB = (int64_t)1 << 20, own = S * (k + 1) * row;
+    if (own > 40 * MiB && ((k > 3 && lines != kSharedLines) || buffer_rows > 48 * MiB / row)) return kLoadStream;
+    return own <= 48 * MiB && buffer_rows <= 60 * MiB / row ? kLoadKeep : kLoadStream;
 }
 // Its transpose reads what combine_bwd has left there either way.  Rows that share lines gain, as the line is wanted again: us of the three
 // backward calls on 16448 x 2224, two (35 MiB of rows per choice) 50.5 / 46.9, 5696 x 15968, one 79.3 / 76.9, 23808 x 3824, two (182 in all) 89.6 /
-// 85.4; but 9168 x 8928, eight (625) 411 / 471, and rows of whole lines 18911 x 1792, three 68.0 / 71.3, 25000 x 1536, two 45.5 / 45.6.
+// 85.4; not with three choices and more (10 to 188 MiB of rows of 1040 to 8016 bytes, either way within 1 %: 6640 x 2000, three 33.5 / 33.5, 8388 x 2000,
+// four 48.6 / 48.5; 9168 x 8928, eight (625) 411 / 471), nor rows of whole lines (18911 x 1792, three 68.0 / 71.3, 25000 x 1536, two 45.5 / 45.6).
 inline LoadPolicy dispatch_bwd_load(RowLines lines, int64_t S, int cpr, int k, bool by_wave) {
     return by_wave && k <= 2 && lines == kSharedLines && S * k * cpr * 16 <= (int64_t)192 << 20 ? kLoadKeep : kLoadStream;
 }

@@ -289,3 +289,24 @@ extern "C" int both(int64_t S, int64_t rows, int cpr, int keeps) { return tamoe:
             s = m * MIB // ((2 * k + 1) * cpr * 16)
             keeps = rules.combine_ld(s, 2 * s * k, cpr, k) == KEEP
             assert both(s, 2 * s * k, cpr, keeps) == (KEEP if m <= (54 if keeps else 88) else STREAM), (m, k)
+
+
+def test_rows_the_combine_keeps_beyond_40_mib(rules, tmp_path):
+    """Between 40 and 48 MiB it matters whether rows share lines, and how large the buffer is."""
+    src, so = tmp_path / "lines.cpp", tmp_path / "lines.so"
+    src.write_text("""#include "store_rules.h"
+using namespace tamoe;
+extern "C" int lines(int64_t S, int64_t rows, int cpr, int k, uint64_t base) { return combine_load(S, rows, cpr, k, row_lines((const void*)base, cpr)); }""")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(so)], check=True)
+    load = ctypes.CDLL(str(so)).lines
+    load.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_uint64]
+    whole, half, shared = 1 << 20, (1 << 20) + 64, (1 << 20) + 16
+    for cpr in (16, 64, 512):
+        for k in (1, 3, 4, 8):
+            S = lambda mib: mib * MIB // ((k + 1) * cpr * 16)   # noqa: E731
+            for base in (whole, half, shared):
+                most = 40 if k > 3 and base != shared else 48
+                assert [load(S(m), S(m) * k, cpr, k, base) for m in (1, 40, most, most + 1, 60)] == [KEEP, KEEP, KEEP, STREAM, STREAM]
+                # a buffer of more rows than pairs
+                assert [load(S(39), _at(m, cpr), cpr, k, base) for m in (48, 60, 61)] == [KEEP, KEEP, STREAM]
+                assert [load(S(44), _at(m, cpr), cpr, k, base) for m in (48, 49)] == [KEEP if most == 48 else STREAM, STREAM]
