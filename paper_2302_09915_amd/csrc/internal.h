@@ -10,6 +10,7 @@
 #include <tuple>
 #include <type_traits>
 
+#include "route_rules.h"
 #include "store_rules.h"
 #include "tamoe.h"
 
@@ -22,15 +23,12 @@ typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 void clear_error();
 
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 inline int elem_bytes(int dtype) { return dtype == TAMOE_F32 ? 4 : 2; }
 
 // ---- launch geometry (host side; the kernels receive what they need as arguments) ----------
 
-// Gate: tokens per workgroup (32, 64, 128 or 256).
-int gate_tile_tokens(int64_t S, int N);
 // Upper bound of the number of gate workgroups over every choice of tile.
 inline int64_t gate_blocks_max(int64_t S) { return ceil_div(S, 32); }
 
@@ -68,11 +66,6 @@ __host__ __device__ constexpr int sum_stride(int N) {
     int pieces = 1;
     while (pieces * 4 < N) pieces *= 2;
     return pieces * 4;
-}
-inline int count_stride(int N, int k) {
-    int pieces = 1;
-    while (pieces * 8 < N * k) pieces *= 2;
-    return pieces * 8;
 }
 
 // What the gate stage left in the workspace for the stages behind it.
@@ -131,19 +124,6 @@ __device__ __forceinline__ void split_chunk(int64_t c, int64_t total, int cpr, i
     }
 }
 
-// Rows of at least 64 chunks (1 KiB) are moved by whole wavefronts: a row takes row_waves(cpr) of them, the
-// last one with idle lanes unless the row is a multiple of 1 KiB.  A wavefront then has one token, whose
-// slots and weights go through the scalar unit, nothing is divided per lane, and a row is a buffer of its
-// own (RowBuffer).  A flat layout of chunks over lanes has none of this, and gains only where most of a
-// wavefront would idle (shorter rows).
-inline bool rows_by_wave(int cpr) { return cpr >= 64; }
-inline int row_waves(int cpr) { return (cpr + 63) / 64; }
-// S rows just over one or two wavefronts, the last of which has fewer than `lanes` lanes and costs what the others
-// cost, in a launch that is bound by that.  (Below 8192 wavefronts it is latency, and neither is better throughout: 2000
-// rows of 1040 bytes, dispatch with one choice 6.6 us by wavefront, 6.9 flat, with three 9.1 and 8.6.)
-inline bool poor_last_wave(int64_t S, int cpr, int lanes) {
-    return row_waves(cpr) <= 3 && cpr % 64 > 0 && cpr % 64 < lanes && S * row_waves(cpr) >= 8192;
-}
 // Wavefront wv of a launch -> row and segment of 64 chunks in it.  shift: pow2_shift(wpr).  The rows of one
 // device's memory are fewer than 2^31 wavefronts.
 __device__ __forceinline__ void split_wave(uint32_t wv, int wpr, int shift, int& row, int& seg) {

@@ -87,12 +87,7 @@ __device__ __forceinline__ int32_t offset_of(const WaveOffsets& o, int e) {
 // the rows are on their way too, then 0.9 us.  What was measured to count is the length of the code, which a wavefront
 // runs once, from cold instruction caches: with bytes for counts (half the requests, three times the additions)
 // small_forward took 17.8 us, with the steps of sum_columns under a condition each 15.9, now 14.8.
-constexpr int kTableThreads = 512;   // or half as many (table_threads)
-constexpr int kTableBatch = 8;   // rows per lane, requested together (one in the smallest tables, twice as many in large ones)
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-
-// Of a scatter that ranks a given routing itself: most pairs, those a thread requests at a time, most tokens of a workgroup.
-constexpr int kGivenPairs = 16384, kGivenBatch = 16, kGivenTokens = 128;
 
 template <int TH>
 struct TableLds {
