@@ -95,7 +95,8 @@ inline int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool b
     if (units > (!by_wave ? 8192 : behind_gate ? 65536 : 32768)) return 0;
     int U = 1;
     while (U < (by_wave ? 8 : 2) && units >= kTableThreads / 64 * U * 2 * 256) U *= 2;
-    if (pieces > kTableBatch * kTableThreads && (!by_wave || units >= 32768)) return 0;
+    // (one choice, and two of so few units, do not have as many pieces: no instances)
+    if (pieces > kTableBatch * kTableThreads && (!by_wave || units >= 32768 || k == 1 || (k == 2 && U == 1))) return 0;
     return U;
 }
 

@@ -14,12 +14,14 @@ static void launch_route_table_u(const RouteArgs& a, const RowPolicies& how, hip
     constexpr int kMiB = kX * (KK > 0 ? KK : TAMOE_MAX_K);                       // of rows
     constexpr bool kKeepsAll = U == 1;   // but for much padding, where 4 MiB of x do not matter
     static_assert(!kKeepsAll || kX + kMiB <= kKeepGiven, "nothing of its size streams");
-    const bool keep = kKeepsAll || how.keep;
     const StorePolicy policy = how.store;
     // the smallest tables in a kernel that is shorter by seven requests and their sums
     const int64_t pieces = (int64_t)a.n_blocks * (a.stride / 8);
     const bool one = U == 1 && pieces <= TH;
     const bool large = pieces > kTableBatch * TH;   // fewer than 32768 units then (table_units)
+    constexpr bool kLarge = TH == kTableThreads && ROWU && KK != 1 && !(KK == 2 && U == 1);
+    constexpr bool kLargeStreams = KK == 0 || (KK > 2 && U == 8);   // otherwise at most 96 MiB behind a gate, and none elsewhere
+    const bool keep = kKeepsAll || how.keep || (large && !kLargeStreams);
     const auto launch_ld = [&](auto st_c, auto ld_c) {
         constexpr int ST = decltype(st_c)::value, LD = decltype(ld_c)::value;
         const auto go = [&](auto b) {
@@ -28,15 +30,16 @@ static void launch_route_table_u(const RouteArgs& a, const RowPolicies& how, hip
         };
         if constexpr (U == 1)
             if (one) return go(std::integral_constant<int, 1>{});
-        if constexpr (TH == kTableThreads && ROWU && (KK != 4 || ST == kStoreThrough || ST == kStoreStream))
+        if constexpr (kLarge && (kLargeStreams || LD == kLoadKeep) && (KK != 4 || ST == kStoreThrough || ST == kStoreStream))
             if (large) return go(std::integral_constant<int, 2 * kTableBatch>{});
         go(std::integral_constant<int, kTableBatch>{});
     };
     const auto launch = [&](auto st_c) {
-        constexpr bool kOut = decltype(st_c)::value == kStoreOut;   // more than scatter_load keeps
-        if constexpr (kOut || !kKeepsAll)
-            if (kOut || !keep) return launch_ld(st_c, std::integral_constant<int, kLoadStream>{});
-        if constexpr (!kOut) launch_ld(st_c, std::integral_constant<int, kLoadKeep>{});
+        constexpr int ST = decltype(st_c)::value;
+        constexpr bool kBeyond = ST == kStoreOut || (ST == kStoreBack && ROWU && KK == 4);   // more than scatter_load keeps
+        if constexpr (kBeyond || !kKeepsAll)
+            if (kBeyond || !keep) return launch_ld(st_c, std::integral_constant<int, kLoadStream>{});
+        if constexpr (!kBeyond) launch_ld(st_c, std::integral_constant<int, kLoadKeep>{});
     };
     if constexpr (kMiB > 16)   // half lines
         if (policy == kStoreStream) return launch(std::integral_constant<int, kStoreStream>{});
