@@ -201,7 +201,8 @@ PADDING_SHAPES = [
     (2000, 64, 2, 500, 1, THROUGH, 0), (9000, 128, 1, 2200, 1, THROUGH, 0), (20000, 128, 1, 2200, 1, THROUGH, 1), (9000, 128, 2, 3300, 1, THROUGH, 1),
     (70000, 128, 1, 4500, 1, OUT, 1), (16000, 128, 8, 9000, 1, OUT, 1), (9000, 125, 2, 2300, 1, THROUGH, 1), (8000, 125, 6, 3300, 1, BACK, 1),
     (70000, 125, 1, 4500, 1, STREAM, 1), (20000, 36, 2, 2600, 0, THROUGH, 0), (16000, 132, 4, 4100, 1, STREAM, 1), (1000, 8, 2, 200, 0, BACK, 0),
-    (20000, 16, 2, 2600, 0, THROUGH, 0), (60000, 32, 2, 8000, 0, BACK, 0), (140000, 32, 2, 18000, 0, OUT, 1), (40000, 36, 2, 5100, 0, STREAM, 0)]
+    (20000, 16, 2, 2600, 0, THROUGH, 0), (60000, 32, 2, 8000, 0, BACK, 0), (140000, 32, 2, 18000, 0, OUT, 1), (40000, 36, 2, 5100, 0, STREAM, 0),
+    (9000, 64, 2, 1200, 1, THROUGH, 0)]
 
 
 @pytest.mark.parametrize("S,chunks,k", [s[:3] for s in STORE_SHAPES])

@@ -258,11 +258,14 @@ def test_loaded_rows(rules, cpr):
 
 
 def test_gpu_tests_reach_every_load_policy(rules):
-    from test_gpu_row_movers import STORE_SHAPES
+    from test_gpu_row_movers import PADDING_SHAPES, STORE_SHAPES
 
-    seen = {"scatter": set(), "combine": set(), "dispatch_bwd": set(), "combine_bwd": set(), "regroup": set()}
-    for S, cpr, k, by_wave, _ in STORE_SHAPES:
-        seen["scatter"].add((by_wave, rules.scatter_ld(S, S * k, cpr, 0)))
+    seen = {"scatter": set(), "padded": set(), "combine": set(), "dispatch_bwd": set(), "combine_bwd": set(), "regroup": set()}
+    for S, cpr, k, C, by_wave, _, _ in PADDING_SHAPES:
+        if S * k > 16384:   # not ranked by the scatter itself
+            seen["padded"].add((by_wave, rules.scatter_ld(S, 16 * C, cpr, 0)))
+    for S, cpr, k, by_wave, _ in STORE_SHAPES:   # packed: as behind a gate
+        seen["scatter"].add((by_wave, rules.scatter_ld(S, S * k, cpr, 1)))
         seen["combine"].add((by_wave, rules.combine_ld(S, S * k, cpr, k)))
         seen["combine_bwd"].add((by_wave, rules.combine_bwd_ld(1 << 20, S, cpr, k)))
         seen["dispatch_bwd"].add((by_wave, rules.dispatch_bwd_ld(1 << 20, S, cpr, k, by_wave)))
