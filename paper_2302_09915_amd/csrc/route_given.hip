@@ -9,7 +9,7 @@ static void launch_u(const RouteArgs& a, const RowPolicies& how, hipStream_t st)
     const dim3 grid((unsigned)(1 + a.copy_blocks + a.N * a.fill_parts)), block(TH);
     const auto launch = [&](auto st_c) {
         constexpr int ST = decltype(st_c)::value;
-        if constexpr (ROWU && U >= 4)   // 8 MiB of x and more; less is loaded to stay whatever the padding
+        if constexpr (ROWU && U >= 4)   // more than 4 MiB of x; less is loaded to stay also beside 84 MiB of padding
             if (!how.keep) {
                 launch_kernel(route_table_kernel<TH, KK, U, ROWU, ST, kLoadStream, 0>, grid, block, st, a.x, a.topk_idx, nullptr, nullptr, a.slot, a.send, a);
                 return;
