@@ -63,8 +63,8 @@ def parse_args():
                     help="number of copies of (x, send, y) that the steps cycle through, so that a small workload's "
                          "rows come from HBM and not from the 256 MB last-level cache (default 1: same buffers)")
     ap.add_argument("--path", choices=["fused", "separate"], default="fused",
-                    help="fused: tamoe_gate_dispatch + tamoe_combine (4 launches per step); separate: tamoe_gate, "
-                         "tamoe_aux_loss, tamoe_dispatch, tamoe_combine (8 launches)")
+                    help="fused: tamoe_gate_dispatch + tamoe_combine (3 or 4 launches per step); separate: tamoe_gate, "
+                         "tamoe_aux_loss, tamoe_dispatch, tamoe_combine (5 to 7 launches)")
     ap.add_argument("--cpu-seconds", type=float, default=12.0, help="target CPU time of the oracle sample")
     return ap.parse_args()
 

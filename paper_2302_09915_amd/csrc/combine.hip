@@ -151,7 +151,8 @@ static void launch_combine_k(const void* recv, int64_t K_rows, const int32_t* sl
     const bool by_wave = combine_by_wave(S, cpr, k);
     const bool out = combine_store(row_lines(y, cpr), S, cpr, k, by_wave) == kStoreOut;
     if constexpr (UNITW) {
-        // what dispatch_bwd_load keeps has two choices at most and shares lines, which combine_store streams
+        // what dispatch_bwd_load keeps has two choices at most and shares lines, which combine_store streams (behind a recv that begins
+        // within a line y may have whole ones: then recv streams too)
         if constexpr (KK == 1 || KK == 2) {
             if (dispatch_bwd_load(row_lines(recv, cpr), S, cpr, k, by_wave) == kLoadKeep && !out)
                 return launch_combine_s<DT, KK, U, true, kStoreStream, kLoadKeep>(recv, K_rows, slot, topk_w, S, k, cpr, y, st);
