@@ -133,12 +133,15 @@ inline LoadPolicy combine_load(int64_t S, int64_t buffer_rows, int cpr, int k, R
     if (own > 40 * MiB && ((k > 3 && lines != kSharedLines) || buffer_rows > 48 * MiB / row)) return kLoadStream;
     return own <= 48 * MiB && buffer_rows <= 60 * MiB / row ? kLoadKeep : kLoadStream;
 }
-// Its transpose reads what combine_bwd has left there either way.  Rows that share lines gain, as the line is wanted again: us of the three
-// backward calls on 16448 x 2224, two (35 MiB of rows per choice) 50.5 / 46.9, 5696 x 15968, one 79.3 / 76.9, 23808 x 3824, two (182 in all) 89.6 /
-// 85.4; not with three choices and more (10 to 188 MiB of rows of 1040 to 8016 bytes, either way within 1 %: 6640 x 2000, three 33.5 / 33.5, 8388 x 2000,
+// Its transpose reads what combine_bwd has left there either way.  Rows that share lines gain, as the line is wanted again, up to 120 MiB of
+// them: us of the three backward calls on 16448 x 2224, two (70 MiB) 50.5 / 46.9, 9791 x 4016, two (75) 60.2 / 56.8, 39321 x 2000, one (75) 75.5 / 72.2,
+// 6867 x 8016, two (105) 79.4 / 77.7, 15697 x 8016, one (120) 109.7 / 107.7; but 15665 x 4016, two (120) 91.3 / 92.3, 8829 x 8016, two (135) 101.2 / 105.6,
+// 45613 x 2000, two (174) 137 / 150, 45431 x 4016, one (174) 165 / 176.  (Passes of forward and backward with nothing between them over the buffers of
+// three layers lose from 60 MiB on: 31457 x 2000, one 130.0 / 132.8, 6867 x 8016, two (105) 164.4 / 167.1.)  Not with three
+// choices and more (10 to 188 MiB of rows of 1040 to 8016 bytes, either way within 1 %: 6640 x 2000, three 33.5 / 33.5, 8388 x 2000,
 // four 48.6 / 48.5; 9168 x 8928, eight (625) 411 / 471), nor rows of whole lines (18911 x 1792, three 68.0 / 71.3, 25000 x 1536, two 45.5 / 45.6).
 inline LoadPolicy dispatch_bwd_load(RowLines lines, int64_t S, int cpr, int k, bool by_wave) {
-    return by_wave && k <= 2 && lines == kSharedLines && S * k * cpr * 16 <= (int64_t)192 << 20 ? kLoadKeep : kLoadStream;
+    return by_wave && k <= 2 && lines == kSharedLines && S * k * cpr * 16 <= (int64_t)120 << 20 ? kLoadKeep : kLoadStream;
 }
 
 // combine_bwd: d_recv goes straight through L2, whose last-level cache keeps what fits of it for the kernel that reads it

@@ -250,8 +250,8 @@ def test_loaded_rows(rules, cpr):
         most = 60 if short else 72
         assert [rules.combine_bwd_ld(at, S(m, 2 * k + 1), cpr, k) for m in (most, most + 1)] == [STREAM if short and cpr % 4 else KEEP, STREAM]
         assert rules.combine_bwd_ld(off, S(most, 2 * k + 1), cpr, k) == (STREAM if short else KEEP)
-        for m, by_wave in ((192, 1), (193, 1), (100, 0)):
-            shared = KEEP if by_wave and k <= 2 and m <= 192 else STREAM
+        for m, by_wave in ((120, 1), (121, 1), (100, 0)):
+            shared = KEEP if by_wave and k <= 2 and m <= 120 else STREAM
             assert rules.dispatch_bwd_ld(off, S(m, k), cpr, k, by_wave) == shared
             assert rules.dispatch_bwd_ld(at, S(m, k), cpr, k, by_wave) == (STREAM if cpr % 4 == 0 else shared)
     assert [rules.regroup_ld(_at(m, cpr), cpr) for m in (3, 5, 24, 25)] == [STREAM, KEEP, KEEP, STREAM]
