@@ -106,6 +106,9 @@ inline int table_units(int64_t S, int cpr, int N, int k, int tile_tokens, bool b
 // it padding 26.2, 22.4, 4096 x 4 KiB, two 28.7, 23.3; separate calls of 8192 x 256, two 37.5, 33.0, 16384 x 4 KiB, one 68.2, 61.8, 8192 x 8 KiB, two 91.3, 86.8.  Every workgroup reads all pairs:
 // beyond kGivenPairs that takes longer than the launch (with 30000, 10000 x 256, three 15.8, 23.5).  It should be one of at most
 // 256, as many units to a wavefront as that takes (5003 x 2000, three: 626 workgroups 23.0, 313 21.1; 3200 x 1 KiB, five 19.0, 16.1).
+// It reads the rows of dropped tokens too, which the launch behind a ranking leaves out: with one choice and two of five pairs dropped it loses
+// beyond 48 MiB of x what it gains where few are (renormalisation, dispatch_padded and combine of 16384 x 4 KiB 45.6, 47.6, none dropped 54.0, 51.6; separate
+// calls of 12000 x 8 KiB 74.7, 77.7, none dropped 96.0, 91.0; of 16384 x 4 KiB 55.0, 50.5).
 inline int given_units(int64_t S, int cpr, int N, int k, int* threads) {
     const int64_t units = move_units(S, cpr, k);
     const bool by_wave = scatter_by_wave(S, cpr, k);
