@@ -36,7 +36,8 @@ def T():
     (8300, 504, 16, 4, 2), (8300, 512, 16, 4, 2), (16500, 520, 9, 3, 2), (32768, 136, 32, 8, 2), (8300, 128, 20, 4, 2),
     # shared steps and private ones: either side of the workgroups, steps and experts where one takes over
     (9700, 576, 16, 4, 2), (9600, 576, 16, 4, 2), (9700, 512, 16, 4, 2), (8300, 576, 32, 8, 2), (8800, 1600, 20, 4, 2), (8300, 1600, 20, 4, 2),
-    (16500, 320, 32, 8, 2), (16500, 384, 32, 8, 2), (7700, 1152, 32, 8, 2), (7680, 1152, 32, 8, 2), (4700, 1088, 48, 8, 2), (4600, 1088, 48, 8, 2),
+    (16500, 320, 32, 8, 2), (16500, 384, 32, 8, 2), (7700, 1152, 32, 8, 2), (7680, 1152, 32, 8, 2), (5760, 1664, 32, 8, 2),
+    (5770, 1664, 32, 8, 2), (5770, 1536, 20, 4, 2), (5770, 1280, 17, 1, 1), (4700, 1088, 48, 8, 2), (4600, 1088, 48, 8, 2),
     (4700, 1152, 64, 8, 2), (6700, 1408, 50, 5, 2), (6600, 1408, 50, 5, 2), (70, 192, 64, 8, 2), (70, 288, 64, 8, 2), (70, 480, 64, 8, 2), (70, 576, 64, 8, 2),
     (70, 544, 64, 8, 2), (70, 608, 64, 8, 2), (70, 1216, 40, 8, 2), (70, 320, 128, 8, 2), (70, 352, 128, 8, 2), (70, 384, 100, 4, 2),
     (40, 524296, 16, 4, 2), (33, 524352, 20, 4, 2),                                          # rows of more than 1 MiB
